@@ -33,11 +33,11 @@
 //     several leaf tiles, each ring is read once into per-row lists of its
 //     band edges in LDS, and every tile scatters from its row's list.
 //   - The pair's MBRs and shoelace areas are reduced by the wave that takes
-//     the pair, from the same coalesced ring loads it needs anyway; only the
-//     pairs with many vertices ("heavy", claimed first: a largest-first
-//     order) get them from a prepass, run by a quarter of the medium
-//     sweep's waves beside the others' computation, so that any wave can
-//     take one of their boxes.
+//     the pair, from the same coalesced ring loads it needs anyway; the
+//     pairs with many vertices ("long", claimed first: a largest-first
+//     order) get them from two waves, one per ring, which count the pair at
+//     once unless its box has more than 64 leaf tiles: then any wave of the
+//     persistent kernel can take one of its boxes.
 //   - One persistent grid.  Waves claim, in this order: boxes from their
 //     queue, heavy pairs, chunks of the other pairs, boxes from any queue.
 //     Claims go through per-stream counters (one stream per XCD) on cache
@@ -190,20 +190,6 @@ __device__ __forceinline__ void wave_sync_lds() {
 }
 
 // ------------------------------------------------------------- ring scans
-// A lane's view of the first two 64-vertex chunks of a ring: vertex k and its
-// successor for k = lane and k = lane + 64.  Loaded once (coalesced), used for
-// the extent, the area and the leaf edges.
-struct RingRegs {
-  int2 v0, w0, v1, w1;
-};
-
-// The first two chunks of a ring when they are already in registers
-// (vertex lane in v0, vertex lane + 64 in v1, (0, 0) past the end).
-struct Held {
-  bool have;
-  int2 v0, v1;
-};
-
 // The value of the next lane (DPP wave shift left by one; lane 63 reads 0).
 __device__ __forceinline__ int2 next_lane(int2 v) {
   return make_int2(__builtin_amdgcn_update_dpp(0, v.x, 0x130, 0xf, 0xf, false),
@@ -254,183 +240,6 @@ struct RingStream {
     return true;
   }
 };
-
-// Load the first two 64-vertex chunks of a ring with one coalesced load each;
-// each vertex's successor comes from the neighbouring lane, lane 63's from
-// the next chunk, and the last vertex's is vertex 0.
-__device__ __forceinline__ void load_ring2(const int2* xy, int64_t o, int nv, int lane, RingRegs& r,
-                                           int2& first, const Held& pre) {
-  const int k0 = lane, k1 = lane + kWave;
-  r.v0 = pre.have ? pre.v0 : (k0 < nv ? xy[o + k0] : make_int2(0, 0));
-  r.v1 = pre.have ? pre.v1 : (k1 < nv ? xy[o + k1] : make_int2(0, 0));
-  first = lane_value(r.v0, 0);
-  const int2 a64 = nv > kWave ? lane_value(r.v1, 0) : first;
-  const int2 a128 = nv > 2 * kWave ? xy[o + 2 * kWave] : first;
-  int2 s0 = next_lane(r.v0), s1 = next_lane(r.v1);
-  if (lane == kWave - 1) {
-    s0 = a64;
-    s1 = a128;
-  }
-  if (k0 + 1 == nv) s0 = first;
-  if (k1 + 1 == nv) s1 = first;
-  r.w0 = s0;
-  r.w1 = s1;
-}
-
-// Extent and |shoelace|/2 of one ring (Section 3.2's area formula), reduced
-// across the wave.  Lanes past the end of the ring stand at the first vertex:
-// they leave the extent alone and add a zero shoelace term.  The terms use
-// coordinates relative to the first vertex in wrapping 32-bit arithmetic with
-// 24-bit multiplies, which is exact when the extent is below 2^14 on both
-// axes (twice the area is then below 2^29); a wider ring has its area summed
-// again in 64 bits.  Empty rings and rings with |coordinate| > 2^30 come back
-// empty.
-__device__ __forceinline__ void ring_extent(const int2* xy, int64_t o, int64_t nv64, int lane, RingRegs& r, Meta& m,
-                                            int64_t& area, const Held& pre = Held{false, {0, 0}, {0, 0}}) {
-  const int nv = uniform((int)nv64);
-  int2 first;
-  load_ring2(xy, o, nv, lane, r, first, pre);
-  int x0, y0, x1, y1;
-  uint32_t twice;
-  {
-    const bool ok = lane < nv;
-    const int vx = ok ? r.v0.x : first.x, vy = ok ? r.v0.y : first.y;
-    x0 = x1 = vx;
-    y0 = y1 = vy;
-    const int dx = vx - first.x, dy = vy - first.y;
-    twice = (uint32_t)__mul24(dx, r.w0.y - first.y) - (uint32_t)__mul24(r.w0.x - first.x, dy);
-  }
-  if (nv > kWave) {
-    const bool ok = lane + kWave < nv;
-    const int vx = ok ? r.v1.x : first.x, vy = ok ? r.v1.y : first.y;
-    x0 = min(x0, vx);
-    y0 = min(y0, vy);
-    x1 = max(x1, vx);
-    y1 = max(y1, vy);
-    const int dx = vx - first.x, dy = vy - first.y;
-    twice += (uint32_t)__mul24(dx, r.w1.y - first.y) - (uint32_t)__mul24(r.w1.x - first.x, dy);
-  }
-  if (nv > 2 * kWave) {
-    RingStream rs(xy, o, nv, lane, 2 * kWave, &first);
-#pragma unroll 1
-    do {
-      rs.ahead();
-      const int2 w = rs.succ();
-      const bool ok = rs.valid();
-      const int vx = ok ? rs.cur.x : first.x, vy = ok ? rs.cur.y : first.y;
-      x0 = min(x0, vx);
-      y0 = min(y0, vy);
-      x1 = max(x1, vx);
-      y1 = max(y1, vy);
-      const int dx = vx - first.x, dy = vy - first.y;
-      twice += (uint32_t)__mul24(dx, w.y - first.y) - (uint32_t)__mul24(w.x - first.x, dy);
-    } while (rs.next());
-  }
-  m.x0 = wave_min_i32(x0);
-  m.y0 = wave_min_i32(y0);
-  m.x1 = wave_max_i32(x1);
-  m.y1 = wave_max_i32(y1);
-  const int32_t t = (int32_t)wave_sum_u32(twice);
-  if (side_u(m.x0, m.x1) < 16384u && side_u(m.y0, m.y1) < 16384u) {
-    area = (int64_t)(t < 0 ? -(int64_t)t : (int64_t)t) / 2;
-  } else {
-    uint64_t tw = 0;
-    RingStream rs(xy, o, nv, lane);
-#pragma unroll 1
-    do {
-      rs.ahead();
-      const int2 w = rs.succ();
-      if (rs.valid()) tw += (uint64_t)((int64_t)rs.cur.x * w.y) - (uint64_t)((int64_t)w.x * rs.cur.y);
-    } while (rs.next());
-    // twice the area is at most 2^63 in size, so the magnitude of the wrapped
-    // sum is exact in unsigned form
-    const uint64_t t64 = wave_sum_u64(tw);
-    area = (int64_t)(((int64_t)t64 < 0 ? 0 - t64 : t64) / 2);
-  }
-  if (nv <= 0 || m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord) {
-    m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};  // covers nothing
-    area = 0;
-  }
-}
-
-// The same extent and area for the prepass of listed (long) rings: each
-// lane loads its vertices and their successors directly, kScanBatch chunks
-// of 64 per round trip, so that a long ring costs few memory latencies (four:
-// the prepass shares its kernel with the medium sweep, whose computation
-// hides them).
-constexpr int kScanBatch = 4;
-__device__ __forceinline__ void ring_scan(const int2* xy, int64_t o, int64_t nv64, int lane, Meta& m, int64_t& area) {
-  const int nv = uniform((int)nv64);
-  m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};  // covers nothing
-  area = 0;
-  if (nv <= 0) return;
-  const int2* R = xy + o;
-  const int2 f = R[0];
-  int x0 = f.x, y0 = f.y, x1 = f.x, y1 = f.y;
-  uint32_t twice = 0;  // relative to the first vertex, wrapping (exact for extents below 2^14)
-#pragma unroll 1
-  for (int base = 0; base < nv; base += kScanBatch * kWave) {
-    int2 v[kScanBatch], w[kScanBatch];
-#pragma unroll
-    for (int c = 0; c < kScanBatch; ++c) {
-      v[c] = w[c] = f;
-      if (base + c * kWave < nv) {
-        const int k = base + c * kWave + lane;
-        v[c] = R[min(k, nv - 1)];
-        w[c] = R[k + 1 < nv ? k + 1 : 0];
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < kScanBatch; ++c) {
-      if (base + c * kWave + lane < nv) {
-        x0 = min(x0, v[c].x);
-        y0 = min(y0, v[c].y);
-        x1 = max(x1, v[c].x);
-        y1 = max(y1, v[c].y);
-        twice += (uint32_t)__mul24(v[c].x - f.x, w[c].y - f.y) - (uint32_t)__mul24(w[c].x - f.x, v[c].y - f.y);
-      }
-    }
-  }
-  m.x0 = wave_min_i32(x0);
-  m.y0 = wave_min_i32(y0);
-  m.x1 = wave_max_i32(x1);
-  m.y1 = wave_max_i32(y1);
-  if (side_u(m.x0, m.x1) < 16384u && side_u(m.y0, m.y1) < 16384u) {
-    const int32_t t = (int32_t)wave_sum_u32(twice);
-    area = (int64_t)(t < 0 ? -(int64_t)t : (int64_t)t) / 2;
-  } else {
-    // twice the area is at most 2^63 in size, so the magnitude of the
-    // wrapped 64-bit sum is exact in unsigned form
-    uint64_t tw = 0;
-#pragma unroll 1
-    for (int base = 0; base < nv; base += kScanBatch * kWave) {
-      int2 v[kScanBatch], w[kScanBatch];
-#pragma unroll
-      for (int c = 0; c < kScanBatch; ++c) {
-        v[c] = w[c] = f;
-        if (base + c * kWave < nv) {
-          const int k = base + c * kWave + lane;
-          v[c] = R[min(k, nv - 1)];
-          w[c] = R[k + 1 < nv ? k + 1 : 0];
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < kScanBatch; ++c)
-        if (base + c * kWave + lane < nv)
-          tw += (uint64_t)((int64_t)v[c].x * w[c].y) - (uint64_t)((int64_t)w[c].x * v[c].y);
-    }
-    const uint64_t t64 = wave_sum_u64(tw);
-    area = (int64_t)(((int64_t)t64 < 0 ? 0 - t64 : t64) / 2);
-  }
-  if (m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord) {
-    m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
-    area = 0;
-  }
-}
-
-__device__ __forceinline__ bool coords_bad(const Meta& m, int64_t nv) {
-  return nv > 0 && m.x0 == INT_MAX;
-}
 
 // The ablations of Section 5.2 (SCCG_F_PIXEL_ONLY, SCCG_F_NO_SEP) count the
 // union directly, over the bounding box of both MBRs, instead of deriving it
@@ -500,46 +309,29 @@ __device__ __forceinline__ void slot_xor(M* slots, int k, uint64_t rr) {
   __hip_atomic_fetch_xor(slots + k, (M)rr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
-// Scatter the leaf edges of one ring into slots[base ..).  The first two
-// 64-vertex chunks come from registers when `r` is given, the rest (or all)
-// from global memory.  With `full` given, edges right of the whole group
-// (they toggle every column) are XORed into *full (per lane) instead of
-// slot 0, so that they do not all hit one LDS address.
-template <typename M>
-__device__ __forceinline__ void scatter_ring(Ctx& c, const int2* xy, int64_t o, int64_t nv, const RingRegs* r,
-                                             int tx0, int ty0, int th, int W, M* slots, int base,
-                                             uint64_t* full = nullptr) {
-  const int lane = c.lane;
+// Scatter the leaf edges of one ring into slots[base ..).  Edges right of the
+// whole group (they toggle every column) are XORed into *full (per lane)
+// instead of slot 0, so that they do not all hit one LDS address.
+__device__ __forceinline__ void scatter_ring(Ctx& c, const int2* xy, int64_t o, int64_t nv, int tx0, int ty0, int th,
+                                             int W, uint64_t* slots, int base, uint64_t* full) {
   const int n = uniform((int)nv);
   uint32_t kept = 0;
-  auto one = [&](int2 v, int2 w, bool ok) {
-    int slot = 0;
-    uint64_t rr = 0;
-    const bool keep = ok && leaf_edge(v, w, tx0, ty0, th, W, slot, rr);
-    if (keep) {
-      if (full && slot == 0)
-        *full ^= rr;
-      else
-        slot_xor(slots, base + slot, rr);
-    }
-    if (c.stats) kept += (uint32_t)__popcll(ballot(keep));
-  };
-  int b0 = 0;
-  int2 first;
-  if (r) {
-    // the first two chunks are in registers
-    one(r->v0, r->w0, lane < n);
-    if (n > kWave) one(r->v1, r->w1, kWave + lane < n);
-    b0 = 2 * kWave;
-    first = lane_value(r->v0, 0);
-  }
-  if (b0 < n) {
-    RingStream rs(xy, o, n, lane, b0, r ? &first : nullptr);
+  if (n > 0) {
+    RingStream rs(xy, o, n, c.lane);
 #pragma unroll 1
     do {
       rs.ahead();
       const int2 w = rs.succ();
-      one(rs.cur, w, rs.valid());
+      int slot = 0;
+      uint64_t rr = 0;
+      const bool keep = rs.valid() && leaf_edge(rs.cur, w, tx0, ty0, th, W, slot, rr);
+      if (keep) {
+        if (slot == 0)
+          *full ^= rr;
+        else
+          slot_xor(slots, base + slot, rr);
+      }
+      if (c.stats) kept += (uint32_t)__popcll(ballot(keep));
     } while (rs.next());
   }
   if (c.stats) {
@@ -560,61 +352,6 @@ __device__ __forceinline__ M fresh_zero() {
   return (M)(((uint64_t)hi << 32) | lo);
 }
 
-// Intersection count of a small pair (box <= 64 x 64 = one leaf tile).
-// Narrow boxes (w <= 32) run p in lanes 0-31 and q in lanes 32-63 with one
-// scan; short boxes (h <= 32) use 32-bit row masks.
-template <bool kRows64>
-__device__ __forceinline__ int64_t leaf_small(Ctx& c, const PairInfo& pi, const RingRegs& rp, const RingRegs& rq,
-                                              int tw, int th, bool direct) {
-  using M = typename std::conditional<kRows64, uint64_t, uint32_t>::type;
-  const BatchArgs& a = *c.a;
-  const int lane = c.lane;
-  const int tx0 = pi.box.x0, ty0 = pi.box.y0;
-  M* slots = reinterpret_cast<M*>(c.slots);
-  uint32_t n = 0, nu = 0;
-  if (tw <= 32) {
-    slots[lane] = fresh_zero<M>();
-    wave_sync_lds();
-    scatter_ring(c, a.A.xy, pi.op, pi.np, &rp, tx0, ty0, th, 32, slots, 0);
-    scatter_ring(c, a.B.xy, pi.oq, pi.nq, &rq, tx0, ty0, th, 32, slots, 32);
-    wave_sync_lds();
-    const M m = wave_prefix_xor<true>(slots[lane]);
-    // lanes 0-31 hold p's columns, lanes 32-63 q's: bring q's beside p's
-    M mq;
-    if (kRows64) {
-      const uint64_t m64 = (uint64_t)m;
-      const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)m64, 32, kWave);
-      const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(m64 >> 32), 32, kWave);
-      mq = (M)(((uint64_t)hi << 32) | lo);
-    } else {
-      mq = (M)(uint32_t)__shfl_xor((int)(uint32_t)m, 32, kWave);
-    }
-    if (lane < 32 && 31 - lane < tw) {
-      n = (uint32_t)__popcll((uint64_t)(m & mq));
-      nu = (uint32_t)__popcll((uint64_t)(m | mq));
-    }
-  } else {
-    slots[lane] = fresh_zero<M>();
-    slots[kWave + lane] = fresh_zero<M>();
-    wave_sync_lds();
-    scatter_ring(c, a.A.xy, pi.op, pi.np, &rp, tx0, ty0, th, kWave, slots, 0);
-    scatter_ring(c, a.B.xy, pi.oq, pi.nq, &rq, tx0, ty0, th, kWave, slots, kWave);
-    wave_sync_lds();
-    const M mp = wave_prefix_xor<false>(slots[lane]);
-    const M mq = wave_prefix_xor<false>(slots[kWave + lane]);
-    if (kWave - 1 - lane < tw) {
-      n = (uint32_t)__popcll((uint64_t)(mp & mq));
-      nu = (uint32_t)__popcll((uint64_t)(mp | mq));
-    }
-  }
-  wave_sync_lds();
-  if (c.stats) {
-    stat_add(c, 1, 1ull);
-    stat_add(c, 0, 2ull * (unsigned long long)tw * th);
-  }
-  return (int64_t)pack_counts(n, nu, direct);
-}
-
 // Pixels of the tile [tx0, tx0+tw) x [ty0, ty0+th) inside both polygons; a
 // polygon known to contain the tile is not scattered (all rows set).
 __device__ __forceinline__ uint64_t leaf_count(Ctx& c, const PairInfo& pi, int tx0, int ty0, int tw, int th, bool kp,
@@ -626,8 +363,8 @@ __device__ __forceinline__ uint64_t leaf_count(Ctx& c, const PairInfo& pi, int t
   slots[kWave + lane] = fresh_zero<uint64_t>();
   wave_sync_lds();
   uint64_t fp = 0, fq = 0;
-  if (!kp) scatter_ring(c, a.A.xy, pi.op, pi.np, (const RingRegs*)nullptr, tx0, ty0, th, kWave, slots, 0, &fp);
-  if (!kq) scatter_ring(c, a.B.xy, pi.oq, pi.nq, (const RingRegs*)nullptr, tx0, ty0, th, kWave, slots, kWave, &fq);
+  if (!kp) scatter_ring(c, a.A.xy, pi.op, pi.np, tx0, ty0, th, kWave, slots, 0, &fp);
+  if (!kq) scatter_ring(c, a.B.xy, pi.oq, pi.nq, tx0, ty0, th, kWave, slots, kWave, &fq);
   wave_sync_lds();
   const uint64_t full = row_range(0, th);
   const uint64_t mp = kp ? full : wave_prefix_xor<false>(slots[lane]) ^ wave_xor64(fp);
@@ -1067,12 +804,20 @@ __device__ __forceinline__ int lpt_bucket(const BatchArgs& a, int64_t n) {
 constexpr int kSweepRing = 2 * kWave;                 // longest ring of the union sweep
 constexpr int kMediumRing = 4 * kWave;                // longest ring of the medium sweep
 constexpr int kSweepWaves = 4;                        // waves per workgroup of the sweep
-constexpr int kSweepRowTiles = 4;                     // widest box (in leaf tiles) the sweep pixelizes
 // Occupancy target of the sweep (waves per SIMD), a build-time tuning knob;
 // the sweep that also counts pair boxes holds more wave-uniform values and
 // runs fewer waves, each with the largest scalar register file.
 #ifndef SCCG_SWEEP_WAVES_PER_EU
 #define SCCG_SWEEP_WAVES_PER_EU 8
+#endif
+#ifndef SCCG_SHARE_RUN
+#define SCCG_SHARE_RUN 1
+#endif
+#ifndef SCCG_TEAM_TILES
+#define SCCG_TEAM_TILES 14
+#endif
+#ifndef SCCG_MEDIUM_WAVES_PER_EU
+#define SCCG_MEDIUM_WAVES_PER_EU 5
 #endif
 #ifndef SCCG_SWEEP_PB_WAVES_PER_EU
 #define SCCG_SWEEP_PB_WAVES_PER_EU 6
@@ -1454,134 +1199,6 @@ __device__ __forceinline__ int64_t ring_area_regs(const int2 (&d)[N], int nr, in
   return (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
 }
 
-// Extent and area of a ring held in registers (see ring_extent_regs and
-// ring_area_regs); an empty or rejected ring has area 0, and a rejected one
-// sets `bad`.
-template <int N>
-__device__ __forceinline__ void ring_meta_regs(const int2 (&d)[N], int nr, int lane, Meta& m, int64_t& area,
-                                               bool& bad) {
-  bad = ring_extent_regs(d, nr, m);
-  area = nr > 0 && !bad ? ring_area_regs(d, nr, lane, m) : 0;
-}
-
-// Count of a pair box [bx0, bx1) x [by0, by1) at most kSweepRowTiles leaf
-// tiles wide, from the rings in registers: the vertex form of the crossing
-// test (see union_counts) with the box clipping it.  A corner left of the
-// box toggles none of its columns and one right of it all of them; a corner
-// below a band row of the box sets all of the band's rows and one above it
-// none.  Each band row is laid out as in leaf_rows: the columns of both
-// rings in one slot array each, tiles scanned right to left with the XOR of
-// the tiles to their right carried.  kQ: q's first slot (p's is slot 0); a
-// box gx tiles wide uses slots [0, gx kWave) and [kQ, kQ + gx kWave).
-template <int N, int kQ = kSweepRowTiles * kWave>
-__device__ __forceinline__ uint64_t sweep_rows(Ctx& c, const PairRegs<N>& r, int np, int nq, const Meta& box) {
-  const int lane = c.lane;
-  const int bw = box.x1 - box.x0, bh = box.y1 - box.y0;
-  const int gx = (bw + kTile - 1) / kTile, gy = (bh + kTile - 1) / kTile;
-  const int wpad = gx * kTile;
-  // per vertex: its slot position when it is a corner right of the box's
-  // left side, else -1
-  int posp[N], posq[N];
-  {
-    uint64_t cm[N];
-    ring_corners(r.p, np, cm);
-#pragma unroll
-    for (int ch = 0; ch < N; ++ch) {
-      const int dx = min(r.p[ch].x, box.x0 + wpad) - box.x0;
-      posp[ch] = lane_in(cm[ch]) && dx > 0 ? wpad - dx : -1;
-    }
-    ring_corners(r.q, nq, cm);
-#pragma unroll
-    for (int ch = 0; ch < N; ++ch) {
-      const int dx = min(r.q[ch].x, box.x0 + wpad) - box.x0;
-      posq[ch] = lane_in(cm[ch]) && dx > 0 ? kQ + wpad - dx : -1;
-    }
-  }
-  uint64_t* slots = c.slots;
-  uint32_t ni = 0;
-#pragma unroll 1
-  for (int j = 0; j < gy; ++j) {
-    const int ry0 = box.y0 + kTile * j, th = min(kTile, box.y1 - ry0);
-    const uint64_t full = row_range(0, th);
-#pragma unroll 1
-    for (int b = 0; b < gx; ++b) {
-      slots[b * kWave + lane] = fresh_zero<uint64_t>();
-      slots[kQ + b * kWave + lane] = fresh_zero<uint64_t>();
-    }
-    wave_sync_lds();
-#pragma unroll
-    for (int ch = 0; ch < N; ++ch) {
-      if (ch * kWave < np) {
-        const int ty = min(r.p[ch].y, ry0 + kTile) - ry0;
-        if (posp[ch] >= 0 && ty < kTile) slot_xor(slots, posp[ch], ty <= 0 ? ~0ull : ~0ull << ty);
-      }
-      if (ch * kWave < nq) {
-        const int ty = min(r.q[ch].y, ry0 + kTile) - ry0;
-        if (posq[ch] >= 0 && ty < kTile) slot_xor(slots, posq[ch], ty <= 0 ? ~0ull : ~0ull << ty);
-      }
-    }
-    wave_sync_lds();
-    uint64_t carry_p = 0, carry_q = 0;
-#pragma unroll 1
-    for (int i = gx - 1; i >= 0; --i) {
-      const int b = gx - 1 - i;
-      const uint64_t xp = wave_prefix_xor<false>(slots[b * kWave + lane]);
-      const uint64_t xq = wave_prefix_xor<false>(slots[kQ + b * kWave + lane]);
-      const int tw = min(kTile, bw - kTile * i);
-      if (kWave - 1 - lane < tw) ni += (uint32_t)__popcll((xp ^ carry_p) & (xq ^ carry_q) & full);
-      carry_p ^= (uint64_t)readlane64((int64_t)xp, kWave - 1);
-      carry_q ^= (uint64_t)readlane64((int64_t)xq, kWave - 1);
-    }
-    wave_sync_lds();
-  }
-  if (c.stats) {
-    stat_add(c, 1, (unsigned long long)gx * gy);
-    stat_add(c, 0, 2ull * (unsigned long long)bw * bh);
-    stat_add(c, 10, (unsigned long long)(np + nq) * gy);
-  }
-  return wave_sum_u32(ni);
-}
-
-// A sweep pair held in registers that the union tile does not take: MBRs and
-// areas, then the pair box (the union box when the union is counted
-// directly).  Returns the pair's class: done (an empty box, or a box side
-// out of range: I and U are final), or small / large (the pair is to be
-// listed for the persistent kernel with `box`, I = 0 and U = |p| + |q|, or 0
-// when the union is counted directly, as the values its boxes add to).
-template <int N>
-__device__ __forceinline__ uint8_t sweep_meta(Ctx& c, const PairRegs<N>& r, int np, int nq, int64_t& I, int64_t& U,
-                                              Meta& box) {
-  const BatchArgs& a = *c.a;
-  Meta mp, mq;
-  int64_t ap, aq;
-  bool bp, bq;
-  ring_meta_regs(r.p, np, c.lane, mp, ap, bp);
-  ring_meta_regs(r.q, nq, c.lane, mq, aq, bq);
-  if (c.lane == 0 && (bp || bq)) latch_error(a.err, kErrCoord);
-  const bool direct = direct_union(a);
-  box = direct ? union_box(mp, mq) : pair_box(mp, mq);
-  I = 0;
-  U = direct ? 0 : ap + aq;
-  if (box.x0 >= box.x1 || box.y0 >= box.y1) {
-    stat_add(c, 12, (unsigned long long)(np + nq));
-    stat_add(c, 7, 1ull);  // empty pair box: nothing in common
-    return kClsDone;
-  }
-  const uint32_t bw = side_u(box.x0, box.x1), bh = side_u(box.y0, box.y1);
-  if (bw > (uint32_t)kMaxSide || bh > (uint32_t)kMaxSide) {
-    if (c.lane == 0) latch_error(a.err, kErrSide);
-    stat_add(c, 12, (unsigned long long)(np + nq));
-    stat_add(c, 7, 1ull);
-    U = 0;
-    return kClsDone;
-  }
-  const bool small = bw <= (uint32_t)kTile && bh <= (uint32_t)kTile;
-  stat_add(c, 12, (unsigned long long)(np + nq));
-  stat_add(c, small ? 5 : 6, 1ull);
-  stat_add(c, 11, (unsigned long long)bw * bh);
-  return small ? kClsSmall : kClsLarge;
-}
-
 // A sweep pair as the setup pass recorded it (wave-uniform), taken from the
 // chunk's records held one per lane.
 struct SweepRec {
@@ -1653,6 +1270,32 @@ __device__ __forceinline__ int64_t claim_chunk(Counter* next, int64_t n, int chu
   }
   return -1;
 }
+
+// The share of n items of one wave of a launch whose workgroups have `per_wg`
+// waves: runs of consecutive items, interleaved over the waves so that all of
+// them work in the same part of the list (rings that neighbouring pairs share
+// stay in the caches), with the waves in an order that puts neighbouring runs
+// on one XCD.  Runs are short where the share is, so that shares differ by
+// little.
+struct WaveShare {
+  int64_t count;  // items of this wave
+  int64_t me, n_waves;
+  int run;
+  __device__ __forceinline__ WaveShare(int64_t n, int per_wg, int w) {
+    const unsigned g = gridDim.x, b = blockIdx.x;
+    const unsigned at = g % kStreams == 0 ? (b % kStreams) * (g / kStreams) + b / kStreams : b;
+    n_waves = uniform64((int64_t)g * per_wg);
+    me = uniform64((int64_t)at * per_wg + w);
+    run = uniform((int)max((int64_t)1, min((int64_t)SCCG_SHARE_RUN, n / (n_waves * 8))));
+    const int64_t round = n_waves * run, full = n / round;
+    count = uniform64(full * run + max((int64_t)0, min((int64_t)run, n - full * round - me * run)));
+  }
+  // the list index of the wave's item k
+  __device__ __forceinline__ int64_t entry(int64_t k) const {
+    const int64_t turn = (int64_t)((uint32_t)k / (uint32_t)run);
+    return (turn * n_waves + me) * run + ((uint32_t)k - (uint32_t)turn * (uint32_t)run);
+  }
+};
 
 // The rings of a sweep pair (lane L: vertices L and 64 + L, clamped to the
 // last), or for any other record a read of `dummy`: the same loads in every
@@ -1791,53 +1434,6 @@ __device__ __forceinline__ void sweep_one_pb(Ctx& c, const SweepRec& s, const Pa
   dmask |= 1ull << j;
 }
 
-// The prepass of a pair the setup pass listed (entry k of its buckets laid
-// end to end, largest first, nb[b] entries in bucket b): one wave reduces
-// the MBRs and areas of both rings and records the pair box and the pair's
-// class; the outputs start at I = 0, U = |p| + |q| (boxes add to I and
-// subtract from U atomically).
-__device__ __forceinline__ void prepass_one(const BatchArgs& a, int64_t k, const int64_t (&nb)[kLptBuckets], int lane,
-                                            bool stats) {
-  int64_t kk = k;
-  int bk = kLptBuckets - 1;
-#pragma unroll
-  for (int b = kLptBuckets - 1; b > 0; --b) {
-    if (bk == b && kk >= nb[b]) {
-      kk -= nb[b];
-      bk = b - 1;
-    }
-  }
-  const int64_t i = a.l_list[(int64_t)bk * a.n_pairs + kk];
-  const int64_t ia = a.pa[i], ib = a.pb[i];
-  const int64_t op = a.A.off[ia], oq = a.B.off[ib];
-  Meta mp, mq;
-  int64_t ap, aq;
-  ring_scan(a.A.xy, op, a.A.off[ia + 1] - op, lane, mp, ap);
-  ring_scan(a.B.xy, oq, a.B.off[ib + 1] - oq, lane, mq, aq);
-  if (lane != 0) return;
-  if (stats) atomicAdd(&a.st->stats[12], (unsigned long long)(a.A.off[ia + 1] - op + a.B.off[ib + 1] - oq));
-  if (coords_bad(mp, a.A.off[ia + 1] - op) || coords_bad(mq, a.B.off[ib + 1] - oq)) latch_error(a.err, kErrCoord);
-  const Meta b = direct_union(a) ? union_box(mp, mq) : pair_box(mp, mq);
-  *reinterpret_cast<int4*>(a.hbox + i) = make_int4(b.x0, b.y0, b.x1, b.y1);
-  const int64_t w = (int64_t)b.x1 - b.x0, h = (int64_t)b.y1 - b.y0;
-  uint8_t cls = kClsDone;
-  a.inter[i] = 0;
-  a.uni[i] = direct_union(a) ? 0 : ap + aq;
-  if (b.x0 >= b.x1 || b.y0 >= b.y1) {
-    cls = kClsDone;
-  } else if (w > kMaxSide || h > kMaxSide) {
-    latch_error(a.err, kErrSide);
-    a.uni[i] = 0;
-  } else {
-    cls = (w <= kTile && h <= kTile) ? kClsSmall : kClsLarge;
-    if (stats) {
-      atomicAdd(&a.st->stats[cls == kClsSmall ? 5 : 6], 1ull);
-      atomicAdd(&a.st->stats[11], (unsigned long long)(w * h));
-    }
-  }
-  a.cls[i] = cls;
-}
-
 // kPairBox: pairs whose union box exceeds a leaf tile are counted on their
 // pair box when it fits one (the same counts as the medium sweep's, without
 // loading the rings again); a separate instance keeps the extra registers
@@ -1861,9 +1457,6 @@ k_batch_sweep(BatchArgs args) {
   const int lane = c.lane;
   const bool union_ok = direct_union(a) || !(a.flags & SCCG_F_NO_UNION_TILE);
   const unsigned long long t_start = wave_stamp(a);
-  // the prepass (run beside the medium sweep) takes the pairs the setup pass
-  // listed: their counts, taken here, before the medium sweep lists more
-  if (blockIdx.x == 0 && threadIdx.x < kLptBuckets) a.st->p_count[threadIdx.x].v = a.st->l_count[threadIdx.x].v;
   // claim streams found exhausted (wave-uniform); a wave claims only from
   // its own XCD's stream (the streams hold equal interleaved shares), so
   // that running dry costs it one claim, not one per stream (a grid too
@@ -1918,20 +1511,333 @@ k_batch_sweep(BatchArgs args) {
   wave_stamps(a, 0, t_start, lane);
 }
 
+// ------------------------------------------------- boxes of several leaf tiles
+// A pair box of at most kTileBox leaf tiles is pixelized whole, from one pass
+// over each ring per stripe of tiles (most boxes are one stripe), by the
+// vertex form of the crossing test (see union_counts) carried across tiles:
+//   - the slots of a stripe hold, per band (64 rows), one 64-bit row mask per
+//     column.  A corner XORs the rows of its own band at or above it into its
+//     column's slot of that band only: one LDS atomic per vertex, however tall
+//     the box is.  In the bands above it the corner toggles every row, which
+//     the scan recovers by itself: the top row of a column's parities in one
+//     band is what the rows of the next band start from.
+//   - a lane owns `cols` neighbouring columns of a band (cols = the stripe's
+//     width in tiles), so that one 64-lane scan serves the whole row: it XORs
+//     its columns up, the lanes scan their totals, and each column takes the
+//     scan's offset and the carry from the band below.  Per 64x64 tile and
+//     ring that is about 7 + 14 / cols vector instructions; a scan per tile
+//     took 24 and its carries.
+//   - corners left of the stripe toggle none of its columns, those right of
+//     it all of them; those below it count as standing in its first row, those
+//     above it not at all.  So stripes are independent of each other, and a
+//     pixel of the last tiles past the pair box lies outside MBR(p) or MBR(q)
+//     and adds nothing to the intersection.
+// Column k of lane L stands at position L cols + k from the right and at slot
+// (band cols + k) 64 + L, which every lane reads without bank conflicts.
+// Measured: 8191 pairs of merged blobs (530 vertices a ring, boxes of about
+// 4 x 4 tiles) 1562 -> 76 us and 15,724 five-fold scaled pairs 561 -> 51 us,
+// against tiles scattered one by one, or a band row at a time, from rings
+// streamed anew for each.
+constexpr int kTileBox = 64;   // most leaf tiles of a box pixelized this way
+constexpr int kMaxCols = 8;    // widest stripe, in tiles
+// A box is classified instead (Lemma 1, in the persistent kernel) when the
+// caller asks for it from fewer tiles than the default.
+constexpr int kDefaultClassifyCells = 26;
+__device__ __forceinline__ bool tile_box(const BatchArgs& a, int gx, int gy) {
+  const int t = gx * gy;
+  return t == 1 || (t <= kTileBox && (t < a.min_classify_cells || a.min_classify_cells >= kDefaultClassifyCells));
+}
+
+// Extents of a lane's vertices, minima and complemented maxima, so that all
+// four reduce by minimum.
+struct Ext {
+  int x0, y0, nx1, ny1;
+};
+// Wave minimum of four values at once: two half swaps and a row swap leave
+// each value in one row of 16 lanes, which four row steps reduce together.
+__device__ __forceinline__ Ext wave_min4(const Ext& e) {
+  const auto s0 = __builtin_amdgcn_permlane32_swap(e.x0, e.y0, false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(e.nx1, e.ny1, false, false);
+  const int a = min((int)s0[0], (int)s0[1]), b = min((int)s1[0], (int)s1[1]);
+  const auto s2 = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  int x = min((int)s2[0], (int)s2[1]);
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0xb1, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x4e, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x141, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x140, 0xf, 0xf, false));
+  return Ext{__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 16),
+             __builtin_amdgcn_readlane(x, 48)};
+}
+
+// Extents, doubled area and corners of a ring of nr (>= 1) vertices held in N
+// chunks of 64 (lanes past the end hold the last vertex again).  f: its first
+// vertex; carry: whether the closing edge is vertical.  tn gains twice the signed area, summed as (x + x') (y' - y) over the edges with x
+// relative to f, modulo 2^32: exact for a ring at most kMaxSide wide and
+// tall.  Returns the corners, vertices with exactly one vertical edge: bit c
+// for the lane's vertex of chunk c (kept per lane: N wave-wide masks are more
+// scalar registers than there are).
+template <int N>
+__device__ __forceinline__ uint32_t ring_pass(const int2 (&d)[N], int nr, int lane, int2 f, uint32_t carry, Ext& e,
+                                              uint32_t& tn) {
+  uint32_t corners = 0;
+  const int nc = (nr + kWave - 1) / kWave, le = (nr - 1) & (kWave - 1);
+#pragma unroll
+  for (int c = 0; c < N; ++c) {
+    if (c < nc) {
+      const bool last = c == nc - 1;
+      const int2 n0 = lane_value(d[c + 1 < N ? c + 1 : c], 0);
+      const int2 nx = last ? f : n0;
+      int sx = __builtin_amdgcn_update_dpp(nx.x, d[c].x, 0x130, 0xf, 0xf, false);  // the next lane's
+      int sy = __builtin_amdgcn_update_dpp(nx.y, d[c].y, 0x130, 0xf, 0xf, false);
+      if (last && le != kWave - 1) {
+        // past the end: edges of no length
+        sx = lane == le ? f.x : lane > le ? d[c].x : sx;
+        sy = lane == le ? f.y : lane > le ? d[c].y : sy;
+      }
+      const uint64_t b = ballot(d[c].x == sx);
+      corners |= lane_in((b ^ ((b << 1) | carry)) & (last ? ~0ull >> (kWave - 1 - le) : ~0ull)) ? 1u << c : 0u;
+      carry = (uint32_t)(b >> (kWave - 1));
+      e.x0 = min(e.x0, d[c].x);
+      e.y0 = min(e.y0, d[c].y);
+      e.nx1 = min(e.nx1, ~d[c].x);
+      e.ny1 = min(e.ny1, ~d[c].y);
+      tn += (uint32_t)__mul24((int)((uint32_t)d[c].x + (uint32_t)sx - 2u * (uint32_t)f.x),
+                              (int)((uint32_t)sy - (uint32_t)d[c].y));
+    }
+  }
+  return corners;
+}
+
+// |shoelace|/2 of a ring wider or taller than kMaxSide, streamed: summed
+// modulo 2^64, in which twice the area (at most 2^63 in size) is exact.
+__device__ __forceinline__ int64_t ring_area_wide(const int2* xy, int64_t o, int nv, int lane) {
+  uint64_t tw = 0;
+  RingStream rs(xy, o, nv, lane);
+#pragma unroll 1
+  do {
+    rs.ahead();
+    const int2 w = rs.succ();
+    if (rs.valid()) tw += (uint64_t)((int64_t)rs.cur.x * w.y) - (uint64_t)((int64_t)w.x * rs.cur.y);
+  } while (rs.next());
+  const uint64_t t = wave_sum_u64(tw);
+  return (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
+}
+
+// Extent and area of a non-empty ring from its lanes' extents and doubled
+// areas (see ring_pass).  A ring with a coordinate beyond 2^30 sets `bad` and
+// covers nothing.
+__device__ __forceinline__ void ring_meta(const int2* xy, int64_t o, int nv, int lane, const Ext& lanes, uint32_t tn,
+                                          Meta& m, int64_t& area, bool& bad) {
+  const Ext r = wave_min4(lanes);
+  m = Meta{r.x0, r.y0, ~r.nx1, ~r.ny1};
+  bad = m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord;
+  if (bad) {
+    m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
+    area = 0;
+  } else if (side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide) {
+    const int32_t t = (int32_t)wave_sum_u32(tn);
+    area = (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
+  } else {
+    area = ring_area_wide(xy, o, nv, lane);
+  }
+}
+
+// A stripe of tiles: `cols` tiles wide from x0, `bands` of 64 rows from y0.
+struct Stripe {
+  int x0, y0, cols, bands;
+  uint32_t inv;  // ceil(2^16 / cols): position / cols = (position inv) >> 16 below 512
+};
+
+// XOR the end (x, y) of a vertical edge into the stripe's slots, when `take`.
+__device__ __forceinline__ void stripe_xor(uint64_t* slots, int2 v, bool take, const Stripe& s) {
+  const int wpad = s.cols * kTile, sh = s.bands * kTile;
+  const int dx = min(v.x, s.x0 + wpad) - s.x0;
+  const int ty = max(min(v.y, s.y0 + sh) - s.y0, 0);
+  const uint32_t pos = (uint32_t)(wpad - dx);
+  const uint32_t q = __umul24(pos, s.inv) >> 16;
+  const uint32_t at = __umul24((uint32_t)ty >> 6, (uint32_t)wpad) + (pos << 6) - __umul24(q, (uint32_t)(wpad - 1));
+  if (take & (dx > 0) & (ty < sh)) slot_xor(slots, (int)at, ~0ull << (ty & 63));
+}
+// The corners of a ring in registers (see ring_pass).
+template <int N>
+__device__ __forceinline__ void stripe_scatter(uint64_t* slots, const int2 (&d)[N], uint32_t corners, int nr,
+                                               const Stripe& s) {
+  // made anew for each stripe: tests of the chunks and corners that the
+  // compiler hoists out of the stripes' loop are dozens of spilled registers
+  asm volatile("" : "+v"(corners), "+s"(nr));
+#pragma unroll
+  for (int c = 0; c < N; ++c)
+    if (c * kWave < nr) stripe_xor(slots, d[c], (corners >> c) & 1u, s);
+}
+// A longer ring, streamed: both ends of every vertical edge.
+__device__ __forceinline__ void stripe_stream(uint64_t* slots, const int2* xy, int64_t o, int nv, int lane,
+                                              const Stripe& s) {
+  RingStream rs(xy, o, nv, lane);
+#pragma unroll 1
+  do {
+    rs.ahead();
+    const int2 w = rs.succ();
+    const bool vertical = rs.valid() && rs.cur.x == w.x;
+    stripe_xor(slots, rs.cur, vertical, s);
+    stripe_xor(slots, w, vertical, s);
+  } while (rs.next());
+}
+
+// The scan of one band of one ring: what every column of the lane takes from
+// the lanes right of it.  The columns' slots are read twice, here and by the
+// caller: held in registers they cost the kernel a wave per SIMD.
+template <int C>
+__device__ __forceinline__ uint64_t band_offset(const uint64_t* s, int lane) {
+  uint64_t t = s[lane];
+#pragma unroll
+  for (int k = 1; k < C; ++k) t ^= s[k * kWave + lane];
+  t ^= wave_prefix_xor<false>(t);
+  asm volatile("" ::: "memory");  // or the compiler keeps the slots in registers after all
+  return t;
+}
+// A column's parities from the slots up to it and its carry, which holds all
+// ones when the row below the band is inside, and then the band's top row.
+__device__ __forceinline__ uint64_t column_parities(uint64_t run, uint32_t& carry) {
+  const uint32_t lo = (uint32_t)run ^ carry, hi = (uint32_t)(run >> 32) ^ carry;
+  carry = (uint32_t)((int32_t)hi >> 31);
+  return ((uint64_t)hi << 32) | lo;
+}
+
+// A lane's share of the pixels inside both rings, from both rings' slots.
+template <int C>
+__device__ __forceinline__ uint32_t stripe_count(const uint64_t* sp, const uint64_t* sq, int bands, int lane) {
+  uint32_t cp[C] = {}, cq[C] = {}, n = 0;
+#pragma unroll 1
+  for (int j = 0; j < bands; ++j, sp += C * kWave, sq += C * kWave) {
+    uint64_t p = band_offset<C>(sp, lane), q = band_offset<C>(sq, lane);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      p ^= sp[k * kWave + lane];
+      q ^= sq[k * kWave + lane];
+      n += (uint32_t)__popcll(column_parities(p, cp[k]) & column_parities(q, cq[k]));
+    }
+  }
+  return n;
+}
+// One ring's slots turned into parities in place.
+template <int C>
+__device__ __forceinline__ void stripe_scan(uint64_t* s, int bands, int lane) {
+  uint32_t carry[C] = {};
+#pragma unroll 1
+  for (int j = 0; j < bands; ++j, s += C * kWave) {
+    uint64_t t = band_offset<C>(s, lane);
+#pragma unroll
+    for (int k = 0; k < C; ++k) {
+      t ^= s[k * kWave + lane];
+      s[k * kWave + lane] = column_parities(t, carry[k]);
+    }
+  }
+}
+#define SCCG_BY_COLS(cols, CALL) \
+  switch (cols) {                \
+    case 1: CALL(1); break;      \
+    case 2: CALL(2); break;      \
+    case 3: CALL(3); break;      \
+    case 4: CALL(4); break;      \
+    case 5: CALL(5); break;      \
+    case 6: CALL(6); break;      \
+    case 7: CALL(7); break;      \
+    default: CALL(8); break;     \
+  }
+
+// Calls f(stripe) for the stripes of a box gx x gy tiles large, with room for
+// `cap` tiles and at most `most` columns each.
+template <typename F>
+__device__ __forceinline__ void for_stripes(const Meta& box, int gx, int gy, int cap, int most, F f) {
+  const int nx = (gx + most - 1) / most, cols = (gx + nx - 1) / nx;
+  const int bands = min(cap / cols, gy);
+#pragma unroll 1
+  for (int x = 0; x < gx; x += cols) {
+    const int w = min(cols, gx - x);
+#pragma unroll 1
+    for (int y = 0; y < gy; y += bands)
+      f(Stripe{box.x0 + x * kTile, box.y0 + y * kTile, w, min(bands, gy - y),
+               (uint32_t)((65536 + w - 1) / w)});
+  }
+}
+
+// The intersection counted on a pair box of one leaf tile, from rings whose
+// corners are known: as pair_box_count.  kHalves: the box is at most 32 wide,
+// p's columns in lanes 0-31 and q's in 32-63; M: 32-bit rows when it is at
+// most 32 tall.
+template <bool kHalves, typename M, int N>
+__device__ __forceinline__ uint32_t corner_count(uint64_t* slot_words, const int2 (&p)[N], uint32_t cp, int np,
+                                                 const int2 (&q)[N], uint32_t cq, int nq, const Meta& box, int lane) {
+  constexpr int W = kHalves ? 32 : kWave, R = (int)sizeof(M) * 8;
+  M* slots = reinterpret_cast<M*>(slot_words);
+  slots[lane] = (M)0;
+  if (!kHalves) slots[kWave + lane] = (M)0;
+  wave_sync_lds();
+  auto scatter = [&](const int2(&d)[N], uint32_t corners, int nr, int base) {
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+      if (c * kWave < nr) {
+        const int dx = min(d[c].x, box.x0 + W) - box.x0;
+        const int ty = max(min(d[c].y, box.y0 + R) - box.y0, 0);
+        if ((((corners >> c) & 1u) != 0u) & (dx > 0) & (ty < R)) slot_xor(slots + base + W - dx, 0, (M)(~(M)0 << ty));
+      }
+    }
+  };
+  scatter(p, cp, np, 0);
+  scatter(q, cq, nq, W);
+  wave_sync_lds();
+  uint32_t n;
+  if (kHalves) {
+    const M m = wave_prefix_xor<true>(slots[lane]);
+    const M o = upper_half(m);
+    n = lane < 32 ? (uint32_t)__popcll((uint64_t)(m & o)) : 0u;
+  } else {
+    n = (uint32_t)__popcll((uint64_t)(wave_prefix_xor<false>(slots[lane]) & wave_prefix_xor<false>(slots[kWave + lane])));
+  }
+  wave_sync_lds();
+  return n;
+}
+
 // ------------------------------------------------------------ medium sweep
-// Second pass over the medium list: pairs with rings of at most kMediumRing
-// vertices that the union sweep did not finish (a ring over kSweepRing
-// vertices, a pair box larger than a leaf tile, or, with the union counted
-// directly, a union box larger than one).  MBRs and areas come from the
-// rings in registers; a pair box at most kSweepRowTiles tiles wide is
-// pixelized at once (a box the persistent kernel would not classify), a
-// larger one is listed with its box.  A claim takes 64 consecutive entries.
-// The same kernel runs the prepass of the pairs the setup pass listed: its
-// ring scans wait on memory while the medium pairs compute, so a quarter of
-// the waves start with it and the rest with the medium list, each turning
-// to the other list when its own runs dry.  (Six waves per SIMD, a few registers
-// spilled: at the unconstrained register count only four fit.)
-//
+// Second pass, two kinds of pairs:
+//   - the long pairs the setup pass listed (a ring over kMediumRing vertices,
+//     or at least heavy_verts in all), largest bucket first, two waves per
+//     pair, one per ring: each loads its ring (kLongChunks chunks at once),
+//     reduces its MBR and area, scatters and scans its own slots without
+//     waiting for the other, and both count the tiles; two barriers per
+//     stripe.
+//   - then the medium list: pairs with rings of at most kMediumRing vertices
+//     that the union sweep did not finish (a ring over kSweepRing vertices, a
+//     pair box larger than a leaf tile, or, with the union counted directly,
+//     a union box larger than one), one wave per pair, rings in registers.
+// Both pixelize boxes of up to kTileBox tiles at once; a larger one, one to be
+// classified, or any one when the union is counted directly, is listed with
+// its box for the persistent kernel, I = 0 and U = |p| + |q| (0 when the union
+// is counted directly) as the values its boxes add to.
+// Bound by instruction issue; five waves per SIMD with 14 tiles of slots per
+// ring: four (with 18 tiles) or six (12 tiles, registers spilled) were 3 to 5 %
+// slower on the heavy-tailed mix.
+constexpr int kTeamWaves = 2;    // waves per workgroup: one pair's team, or two waves with a pair each
+constexpr int kLongChunks = 16;  // chunks of a long ring in registers; a longer ring is taken in parts
+constexpr int kTeamTiles = SCCG_TEAM_TILES;   // tiles per ring and stripe of a team
+constexpr int kWaveTiles = kTeamTiles / 2;   // tiles per ring and stripe of a single wave
+static_assert(2 * kWaveTiles <= kTeamTiles && kMaxCols <= kTeamTiles, "the team's slots hold either kind's stripes");
+
+// What the two waves of a team tell each other of their rings.
+struct TeamRing {
+  Meta m;
+  int64_t area;
+  int32_t nv, bad;
+};
+
+// A pair left to the persistent kernel (one lane).
+__device__ __forceinline__ void list_run(const BatchArgs& a, int64_t i, int64_t verts, const Meta& box) {
+  const int bk = lpt_bucket(a, verts);
+  const unsigned long long k = atomicAdd(&a.st->l_count[bk].v, 1ull);
+  a.run_list[(int64_t)bk * a.n_pairs + (int64_t)k] = (int32_t)i;
+  *reinterpret_cast<int4*>(a.hbox + i) = make_int4(box.x0, box.y0, box.x1, box.y1);
+}
+
 // Every chunk of both rings of a medium pair (clamped to each ring's last
 // vertex), or for no pair reads of `dummy`.
 __device__ __forceinline__ void medium_load(const BatchArgs& a, const SweepRec& s, const int2* dummy, int lane,
@@ -1946,45 +1852,219 @@ __device__ __forceinline__ void medium_load(const BatchArgs& a, const SweepRec& 
   }
 }
 
+// What a pair's MBRs and areas make of it: its class, its box and the counts
+// it has before any box is counted.  kClsDone: I and U are final.
+__device__ __forceinline__ uint8_t pair_class(Ctx& c, const Meta& mp, const Meta& mq, int64_t areas, int64_t verts,
+                                              bool bad, bool tell, int64_t& U, Meta& box) {
+  const BatchArgs& a = *c.a;
+  if (tell && bad && c.lane == 0) latch_error(a.err, kErrCoord);
+  const bool direct = direct_union(a);
+  box = direct ? union_box(mp, mq) : pair_box(mp, mq);
+  U = direct ? 0 : areas;
+  if (tell) stat_add(c, 12, (unsigned long long)verts);
+  const bool empty = box.x0 >= box.x1 || box.y0 >= box.y1;
+  const uint32_t bw = side_u(box.x0, box.x1), bh = side_u(box.y0, box.y1);
+  const bool wide = !empty && (bw > (uint32_t)kMaxSide || bh > (uint32_t)kMaxSide);
+  if (wide) {
+    if (tell && c.lane == 0) latch_error(a.err, kErrSide);
+    U = 0;
+  }
+  if (empty || wide) return kClsDone;
+  const bool small = bw <= (uint32_t)kTile && bh <= (uint32_t)kTile;
+  if (tell) {
+    stat_add(c, small ? 5 : 6, 1ull);
+    stat_add(c, 11, (unsigned long long)bw * bh);
+  }
+  return small ? kClsSmall : kClsLarge;
+}
+
 __device__ __forceinline__ void medium_one(Ctx& c, const SweepRec& s, const PairRegs<kMediumChunks>& r, int64_t i) {
   const BatchArgs& a = *c.a;
-  int64_t I = 0, U = 0;
-  Meta box{0, 0, 0, 0};
-  uint8_t cls = sweep_meta(c, r, s.np, s.nq, I, U, box);
-  if (cls != kClsDone && !direct_union(a)) {
+  const int lane = c.lane;
+  Meta mp{INT_MAX, INT_MAX, INT_MIN, INT_MIN}, mq = mp, box;
+  int64_t ap = 0, aq = 0, I = 0, U = 0;
+  bool bp = false, bq = false;
+  auto meta = [&](const int2(&d)[kMediumChunks], const int2* xy, int64_t o, int nv, Meta& m, int64_t& area,
+                  bool& bad) -> uint32_t {
+    if (nv <= 0) return 0;
+    Ext e{d[0].x, d[0].y, ~d[0].x, ~d[0].y};
+    const int2 f = lane_value(d[0], 0);
+    // every chunk is loaded, so the last lane of the last one holds the last vertex
+    uint32_t tn = 0;
+    const uint32_t carry = __builtin_amdgcn_readlane(d[kMediumChunks - 1].x, kWave - 1) == f.x ? 1u : 0u;
+    const uint32_t corners = ring_pass<kMediumChunks>(d, nv, lane, f, carry, e, tn);
+    ring_meta(xy, o, nv, lane, e, tn, m, area, bad);
+    return corners;
+  };
+  const uint32_t cp = meta(r.p, a.A.xy, s.op, s.np, mp, ap, bp);
+  const uint32_t cq = meta(r.q, a.B.xy, s.oq, s.nq, mq, aq, bq);
+  const uint8_t cls = pair_class(c, mp, mq, ap + aq, (int64_t)s.np + s.nq, bp || bq, true, U, box);
+  bool listed = false;
+  if (cls == kClsDone) {
+    stat_add(c, 7, 1ull);  // an empty or rejected box: nothing in common
+  } else {
     const int gx = (box.x1 - box.x0 + kTile - 1) / kTile, gy = (box.y1 - box.y0 + kTile - 1) / kTile;
-    if (gx * gy == 1) {
-      I = (int64_t)pair_box_count(c, r, s.np, s.nq, box);
-      U -= I;
-      cls = kClsDone;
-    } else if (gx <= kSweepRowTiles && gy <= kMaxGrid && gx * gy < a.min_classify_cells) {
-      I = (int64_t)sweep_rows(c, r, s.np, s.nq, box);
-      U -= I;
-      cls = kClsDone;
+    if (direct_union(a) || !tile_box(a, gx, gy)) {
+      listed = true;
+    } else {
+      uint32_t n = 0, passes = 0;
+      const int bw = box.x1 - box.x0, bh = box.y1 - box.y0;
+      if (gx * gy == 1) {
+        passes = 1;
+#define SCCG_CORNERS(HALVES, M) corner_count<HALVES, M>(c.slots, r.p, cp, s.np, r.q, cq, s.nq, box, lane)
+        if (bw <= 32)
+          n = bh <= 32 ? SCCG_CORNERS(true, uint32_t) : SCCG_CORNERS(true, uint64_t);
+        else
+          n = bh <= 32 ? SCCG_CORNERS(false, uint32_t) : SCCG_CORNERS(false, uint64_t);
+#undef SCCG_CORNERS
+      } else {
+        for_stripes(box, gx, gy, kWaveTiles, min(kWaveTiles, kMaxCols), [&](const Stripe& st) {
+          uint64_t* sp = c.slots;
+          uint64_t* sq = c.slots + st.cols * st.bands * kTile;
+#pragma unroll 1
+          for (int t = 0; t < 2 * st.cols * st.bands; ++t) sp[t * kWave + lane] = fresh_zero<uint64_t>();
+          wave_sync_lds();
+          stripe_scatter(sp, r.p, cp, s.np, st);
+          stripe_scatter(sq, r.q, cq, s.nq, st);
+          wave_sync_lds();
+#define SCCG_COUNT(C) n += stripe_count<C>(sp, sq, st.bands, lane)
+          SCCG_BY_COLS(st.cols, SCCG_COUNT)
+#undef SCCG_COUNT
+          wave_sync_lds();
+          passes += 1;
+        });
+      }
+      I = (int64_t)wave_sum_u32(n);
+      if (c.stats) {
+        stat_add(c, 1, (unsigned long long)gx * gy);
+        stat_add(c, 0, 2ull * (unsigned long long)bw * bh);
+        stat_add(c, 10, (unsigned long long)(s.np + s.nq) * passes);
+        stat_add(c, 14, (unsigned long long)(s.np + s.nq) * passes);
+      }
     }
   }
-  if (c.lane == 0) {
+  if (lane == 0) {
     a.inter[i] = I;
-    a.uni[i] = U;
-    if (cls != kClsDone) {
-      const int bk = lpt_bucket(a, (int64_t)s.np + s.nq);
-      const unsigned long long k = atomicAdd(&a.st->l_count[bk].v, 1ull);
-      a.l_list[(int64_t)bk * a.n_pairs + (int64_t)k] = (int32_t)i;
-      *reinterpret_cast<int4*>(a.hbox + i) = make_int4(box.x0, box.y0, box.x1, box.y1);
+    a.uni[i] = U - I;
+    if (listed) {
+      list_run(a, i, (int64_t)s.np + s.nq, box);
       a.cls[i] = cls;
     }
   }
 }
 
+// One long pair, both waves of the team (wave w has ring w).
 template <bool kStats>
-__global__ void __launch_bounds__(kSweepWaves* kWave) __attribute__((amdgpu_waves_per_eu(6))) k_batch_medium(BatchArgs args) {
-  constexpr int kMediumSlots = 2 * kSweepRowTiles * kWave;
-  __shared__ __align__(16) uint64_t medium_slots[kSweepWaves * kMediumSlots];
+__device__ __forceinline__ void long_one(Ctx& c, int64_t i, int w, uint64_t* team_slots, TeamRing* ex) {
+  const BatchArgs& a = *c.a;
+  const int lane = c.lane;
+  const int2* xy = w ? a.B.xy : a.A.xy;
+  const int64_t* off = (w ? a.B.off + a.pb[i] : a.A.off + a.pa[i]);
+  const int64_t o = uniform64(off[0]);
+  const int nv = uniform((int)(off[1] - o));
+  const int2* R = xy + o;
+  uint64_t* slots = team_slots + w * kTeamTiles * kTile;
+  int2 d[kLongChunks];
+  const bool held = nv <= kLongChunks * kWave;
+  Meta m{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
+  int64_t area = 0;
+  bool bad = false;
+  uint32_t corners = 0;
+  if (nv > 0) {
+    Ext e{INT_MAX, INT_MAX, INT_MAX, INT_MAX};
+    uint32_t tn = 0;
+    if (held) {
+#pragma unroll
+      for (int q = 0; q < kLongChunks; ++q)
+        if (q * kWave < nv) d[q] = R[min(q * kWave + lane, nv - 1)];
+      const int x_last = uniform(R[nv - 1].x);
+      const int2 f = lane_value(d[0], 0);
+      corners = ring_pass<kLongChunks>(d, nv, lane, f, x_last == f.x ? 1u : 0u, e, tn);
+    } else {
+      RingStream rs(xy, o, nv, lane);
+      const int2 f = rs.first;
+#pragma unroll 1
+      do {
+        rs.ahead();
+        const int2 v = rs.cur, x = rs.succ();
+        e = Ext{min(e.x0, v.x), min(e.y0, v.y), min(e.nx1, ~v.x), min(e.ny1, ~v.y)};
+        const uint32_t t = (uint32_t)__mul24((int)((uint32_t)v.x + (uint32_t)x.x - 2u * (uint32_t)f.x),
+                                             (int)((uint32_t)x.y - (uint32_t)v.y));
+        tn += rs.valid() ? t : 0u;
+      } while (rs.next());
+    }
+    ring_meta(xy, o, nv, lane, e, tn, m, area, bad);
+  }
+  if (lane == 0) ex[w] = TeamRing{m, area, nv, bad ? 1 : 0};
+  __syncthreads();
+  const TeamRing rp = ex[0], rq = ex[1];
+  Meta box;
+  int64_t U = 0;
+  const int64_t verts = (int64_t)uniform(rp.nv) + uniform(rq.nv);
+  const uint8_t cls = pair_class(c, rp.m, rq.m, rp.area + rq.area, verts, (rp.bad | rq.bad) != 0, w == 0, U, box);
+  box = Meta{uniform(box.x0), uniform(box.y0), uniform(box.x1), uniform(box.y1)};
+  const int gx = (box.x1 - box.x0 + kTile - 1) / kTile, gy = (box.y1 - box.y0 + kTile - 1) / kTile;
+  const bool settled = uniform(cls) == kClsDone;
+  const bool listed = !settled && (direct_union(a) || !tile_box(a, gx, gy));
+  uint32_t n = 0;
+  if (!settled && !listed) {
+    uint32_t passes = 0;
+    for_stripes(box, gx, gy, kTeamTiles, kMaxCols, [&](const Stripe& st) {
+      const int tiles = st.cols * st.bands;
+#pragma unroll 1
+      for (int t = 0; t < tiles; ++t) slots[t * kWave + lane] = fresh_zero<uint64_t>();
+      wave_sync_lds();
+      if (nv > 0) {
+        if (held)
+          stripe_scatter(slots, d, corners, nv, st);
+        else
+          stripe_stream(slots, xy, o, nv, lane, st);
+      }
+      wave_sync_lds();
+#define SCCG_SCAN(C) stripe_scan<C>(slots, st.bands, lane)
+      SCCG_BY_COLS(st.cols, SCCG_SCAN)
+#undef SCCG_SCAN
+      __syncthreads();
+#pragma unroll 1
+      for (int t = w * kWave + lane; t < tiles * kTile; t += kTeamWaves * kWave)
+        n += (uint32_t)__popcll(team_slots[t] & team_slots[kTeamTiles * kTile + t]);
+      __syncthreads();
+      passes += 1;
+    });
+    n = wave_sum_u32(n);
+    if (kStats) {
+      stat_add(c, 14, (unsigned long long)nv * passes);
+      stat_add(c, 10, (unsigned long long)nv * passes);
+      if (w == 0) {
+        stat_add(c, 1, (unsigned long long)gx * gy);
+        stat_add(c, 0, 2ull * (unsigned long long)(box.x1 - box.x0) * (unsigned long long)(box.y1 - box.y0));
+      }
+    }
+    // wave 1's share reaches wave 0 through its entry of the exchange
+    if (w == 1 && lane == 0) ex[1].nv = (int)n;
+    __syncthreads();
+    n += w == 0 ? (uint32_t)uniform(ex[1].nv) : 0u;
+  }
+  if (w == 0 && lane == 0) {
+    a.inter[i] = (int64_t)n;
+    a.uni[i] = U - (int64_t)n;
+    a.cls[i] = cls;
+    if (listed) list_run(a, i, verts, box);
+  }
+}
+
+template <bool kStats>
+__global__ void __launch_bounds__(kTeamWaves* kWave) __attribute__((amdgpu_waves_per_eu(SCCG_MEDIUM_WAVES_PER_EU)))
+k_batch_medium(BatchArgs args) {
+  __shared__ __align__(16) uint64_t team_slots[2 * kTeamTiles * kTile];
+  __shared__ TeamRing ex[2][2];
+  __shared__ int64_t claimed[2];
+  const int w = uniform((int)(threadIdx.x / kWave));
   Ctx c;
   c.a = &args;
   c.stats = kStats;
   c.lane = lane_id();
-  c.slots = medium_slots + (threadIdx.x / kWave) * kMediumSlots;
+  c.slots = team_slots + w * 2 * kWaveTiles * kTile;
   c.local = nullptr;
   c.lsp = 0;
   c.home = 0;
@@ -1992,61 +2072,69 @@ __global__ void __launch_bounds__(kSweepWaves* kWave) __attribute__((amdgpu_wave
   const BatchArgs& a = args;
   const int lane = c.lane;
   const unsigned long long t_start = wave_stamp(a);
-  // the prepass entries (the setup pass's listed pairs, counted by the union
-  // sweep), one per claim
-  int64_t nb[kLptBuckets], n_pre = 0;
+  const uint32_t own = kSweepSteal || gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
+  uint32_t p_empty = own;
+  // the long pairs, bucket after bucket from the largest, one pair per claim;
+  // wave 0 claims the next one while the team works on the one in hand
+  int64_t nb[kLptBuckets], n_long = 0;
 #pragma unroll
   for (int b = 0; b < kLptBuckets; ++b) {
     nb[b] = (int64_t)a.st->p_count[b].v;
-    n_pre += nb[b];
+    n_long += nb[b];
+  }
+  if (n_long > 0) {
+    int64_t next = -1;
+    if (w == 0) next = claim_chunk(a.st->p_next, n_long, 1, c.xcd, lane, p_empty);
+#pragma unroll 1
+    for (int it = 0;; it ^= 1) {
+      if (w == 0) {
+        if (lane == 0) claimed[it] = next;
+        if (next >= 0) next = claim_chunk(a.st->p_next, n_long, 1, c.xcd, lane, p_empty);
+      }
+      __syncthreads();
+      const int64_t k = uniform64(claimed[it]);
+      if (k < 0) break;
+      int64_t kk = k;
+      int bk = kLptBuckets - 1;
+#pragma unroll
+      for (int b = kLptBuckets - 1; b > 0; --b) {
+        if (bk == b && kk >= nb[b]) {
+          kk -= nb[b];
+          bk = b - 1;
+        }
+      }
+      long_one<kStats>(c, uniform64((int64_t)a.l_list[(int64_t)bk * a.n_pairs + kk]), w, team_slots, ex[it]);
+    }
+    __syncthreads();
   }
   const int64_t n_med = (int64_t)a.st->m_count.v;
-  // entries per claim: 64, or fewer when the list gives the grid's waves
-  // less than 8 claims each
-  const int64_t per_wave = n_med / ((int64_t)gridDim.x * kSweepWaves * 8);
-  const int chunk = (int)max((int64_t)1, min((int64_t)kWave, per_wave));
-  const uint32_t own = kSweepSteal || gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
-  uint32_t m_empty = own, p_empty = own;
-  // the first wave of each workgroup starts with the prepass, which waits on
-  // memory, the others with the medium list, which computes; each turns to
-  // the other list when its own runs dry (a quarter of the waves measured
-  // faster than a half, an eighth or none)
-  const bool pre_first = threadIdx.x / kWave == 0;
+  // every wave takes an equal share of the list, in runs of `run` consecutive
+  // entries that interleave over the waves: the pairs are alike enough, and a
+  // claim per few entries left each wave waiting on a counter, the list, the
+  // records and the rings in turn (200,000 uniform pairs, 26,000 of them here:
+  // 74 us with claims)
+  const WaveShare share(n_med, kTeamWaves, w);
 #pragma unroll 1
-  for (int phase = 0; phase < 2; ++phase) {
-    if ((phase == 0) == pre_first) {
+  for (int64_t k0 = 0; k0 < share.count; k0 += kWave) {
+    const int cnt = uniform((int)min((int64_t)kWave, share.count - k0));
+    // lane j: pair index and record of the wave's entry k0 + j
+    const int idx = lane < cnt ? a.m_list[share.entry(k0 + lane)] : 0;
+    const ChunkRecs cr = gather_recs(a, idx, lane < cnt);
+    const int2* dummy = reinterpret_cast<const int2*>(a.rec + __builtin_amdgcn_readfirstlane(idx));
+    // the pair in hand (sc, rc) and the next one (sn, rn), whose loads are in
+    // flight while the pair in hand is processed: every chunk of both rings,
+    // loaded the same way whatever the pair, so that the compiler waits only
+    // for the pair in hand's loads
+    PairRegs<kMediumChunks> rc, rn;
+    SweepRec sc = sweep_rec(cr, 0);
+    medium_load(a, sc, dummy, lane, rc);
 #pragma unroll 1
-      for (;;) {
-        const int64_t k = claim_chunk(a.st->p_next, n_pre, 1, c.xcd, lane, p_empty);
-        if (k < 0) break;
-        prepass_one(a, k, nb, lane, kStats);
-      }
-      continue;
-    }
-#pragma unroll 1
-    for (;;) {
-      const int64_t e0 = claim_chunk(a.st->m_next, n_med, chunk, c.xcd, lane, m_empty);
-      if (e0 < 0) break;
-      const int cnt = uniform((int)min((int64_t)chunk, n_med - e0));
-      // lane j: pair index and record of entry e0 + j
-      const int idx = lane < cnt ? a.m_list[e0 + lane] : 0;
-      const ChunkRecs cr = gather_recs(a, idx, lane < cnt);
-      const int2* dummy = reinterpret_cast<const int2*>(a.rec + __builtin_amdgcn_readfirstlane(idx));
-      // the pair in hand (sc, rc) and the next one (sn, rn), whose loads are in
-      // flight while the pair in hand is processed: every chunk of both rings,
-      // loaded the same way whatever the pair, so that the compiler waits only
-      // for the pair in hand's loads
-      PairRegs<kMediumChunks> rc, rn;
-      SweepRec sc = sweep_rec(cr, 0);
-      medium_load(a, sc, dummy, lane, rc);
-#pragma unroll 1
-      for (int j = 0; j < cnt; ++j) {
-        const SweepRec sn = j + 1 < cnt ? sweep_rec(cr, j + 1) : SweepRec{0, 0, 0, 0, kClsDone};
-        medium_load(a, sn, dummy, lane, rn);
-        medium_one(c, sc, rc, (int64_t)__builtin_amdgcn_readlane(idx, j));
-        sc = sn;
-        rc = rn;
-      }
+    for (int j = 0; j < cnt; ++j) {
+      const SweepRec sn = j + 1 < cnt ? sweep_rec(cr, j + 1) : SweepRec{0, 0, 0, 0, kClsDone};
+      medium_load(a, sn, dummy, lane, rn);
+      medium_one(c, sc, rc, (int64_t)__builtin_amdgcn_readlane(idx, j));
+      sc = sn;
+      rc = rn;
     }
   }
   wave_stamps(a, 1, t_start, lane);
@@ -2107,9 +2195,8 @@ __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args)
         l_empty = l_start;
         continue;
       }
-      pi = heavy_info(a, (int64_t)a.l_list[(int64_t)bucket * a.n_pairs + e]);
+      pi = heavy_info(a, (int64_t)a.run_list[(int64_t)bucket * a.n_pairs + e]);
       const uint8_t cls = a.cls[pi.pair];
-      if (cls == kClsDone) continue;  // settled by the prepass
       have = true;
       if (cls == kClsLarge) task = root_task(pi);
     }
@@ -2215,7 +2302,7 @@ __global__ void __launch_bounds__(256) k_batch_setup(BatchArgs a, int per) {
   const unsigned long long total = scan[255];
   if (tid < kLptBuckets) {
     const unsigned long long nb = (total >> (16 * tid)) & 0xffffull;
-    base_s[tid] = nb ? atomicAdd(&a.st->l_count[tid].v, nb) : 0ull;
+    base_s[tid] = nb ? atomicAdd(&a.st->p_count[tid].v, nb) : 0ull;
   } else if (tid == kLptBuckets) {
     const unsigned long long nm = mscan[255];
     mbase_s = nm ? atomicAdd(&a.st->m_count.v, nm) : 0ull;
@@ -2276,11 +2363,12 @@ int batch_sweep_occupancy(bool pair_box) {
 
 int batch_medium_occupancy() {
   int n = 0;
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_medium<false>, kSweepWaves * kWave, 0);
+  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_batch_medium<false>, kTeamWaves * kWave, 0);
   return e == hipSuccess && n > 0 ? n : 1;
 }
 
 int batch_sweep_waves_per_wg() { return kSweepWaves; }
+int batch_medium_waves_per_wg() { return kTeamWaves; }
 
 hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_grid, bool pair_box, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
@@ -2296,10 +2384,11 @@ hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_gr
     hipLaunchKernelGGL((k_batch_sweep<false, true>), dim3(sweep_grid), b, 0, s, a);
   else
     hipLaunchKernelGGL((k_batch_sweep<false, false>), dim3(sweep_grid), b, 0, s, a);
+  const dim3 bm(kTeamWaves * kWave);
   if (a.stats_on)
-    hipLaunchKernelGGL(k_batch_medium<true>, dim3(medium_grid), b, 0, s, a);
+    hipLaunchKernelGGL(k_batch_medium<true>, dim3(medium_grid), bm, 0, s, a);
   else
-    hipLaunchKernelGGL(k_batch_medium<false>, dim3(medium_grid), b, 0, s, a);
+    hipLaunchKernelGGL(k_batch_medium<false>, dim3(medium_grid), bm, 0, s, a);
   return hipGetLastError();
 }
 

@@ -187,7 +187,7 @@ int ensure_pairs(sccg_ctx* c, int64_t n) {
   int64_t want = n + n / 4 + 1024;
   int r;
   if ((r = grow(c, &c->cls, want, "pair classes")) || (r = grow(c, &c->rec, want, "pair records")) ||
-      (r = grow(c, &c->l_list, want * (kLptBuckets + 1), "pair lists")) || (r = grow(c, &c->hbox, want, "heavy boxes"))) {
+      (r = grow(c, &c->l_list, want * kPairLists, "pair lists")) || (r = grow(c, &c->hbox, want, "heavy boxes"))) {
     c->cap_pairs = 0;
     return r;
   }
@@ -274,7 +274,7 @@ constexpr size_t kNaQueue = na_align(sizeof(BatchState));
 constexpr size_t kNaRec = kNaQueue + na_align(sizeof(unsigned long long) * kNoAllocQueueSlots);
 constexpr size_t kNaHbox = kNaRec + na_align(sizeof(PairRec) * kNoAllocMaxPairs);
 constexpr size_t kNaList = kNaHbox + na_align(sizeof(Meta) * kNoAllocMaxPairs);
-constexpr size_t kNaCls = kNaList + na_align(sizeof(int32_t) * (kLptBuckets + 1) * kNoAllocMaxPairs);
+constexpr size_t kNaCls = kNaList + na_align(sizeof(int32_t) * kPairLists * kNoAllocMaxPairs);
 constexpr size_t kNoAllocBytes = kNaCls + na_align(kNoAllocMaxPairs);
 
 struct NoAllocDevice {
@@ -568,7 +568,8 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   ba.cls = c->cls;
   ba.rec = c->rec;
   ba.l_list = c->l_list;
-  ba.m_list = c->l_list + (size_t)kLptBuckets * (size_t)n_pairs;
+  ba.run_list = c->l_list + (size_t)kLptBuckets * (size_t)n_pairs;
+  ba.m_list = ba.run_list + (size_t)kLptBuckets * (size_t)n_pairs;
   ba.hbox = c->hbox;
   ba.st = c->st;
   ba.queue = c->queue;
@@ -587,7 +588,7 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   if (c->stamps_on) {
     // every wave of the sweeps and of the persistent kernel stamps its start and end
     const int64_t sweep_waves = (int64_t)sweep_grid * batch_sweep_waves_per_wg();
-    const int64_t medium_waves = (int64_t)medium_grid * batch_sweep_waves_per_wg();
+    const int64_t medium_waves = (int64_t)medium_grid * batch_medium_waves_per_wg();
     const int64_t run_waves = (int64_t)grid * c->p.waves_per_wg;
     const int64_t want = std::max(std::max(sweep_waves, medium_waves), run_waves);
     if (want > c->wave_cap) {
@@ -686,7 +687,8 @@ int sccg_area_pairs_noalloc(sccg_ctx* c, const sccg_polys* A, const sccg_polys* 
   ba.rec = reinterpret_cast<PairRec*>(base + kNaRec);
   ba.hbox = reinterpret_cast<Meta*>(base + kNaHbox);
   ba.l_list = reinterpret_cast<int32_t*>(base + kNaList);
-  ba.m_list = ba.l_list + (size_t)kLptBuckets * (size_t)n_pairs;
+  ba.run_list = ba.l_list + (size_t)kLptBuckets * (size_t)n_pairs;
+  ba.m_list = ba.run_list + (size_t)kLptBuckets * (size_t)n_pairs;
   ba.cls = base + kNaCls;
   ba.queue_cap = cap;
   ba.n_queues = nq;

@@ -90,15 +90,17 @@ constexpr int kStreams = 8;
 // setup pass can see): at least 4, 2 or 1 times heavy_verts, and the rest;
 // the persistent kernel claims the largest bucket first.
 constexpr int kLptBuckets = 4;
+// 4-byte list entries per pair: the long pairs' buckets, the persistent
+// kernel's, the medium list
+constexpr int kPairLists = 2 * kLptBuckets + 1;
 
 struct BatchState {
-  Counter l_count[kLptBuckets];            // pairs listed per bucket
+  Counter l_count[kLptBuckets];            // pairs listed for the persistent kernel per bucket
   Counter l_next[kLptBuckets][kStreams];   // per-stream claim counters over each bucket
   Counter s_next[kStreams];   // per-stream claim counters over pair chunks (the sweep)
   Counter m_count;            // medium pairs listed (by the setup pass and the sweep)
-  Counter m_next[kStreams];   // per-stream claim counters over chunks of the medium list
-  Counter p_count[kLptBuckets];  // pairs the setup pass listed per bucket (the prepass's share)
-  Counter p_next[kStreams];      // per-stream claim counters over the prepass's entries
+  Counter p_count[kLptBuckets];  // long pairs listed by the setup pass per bucket
+  Counter p_next[kStreams];      // per-stream claim counters over the long pairs
   Counter q_head[kMaxGrid];   // per-queue ticket counters
   Counter q_tail[kMaxGrid];   // per-queue reservation counters
   unsigned long long stats[kNumStats];
@@ -123,7 +125,8 @@ struct BatchArgs {
   uint32_t* err;
   uint8_t* cls;                  // [n_pairs]
   PairRec* rec;                  // [n_pairs]
-  int32_t* l_list;               // [kLptBuckets][n_pairs] listed pairs, bucket b from b * n_pairs
+  int32_t* l_list;               // [kLptBuckets][n_pairs] long pairs, bucket b from b * n_pairs
+  int32_t* run_list;             // [kLptBuckets][n_pairs] pairs listed for the persistent kernel
   int32_t* m_list;               // [n_pairs] medium pairs, in the order they were listed
   Meta* hbox;                    // [n_pairs] pair box of a listed pair (by pair index)
   BatchState* st;
@@ -160,6 +163,7 @@ int batch_occupancy(int waves_per_wg);
 int batch_sweep_occupancy(bool pair_box);
 int batch_medium_occupancy();
 int batch_sweep_waves_per_wg();
+int batch_medium_waves_per_wg();
 
 // Set-level Jaccard: per-set accumulators (a cache line each), a chunk
 // counter and `grid` workgroups that claim chunks of the pair range.

@@ -1,0 +1,82 @@
+"""Pair boxes of several leaf tiles, counted in stripes of tiles: boxes around
+the stripes' and the path's limits in tiles, rings around the limits of the
+register chunks, against closed forms."""
+
+import numpy as np
+import pytest
+
+import paper_1208_0277_amd as sccg
+from sccg_gen import concat
+from tests.gpu_util import assert_exact, device_workload, run
+from tests.shapes import band_rects, band_ring, rects_area, rects_inter
+
+pytestmark = pytest.mark.gpu
+
+#: extents of the pair box: one and two tiles, one stripe and several of a wave
+#: (7 tiles) and of a team (15 tiles, 8 wide), 64 tiles and just above, flat and tall
+BOXES = [(65, 64), (128, 129), (192, 130), (193, 193), (320, 320), (448, 65), (449, 64), (512, 512), (513, 512), (64, 1024),
+         (130, 960), (1024, 65), (961, 250), (4096, 64), (4100, 60)]
+
+
+def _band_polygon(width, height, verts, slope, dx, dy):
+    """A polygon of about `verts` vertices (4 a band) that spans width x height
+    exactly, its bands shifting left or right over a quarter of its width."""
+    nb = max(1, min(verts // 4, height, max(1, width // 8)))
+    y = [dy + height * k // nb for k in range(nb + 1)]
+    span = width // 4
+    at = [span * k // max(1, nb - 1) if nb > 1 else 0 for k in range(nb)]
+    if slope < 0:
+        at = at[::-1]
+    a = [dx + v for v in at]
+    b = [v + width - (span if nb > 1 else 0) for v in a]
+    return y, a, b
+
+
+def _padded(ring, verts):
+    """The ring with vertices repeated until it has `verts`."""
+    extra = verts - len(ring)
+    return np.repeat(ring, [1 + extra] + [1] * (len(ring) - 1), axis=0).astype(np.int32) if extra > 0 else ring
+
+
+@pytest.mark.parametrize("params", [{}, {"heavy_verts": 16}, {"min_classify_cells": 65, "min_queue_cells": 65},
+                                    {"min_classify_cells": 1}, {"sweep_pair_box": 2}])
+def test_boxes_of_several_tiles(params):
+    ra, rb, expect = [], [], []
+    for k, (w, h) in enumerate(BOXES):
+        for verts in (8, 127, 192, 193, 256, 257, 1024, 1025, 2060):
+            pa = _band_polygon(w + 3, h + 5, verts, 1, -7 - 11 * k, 3 * k - 40)
+            pb = _band_polygon(w + 9, h + 2, verts, -1, -7 - 11 * k + 3, 3 * k - 40 + 5)
+            ra.append(_padded(band_ring(*pa), verts))
+            rb.append(_padded(band_ring(*pb), max(8, verts - 64 * (k % 2))))
+            qa, qb = band_rects(*pa), band_rects(*pb)
+            i = rects_inter(qa, qb)
+            expect.append((i, rects_area(qa) + rects_area(qb) - i))
+    idx = np.arange(len(ra), dtype=np.int32)
+    A, B = concat(ra), concat(rb)
+    assert {192, 193, 256, 257, 1024, 1025} <= set(np.diff(A.off).tolist())
+    c = sccg.Context(0, **params)
+    try:
+        I, U = run(c, device_workload(A, B, idx, idx), sccg.SCCG_BATCHED)
+    finally:
+        c.close()
+    assert_exact(I, U, np.array([e[0] for e in expect]), np.array([e[1] for e in expect]), f"tiles {params}")
+
+
+def test_a_ring_wider_than_an_area_of_32_bits_holds():
+    """A long ring above 32767 pixels a side (its area is summed in 64 bits)
+    against a small one, both as p and as q."""
+    wide = _band_polygon(40000, 50000, 400, 1, -20000, -20000)
+    small = _band_polygon(200, 150, 300, -1, -100, 90)
+    qa, qb = band_rects(*wide), band_rects(*small)
+    i = rects_inter(qa, qb)
+    u = rects_area(qa) + rects_area(qb) - i
+    for pad in (400, 1300):
+        A = concat([_padded(band_ring(*wide), pad), _padded(band_ring(*small), 300)])
+        B = concat([_padded(band_ring(*small), 300), _padded(band_ring(*wide), pad)])
+        idx = np.arange(2, dtype=np.int32)
+        c = sccg.Context(0)
+        try:
+            I, U = run(c, device_workload(A, B, idx, idx), sccg.SCCG_BATCHED)
+        finally:
+            c.close()
+        assert_exact(I, U, np.array([i, i]), np.array([u, u]), f"wide ring of {pad} vertices")
