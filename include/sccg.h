@@ -112,7 +112,8 @@ typedef struct {
   int32_t box_threshold;  /* PLAIN: pixelize when BOXSIZE < T (default wg_size^2/2, Section 3.4)     */
   int32_t split_gx;       /* PLAIN: sub-box grid; split_gx*split_gy == wg_size (default square-ish) */
   int32_t split_gy;
-  int32_t queue_chunk;    /* BATCHED: pairs claimed per counter access, 1..64 (default 16)            */
+  int32_t queue_chunk;    /* BATCHED: most consecutive pairs a wave of the first sweep takes, 1..64
+                             (default 16)                                                            */
   int32_t lds_vertex_cap; /* PLAIN: vertices of both rings staged in LDS, 1..4096 (default 1024; above
                              it the rings are read from global memory)                               */
   uint32_t flags;         /* SCCG_F_*                                                                 */
@@ -123,11 +124,13 @@ typedef struct {
   int32_t min_queue_cells;/* BATCHED: a split publishes its boxes to the queue only when at least this
                              many continue (default 8); fewer stay with the splitting wave          */
   int32_t n_queues;       /* BATCHED: device queues, 1..8 (default 8, one per XCD)                   */
-  int32_t heavy_verts;    /* BATCHED: pairs with at least this many vertices (both rings) are claimed
-                             first and may share their boxes through the queue (default 512)        */
+  int32_t heavy_verts;    /* BATCHED: pairs with at least this many vertices (both rings) are taken
+                             largest first, by two waves each (default 512)                         */
   int32_t min_classify_cells; /* BATCHED: a split into 64-pixel leaf tiles classifies its tiles (Lemma
                              1) only when it has at least this many, 1..65; a smaller split pixelizes
-                             every tile of a polygon not known to contain it (default 26)           */
+                             every tile of a polygon not known to contain it (default 26).  A pair box
+                             of at most 64 tiles is pixelized whole, in few passes over the rings,
+                             when it has fewer tiles than this or this is at least the default      */
   int32_t sweep_pair_box; /* BATCHED: 2 = the union sweep also counts, on its pair box MBR(p) ∩ MBR(q)
                              (Section 3.2), a pair whose union box exceeds a 64 x 64 leaf tile but
                              whose pair box fits one, from the rings it already holds; pays on mixes
@@ -235,7 +238,7 @@ int sccg_host_area_pairs(const sccg_polys* A, const sccg_polys* B, int64_t n_pai
  * BATCHED mode of sccg_area_pairs, with the same arguments and the same
  * results, that calls no hipMalloc, hipFree or other allocating routine.
  * Its scratch (batched state, task queues, per-pair records and lists) is a
- * static device array of about 19 MiB that every GPU the library runs on
+ * static device array of about 17 MiB that every GPU the library runs on
  * holds until the process ends; its device address is taken once per device
  * by sccg_create.  Limits: at most 2^18 = 262144 pairs per call (more gives
  * SCCG_E_ARG with a message naming the limit), task queues of at most 2^17
@@ -281,11 +284,11 @@ int sccg_sync(sccg_ctx* ctx);
  *       PLAIN, sub-boxes x ring edges tested
  *   [10] ring edges read while staging leaf tiles (BATCHED)
  *   [11] covered pixels: sum of the non-empty pair-box areas (BATCHED)
- *   [12] vertices reduced for MBRs and areas: by the prepass of listed pairs
- *        and by the medium sweep (BATCHED)
+ *   [12] vertices reduced for MBRs and areas, of pairs not counted on their
+ *        union tile (BATCHED)
  *   [13] vertices reduced for union boxes only, of pairs counted on one leaf tile (BATCHED)
- *   [14] leaf vertex updates: vertices XORed into a leaf slot by the union
- *        tile's vertex form of the crossing test (BATCHED)
+ *   [14] leaf vertex updates: vertices XORed into leaf slots by the vertex
+ *        form of the crossing test, once per stripe of tiles (BATCHED)
  * Writes min(n, 16) values to out; returns that count (or an error < 0). */
 int sccg_set_stats(sccg_ctx* ctx, int enable);
 int sccg_get_stats(sccg_ctx* ctx, int64_t* out, int n);

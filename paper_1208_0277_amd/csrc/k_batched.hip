@@ -1,4 +1,5 @@
-// BATCHED mode: every pair of a call in one persistent launch.
+// BATCHED mode: every pair of a call in three launches, the union sweep, the
+// medium sweep with the long pairs, and the persistent kernel.
 //
 // The method is PixelBox (Section 3): a pair box is split into sampling
 // boxes, each box is classified against both polygons with Lemma 1 (open-
@@ -38,11 +39,12 @@
 //     order) get them from two waves, one per ring, which count the pair at
 //     once unless its box has more than 64 leaf tiles: then any wave of the
 //     persistent kernel can take one of its boxes.
-//   - One persistent grid.  Waves claim, in this order: boxes from their
-//     queue, heavy pairs, chunks of the other pairs, boxes from any queue.
-//     Claims go through per-stream counters (one stream per XCD) on cache
-//     lines of their own.  A heavy pair's split publishes its continuing
-//     boxes to a device queue when there are enough of them, so that idle
+//   - The sweeps share their pairs out statically; the persistent grid's
+//     waves claim, in this order: boxes from their queue, listed pairs, boxes
+//     from any queue.  Claims go through per-stream counters (one stream per
+//     XCD) on cache lines of their own, and so do the appends to the lists: a
+//     counter takes an atomic every 7 ns.  A listed pair's split publishes its
+//     continuing boxes to a device queue when there are enough of them, so that idle
 //     waves share the pair.  Queue slots are single 64-bit words written and
 //     taken with atomics, so no cache flushes are needed; a consumer that
 //     overshoots the tail marks the slot skipped and the producer keeps that
@@ -61,7 +63,6 @@
 
 namespace sccg {
 
-constexpr int kLeafSlots = 2 * kWave;  // per-wave leaf slots: one per column of p and of q
 constexpr int kLocalCap = 256;          // per-wave stack of boxes to process inline
 constexpr uint32_t kSpinLimit = 1u << 22;
 // per-wave LDS of the persistent kernel: the slots of one band row of each
@@ -70,7 +71,6 @@ constexpr uint32_t kSpinLimit = 1u << 22;
 constexpr int kRowSlotsPerWave = 2 * kMaxGrid * kWave;
 constexpr int kLdsPerWave = kRowSlotsPerWave * 8 + kLocalCap * 8;
 constexpr unsigned long long kSkip = 1ull;  // slot abandoned by an overshooting consumer
-constexpr int kSetupPerThread = 16;         // most pairs per thread of the setup pass
 
 int batch_lds_bytes_per_wave() { return kLdsPerWave; }
 
@@ -119,7 +119,7 @@ struct Ctx {
   const BatchArgs* a;
   bool stats;       // work counters on (a compile-time false in the sweeps' plain instances)
   int lane;
-  uint64_t* slots;  // per-wave leaf slots (kLeafSlots; in the persistent kernel, two band rows' worth)
+  uint64_t* slots;  // per-wave leaf slots
   uint64_t* local;  // per-wave inline stack, kLocalCap entries
   int lsp;          // inline stack depth (wave-uniform)
   int home;         // preferred queue
@@ -756,7 +756,7 @@ __device__ __forceinline__ uint64_t root_task(const PairInfo& pi) {
   return task_word(pi.hidx < 0 ? 0 : pi.hidx, cl, 0, 0, false, false);
 }
 
-// A listed pair (its box from the prepass or the sweep).  Its index also
+// A listed pair (its box from the medium sweep).  Its index also
 // names it in the task words of its boxes.
 __device__ __forceinline__ PairInfo heavy_info(const BatchArgs& a, int64_t pair) {
   PairInfo pi;
@@ -793,43 +793,45 @@ __device__ __forceinline__ int lpt_bucket(const BatchArgs& a, int64_t n) {
 #endif
 
 // -------------------------------------------------------------------- sweep
-// First pass of a batched call: every pair the setup pass did not list as
-// heavy, one pair at a time per wave, a chunk of consecutive pairs per claim.
-// A pair whose two rings have at most kSweepRing vertices each is loaded
-// into registers, both rings as one stream of positions (p's vertices, then
-// q's); when the union of its MBRs fits one leaf tile it is counted there
-// at once (below Section 3.4's pixelization threshold, I and U directly).
-// Every other pair gets its MBRs and areas from its rings and is appended,
-// with its pair box, to the persistent kernel's list.
-constexpr int kSweepRing = 2 * kWave;                 // longest ring of the union sweep
-constexpr int kMediumRing = 4 * kWave;                // longest ring of the medium sweep
+// First pass of a batched call: every pair, one at a time per wave.  A wave
+// looks at up to 64 pairs of its share at once, a pair per lane: index check,
+// ring offsets and lengths, and the class.  Long pairs (a ring over
+// kMediumRing vertices, or heavy_verts in all) and medium ones (a ring over
+// kSweepRing vertices, or an empty one) are listed for the second pass.  Of
+// the others the wave holds both rings in registers, the next pair's loads in
+// flight; when the union of their MBRs fits one leaf tile the pair is counted
+// there at once (below Section 3.4's pixelization threshold, I and U
+// directly), else it is listed as well, as is a union box of exactly 64 rows
+// (see box_count).
+constexpr int kUnionChunks = 3;                       // 64-vertex chunks per ring in the union sweep
+constexpr int kMediumChunks = 4;                      // and in the medium sweep
+constexpr int kSweepRing = kUnionChunks * kWave;      // longest ring of the union sweep
+constexpr int kMediumRing = kMediumChunks * kWave;    // longest ring of the medium sweep
 constexpr int kSweepWaves = 4;                        // waves per workgroup of the sweep
-// Occupancy target of the sweep (waves per SIMD), a build-time tuning knob;
-// the sweep that also counts pair boxes holds more wave-uniform values and
-// runs fewer waves, each with the largest scalar register file.
-#ifndef SCCG_SWEEP_WAVES_PER_EU
-#define SCCG_SWEEP_WAVES_PER_EU 8
-#endif
-#ifndef SCCG_SHARE_RUN
-#define SCCG_SHARE_RUN 1
-#endif
+// Occupancy targets (waves per SIMD) and the tiles of a team's stripes,
+// build-time tuning knobs.  The union sweep waits on memory where rings are
+// short (200,000 uniform pairs: 101 -> 76 us, 4.1 TB/s of rings; the heavy-tailed
+// 2M 570 + 38 of a setup pass -> 494 us): eight waves beat seven by 2 %, and
+// with pair boxes (2.6M candidate pairs of dense tiles) 1159 us against 1213
+// with seven and 1294 with six.
 #ifndef SCCG_TEAM_TILES
 #define SCCG_TEAM_TILES 14
 #endif
 #ifndef SCCG_MEDIUM_WAVES_PER_EU
 #define SCCG_MEDIUM_WAVES_PER_EU 5
 #endif
-#ifndef SCCG_SWEEP_PB_WAVES_PER_EU
-#define SCCG_SWEEP_PB_WAVES_PER_EU 6
+#ifndef SCCG_SWEEP_WAVES_PER_EU
+#define SCCG_SWEEP_WAVES_PER_EU 8
 #endif
+#ifndef SCCG_RUN_STEAL
+#define SCCG_RUN_STEAL 0
+#endif
+// whether the persistent kernel's waves also claim listed pairs from other
+// XCDs' streams
+constexpr bool kRunSteal = SCCG_RUN_STEAL != 0;
 
 // the lanes named by a wave-uniform mask (the mask is the lane condition)
 __device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-
-// lanes [0, n) of a chunk, for any n
-__device__ __forceinline__ uint64_t lanes_lt(int n) {
-  return n <= 0 ? 0ull : (n >= kWave ? ~0ull : (1ull << n) - 1ull);
-}
 
 // Lane L < 32 gets lane L + 32's value (v_permlane32_swap).
 __device__ __forceinline__ uint32_t upper_half(uint32_t v) {
@@ -838,415 +840,103 @@ __device__ __forceinline__ uint32_t upper_half(uint32_t v) {
 __device__ __forceinline__ uint64_t upper_half(uint64_t v) {
   return ((uint64_t)upper_half((uint32_t)(v >> 32)) << 32) | upper_half((uint32_t)v);
 }
+// m & the other half's m, in every lane
+__device__ __forceinline__ uint32_t both_halves(uint32_t v) {
+  const auto s = __builtin_amdgcn_permlane32_swap((int)v, (int)v, false, false);
+  return (uint32_t)s[0] & (uint32_t)s[1];
+}
+__device__ __forceinline__ uint64_t both_halves(uint64_t v) {
+  return ((uint64_t)both_halves((uint32_t)(v >> 32)) << 32) | both_halves((uint32_t)v);
+}
 
-// The value of the next lane (DPP wave shift left by one; lane 63 reads 0).
-__device__ __forceinline__ int next_lane_x(int x) { return __builtin_amdgcn_update_dpp(0, x, 0x130, 0xf, 0xf, false); }
-
-// A sweep pair in registers: each ring in up to N 64-vertex chunks, lane L
-// of chunk c holding vertex 64 c + L (lanes past the end hold the ring's last
-// vertex again: neutral for extents).
-constexpr int kUnionChunks = kSweepRing / kWave;    // chunks per ring in the union sweep
-constexpr int kMediumChunks = kMediumRing / kWave;  // chunks per ring in the medium sweep
+// A pair in registers: each ring in up to N 64-vertex chunks, lane L of chunk
+// c holding vertex 64 c + L.
 template <int N>
 struct PairRegs {
   int2 p[N], q[N];
 };
-// pairs of the union sweep whose rings are in flight beyond the pair in
-// hand (deeper lookahead measured no faster: the sweep is bound by
-// instruction issue, not by load latency)
-constexpr int kSweepAhead = 1;
-#ifndef SCCG_RUN_STEAL
-#define SCCG_RUN_STEAL 0
-#endif
-// whether the persistent kernel's waves also claim listed pairs from other
-// XCDs' streams
-constexpr bool kRunSteal = SCCG_RUN_STEAL != 0;
-#ifndef SCCG_SWEEP_STEAL
-#define SCCG_SWEEP_STEAL 0
-#endif
-// whether the sweeps' waves also claim from other XCDs' streams
-constexpr bool kSweepSteal = SCCG_SWEEP_STEAL != 0;
 
+// Extents of a lane's vertices, minima and complemented maxima, so that all
+// four reduce by minimum.
+struct Ext {
+  int x0, y0, nx1, ny1;
+};
+__device__ __forceinline__ Ext ext_of(int2 v) { return Ext{v.x, v.y, ~v.x, ~v.y}; }
+__device__ __forceinline__ void ext_add(Ext& e, int2 v) {
+  e = Ext{min(e.x0, v.x), min(e.y0, v.y), min(e.nx1, ~v.x), min(e.ny1, ~v.y)};
+}
+// Wave minimum of four values at once: two half swaps and a row swap leave
+// each value in one row of 16 lanes, which four row steps reduce together
+// (10 steps for the four, where a reduction of each takes 24).
+__device__ __forceinline__ Ext wave_min4(const Ext& e) {
+  const auto s0 = __builtin_amdgcn_permlane32_swap(e.x0, e.y0, false, false);
+  const auto s1 = __builtin_amdgcn_permlane32_swap(e.nx1, e.ny1, false, false);
+  const int a = min((int)s0[0], (int)s0[1]), b = min((int)s1[0], (int)s1[1]);
+  const auto s2 = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  int x = min((int)s2[0], (int)s2[1]);
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0xb1, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x4e, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x141, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x140, 0xf, 0xf, false));
+  return Ext{__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 16),
+             __builtin_amdgcn_readlane(x, 48)};
+}
+__device__ __forceinline__ Meta meta_of(const Ext& e) { return Meta{e.x0, e.y0, ~e.nx1, ~e.ny1}; }
+__device__ __forceinline__ bool out_of_range(const Meta& m) {
+  return m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord;
+}
 
-// lanes [0, k) for 0 <= k <= 63, and lanes [0, m) for 1 <= m <= 64
-__device__ __forceinline__ uint64_t lanes_below_k(int k) { return (1ull << k) - 1ull; }
-__device__ __forceinline__ uint64_t lanes_upto_m(int m) { return ~0ull >> (kWave - m); }
-
-// The corners of a ring held in registers: the vertices whose two edges are
-// not both vertical or both horizontal (bit L of word c: vertex 64 c + L).
-// A vertex's edge to its successor is vertical iff both have the same x;
-// the successor is the next lane, the next chunk's first lane, and after
-// the last vertex the first.
-template <int N>
-__device__ __forceinline__ void ring_corners(const int2 (&d)[N], int nr, uint64_t (&cm)[N]) {
-#pragma unroll
-  for (int c = 0; c < N; ++c) cm[c] = 0;
-  if (nr <= 0) return;
-  const int nc = (nr + kWave - 1) / kWave;
-  const int le = (nr - 1) & (kWave - 1);  // lane of the last vertex, in the last chunk
-  const int xl_lane = nc == 1 ? d[0].x : nc == 2 ? d[1 < N ? 1 : N - 1].x : nc == 3 ? d[2 < N ? 2 : N - 1].x
-                                                                              : d[N - 1].x;
-  const uint64_t last = __builtin_amdgcn_readlane(xl_lane, le) == __builtin_amdgcn_readlane(d[0].x, 0) ? 1ull : 0ull;
-  uint64_t carry = last;  // the edge before vertex 0 is the ring's last
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    if (c < nc) {
-      int xs;
-      if (c + 1 < N && c + 1 < nc)
-        xs = __builtin_amdgcn_update_dpp(__builtin_amdgcn_readlane(d[c + 1 < N ? c + 1 : c].x, 0), d[c].x,
-                                         0x130, 0xf, 0xf, false);
-      else
-        xs = next_lane_x(d[c].x);
-      uint64_t b = ballot(d[c].x == xs);
-      if (c == nc - 1) b = (b & lanes_below_k(le)) | (last << le);
-      cm[c] = (b ^ ((b << 1) | carry)) & (c == nc - 1 ? lanes_upto_m(nr - c * kWave) : ~0ull);
-      carry = b >> 63;
-    }
+// The share of n items of one wave of a launch whose workgroups have `per_wg`
+// waves: runs of at most `longest` consecutive items, interleaved over the
+// waves so that all of them work in the same part of the list, with the waves
+// in an order that puts neighbouring runs on one XCD (rings that neighbouring
+// pairs share stay in its L2).
+struct WaveShare {
+  int64_t count;  // items of this wave
+  int64_t me, n_waves;
+  int run;
+  __device__ __forceinline__ WaveShare(int64_t n, int per_wg, int w, int longest) {
+    const unsigned g = gridDim.x, b = blockIdx.x;
+    const unsigned at = g % kStreams == 0 ? (b % kStreams) * (g / kStreams) + b / kStreams : b;
+    n_waves = uniform64((int64_t)g * per_wg);
+    me = uniform64((int64_t)at * per_wg + w);
+    run = uniform((int)share_run(n, n_waves, longest));
+    const int64_t round = n_waves * run, full = n / round;
+    count = uniform64(full * run + max((int64_t)0, min((int64_t)run, n - full * round - me * run)));
   }
-}
-
-// Scatter of one ring of a union tile (see union_counts): every corner XORs
-// the rows at or above it into the slot of the rightmost column left of it.
-// `base`: the ring's first slot.  kClip: vertices may lie outside the tile
-// (see union_counts).  Returns the vertices scattered.
-template <typename M, int W, int R, int N, bool kClip = false>
-__device__ __forceinline__ uint32_t ring_scatter(M* slots, const int2 (&d)[N], int nr, int x0, int y0,
-                                                 int lane, int base) {
-  if (nr <= 0) return 0;
-  uint64_t cm[N];
-  ring_corners(d, nr, cm);
-  uint32_t kept = 0;
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    if (c * kWave < nr) {
-      const int dx = kClip ? min(d[c].x, x0 + W) - x0 : d[c].x - x0;
-      const int ty = kClip ? max(min(d[c].y, y0 + R) - y0, 0) : d[c].y - y0;
-      const uint64_t keep = cm[c] & ballot(dx > 0) & ballot(ty < R);
-      M* sp = slots + (base + W - dx);
-      if (lane_in(keep)) slot_xor(sp, 0, (M)(~(M)0 << ty));
-      kept += (uint32_t)__popcll(keep);
-    }
+  // the list index of the wave's item k
+  __device__ __forceinline__ int64_t entry(int64_t k) const {
+    const int64_t turn = (int64_t)((uint32_t)k / (uint32_t)run);
+    return (turn * n_waves + me) * run + ((uint32_t)k - (uint32_t)turn * (uint32_t)run);
   }
-  return kept;
-}
+};
 
-// Counts of a pair whose MBR union [x0, x0 + W) x [y0, y0 + R) fits one leaf
-// tile, from its rings in registers, packed as I | U << 16.
-//
-// Pixel (x, y) is inside a ring iff an odd number of its vertical edges lie
-// right of x with a span holding row y (Section 3.1).  A vertical edge from
-// (X, ya) to (X, yb) holds row y iff exactly one of ya, yb is <= y, so its
-// term is the XOR of one term per end: "rows >= y_end, in the columns left of
-// X".  Summed over a ring, a vertex contributes its term once for each
-// vertical edge it bounds: once at a corner, twice (no effect) between two
-// vertical edges, never between two horizontal ones.  So every vertex whose
-// two edges are not both vertical or both horizontal XORs the mask of rows
-// >= y_v into the slot of the rightmost column left of x_v, and the prefix
-// XOR over the columns (lanes, in reverse order as in the other leaves)
-// gives every column's crossing parities.  Every vertex lies in the tile:
-// rows and columns past the union box come out outside, and nothing needs
-// clipping.  kHalves: W = 32, p's columns in lanes 0-31 and q's in lanes
-// 32-63, one scan; else W = 64 and one scan per ring.  M: 32- or 64-bit rows.
-//
-// kClip: the tile [x0, x0 + W) x [y0, y0 + R) is a pair box, and vertices
-// may lie outside it.  A corner left of it toggles none of its columns and
-// one right of it all of them (its x is taken as x0 + W); a corner below it
-// sets all of its rows and one above it none.  Every pixel's parities in the
-// tile stay exact, and a pixel of the tile outside the pair box is outside
-// MBR(p) or MBR(q), so the intersection count is exact; the union count is
-// not (the caller takes U from the areas).
-template <bool kHalves, typename M, int N, bool kClip = false>
-__device__ __forceinline__ uint32_t union_counts(Ctx& c, const PairRegs<N>& r, int np, int nq, int x0, int y0) {
-  constexpr int W = kHalves ? 32 : kWave;
-  constexpr int R = (int)sizeof(M) * 8;
-  const int lane = c.lane;
-  M* slots = reinterpret_cast<M*>(c.slots);
-  slots[lane] = (M)0;
-  if (!kHalves) slots[kWave + lane] = (M)0;
-  wave_sync_lds();
-  uint32_t kept = ring_scatter<M, W, R, N, kClip>(slots, r.p, np, x0, y0, lane, 0);
-  kept += ring_scatter<M, W, R, N, kClip>(slots, r.q, nq, x0, y0, lane, W);
-  wave_sync_lds();
-  uint32_t t;
-  if (kHalves) {
-    const M m = wave_prefix_xor<true>(slots[lane]);
-    const M o = upper_half(m);
-    const uint32_t ni = lane < 32 ? (uint32_t)__popcll((uint64_t)(m & o)) : 0u;
-    const uint32_t nu = lane < 32 ? (uint32_t)__popcll((uint64_t)(m | o)) : 0u;
-    t = wave_sum_u32(ni | (nu << 16));
-  } else {
-    const M mp = wave_prefix_xor<false>(slots[lane]);
-    const M mq = wave_prefix_xor<false>(slots[kWave + lane]);
-    t = wave_sum_u32((uint32_t)__popcll((uint64_t)(mp & mq)) | ((uint32_t)__popcll((uint64_t)(mp | mq)) << 16));
-  }
-  wave_sync_lds();
-  stat_add(c, 14, (unsigned long long)kept);
-  return t;
-}
-
-// Scan and count of a union tile's 64-bit slots (see union_counts), packed as
-// I | U << 16.  kHalves: W = 32, p's columns in slots 0-31 and q's in 32-63;
-// else p's in 0-63 and q's in 64-127.  kRows64: rows 32-63 are in use
-// (else those bits are all zero: rows past the union box come out outside).
-template <bool kHalves, bool kRows64>
-__device__ __forceinline__ uint32_t union_tile_count(const uint64_t* slots, int lane) {
-  using M = typename std::conditional<kRows64, uint64_t, uint32_t>::type;
-  auto slot = [&](int k) -> M {
-    if (kRows64) return (M)slots[k];
-    return (M)reinterpret_cast<const uint32_t*>(slots)[2 * k];  // low word: rows 0-31
-  };
-  uint32_t ni, nu;
-  if (kHalves) {
-    const M m = wave_prefix_xor<true>(slot(lane));
-    const M o = upper_half(m);
-    ni = lane < 32 ? (uint32_t)__popcll((uint64_t)(m & o)) : 0u;
-    nu = lane < 32 ? (uint32_t)__popcll((uint64_t)(m | o)) : 0u;
-  } else {
-    const M mp = wave_prefix_xor<false>(slot(lane));
-    const M mq = wave_prefix_xor<false>(slot(kWave + lane));
-    ni = (uint32_t)__popcll((uint64_t)(mp & mq));
-    nu = (uint32_t)__popcll((uint64_t)(mp | mq));
-  }
-  return wave_sum_u32(ni | (nu << 16));
-}
-
-// One ring of at most 64 vertices (lane L: vertex L; lanes past the end hold
-// the last vertex again) scattered into a union tile's 64-bit slots from
-// `base` on (see union_counts).  Each lane finds whether its vertex is a
-// corner from its two neighbours' x (the last vertex's successor is the
-// first, the first's predecessor the last), so that the lane masks combine
-// in few scalar steps.  Returns the vertices scattered.
-__device__ __forceinline__ uint32_t scatter_small_ring(uint64_t* slots, int2 v, int nr, int x0, int y0, int W, int base,
-                                                       int lane) {
-  if (nr <= 0) return 0;
-  const int le = nr - 1;
-  const int x_first = __builtin_amdgcn_readfirstlane(v.x), x_last = __builtin_amdgcn_readlane(v.x, le);
-  // the neighbours' x, read by every lane before the selections
-  const int xn = next_lane_x(v.x), xb = __builtin_amdgcn_update_dpp(0, v.x, 0x138, 0xf, 0xf, false);  // wave_shr:1
-  const int xs = lane == le ? x_first : xn;
-  const int xp = lane == 0 ? x_last : xb;
-  const int dx = v.x - x0, ty = v.y - y0;
-  const bool keep = (lane <= le) & ((v.x == xs) != (v.x == xp)) & (dx > 0) & (ty < kWave);
-  if (keep) slot_xor(slots + (base + W - dx), 0, ~0ull << ty);
-  return (uint32_t)__popcll(ballot(keep));
-}
-
-// A pair whose rings have at most 64 vertices each, one chunk per ring in
-// registers: when the union of its MBRs fits one leaf tile (and every
-// coordinate is in range), its counts packed as I | U << 16 in t, and true.
-// The counts of such a pair on its union box [x0, x1) x [y0, y1), which fits
-// one leaf tile, packed as I | U << 16 in t.
-__device__ __forceinline__ void union_small_box(Ctx& c, int2 vp, int np, int2 vq, int nq, int x0, int y0, int x1,
-                                                int y1, uint32_t& t) {
-  const int lane = c.lane;
-  const int uw = x1 - x0, uh = y1 - y0;
-  const int W = uw <= 32 ? 32 : kWave;
-  uint64_t* slots = c.slots;
-  slots[lane] = fresh_zero<uint64_t>();
-  slots[kWave + lane] = fresh_zero<uint64_t>();
-  wave_sync_lds();
-  uint32_t kept = scatter_small_ring(slots, vp, np, x0, y0, W, 0, lane);
-  kept += scatter_small_ring(slots, vq, nq, x0, y0, W, W, lane);
-  wave_sync_lds();
-  if (W == 32)
-    t = uh <= 32 ? union_tile_count<true, false>(slots, lane) : union_tile_count<true, true>(slots, lane);
-  else
-    t = uh <= 32 ? union_tile_count<false, false>(slots, lane) : union_tile_count<false, true>(slots, lane);
-  wave_sync_lds();
-  if (c.stats) {
-    const int n = np + nq;
-    stat_add(c, 14, (unsigned long long)kept);
-    stat_add(c, 5, 1ull);
-    stat_add(c, 11, (unsigned long long)uw * uh);
-    stat_add(c, 13, (unsigned long long)n);
-    stat_add(c, 1, 1ull);
-    stat_add(c, 0, 2ull * (unsigned long long)uw * uh);
-    stat_add(c, 10, (unsigned long long)n);
-  }
-}
-
-__device__ __forceinline__ bool union_small(Ctx& c, int2 vp, int np, int2 vq, int nq, uint32_t& t) {
-  const int2 a = np > 0 ? vp : vq, b = nq > 0 ? vq : vp;  // an empty ring takes the other's vertices
-  const int x0 = wave_min_i32(min(a.x, b.x)), y0 = wave_min_i32(min(a.y, b.y));
-  const int x1 = wave_max_i32(max(a.x, b.x)), y1 = wave_max_i32(max(a.y, b.y));
-  if (!(x0 >= -kMaxCoord && y0 >= -kMaxCoord && x1 <= kMaxCoord && y1 <= kMaxCoord &&
-        side_u(x0, x1) <= (uint32_t)kTile && side_u(y0, y1) <= (uint32_t)kTile))
-    return false;
-  union_small_box(c, vp, np, vq, nq, x0, y0, x1, y1, t);
-  return true;
-}
-
-// The counts of such a pair on its union box [x0, x1) x [y0, y1), which fits
-// one leaf tile, packed as I | U << 16 in t.
-template <int N>
-__device__ __forceinline__ void union_pair_box(Ctx& c, const PairRegs<N>& r, int np, int nq, int x0, int y0, int x1,
-                                               int y1, uint32_t& t) {
-  const int uw = x1 - x0, uh = y1 - y0;
-  if (uw <= 32)
-    t = uh <= 32 ? union_counts<true, uint32_t, N>(c, r, np, nq, x0, y0)
-                 : union_counts<true, uint64_t, N>(c, r, np, nq, x0, y0);
-  else
-    t = uh <= 32 ? union_counts<false, uint32_t, N>(c, r, np, nq, x0, y0)
-                 : union_counts<false, uint64_t, N>(c, r, np, nq, x0, y0);
-  if (c.stats) {
-    const int n = np + nq;
-    stat_add(c, 5, 1ull);
-    stat_add(c, 11, (unsigned long long)uw * uh);
-    stat_add(c, 13, (unsigned long long)n);
-    stat_add(c, 1, 1ull);
-    stat_add(c, 0, 2ull * (unsigned long long)uw * uh);
-    stat_add(c, 10, (unsigned long long)n);
-  }
-}
-
-// A pair held in registers: when the union of its MBRs fits one leaf tile
-// (and every coordinate is in range), its counts packed as I | U << 16 in t,
-// and true.
-template <int N>
-__device__ __forceinline__ bool union_pair(Ctx& c, const PairRegs<N>& r, int np, int nq, uint32_t& t) {
-  const int2 f = np > 0 ? r.p[0] : r.q[0];  // lanes of an empty ring take this vertex
-  int mnx = f.x, mny = f.y, mxx = f.x, mxy = f.y;
-  auto add = [&](int2 v) {
-    mnx = min(mnx, v.x);
-    mny = min(mny, v.y);
-    mxx = max(mxx, v.x);
-    mxy = max(mxy, v.y);
-  };
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    if (c > 0 && c * kWave < np) add(r.p[c]);
-    if (c * kWave < nq) add(r.q[c]);
-  }
-  const int x0 = wave_min_i32(mnx), y0 = wave_min_i32(mny);
-  const int x1 = wave_max_i32(mxx), y1 = wave_max_i32(mxy);
-  if (!(x0 >= -kMaxCoord && y0 >= -kMaxCoord && x1 <= kMaxCoord && y1 <= kMaxCoord &&
-        side_u(x0, x1) <= (uint32_t)kTile && side_u(y0, y1) <= (uint32_t)kTile))
-    return false;
-  union_pair_box<N>(c, r, np, nq, x0, y0, x1, y1, t);
-  return true;
-}
-
-// Extent of a ring held in registers (one or more chunks, lanes past the end
-// holding the last vertex again): pixels [x0, x1) x [y0, y1) of its vertices.
-// An empty ring, or one with a coordinate beyond 2^30 (returns true), comes
-// back as the empty extent {INT_MAX, INT_MAX, INT_MIN, INT_MIN}.
-template <int N>
-__device__ __forceinline__ bool ring_extent_regs(const int2 (&d)[N], int nr, Meta& m) {
-  m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
-  if (nr <= 0) return false;
-  const int nc = (nr + kWave - 1) / kWave;
-  int mnx = d[0].x, mny = d[0].y, mxx = mnx, mxy = mny;
-#pragma unroll
-  for (int c = 1; c < N; ++c) {
-    if (c < nc) {
-      mnx = min(mnx, d[c].x);
-      mny = min(mny, d[c].y);
-      mxx = max(mxx, d[c].x);
-      mxy = max(mxy, d[c].y);
-    }
-  }
-  const Meta e{wave_min_i32(mnx), wave_min_i32(mny), wave_max_i32(mxx), wave_max_i32(mxy)};
-  if (e.x0 < -kMaxCoord || e.y0 < -kMaxCoord || e.x1 > kMaxCoord || e.y1 > kMaxCoord) return true;
-  m = e;
-  return false;
-}
-
-// |shoelace|/2 of a non-empty ring held in registers whose extent e is in
-// range (Section 3.2's area formula).  Twice the signed area is summed modulo
-// 2^32 for a ring at most 32767 pixels on a side, else modulo 2^64, and its
-// magnitude taken, which is exact while it stays within 2^31 (2^63).
-template <int N>
-__device__ __forceinline__ int64_t ring_area_regs(const int2 (&d)[N], int nr, int lane, const Meta& e) {
-  const int nc = (nr + kWave - 1) / kWave;
-  // A simple ring at most 32767 pixels wide and tall has |twice its area|
-  // below 2^31: summed from coordinates relative to its first vertex (the
-  // sum does not depend on the origin) it is exact modulo 2^32 in 32-bit
-  // lanes.
-  const bool narrow = side_u(e.x0, e.x1) <= (uint32_t)kMaxSide && side_u(e.y0, e.y1) <= (uint32_t)kMaxSide;
-  // each vertex's successor: the next lane, the next chunk's first lane, and
-  // the first vertex after the last
-  const int le = (nr - 1) & (kWave - 1);
-  const int2 f = lane_value(d[0], 0);
-  uint64_t tw = 0;
-  uint32_t tn = 0;
-#pragma unroll
-  for (int c = 0; c < N; ++c) {
-    if (c < nc) {
-      const bool last_chunk = c == nc - 1;
-      const int2 nx = last_chunk ? f : lane_value(d[c + 1 < N ? c + 1 : c], 0);
-      int sx = __builtin_amdgcn_update_dpp(nx.x, d[c].x, 0x130, 0xf, 0xf, false);
-      int sy = __builtin_amdgcn_update_dpp(nx.y, d[c].y, 0x130, 0xf, 0xf, false);
-      if (last_chunk && lane == le) {
-        sx = f.x;
-        sy = f.y;
-      }
-      if (!last_chunk || lane <= le) {
-        if (narrow) {
-          const uint32_t ux = (uint32_t)d[c].x - (uint32_t)f.x, uy = (uint32_t)d[c].y - (uint32_t)f.y;
-          const uint32_t vx = (uint32_t)sx - (uint32_t)f.x, vy = (uint32_t)sy - (uint32_t)f.y;
-          tn += ux * vy - vx * uy;
-        } else {
-          tw += (uint64_t)((int64_t)d[c].x * sy) - (uint64_t)((int64_t)sx * d[c].y);
-        }
-      }
-    }
-  }
-  if (narrow) {
-    const int32_t t = (int32_t)wave_sum_u32(tn);
-    return (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
-  }
-  const uint64_t t = wave_sum_u64(tw);
-  return (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
-}
-
-// A sweep pair as the setup pass recorded it (wave-uniform), taken from the
-// chunk's records held one per lane.
-struct SweepRec {
+// Both rings of a pair, as the pair arrays and the offsets give them.
+struct PairRec {
   int64_t op, oq;
-  int np, nq, cls;
+  int32_t np, nq;
 };
-struct ChunkRecs {
-  int op_lo, op_hi, oq_lo, oq_hi, np, nq, cls;
-};
-__device__ __forceinline__ SweepRec sweep_rec(const ChunkRecs& cr, int j) {
-  SweepRec s;
-  s.op = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cr.op_hi, j) << 32) |
-                   (uint32_t)__builtin_amdgcn_readlane(cr.op_lo, j));
-  s.oq = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane(cr.oq_hi, j) << 32) |
-                   (uint32_t)__builtin_amdgcn_readlane(cr.oq_lo, j));
-  s.np = __builtin_amdgcn_readlane(cr.np, j);
-  s.nq = __builtin_amdgcn_readlane(cr.nq, j);
-  s.cls = __builtin_amdgcn_readlane(cr.cls, j);
-  return s;
+__device__ __forceinline__ PairRec pair_rec(const BatchArgs& a, int64_t ia, int64_t ib) {
+  PairRec r;
+  r.op = a.A.off[ia];
+  r.oq = a.B.off[ib];
+  r.np = (int32_t)(a.A.off[ia + 1] - r.op);
+  r.nq = (int32_t)(a.B.off[ib + 1] - r.oq);
+  return r;
 }
-// the records of pairs i0 + lane (lane < cnt) of a chunk, one coalesced load
-__device__ __forceinline__ ChunkRecs chunk_recs(const BatchArgs& a, int64_t i0, int cnt, int lane) {
-  ChunkRecs cr{0, 0, 0, 0, 0, 0, kClsDone};
-  if (lane < cnt) {
-    const int4 h = *reinterpret_cast<const int4*>(a.rec + i0 + lane);
-    const int4 t = *(reinterpret_cast<const int4*>(a.rec + i0 + lane) + 1);
-    cr = ChunkRecs{h.x, h.y, h.z, h.w, t.x, t.y, t.z};
-  }
-  return cr;
+// Lane j's record, in every lane.
+__device__ __forceinline__ PairRec rec_of_lane(const PairRec& r, int j) {
+  return PairRec{readlane64(r.op, j), readlane64(r.oq, j), __builtin_amdgcn_readlane(r.np, j),
+                 __builtin_amdgcn_readlane(r.nq, j)};
 }
 
-// the record of pair idx in every lane with `valid` set
-__device__ __forceinline__ ChunkRecs gather_recs(const BatchArgs& a, int idx, bool valid) {
-  ChunkRecs cr{0, 0, 0, 0, 0, 0, kClsDone};
-  if (valid) {
-    const int4 h = *reinterpret_cast<const int4*>(a.rec + idx);
-    const int4 t = *(reinterpret_cast<const int4*>(a.rec + idx) + 1);
-    cr = ChunkRecs{h.x, h.y, h.z, h.w, t.x, t.y, t.z};
-  }
-  return cr;
-}
-
-// Append pairs i0 + j (bit j of `m`) to a list with one reservation.
-__device__ __forceinline__ void list_append(Counter& count, int32_t* list, uint64_t m, int64_t i0, int lane) {
+// Append each lane's value to a list, for the lanes in `m`, with one
+// reservation.
+__device__ __forceinline__ void list_append(Counter& count, int32_t* list, uint64_t m, int32_t value, int lane) {
   unsigned long long base = 0;
   if (lane == 0) base = atomicAdd(&count.v, (unsigned long long)__popcll(m));
   base = (unsigned long long)uniform64((int64_t)__shfl((long long)base, 0, kWave));
-  if (lane_in(m)) list[base + (unsigned long long)lanes_below(m)] = (int32_t)(i0 + lane);
+  if (lane_in(m)) list[base + (unsigned long long)lanes_below(m)] = value;
 }
 
 // Claim a chunk of `chunk` consecutive entries from per-stream counters (one
@@ -1271,242 +961,414 @@ __device__ __forceinline__ int64_t claim_chunk(Counter* next, int64_t n, int chu
   return -1;
 }
 
-// The share of n items of one wave of a launch whose workgroups have `per_wg`
-// waves: runs of consecutive items, interleaved over the waves so that all of
-// them work in the same part of the list (rings that neighbouring pairs share
-// stay in the caches), with the waves in an order that puts neighbouring runs
-// on one XCD.  Runs are short where the share is, so that shares differ by
-// little.
-struct WaveShare {
-  int64_t count;  // items of this wave
-  int64_t me, n_waves;
-  int run;
-  __device__ __forceinline__ WaveShare(int64_t n, int per_wg, int w) {
-    const unsigned g = gridDim.x, b = blockIdx.x;
-    const unsigned at = g % kStreams == 0 ? (b % kStreams) * (g / kStreams) + b / kStreams : b;
-    n_waves = uniform64((int64_t)g * per_wg);
-    me = uniform64((int64_t)at * per_wg + w);
-    run = uniform((int)max((int64_t)1, min((int64_t)SCCG_SHARE_RUN, n / (n_waves * 8))));
-    const int64_t round = n_waves * run, full = n / round;
-    count = uniform64(full * run + max((int64_t)0, min((int64_t)run, n - full * round - me * run)));
+// The batched state needs no reset of its own before a call: each kernel
+// leaves what it is done with ready for the next one, in the order of the
+// stream.
+//   - The sweep (this function, all workgroups) clears the queue slots the
+//     previous call used and, in its first workgroup, the counters that only
+//     the later kernels of a call touch.
+//   - The medium sweep sets the queues' heads and tails back (the sweep has
+//     just used them to find those slots).
+//   - The persistent kernel sets the counts of the lists that the sweep
+//     appends to back (the medium sweep has read them).
+__device__ __forceinline__ void next_call_state(const BatchArgs& a) {
+  BatchState& st = *a.st;
+  const unsigned t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    if (t < (unsigned)kLptBuckets) st.l_count[t].v = 0;
+    if (t < (unsigned)kStreams) st.p_next[t].v = 0;
+    if (t < (unsigned)(kLptBuckets * kStreams)) st.l_next[t / kStreams][t % kStreams].v = 0;
   }
-  // the list index of the wave's item k
-  __device__ __forceinline__ int64_t entry(int64_t k) const {
-    const int64_t turn = (int64_t)((uint32_t)k / (uint32_t)run);
-    return (turn * n_waves + me) * run + ((uint32_t)k - (uint32_t)turn * (uint32_t)run);
+  for (int q = 0; q < a.n_queues; ++q) {
+    unsigned long long used = max(st.q_tail[q].v, st.q_head[q].v);
+    if (used > (unsigned long long)a.queue_cap) used = (unsigned long long)a.queue_cap;
+    unsigned long long* base = a.queue + (size_t)q * a.queue_cap;
+    for (unsigned long long k = (unsigned long long)blockIdx.x * blockDim.x + t; k < used;
+         k += (unsigned long long)gridDim.x * blockDim.x)
+      base[k] = 0;
   }
-};
+}
 
-// The rings of a sweep pair (lane L: vertices L and 64 + L, clamped to the
-// last), or for any other record a read of `dummy`: the same loads in every
-// case, so that the compiler can count the loads in flight and wait only
-// for those of the pair in hand, not for the ones just issued ahead of it.
-__device__ __forceinline__ void sweep_load(const BatchArgs& a, const SweepRec& s, const int2* dummy, int lane,
-                                           PairRegs<kUnionChunks>& r) {
-  const bool mine = s.cls == kClsSweep;
-  const int2* P = mine && s.np > 0 ? a.A.xy + s.op : dummy;
-  const int2* Q = mine && s.nq > 0 ? a.B.xy + s.oq : dummy;
-  const int lp = mine ? max(s.np - 1, 0) : 0, lq = mine ? max(s.nq - 1, 0) : 0;
+// --------------------------------------------------- rings of the union sweep
+// Pixel (x, y) is inside a ring iff an odd number of its vertical edges lie
+// right of x with a span holding row y (Section 3.1).  A vertical edge from
+// (X, ya) to (X, yb) holds row y iff exactly one of ya, yb is <= y, so its
+// term is the XOR of one term per end: "rows >= y_end, in the columns left of
+// X".  Summed over a ring, a vertex contributes its term once for each
+// vertical edge it bounds: once at a corner, twice (no effect) between two
+// vertical edges, never between two horizontal ones.  So every vertex whose
+// two edges are not both vertical or both horizontal XORs the mask of rows
+// >= y_v into the slot of the rightmost column left of x_v, and the prefix
+// XOR over the columns (lanes, in reverse order as in the other leaves)
+// gives every column's crossing parities (the vertex form of the test).
+
+// Where the slots of one wave stand.  Column k from the right of a ring has
+// slot k; slot W takes the corners on the tile's left side, which have no
+// column left of them, and is never read.
+//   halves (W = 32): p's slots are 0-32, q's from 34, so that lane L < 32
+//     reads p's slot L and the others q's slot L - 32 at L + 2;
+//   else (W = 64): p's are 0-64, q's from 66.
+constexpr int kHalfQ = 34, kFullQ = 66;
+constexpr int kSweepSlots = 132;
+
+// The lanes whose vertex has a vertical edge to its successor, in a chunk
+// whose lanes past the ring's end hold the first vertex again: the next lane,
+// and for lane 63 lane 0 of `after` (the last lane of its rotation) or of the
+// chunk itself.
+__device__ __forceinline__ uint64_t vertical_edges(int x, int after) {
+  const int t = __builtin_amdgcn_update_dpp(0, after, 0x134, 0xf, 0xf, false);  // wave_rol:1
+  return ballot(x == __builtin_amdgcn_update_dpp(t, x, 0x130, 0xf, 0xf, false));
+}
+__device__ __forceinline__ uint64_t vertical_edges(int x) {
+  return ballot(x == __builtin_amdgcn_update_dpp(0, x, 0x134, 0xf, 0xf, false));
+}
+
+// XOR a chunk's corners (the lanes `corners`) into the slots at `base`, of a
+// tile of W columns and R rows whose right side is at x1 and bottom at y0.
+// kClip: vertices may lie outside the tile (see box_count).
+template <int W, typename M, bool kClip>
+__device__ __forceinline__ void chunk_xor(M* base, int2 v, uint64_t corners, int x1, int y0) {
+  constexpr int R = (int)sizeof(M) * 8;
+  if (kClip) {
+    v.x = clamp_to(v.x, x1 - W, x1);
+    v.y = clamp_to(v.y, y0, y0 + R - 1);
+  }
+  const int pos = x1 - v.x, ty = v.y - y0;
+  if (lane_in(corners)) slot_xor(base + pos, 0, (M)(~(M)0 << ty));
+}
+
+// The corners of a whole ring into its slots (kOne: of at most 64 vertices).
+// The chunks come by value: by reference the compiler merges the calls below
+// on a chosen address, and the registers become memory.
+template <int W, typename M, bool kClip, bool kOne>
+__device__ __forceinline__ void ring_xor(M* base, int2 d0, int2 d1, int2 d2, int nr, int x1, int y0) {
+  static_assert(kUnionChunks == 3, "the chunks of a sweep ring");
+  if (kOne || nr <= kWave) {
+    const uint64_t b = vertical_edges(d0.x);
+    const uint64_t corners = (b ^ ((b << 1) | ((b >> (nr - 1)) & 1ull))) & (~0ull >> (kWave - nr));
+    chunk_xor<W, M, kClip>(base, d0, corners, x1, y0);
+  } else if (nr <= 2 * kWave) {
+    const uint64_t b0 = vertical_edges(d0.x, d1.x), b1 = vertical_edges(d1.x, d0.x);
+    const uint64_t in = ~0ull >> (2 * kWave - nr);
+    chunk_xor<W, M, kClip>(base, d0, b0 ^ ((b0 << 1) | ((b1 >> (nr - 1 - kWave)) & 1ull)), x1, y0);
+    chunk_xor<W, M, kClip>(base, d1, (b1 ^ ((b1 << 1) | (b0 >> 63))) & in, x1, y0);
+  } else {
+    const uint64_t b0 = vertical_edges(d0.x, d1.x), b1 = vertical_edges(d1.x, d2.x), b2 = vertical_edges(d2.x, d0.x);
+    const uint64_t in = ~0ull >> (3 * kWave - nr);
+    chunk_xor<W, M, kClip>(base, d0, b0 ^ ((b0 << 1) | ((b2 >> (nr - 1 - 2 * kWave)) & 1ull)), x1, y0);
+    chunk_xor<W, M, kClip>(base, d1, b1 ^ ((b1 << 1) | (b0 >> 63)), x1, y0);
+    chunk_xor<W, M, kClip>(base, d2, (b2 ^ ((b2 << 1) | (b1 >> 63))) & in, x1, y0);
+  }
+}
+
+// Counts of a pair on the tile at (x0, y0), W = 32 or 64 columns wide, M's
+// bits tall: twice I in the high half of the word, |p| + |q| within the tile
+// in the low half, summed over the wave.  Rows and columns of the tile past
+// the union box come out outside.
+template <bool kHalves, typename M, bool kClip, bool kOne>
+__device__ __forceinline__ uint32_t tile_counts(uint64_t* words, int lane, const PairRegs<kUnionChunks>& r, int np,
+                                                int nq, int x0, int y0) {
+  constexpr int W = kHalves ? 32 : kWave;
+  M* slots = reinterpret_cast<M*>(words);
+  M* mine = slots + (kHalves ? lane + 2 * (lane >> 5) : lane);
+  *mine = (M)0;
+  if (!kHalves) mine[kFullQ] = (M)0;
+  wave_sync_lds();
+  ring_xor<W, M, kClip, kOne>(slots, r.p[0], r.p[1], r.p[2], np, x0 + W, y0);
+  ring_xor<W, M, kClip, kOne>(slots + (kHalves ? kHalfQ : kFullQ), r.q[0], r.q[1], r.q[2], nq, x0 + W, y0);
+  wave_sync_lds();
+  uint32_t t;
+  if (kHalves) {
+    const M m = wave_prefix_xor<true>(*mine);
+    // both halves hold the columns' common pixels
+    t = (uint32_t)__popcll((uint64_t)m) + ((uint32_t)__popcll((uint64_t)both_halves(m)) << 16);
+  } else {
+    const M mp = wave_prefix_xor<false>(*mine);
+    const M mq = wave_prefix_xor<false>(mine[kFullQ]);
+    t = (uint32_t)__popcll((uint64_t)mp) + (uint32_t)__popcll((uint64_t)mq) +
+        ((uint32_t)__popcll((uint64_t)(mp & mq)) << 17);
+  }
+  wave_sync_lds();
+  return wave_sum_u32(t);
+}
+
+// The counts of a pair on a box at most 64 wide and less than 64 tall (see
+// tile_counts): the union of its MBRs, or, kClip, its pair box.  There a
+// corner left of the box toggles none of its columns and one right of it all
+// of them; one below it counts as standing in its first row, and one above
+// the tile's last row in that row, where every column then has as many
+// corners as the ring has right of it, an even number: outside, as a row
+// above the box has to be for the intersection.  (A box of 64 rows has no
+// such row in the tile: the medium sweep takes it.)
+template <bool kClip, bool kOne>
+__device__ __forceinline__ uint32_t box_count(uint64_t* words, int lane, const PairRegs<kUnionChunks>& r, int np, int nq,
+                                              int x0, int y0, uint32_t w, uint32_t h) {
+  if (w <= 32u)
+    return h < 32u ? tile_counts<true, uint32_t, kClip, kOne>(words, lane, r, np, nq, x0, y0)
+                   : tile_counts<true, uint64_t, kClip, kOne>(words, lane, r, np, nq, x0, y0);
+  return h < 32u ? tile_counts<false, uint32_t, kClip, kOne>(words, lane, r, np, nq, x0, y0)
+                 : tile_counts<false, uint64_t, kClip, kOne>(words, lane, r, np, nq, x0, y0);
+}
+template <bool kClip>
+__device__ __forceinline__ uint32_t box_count(uint64_t* words, int lane, const PairRegs<kUnionChunks>& r, int np, int nq,
+                                              bool one, int x0, int y0, uint32_t w, uint32_t h) {
+  return one ? box_count<kClip, true>(words, lane, r, np, nq, x0, y0, w, h)
+             : box_count<kClip, false>(words, lane, r, np, nq, x0, y0, w, h);
+}
+
+// Twice the signed area of a ring at most kMaxSide wide and tall, summed as
+// (x + x') (y' - y) over its edges with x relative to its first vertex,
+// modulo 2^32, in which it is exact.
+__device__ __forceinline__ int64_t ring_area(const int2 (&d)[kUnionChunks], int nr) {
+  const uint32_t f2 = 2u * (uint32_t)__builtin_amdgcn_readlane(d[0].x, 0);
+  uint32_t tn = 0;
 #pragma unroll
   for (int c = 0; c < kUnionChunks; ++c) {
-    r.p[c] = P[min(c * kWave + lane, lp)];
-    r.q[c] = Q[min(c * kWave + lane, lq)];
-  }
-}
-
-// I of a pair whose pair box fits one leaf tile, counted on that box (see
-// union_counts with clipping): its columns in one half of the wave when it
-// is at most 32 wide, 32-bit rows when it is at most 32 tall.
-template <int N>
-__device__ __forceinline__ uint32_t pair_box_count(Ctx& c, const PairRegs<N>& r, int np, int nq, const Meta& box) {
-  const int bw = box.x1 - box.x0, bh = box.y1 - box.y0;
-  uint32_t t;
-  if (bw <= 32)
-    t = bh <= 32 ? union_counts<true, uint32_t, N, true>(c, r, np, nq, box.x0, box.y0)
-                 : union_counts<true, uint64_t, N, true>(c, r, np, nq, box.x0, box.y0);
-  else
-    t = bh <= 32 ? union_counts<false, uint32_t, N, true>(c, r, np, nq, box.x0, box.y0)
-                 : union_counts<false, uint64_t, N, true>(c, r, np, nq, box.x0, box.y0);
-  if (c.stats) {
-    stat_add(c, 1, 1ull);
-    stat_add(c, 0, 2ull * (unsigned long long)bw * bh);
-    stat_add(c, 10, (unsigned long long)(np + nq));
-  }
-  return t & 0xffffu;
-}
-
-// Pair j of the chunk (a sweep pair): counted on its union tile, leaving
-// I | U << 16 in lane j of `packed` and bit j in `wmask` (written out with
-// the chunk); a pair left out (union box larger than a leaf tile) goes to
-// the medium list with the chunk.
-__device__ __forceinline__ void sweep_one(Ctx& c, const SweepRec& s, const PairRegs<kUnionChunks>& r, int j,
-                                          bool union_ok, uint32_t& packed, uint64_t& wmask) {
-  if (s.cls != kClsSweep) return;  // another class, or a bad index
-  const int lane = c.lane;
-  uint32_t t = 0;
-  bool done = s.np + s.nq == 0;  // two empty rings: nothing in either
-  if (done) stat_add(c, 7, 1ull);
-  if (!done && union_ok)
-    done = s.np <= kWave && s.nq <= kWave ? union_small(c, r.p[0], s.np, r.q[0], s.nq, t)
-                                          : union_pair<kUnionChunks>(c, r, s.np, s.nq, t);
-  if (done) {
-    if (lane == j) packed = t;
-    wmask |= 1ull << j;
-  }
-}
-
-// Extent and area of a ring held wave-uniform; area < 0 until it is needed.
-struct RingInfo {
-  Meta m;
-  int64_t area;
-  bool bad;
-};
-
-// Pair j of the chunk (a sweep pair, index i0 + j) when the union sweep also
-// counts pair boxes.  Both rings' extents come first, q's carried over from
-// the previous pair of the wave when it is the same ring (a join's output
-// grouped by one side repeats it).  When their union fits one leaf tile the
-// pair is counted there, as in sweep_one; else, the union not being counted
-// directly, the pair box MBR(p) ∩ MBR(q) decides as in the medium sweep: an
-// empty box (nothing in common) or one that fits a leaf tile gives I and
-// U = |p| + |q| - I (Section 3.2), written out at once with bit j in
-// `dmask`; a box side out of range latches the error and gives I = U = 0; a
-// larger box goes, with nothing counted, to the medium list with the chunk.
-__device__ __forceinline__ void sweep_one_pb(Ctx& c, const SweepRec& s, const PairRegs<kUnionChunks>& r, int64_t i0,
-                                             int j, bool union_ok, uint32_t& packed, uint64_t& wmask, uint64_t& dmask,
-                                             int64_t& q_off, int& q_n, RingInfo& qi) {
-  if (s.cls != kClsSweep) return;  // another class, or a bad index
-  const BatchArgs& a = *c.a;
-  const int lane = c.lane;
-  if (s.np + s.nq == 0) {  // two empty rings: nothing in either
-    stat_add(c, 7, 1ull);
-    if (lane == j) packed = 0;
-    wmask |= 1ull << j;
-    return;
-  }
-  RingInfo pi;
-  pi.bad = ring_extent_regs(r.p, s.np, pi.m);
-  pi.area = -1;
-  if (s.oq != q_off || s.nq != q_n) {
-    qi.bad = ring_extent_regs(r.q, s.nq, qi.m);
-    qi.area = -1;
-    q_off = s.oq;
-    q_n = s.nq;
-  }
-  const bool ok = !pi.bad && !qi.bad;
-  const Meta u = union_box(pi.m, qi.m);  // an empty ring's extent drops out
-  if (union_ok && ok && side_u(u.x0, u.x1) <= (uint32_t)kTile && side_u(u.y0, u.y1) <= (uint32_t)kTile) {
-    uint32_t t;
-    if (s.np <= kWave && s.nq <= kWave)
-      union_small_box(c, r.p[0], s.np, r.q[0], s.nq, u.x0, u.y0, u.x1, u.y1, t);
-    else
-      union_pair_box<kUnionChunks>(c, r, s.np, s.nq, u.x0, u.y0, u.x1, u.y1, t);
-    if (lane == j) packed = t;
-    wmask |= 1ull << j;
-    return;
-  }
-  if (direct_union(a)) return;
-  const Meta box = pair_box(pi.m, qi.m);  // empty when a ring is empty or rejected
-  const bool empty = box.x0 >= box.x1 || box.y0 >= box.y1;
-  const uint32_t bw = side_u(box.x0, box.x1), bh = side_u(box.y0, box.y1);
-  const bool wide = !empty && (bw > (uint32_t)kMaxSide || bh > (uint32_t)kMaxSide);
-  const bool small = !empty && !wide && bw <= (uint32_t)kTile && bh <= (uint32_t)kTile;
-  if (!empty && !wide && !small) return;
-  if (lane == 0 && !ok) latch_error(a.err, kErrCoord);
-  if (lane == 0 && wide) latch_error(a.err, kErrSide);
-  stat_add(c, 12, (unsigned long long)(s.np + s.nq));
-  stat_add(c, small ? 5 : 7, 1ull);
-  if (small) stat_add(c, 11, (unsigned long long)bw * bh);
-  int64_t I = 0, U = 0;
-  if (!wide) {
-    if (pi.area < 0) pi.area = s.np > 0 && !pi.bad ? ring_area_regs(r.p, s.np, lane, pi.m) : 0;
-    if (qi.area < 0) qi.area = s.nq > 0 && !qi.bad ? ring_area_regs(r.q, s.nq, lane, qi.m) : 0;
-    U = pi.area + qi.area;
-    if (small) {
-      I = (int64_t)pair_box_count(c, r, s.np, s.nq, box);
-      U -= I;
+    if (c * kWave < nr) {
+      const int2 f = d[0], g = d[c + 1 < kUnionChunks ? c + 1 : 0];
+      const bool more = (c + 1) * kWave < nr;
+      const int ax = more ? g.x : f.x, ay = more ? g.y : f.y;
+      const int tx = __builtin_amdgcn_update_dpp(0, ax, 0x134, 0xf, 0xf, false);
+      const int ty = __builtin_amdgcn_update_dpp(0, ay, 0x134, 0xf, 0xf, false);
+      const int sx = __builtin_amdgcn_update_dpp(tx, d[c].x, 0x130, 0xf, 0xf, false);
+      const int sy = __builtin_amdgcn_update_dpp(ty, d[c].y, 0x130, 0xf, 0xf, false);
+      tn += (uint32_t)__mul24((int)((uint32_t)d[c].x + (uint32_t)sx - f2), (int)((uint32_t)sy - (uint32_t)d[c].y));
     }
   }
-  if (lane == 0) {
-    a.inter[i0 + j] = I;
-    a.uni[i0 + j] = U;
+  const int32_t t = (int32_t)wave_sum_u32(tn);
+  return (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
+}
+
+// Vertex 64 c + L of a ring of nr vertices in lane L, the first vertex again
+// past its end: neutral for extents, and the last vertex's successor comes
+// out right.  Only the chunks the ring has are loaded.
+typedef const char __attribute__((address_space(1))) * ring_ptr;
+__device__ __forceinline__ void ring_load(ring_ptr ring, int nr, int lane, int2 (&d)[kUnionChunks]) {
+#pragma unroll
+  for (int c = 0; c < kUnionChunks; ++c) {
+    if (c == 0 || c * kWave < nr) {
+      const uint32_t at = c * kWave + lane < nr ? (uint32_t)(c * kWave + lane) * 8u : 0u;
+      const uint64_t v = *reinterpret_cast<const uint64_t __attribute__((address_space(1)))*>(ring + at);
+      d[c] = make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
+    }
   }
-  dmask |= 1ull << j;
+}
+__device__ __forceinline__ void ring_move(int2 (&to)[kUnionChunks], const int2 (&from)[kUnionChunks], int nr) {
+  to[0] = from[0];
+#pragma unroll
+  for (int c = 1; c < kUnionChunks; ++c)
+    if (c * kWave < nr) to[c] = from[c];
+}
+// extents of a ring's lanes
+__device__ __forceinline__ Ext ring_ext(int2 d0, int2 d1, int2 d2, int nr) {
+  Ext e = ext_of(d0);
+  if (nr > kWave) ext_add(e, d1);
+  if (nr > 2 * kWave) ext_add(e, d2);
+  return e;
+}
+
+// The lanes' records of up to 64 sweep pairs: both rings' addresses and
+// lengths (np | nq << 16; each 1 to kSweepRing).
+struct SweepRecs {
+  uint64_t p, q;
+  uint32_t n;
+};
+// one of them, wave-uniform
+struct SweepPair {
+  ring_ptr p, q;
+  int np, nq;
+};
+__device__ __forceinline__ SweepPair sweep_pair(const SweepRecs& r, int j) {
+  const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)r.n, j);
+  return SweepPair{(ring_ptr)readlane64((int64_t)r.p, j), (ring_ptr)readlane64((int64_t)r.q, j), (int)(n & 0xffffu),
+                   (int)(n >> 16)};
 }
 
 // kPairBox: pairs whose union box exceeds a leaf tile are counted on their
 // pair box when it fits one (the same counts as the medium sweep's, without
-// loading the rings again); a separate instance keeps the extra registers
-// off the plain sweep, which most mixes run.  kStats: the work counters are
-// kept (an instance of its own, so that the others carry no test for them).
+// loading the rings again), U from the areas; both rings' extents come
+// first, q's kept while consecutive pairs of the wave share it (a join's
+// output grouped by one side repeats it).  A separate instance keeps the
+// extra registers off the plain sweep, which most mixes run.  kStats: the
+// work counters are kept (an instance of its own, so that the others carry no
+// test for them).
 template <bool kPairBox, bool kStats>
 __global__ void __launch_bounds__(kSweepWaves* kWave)
-    __attribute__((amdgpu_waves_per_eu(kPairBox ? SCCG_SWEEP_PB_WAVES_PER_EU : SCCG_SWEEP_WAVES_PER_EU)))
+    __attribute__((amdgpu_waves_per_eu(SCCG_SWEEP_WAVES_PER_EU)))
 k_batch_sweep(BatchArgs args) {
-  __shared__ __align__(16) uint64_t sweep_slots[kSweepWaves * kLeafSlots];
+  __shared__ __align__(16) uint64_t sweep_slots[kSweepWaves * kSweepSlots];
   Ctx c;
   c.a = &args;
   c.stats = kStats;
   c.lane = lane_id();
-  c.slots = sweep_slots + (threadIdx.x / kWave) * kLeafSlots;
+  c.slots = sweep_slots + (threadIdx.x / kWave) * kSweepSlots;
   c.local = nullptr;
   c.lsp = 0;
   c.home = 0;
-  c.xcd = (int)(blockIdx.x % (unsigned)kStreams);
+  c.xcd = 0;
   const BatchArgs& a = args;
   const int lane = c.lane;
-  const bool union_ok = direct_union(a) || !(a.flags & SCCG_F_NO_UNION_TILE);
+  const bool direct = direct_union(a);
+  const bool union_ok = direct || !(a.flags & SCCG_F_NO_UNION_TILE);
   const unsigned long long t_start = wave_stamp(a);
-  // claim streams found exhausted (wave-uniform); a wave claims only from
-  // its own XCD's stream (the streams hold equal interleaved shares), so
-  // that running dry costs it one claim, not one per stream (a grid too
-  // small to give every stream a workgroup claims from all of them)
-  uint32_t s_empty = kSweepSteal || gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
-  // kPairBox: the last q ring whose extent (and area, once needed) is held
-  int64_t q_off = -1;
-  int q_n = -1;
-  RingInfo qi{Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN}, 0, false};
-  for (;;) {
-    const int64_t i0 = claim_chunk(a.st->s_next, a.n_pairs, a.chunk, c.xcd, lane, s_empty);
-    if (i0 < 0) break;
-    const int cnt = uniform((int)min((int64_t)a.chunk, a.n_pairs - i0));
-    const ChunkRecs cr = chunk_recs(a, i0, cnt, lane);
-    // lane j: I | U << 16 of pair i0 + j when it is counted on its union tile
-    uint32_t packed = 0;
-    uint64_t wmask = 0, dmask = 0;
-    // the pair in hand (s[0], r[0]) and the next kSweepAhead ones, whose ring
-    // loads are in flight while the pair in hand is processed
-    SweepRec s[kSweepAhead + 1];
-    PairRegs<kUnionChunks> r[kSweepAhead + 1];
-    const int2* dummy = reinterpret_cast<const int2*>(a.rec + i0);
-#pragma unroll
-    for (int k = 0; k <= kSweepAhead; ++k) {
-      s[k] = k < cnt ? sweep_rec(cr, k) : SweepRec{0, 0, 0, 0, kClsDone};
-      sweep_load(a, s[k], dummy, lane, r[k]);
-    }
+  next_call_state(a);
+  const WaveShare share(a.n_pairs, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
 #pragma unroll 1
-    for (int j = 0; j < cnt; ++j) {
-      if (kPairBox)
-        sweep_one_pb(c, s[0], r[0], i0, j, union_ok, packed, wmask, dmask, q_off, q_n, qi);
-      else
-        sweep_one(c, s[0], r[0], j, union_ok, packed, wmask);
-#pragma unroll
-      for (int k = 0; k < kSweepAhead; ++k) {
-        s[k] = s[k + 1];
-        r[k] = r[k + 1];
+  for (int64_t k0 = 0; k0 < share.count; k0 += kWave) {
+    const int cnt = uniform((int)min((int64_t)kWave, share.count - k0));
+    const int64_t i = share.entry(k0 + lane);  // the lane's pair
+    SweepRecs rec{0, 0, 0};
+    int64_t verts = 0;
+    int bucket = -1;  // of a long pair
+    bool done = false, medium = false, sweep = false;
+    uint32_t out_i = 0, out_u = 0;  // the lane's pair's counts (not kPairBox: both in out_i, see tile_counts)
+    if (lane < cnt) {
+      const int64_t ia = a.pa[i], ib = a.pb[i];
+      if (ia < 0 || ia >= a.A.n || ib < 0 || ib >= a.B.n) {
+        latch_error(a.err, kErrIndex);
+        done = true;
+        if (kStats) atomicAdd(&a.st->stats[7], 1ull);
+      } else {
+        const PairRec r = pair_rec(a, ia, ib);
+        verts = (int64_t)r.np + r.nq;
+        if (r.np > kMediumRing || r.nq > kMediumRing || verts >= a.heavy_verts)
+          bucket = lpt_bucket(a, verts);
+        else if (r.np > kSweepRing || r.nq > kSweepRing || r.np <= 0 || r.nq <= 0 || (!union_ok && !kPairBox))
+          medium = true;
+        else
+          sweep = true;
+        rec.p = (uint64_t)(a.A.xy + r.op);
+        rec.q = (uint64_t)(a.B.xy + r.oq);
+        rec.n = (uint32_t)r.np | (uint32_t)r.nq << 16;
       }
-      const int jn = j + kSweepAhead + 1;
-      s[kSweepAhead] = jn < cnt ? sweep_rec(cr, jn) : SweepRec{0, 0, 0, 0, kClsDone};
-      sweep_load(a, s[kSweepAhead], dummy, lane, r[kSweepAhead]);
     }
-    // the chunk's union-tile counts go out in one coalesced store per array,
-    // the sweep pairs it left out to the medium list with one reservation
-    if (lane_in(wmask)) {
-      a.inter[i0 + lane] = (int64_t)(packed & 0xffffu);
-      a.uni[i0 + lane] = (int64_t)(packed >> 16);
+    uint64_t todo = ballot(sweep), finished = ballot(done);
+    PairRegs<kUnionChunks> cur, nxt;
+    SweepPair s{nullptr, nullptr, 0, 0};
+    int j = 0;
+    if (todo) {
+      j = __ffsll((long long)todo) - 1;
+      s = sweep_pair(rec, j);
+      ring_load(s.p, s.np, lane, cur.p);
+      ring_load(s.q, s.nq, lane, cur.q);
     }
-    const uint64_t left = ballot(lane < cnt && cr.cls == kClsSweep) & ~(wmask | dmask);
-    if (left) list_append(a.st->m_count, a.m_list, left, i0, lane);
+    // kPairBox: the last q ring whose extent (and area, once needed) is held
+    ring_ptr q_held = nullptr;
+    int q_n = 0;
+    Meta mq{0, 0, 0, 0};
+    int64_t area_q = -1;
+#pragma unroll 1
+    while (todo) {
+      todo &= todo - 1;
+      const bool one = max(s.np, s.nq) <= kWave;
+      Meta u;
+      Meta mp{0, 0, 0, 0};
+      if (kPairBox) {
+        mp = meta_of(wave_min4(ring_ext(cur.p[0], cur.p[1], cur.p[2], s.np)));
+        if (s.q != q_held || s.nq != q_n) {
+          mq = meta_of(wave_min4(ring_ext(cur.q[0], cur.q[1], cur.q[2], s.nq)));
+          area_q = -1;
+          q_held = s.q;
+          q_n = s.nq;
+        }
+        u = union_box(mp, mq);
+      } else {
+        Ext e = ext_of(cur.p[0]);
+        ext_add(e, cur.q[0]);
+        if (!one) {
+          if (s.np > kWave) ext_add(e, cur.p[1]);
+          if (s.nq > kWave) ext_add(e, cur.q[1]);
+          if (s.np > 2 * kWave) ext_add(e, cur.p[2]);
+          if (s.nq > 2 * kWave) ext_add(e, cur.q[2]);
+        }
+        u = meta_of(wave_min4(e));
+      }
+      // The next pair's loads, in flight while this one is counted.  They
+      // follow the use of every vertex in hand: how many they are depends on
+      // the pair, so a wait for older loads would wait for them as well.
+      int jn = j;
+      SweepPair sn = s;
+      if (todo) {
+        jn = __ffsll((long long)todo) - 1;
+        sn = sweep_pair(rec, jn);
+        ring_load(sn.p, sn.np, lane, nxt.p);
+        ring_load(sn.q, sn.nq, lane, nxt.q);
+      }
+      const uint32_t uw = side_u(u.x0, u.x1), uh = side_u(u.y0, u.y1);
+      // every coordinate within 2^30: none plus 2^30 above 2^31
+      const uint32_t far = max(max((uint32_t)u.x0 + kMaxCoord, (uint32_t)u.x1 + kMaxCoord),
+                               max((uint32_t)u.y0 + kMaxCoord, (uint32_t)u.y1 + kMaxCoord));
+      const bool ok = far <= 2u * kMaxCoord;
+      if (ok && (!kPairBox || union_ok) && max(uw, uh + 1u) <= (uint32_t)kTile) {
+        const uint32_t t = box_count<false>(c.slots, lane, cur, s.np, s.nq, one, u.x0, u.y0, uw, uh);
+        if (kPairBox) {
+          out_i = lane == j ? t >> 17 : out_i;
+          out_u = lane == j ? (t & 0xffffu) - (t >> 17) : out_u;
+        } else {
+          out_i = lane == j ? t : out_i;
+        }
+        finished |= 1ull << j;
+        if (kStats) {
+          const unsigned long long n = (unsigned long long)(s.np + s.nq);
+          stat_add(c, 14, n);
+          stat_add(c, 5, 1ull);
+          stat_add(c, 11, (unsigned long long)uw * uh);
+          stat_add(c, 13, n);
+          stat_add(c, 1, 1ull);
+          stat_add(c, 0, 2ull * (unsigned long long)uw * uh);
+          stat_add(c, 10, n);
+        }
+      } else if (kPairBox && ok && !direct) {
+        // the pair box: empty or less than a tile tall, else left to the
+        // medium sweep, as is a ring whose area takes 64 bits
+        const Meta box = pair_box(mp, mq);
+        const bool empty = box.x0 >= box.x1 || box.y0 >= box.y1;
+        const uint32_t bw = side_u(box.x0, box.x1), bh = side_u(box.y0, box.y1);
+        const bool narrow = side_u(mp.x0, mp.x1) <= (uint32_t)kMaxSide && side_u(mp.y0, mp.y1) <= (uint32_t)kMaxSide &&
+                            side_u(mq.x0, mq.x1) <= (uint32_t)kMaxSide && side_u(mq.y0, mq.y1) <= (uint32_t)kMaxSide;
+        if (narrow && (empty || max(bw, bh + 1u) <= (uint32_t)kTile)) {
+          if (area_q < 0) area_q = ring_area(cur.q, s.nq);
+          const uint32_t areas = (uint32_t)(ring_area(cur.p, s.np) + area_q);  // each below 2^30
+          uint32_t n = 0;
+          if (!empty)
+            n = box_count<true>(c.slots, lane, cur, s.np, s.nq, one, box.x0, box.y0, bw, bh) >> 17;
+          out_i = lane == j ? n : out_i;
+          out_u = lane == j ? areas - n : out_u;
+          finished |= 1ull << j;
+          if (kStats) {
+            const unsigned long long nv = (unsigned long long)(s.np + s.nq);
+            stat_add(c, 12, nv);
+            stat_add(c, empty ? 7 : 5, 1ull);
+            if (!empty) {
+              stat_add(c, 11, (unsigned long long)bw * bh);
+              stat_add(c, 1, 1ull);
+              stat_add(c, 0, 2ull * (unsigned long long)bw * bh);
+              stat_add(c, 10, nv);
+              stat_add(c, 14, nv);
+            }
+          }
+        }
+      }
+      s = sn;
+      j = jn;
+      ring_move(cur.p, nxt.p, s.np);
+      ring_move(cur.q, nxt.q, s.nq);
+    }
+    if (lane_in(finished)) {
+      const uint32_t n = kPairBox ? out_i : out_i >> 17;
+      a.inter[i] = (int64_t)n;
+      a.uni[i] = (int64_t)(kPairBox ? out_u : (out_i & 0xffffu) - n);
+    }
+    const uint64_t left = ballot(medium || (sweep && !lane_in(finished)));
+    const int st = (int)(blockIdx.x % (unsigned)kStreams);
+    if (left) list_append(a.st->m_count[st], a.m_list + st * a.stream_cap, left, (int32_t)i, lane);
+    if (ballot(bucket >= 0)) {
+#pragma unroll 1
+      for (int b = 0; b < kLptBuckets; ++b) {
+        const uint64_t m = ballot(bucket == b);
+        if (m) list_append(a.st->p_count[b][st], a.l_list + (b * kStreams + st) * a.stream_cap, m, (int32_t)i, lane);
+      }
+    }
   }
   wave_stamps(a, 0, t_start, lane);
 }
@@ -1514,7 +1376,7 @@ k_batch_sweep(BatchArgs args) {
 // ------------------------------------------------- boxes of several leaf tiles
 // A pair box of at most kTileBox leaf tiles is pixelized whole, from one pass
 // over each ring per stripe of tiles (most boxes are one stripe), by the
-// vertex form of the crossing test (see union_counts) carried across tiles:
+// vertex form of the crossing test (see the union sweep) carried across tiles:
 //   - the slots of a stripe hold, per band (64 rows), one 64-bit row mask per
 //     column.  A corner XORs the rows of its own band at or above it into its
 //     column's slot of that band only: one LDS atomic per vertex, however tall
@@ -1548,27 +1410,6 @@ __device__ __forceinline__ bool tile_box(const BatchArgs& a, int gx, int gy) {
   return t == 1 || (t <= kTileBox && (t < a.min_classify_cells || a.min_classify_cells >= kDefaultClassifyCells));
 }
 
-// Extents of a lane's vertices, minima and complemented maxima, so that all
-// four reduce by minimum.
-struct Ext {
-  int x0, y0, nx1, ny1;
-};
-// Wave minimum of four values at once: two half swaps and a row swap leave
-// each value in one row of 16 lanes, which four row steps reduce together.
-__device__ __forceinline__ Ext wave_min4(const Ext& e) {
-  const auto s0 = __builtin_amdgcn_permlane32_swap(e.x0, e.y0, false, false);
-  const auto s1 = __builtin_amdgcn_permlane32_swap(e.nx1, e.ny1, false, false);
-  const int a = min((int)s0[0], (int)s0[1]), b = min((int)s1[0], (int)s1[1]);
-  const auto s2 = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-  int x = min((int)s2[0], (int)s2[1]);
-  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0xb1, 0xf, 0xf, false));
-  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x4e, 0xf, 0xf, false));
-  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x141, 0xf, 0xf, false));
-  x = min(x, __builtin_amdgcn_update_dpp(0x7fffffff, x, 0x140, 0xf, 0xf, false));
-  return Ext{__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 16),
-             __builtin_amdgcn_readlane(x, 48)};
-}
-
 // Extents, doubled area and corners of a ring of nr (>= 1) vertices held in N
 // chunks of 64 (lanes past the end hold the last vertex again).  f: its first
 // vertex; carry: whether the closing edge is vertical.  tn gains twice the signed area, summed as (x + x') (y' - y) over the edges with x
@@ -1597,10 +1438,7 @@ __device__ __forceinline__ uint32_t ring_pass(const int2 (&d)[N], int nr, int la
       const uint64_t b = ballot(d[c].x == sx);
       corners |= lane_in((b ^ ((b << 1) | carry)) & (last ? ~0ull >> (kWave - 1 - le) : ~0ull)) ? 1u << c : 0u;
       carry = (uint32_t)(b >> (kWave - 1));
-      e.x0 = min(e.x0, d[c].x);
-      e.y0 = min(e.y0, d[c].y);
-      e.nx1 = min(e.nx1, ~d[c].x);
-      e.ny1 = min(e.ny1, ~d[c].y);
+      ext_add(e, d[c]);
       tn += (uint32_t)__mul24((int)((uint32_t)d[c].x + (uint32_t)sx - 2u * (uint32_t)f.x),
                               (int)((uint32_t)sy - (uint32_t)d[c].y));
     }
@@ -1628,9 +1466,8 @@ __device__ __forceinline__ int64_t ring_area_wide(const int2* xy, int64_t o, int
 // covers nothing.
 __device__ __forceinline__ void ring_meta(const int2* xy, int64_t o, int nv, int lane, const Ext& lanes, uint32_t tn,
                                           Meta& m, int64_t& area, bool& bad) {
-  const Ext r = wave_min4(lanes);
-  m = Meta{r.x0, r.y0, ~r.nx1, ~r.ny1};
-  bad = m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord;
+  m = meta_of(wave_min4(lanes));
+  bad = out_of_range(m);
   if (bad) {
     m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
     area = 0;
@@ -1762,7 +1599,7 @@ __device__ __forceinline__ void for_stripes(const Meta& box, int gx, int gy, int
 }
 
 // The intersection counted on a pair box of one leaf tile, from rings whose
-// corners are known: as pair_box_count.  kHalves: the box is at most 32 wide,
+// corners are known (as box_count with clipping).  kHalves: the box is at most 32 wide,
 // p's columns in lanes 0-31 and q's in 32-63; M: 32-bit rows when it is at
 // most 32 tall.
 template <bool kHalves, typename M, int N>
@@ -1800,16 +1637,16 @@ __device__ __forceinline__ uint32_t corner_count(uint64_t* slot_words, const int
 
 // ------------------------------------------------------------ medium sweep
 // Second pass, two kinds of pairs:
-//   - the long pairs the setup pass listed (a ring over kMediumRing vertices,
+//   - the long pairs the sweep listed (a ring over kMediumRing vertices,
 //     or at least heavy_verts in all), largest bucket first, two waves per
 //     pair, one per ring: each loads its ring (kLongChunks chunks at once),
 //     reduces its MBR and area, scatters and scans its own slots without
 //     waiting for the other, and both count the tiles; two barriers per
 //     stripe.
 //   - then the medium list: pairs with rings of at most kMediumRing vertices
-//     that the union sweep did not finish (a ring over kSweepRing vertices, a
-//     pair box larger than a leaf tile, or, with the union counted directly,
-//     a union box larger than one), one wave per pair, rings in registers.
+//     that the union sweep did not finish (a ring over kSweepRing vertices or
+//     an empty one, or a union box larger than a leaf tile), one wave per
+//     pair, rings in registers.
 // Both pixelize boxes of up to kTileBox tiles at once; a larger one, one to be
 // classified, or any one when the union is counted directly, is listed with
 // its box for the persistent kernel, I = 0 and U = |p| + |q| (0 when the union
@@ -1839,9 +1676,9 @@ __device__ __forceinline__ void list_run(const BatchArgs& a, int64_t i, int64_t 
 }
 
 // Every chunk of both rings of a medium pair (clamped to each ring's last
-// vertex), or for no pair reads of `dummy`.
-__device__ __forceinline__ void medium_load(const BatchArgs& a, const SweepRec& s, const int2* dummy, int lane,
-                                            PairRegs<kMediumChunks>& r) {
+// vertex), or for no pair or an empty ring reads of `dummy`.
+__device__ __forceinline__ void medium_load(const BatchArgs& a, const PairRec& s, int lane, PairRegs<kMediumChunks>& r) {
+  const int2* dummy = reinterpret_cast<const int2*>(a.st);
   const int2* P = s.np > 0 ? a.A.xy + s.op : dummy;
   const int2* Q = s.nq > 0 ? a.B.xy + s.oq : dummy;
   const int lp = max(s.np - 1, 0), lq = max(s.nq - 1, 0);
@@ -1878,7 +1715,7 @@ __device__ __forceinline__ uint8_t pair_class(Ctx& c, const Meta& mp, const Meta
   return small ? kClsSmall : kClsLarge;
 }
 
-__device__ __forceinline__ void medium_one(Ctx& c, const SweepRec& s, const PairRegs<kMediumChunks>& r, int64_t i) {
+__device__ __forceinline__ void medium_one(Ctx& c, const PairRec& s, const PairRegs<kMediumChunks>& r, int64_t i) {
   const BatchArgs& a = *c.a;
   const int lane = c.lane;
   Meta mp{INT_MAX, INT_MAX, INT_MIN, INT_MIN}, mq = mp, box;
@@ -1887,7 +1724,7 @@ __device__ __forceinline__ void medium_one(Ctx& c, const SweepRec& s, const Pair
   auto meta = [&](const int2(&d)[kMediumChunks], const int2* xy, int64_t o, int nv, Meta& m, int64_t& area,
                   bool& bad) -> uint32_t {
     if (nv <= 0) return 0;
-    Ext e{d[0].x, d[0].y, ~d[0].x, ~d[0].y};
+    Ext e = ext_of(d[0]);
     const int2 f = lane_value(d[0], 0);
     // every chunk is loaded, so the last lane of the last one holds the last vertex
     uint32_t tn = 0;
@@ -1987,7 +1824,7 @@ __device__ __forceinline__ void long_one(Ctx& c, int64_t i, int w, uint64_t* tea
       do {
         rs.ahead();
         const int2 v = rs.cur, x = rs.succ();
-        e = Ext{min(e.x0, v.x), min(e.y0, v.y), min(e.nx1, ~v.x), min(e.ny1, ~v.y)};
+        ext_add(e, v);
         const uint32_t t = (uint32_t)__mul24((int)((uint32_t)v.x + (uint32_t)x.x - 2u * (uint32_t)f.x),
                                              (int)((uint32_t)x.y - (uint32_t)v.y));
         tn += rs.valid() ? t : 0u;
@@ -2005,6 +1842,7 @@ __device__ __forceinline__ void long_one(Ctx& c, int64_t i, int w, uint64_t* tea
   box = Meta{uniform(box.x0), uniform(box.y0), uniform(box.x1), uniform(box.y1)};
   const int gx = (box.x1 - box.x0 + kTile - 1) / kTile, gy = (box.y1 - box.y0 + kTile - 1) / kTile;
   const bool settled = uniform(cls) == kClsDone;
+  if (settled && w == 0) stat_add(c, 7, 1ull);
   const bool listed = !settled && (direct_union(a) || !tile_box(a, gx, gy));
   uint32_t n = 0;
   if (!settled && !listed) {
@@ -2048,8 +1886,10 @@ __device__ __forceinline__ void long_one(Ctx& c, int64_t i, int w, uint64_t* tea
   if (w == 0 && lane == 0) {
     a.inter[i] = (int64_t)n;
     a.uni[i] = U - (int64_t)n;
-    a.cls[i] = cls;
-    if (listed) list_run(a, i, verts, box);
+    if (listed) {
+      list_run(a, i, verts, box);
+      a.cls[i] = cls;
+    }
   }
 }
 
@@ -2072,16 +1912,28 @@ k_batch_medium(BatchArgs args) {
   const BatchArgs& a = args;
   const int lane = c.lane;
   const unsigned long long t_start = wave_stamp(a);
-  const uint32_t own = kSweepSteal || gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
+  if (blockIdx.x == 0 && threadIdx.x < (unsigned)kMaxGrid) {
+    // the queues of the previous call were cleared by the sweep
+    a.st->q_head[threadIdx.x].v = 0;
+    a.st->q_tail[threadIdx.x].v = 0;
+  }
+  const uint32_t own = gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
   uint32_t p_empty = own;
   // the long pairs, bucket after bucket from the largest, one pair per claim;
-  // wave 0 claims the next one while the team works on the one in hand
-  int64_t nb[kLptBuckets], n_long = 0;
+  // wave 0 claims the next one while the team works on the one in hand.  The
+  // lists' parts stand end to end, lane L's part being that of stream L %
+  // kStreams of bucket kLptBuckets - 1 - L / kStreams, from `first` on.
+  constexpr int kParts = kLptBuckets * kStreams;
+  const int part_b = kLptBuckets - 1 - lane / kStreams, part_s = lane % kStreams;
+  const int n_here = lane < kParts ? (int)a.st->p_count[part_b][part_s].v : 0;
+  int first = n_here;
 #pragma unroll
-  for (int b = 0; b < kLptBuckets; ++b) {
-    nb[b] = (int64_t)a.st->p_count[b].v;
-    n_long += nb[b];
+  for (int d = 1; d < kParts; d <<= 1) {
+    const int v = __shfl_up(first, d, kWave);
+    if (lane >= d) first += v;
   }
+  const int64_t n_long = __builtin_amdgcn_readlane(first, kParts - 1);
+  first -= n_here;
   if (n_long > 0) {
     int64_t next = -1;
     if (w == 0) next = claim_chunk(a.st->p_next, n_long, 1, c.xcd, lane, p_empty);
@@ -2094,44 +1946,58 @@ k_batch_medium(BatchArgs args) {
       __syncthreads();
       const int64_t k = uniform64(claimed[it]);
       if (k < 0) break;
-      int64_t kk = k;
-      int bk = kLptBuckets - 1;
-#pragma unroll
-      for (int b = kLptBuckets - 1; b > 0; --b) {
-        if (bk == b && kk >= nb[b]) {
-          kk -= nb[b];
-          bk = b - 1;
-        }
-      }
-      long_one<kStats>(c, uniform64((int64_t)a.l_list[(int64_t)bk * a.n_pairs + kk]), w, team_slots, ex[it]);
+      const int part = kWave - 1 - __clzll((long long)ballot(lane < kParts && first <= (int)k));
+      const int64_t at = (int64_t)((kLptBuckets - 1 - part / kStreams) * kStreams + part % kStreams) * a.stream_cap;
+      const int64_t i = a.l_list[at + (k - __builtin_amdgcn_readlane(first, part))];
+      long_one<kStats>(c, uniform64(i), w, team_slots, ex[it]);
     }
     __syncthreads();
   }
-  const int64_t n_med = (int64_t)a.st->m_count.v;
+  // the medium list, its streams' parts end to end
+  uint32_t n_part[kStreams], n_med = 0;
+#pragma unroll
+  for (int st = 0; st < kStreams; ++st) {
+    n_part[st] = uniform_u((uint32_t)a.st->m_count[st].v);
+    n_med += n_part[st];
+  }
   // every wave takes an equal share of the list, in runs of `run` consecutive
   // entries that interleave over the waves: the pairs are alike enough, and a
   // claim per few entries left each wave waiting on a counter, the list, the
   // records and the rings in turn (200,000 uniform pairs, 26,000 of them here:
   // 74 us with claims)
-  const WaveShare share(n_med, kTeamWaves, w);
+  const WaveShare share((int64_t)n_med, kTeamWaves, w, 1);
 #pragma unroll 1
   for (int64_t k0 = 0; k0 < share.count; k0 += kWave) {
     const int cnt = uniform((int)min((int64_t)kWave, share.count - k0));
     // lane j: pair index and record of the wave's entry k0 + j
-    const int idx = lane < cnt ? a.m_list[share.entry(k0 + lane)] : 0;
-    const ChunkRecs cr = gather_recs(a, idx, lane < cnt);
-    const int2* dummy = reinterpret_cast<const int2*>(a.rec + __builtin_amdgcn_readfirstlane(idx));
+    int idx = 0;
+    PairRec recs{0, 0, 0, 0};
+    if (lane < cnt) {
+      uint32_t e = (uint32_t)share.entry(k0 + lane);
+      int64_t part = 0;
+      bool found = false;
+#pragma unroll
+      for (int st = 0; st < kStreams; ++st) {
+        found = found || e < n_part[st];
+        if (!found) {
+          e -= n_part[st];
+          part += a.stream_cap;
+        }
+      }
+      idx = a.m_list[part + e];
+      recs = pair_rec(a, a.pa[idx], a.pb[idx]);
+    }
     // the pair in hand (sc, rc) and the next one (sn, rn), whose loads are in
     // flight while the pair in hand is processed: every chunk of both rings,
     // loaded the same way whatever the pair, so that the compiler waits only
     // for the pair in hand's loads
     PairRegs<kMediumChunks> rc, rn;
-    SweepRec sc = sweep_rec(cr, 0);
-    medium_load(a, sc, dummy, lane, rc);
+    PairRec sc = rec_of_lane(recs, 0);
+    medium_load(a, sc, lane, rc);
 #pragma unroll 1
     for (int j = 0; j < cnt; ++j) {
-      const SweepRec sn = j + 1 < cnt ? sweep_rec(cr, j + 1) : SweepRec{0, 0, 0, 0, kClsDone};
-      medium_load(a, sn, dummy, lane, rn);
+      const PairRec sn = j + 1 < cnt ? rec_of_lane(recs, j + 1) : PairRec{0, 0, 0, 0};
+      medium_load(a, sn, lane, rn);
       medium_one(c, sc, rc, (int64_t)__builtin_amdgcn_readlane(idx, j));
       sc = sn;
       rc = rn;
@@ -2141,10 +2007,10 @@ k_batch_medium(BatchArgs args) {
 }
 
 // ----------------------------------------------------------- persistent run
-// Second pass: the listed pairs (heavy pairs from the setup pass, claimed
-// first, then the sweep's pairs whose box is larger than a leaf tile), each
-// with its box from the prepass or the sweep.  Waves claim, in this order:
-// boxes from their queue, listed pairs, boxes from any queue.
+// Third pass: the pairs the medium sweep listed, each with its box: those of
+// more leaf tiles than it counts at once, those to be classified, and every
+// pair of more than one when the union is counted directly.  Waves claim, in
+// this order: boxes from their queue, listed pairs, boxes from any queue.
 template <bool kStats>
 __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -2161,6 +2027,15 @@ __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args)
   c.home = c.xcd % args.n_queues;
   const BatchArgs& a = args;
   const unsigned long long t_start = wave_stamp(a);
+  if (blockIdx.x == 0) {
+    // the lists that the next call's sweep appends to (see next_call_state)
+    for (unsigned t = threadIdx.x; t < (unsigned)((kLptBuckets + 1) * kStreams); t += blockDim.x) {
+      if (t < (unsigned)(kLptBuckets * kStreams))
+        a.st->p_count[t / kStreams][t % kStreams].v = 0;
+      else
+        a.st->m_count[t % kStreams].v = 0;
+    }
+  }
   unsigned long long n_list[kLptBuckets], n_all = 0;
 #pragma unroll
   for (int b = 0; b < kLptBuckets; ++b) {
@@ -2216,133 +2091,9 @@ __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args)
   wave_stamps(a, 2, t_start, c.lane);
 }
 
-// ------------------------------------------------------------ setup / reset
-// Clear the queue slots the previous call touched, then the counters.
-__global__ void __launch_bounds__(256) k_batch_clear_slots(BatchArgs a) {
-  for (int q = 0; q < a.n_queues; ++q) {
-    unsigned long long used = max(a.st->q_tail[q].v, a.st->q_head[q].v);
-    if (used > (unsigned long long)a.queue_cap) used = (unsigned long long)a.queue_cap;
-    unsigned long long* base = a.queue + (size_t)q * a.queue_cap;
-    for (unsigned long long j = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; j < used;
-         j += (unsigned long long)gridDim.x * blockDim.x)
-      base[j] = 0;
-  }
-}
-
-__global__ void k_batch_clear_counters(BatchArgs a) {
-  unsigned long long* p = reinterpret_cast<unsigned long long*>(a.st);
-  const int n = (int)(sizeof(BatchState) / sizeof(unsigned long long));
-  for (int k = threadIdx.x; k < n; k += blockDim.x) p[k] = 0;
-}
-
-// Per pair: index check, the pair's record and class: swept (rings of at
-// most kSweepRing vertices), medium (at most kMediumRing), or listed by
-// vertex count for the prepass and the persistent kernel (longer rings, or
-// at least heavy_verts vertices in all).
-__global__ void __launch_bounds__(256) k_batch_setup(BatchArgs a, int per) {
-  // a block takes per x 256 consecutive pairs (coalesced rows of 256) and
-  // reserves room for its listed pairs with one atomic per bucket: the
-  // per-thread counts of the four buckets travel as 16-bit fields of one
-  // 64-bit scan
-  __shared__ unsigned long long scan[256];
-  __shared__ unsigned long long base_s[kLptBuckets];
-  const int tid = threadIdx.x;
-  const int64_t b0 = (int64_t)blockIdx.x * 256 * per;
-  __shared__ unsigned mscan[256];
-  __shared__ unsigned long long mbase_s;
-  uint32_t lmask = 0;      // bit t: pair t of this thread is listed
-  uint32_t bmask = 0;      // bits 2t, 2t+1: its bucket
-  uint32_t mmask = 0;      // bit t: pair t of this thread is a medium pair
-  unsigned long long cnt = 0;
-  for (int t = 0; t < per; ++t) {
-    const int64_t i = b0 + (int64_t)t * 256 + tid;
-    if (i >= a.n_pairs) break;
-    const int64_t ia = a.pa[i], ib = a.pb[i];
-    uint8_t cls = kClsSweep;
-    PairRec r{0, 0, 0, 0, 0, 0};
-    if (ia < 0 || ia >= a.A.n || ib < 0 || ib >= a.B.n) {
-      latch_error(a.err, kErrIndex);
-      a.inter[i] = 0;
-      a.uni[i] = 0;
-      cls = kClsDone;
-    } else {
-      r.op = a.A.off[ia];
-      r.np = (int32_t)(a.A.off[ia + 1] - r.op);
-      r.oq = a.B.off[ib];
-      r.nq = (int32_t)(a.B.off[ib + 1] - r.oq);
-      const int64_t n = (int64_t)r.np + r.nq;
-      if (r.np > kMediumRing || r.nq > kMediumRing || n >= a.heavy_verts) {
-        const int bk = lpt_bucket(a, n);
-        lmask |= 1u << t;
-        bmask |= (uint32_t)bk << (2 * t);
-        cnt += 1ull << (16 * bk);
-        cls = kClsHeavy;
-      } else if (r.np > kSweepRing || r.nq > kSweepRing) {
-        mmask |= 1u << t;
-        cls = kClsMedium;
-      }
-    }
-    r.cls = cls;
-    a.cls[i] = cls;
-    a.rec[i] = r;
-  }
-  // exclusive prefix of the per-thread counts over the block
-  const unsigned mcnt = (unsigned)__popc(mmask);
-  scan[tid] = cnt;
-  mscan[tid] = mcnt;
-  __syncthreads();
-  for (int d = 1; d < 256; d <<= 1) {
-    const unsigned long long v = tid >= d ? scan[tid - d] : 0ull;
-    const unsigned mv = tid >= d ? mscan[tid - d] : 0u;
-    __syncthreads();
-    scan[tid] += v;
-    mscan[tid] += mv;
-    __syncthreads();
-  }
-  const unsigned long long total = scan[255];
-  if (tid < kLptBuckets) {
-    const unsigned long long nb = (total >> (16 * tid)) & 0xffffull;
-    base_s[tid] = nb ? atomicAdd(&a.st->p_count[tid].v, nb) : 0ull;
-  } else if (tid == kLptBuckets) {
-    const unsigned long long nm = mscan[255];
-    mbase_s = nm ? atomicAdd(&a.st->m_count.v, nm) : 0ull;
-  }
-  __syncthreads();
-  unsigned long long mpos = mbase_s + (mscan[tid] - mcnt);
-  for (uint32_t m = mmask; m; m &= m - 1)
-    a.m_list[mpos++] = (int32_t)(b0 + (int64_t)(__ffs((int)m) - 1) * 256 + tid);
-  const unsigned long long before = scan[tid] - cnt;
-  unsigned long long pos[kLptBuckets];
-#pragma unroll
-  for (int b = 0; b < kLptBuckets; ++b) pos[b] = base_s[b] + ((before >> (16 * b)) & 0xffffull);
-  for (uint32_t m = lmask; m; m &= m - 1) {
-    const int t = __ffs((int)m) - 1;
-    const int bk = (int)((bmask >> (2 * t)) & 3u);
-    const int64_t k = (int64_t)(bk == 3 ? pos[3]++ : bk == 2 ? pos[2]++ : bk == 1 ? pos[1]++ : pos[0]++);
-    a.l_list[(int64_t)bk * a.n_pairs + k] = (int32_t)(b0 + (int64_t)t * 256 + tid);
-  }
-}
-
-__global__ void k_batch_stats_empty(BatchArgs a) {
-  // pairs that ended in setup or in the heavy prepass (stats only)
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < a.n_pairs && a.cls[i] == kClsDone) atomicAdd(&a.st->stats[7], 1ull);
-}
-
-hipError_t launch_batch_reset(const BatchArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_batch_clear_slots, dim3(1024), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_batch_clear_counters, dim3(1), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_batch_setup(const BatchArgs& a, hipStream_t s) {
-  if (a.n_pairs <= 0) return hipSuccess;
-  // enough blocks to fill the chip (about 1024), at most kSetupPerThread pairs per thread
-  const int per = (int)std::max<int64_t>(1, std::min<int64_t>(kSetupPerThread, a.n_pairs / (256 * 1024)));
-  const int64_t per_block = 256 * (int64_t)per;
-  const unsigned blocks = (unsigned)((a.n_pairs + per_block - 1) / per_block);
-  hipLaunchKernelGGL(k_batch_setup, dim3(blocks), dim3(256), 0, s, a, per);
-  return hipGetLastError();
+// ------------------------------------------------------------------ launches
+__global__ void k_batch_clear_stats(BatchState* st) {
+  if (threadIdx.x < (unsigned)kNumStats) st->stats[threadIdx.x] = 0;
 }
 
 int batch_occupancy(int waves_per_wg) {
@@ -2372,6 +2123,7 @@ int batch_medium_waves_per_wg() { return kTeamWaves; }
 
 hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_grid, bool pair_box, hipStream_t s) {
   if (a.n_pairs <= 0) return hipSuccess;
+  if (a.stats_on) hipLaunchKernelGGL(k_batch_clear_stats, dim3(1), dim3(kWave), 0, s, a.st);
   // the instances with counters run the same grids as those without (a
   // workgroup the device cannot hold yet waits its turn; no wave waits on
   // another)
@@ -2399,8 +2151,6 @@ hipError_t launch_batch_persistent(const BatchArgs& a, int grid, int waves_per_w
     hipLaunchKernelGGL(k_batch_run<true>, dim3(grid), dim3(waves_per_wg * kWave), lds, s, a);
   else
     hipLaunchKernelGGL(k_batch_run<false>, dim3(grid), dim3(waves_per_wg * kWave), lds, s, a);
-  if (a.stats_on)
-    hipLaunchKernelGGL(k_batch_stats_empty, dim3((unsigned)((a.n_pairs + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -19,6 +19,12 @@ struct sccg_ctx {
   sccg_params p{};
   std::string msg;
   int cu_count = 1;
+  // workgroups per CU of the batched kernels (0: not asked yet): the union
+  // sweep without and with pair boxes, the medium sweep, and the persistent
+  // kernel by waves per workgroup
+  int occ_sweep[2] = {0, 0};
+  int occ_medium = 0;
+  int occ_run[9] = {};
   // per-polygon scratch
   Meta* metaA = nullptr;
   int64_t* areaA = nullptr;
@@ -32,7 +38,6 @@ struct sccg_ctx {
   uint32_t* err = nullptr;
   // per-pair scratch
   uint8_t* cls = nullptr;
-  PairRec* rec = nullptr;
   int32_t* l_list = nullptr;
   Meta* hbox = nullptr;
   int64_t cap_pairs = 0;
@@ -186,8 +191,8 @@ int ensure_pairs(sccg_ctx* c, int64_t n) {
   drop_graph(c);
   int64_t want = n + n / 4 + 1024;
   int r;
-  if ((r = grow(c, &c->cls, want, "pair classes")) || (r = grow(c, &c->rec, want, "pair records")) ||
-      (r = grow(c, &c->l_list, want * kPairLists, "pair lists")) || (r = grow(c, &c->hbox, want, "heavy boxes"))) {
+  if ((r = grow(c, &c->cls, want, "pair classes")) ||
+      (r = grow(c, &c->l_list, pair_list_room(want), "pair lists")) || (r = grow(c, &c->hbox, want, "heavy boxes"))) {
     c->cap_pairs = 0;
     return r;
   }
@@ -209,8 +214,7 @@ int need(sccg_ctx* c, T** ptr, int64_t& cap, int64_t n, const char* what) {
 
 int ensure_queue(sccg_ctx* c) {
   const int64_t want = (int64_t)c->p.n_queues * c->p.queue_cap;
-  // The reset kernel of a call clears the slots the previous call used,
-  // found from that call's head and tail counters in that call's layout, so
+  // The sweep of a call clears the slots the previous call used, found from that call's head and tail counters in that call's layout, so
   // the slots are cleared here whenever the layout changes.
   if (c->queue && c->queue_slots == want && c->queue_nq == c->p.n_queues && c->queue_per == c->p.queue_cap)
     return SCCG_OK;
@@ -231,6 +235,39 @@ int ensure_queue(sccg_ctx* c) {
   c->queue_nq = c->p.n_queues;
   c->queue_per = c->p.queue_cap;
   return SCCG_OK;
+}
+
+// Workgroups of the batched kernels: as many as fit on the device at once, and
+// no more than the pairs can use (a wave per pair in the union sweep, a
+// workgroup per long pair or a wave per medium one in the medium sweep).  The
+// persistent kernel shares the boxes of few pairs among all its waves.
+struct BatchGrids {
+  int sweep, medium, run;
+};
+BatchGrids batch_grids(sccg_ctx* c, int64_t n_pairs) {
+  const bool pair_box = c->p.sweep_pair_box == 2;
+  int& os = c->occ_sweep[pair_box ? 1 : 0];
+  int& orun = c->occ_run[c->p.waves_per_wg];
+  if (!os) os = batch_sweep_occupancy(pair_box);
+  if (!c->occ_medium) c->occ_medium = batch_medium_occupancy();
+  BatchGrids g;
+  const int64_t per_wg = batch_sweep_waves_per_wg();
+  g.sweep = (int)std::min<int64_t>((int64_t)c->cu_count * os, (n_pairs + per_wg - 1) / per_wg);
+  g.medium = (int)std::min<int64_t>((int64_t)c->cu_count * c->occ_medium, n_pairs);
+  g.run = c->p.grid;
+  if (g.run == 0) {
+    if (!orun) orun = batch_occupancy(c->p.waves_per_wg);
+    g.run = c->cu_count * orun;
+  }
+  return g;
+}
+
+// The lists of a call, one after the other from ba.l_list (pair_list_room).
+void place_lists(BatchArgs& ba, const BatchGrids& g) {
+  const int64_t waves = (int64_t)g.sweep * batch_sweep_waves_per_wg();
+  ba.stream_cap = stream_cap_of(g.sweep, batch_sweep_waves_per_wg(), most_share(ba.n_pairs, waves, ba.chunk));
+  ba.m_list = ba.l_list + kLptBuckets * kStreams * ba.stream_cap;
+  ba.run_list = ba.m_list + kStreams * ba.stream_cap;
 }
 
 // Start/stop events for the next timed launch (created on first use).
@@ -271,15 +308,14 @@ constexpr int64_t kNoAllocQueueSlots = int64_t(1) << 17;  // all queues together
 constexpr int kNoAllocMaxDevices = 64;
 constexpr size_t na_align(size_t n) { return (n + 255) / 256 * 256; }
 constexpr size_t kNaQueue = na_align(sizeof(BatchState));
-constexpr size_t kNaRec = kNaQueue + na_align(sizeof(unsigned long long) * kNoAllocQueueSlots);
-constexpr size_t kNaHbox = kNaRec + na_align(sizeof(PairRec) * kNoAllocMaxPairs);
+constexpr size_t kNaHbox = kNaQueue + na_align(sizeof(unsigned long long) * kNoAllocQueueSlots);
 constexpr size_t kNaList = kNaHbox + na_align(sizeof(Meta) * kNoAllocMaxPairs);
-constexpr size_t kNaCls = kNaList + na_align(sizeof(int32_t) * kPairLists * kNoAllocMaxPairs);
+constexpr size_t kNaCls = kNaList + na_align(sizeof(int32_t) * pair_list_room(kNoAllocMaxPairs));
 constexpr size_t kNoAllocBytes = kNaCls + na_align(kNoAllocMaxPairs);
 
 struct NoAllocDevice {
   unsigned char* ptr = nullptr;  // device address of `scratch` on this GPU
-  int32_t nq = 0, cap = 0;       // queue layout of the last call (0: every slot clear)
+  int32_t nq = 0, cap = 0;       // queue layout of the last call (0: every slot clear, -1: a call failed)
 };
 std::mutex g_noalloc_mu;
 NoAllocDevice g_noalloc[kNoAllocMaxDevices];
@@ -373,7 +409,7 @@ int sccg_destroy(sccg_ctx* c) {
   drop_graph(c);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   void* ptrs[] = {c->metaA,  c->areaA,  c->bigA,        c->metaB,  c->areaB,   c->bigB,    c->big_count,
-                  c->err,    c->cls,    c->rec,         c->l_list, c->hbox,    c->st,      c->queue,
+                  c->err,    c->cls,    c->l_list, c->hbox,    c->st,      c->queue,
                   c->plain_stats, c->wave_t,
                   c->j_bbox, c->j_grid, c->j_cells,     c->j_cell_base, c->j_sums, c->j_count, c->j_start,
                   c->j_list, c->j_bcount, c->j_bstart, c->j_acc};
@@ -474,22 +510,18 @@ __global__ void k_zero_stats(unsigned long long* s) {
   if ((int)threadIdx.x < kNumStats) s[threadIdx.x] = 0;
 }
 
-// The launches of one BATCHED call on the context's stream: reset, setup,
-// the union sweep, the medium sweep with the prepass of the listed pairs,
-// the persistent kernel.  (A prepass on a second stream beside the sweeps
-// measured no faster: the union sweep holds every wave slot.)
-static int launch_batch_sequence(sccg_ctx* c, const BatchArgs& ba, int sweep_grid, int medium_grid, int grid) {
+// The launches of one BATCHED call on the context's stream: the union sweep,
+// the medium sweep with the long pairs, the persistent kernel.
+static int launch_batch_sequence(sccg_ctx* c, const BatchArgs& ba, const BatchGrids& g) {
   hipError_t e;
-  if ((e = launch_batch_reset(ba, c->stream)) != hipSuccess) return hip_fail(c, e, "batch reset");
-  if ((e = launch_batch_setup(ba, c->stream)) != hipSuccess) return hip_fail(c, e, "batch setup");
-  if ((e = launch_batch_sweeps(ba, sweep_grid, medium_grid, c->p.sweep_pair_box == 2, c->stream)) != hipSuccess)
+  if ((e = launch_batch_sweeps(ba, g.sweep, g.medium, c->p.sweep_pair_box == 2, c->stream)) != hipSuccess)
     return hip_fail(c, e, "batch sweeps");
-  if ((e = launch_batch_persistent(ba, grid, c->p.waves_per_wg, c->stream)) != hipSuccess)
+  if ((e = launch_batch_persistent(ba, g.run, c->p.waves_per_wg, c->stream)) != hipSuccess)
     return hip_fail(c, e, "batch persistent kernel");
   return SCCG_OK;
 }
 
-static int launch_batched(sccg_ctx* c, const BatchArgs& ba, int sweep_grid, int medium_grid, int grid) {
+static int launch_batched(sccg_ctx* c, const BatchArgs& ba, const BatchGrids& g) {
   hipError_t e;
   hipEvent_t t0 = nullptr, t1 = nullptr;
   if (c->timing_on) {
@@ -497,7 +529,7 @@ static int launch_batched(sccg_ctx* c, const BatchArgs& ba, int sweep_grid, int 
     if (r) return r;
     HIP_TRY(c, hipEventRecord(t0, c->stream));
   }
-  if (int r = launch_batch_sequence(c, ba, sweep_grid, medium_grid, grid)) return r;
+  if (int r = launch_batch_sequence(c, ba, g)) return r;
   if (c->timing_on) HIP_TRY(c, hipEventRecord(t1, c->stream));
   return SCCG_OK;
 }
@@ -566,10 +598,7 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   ba.uni = out_union;
   ba.err = c->err;
   ba.cls = c->cls;
-  ba.rec = c->rec;
   ba.l_list = c->l_list;
-  ba.run_list = c->l_list + (size_t)kLptBuckets * (size_t)n_pairs;
-  ba.m_list = ba.run_list + (size_t)kLptBuckets * (size_t)n_pairs;
   ba.hbox = c->hbox;
   ba.st = c->st;
   ba.queue = c->queue;
@@ -581,15 +610,13 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   ba.min_classify_cells = c->p.min_classify_cells;
   ba.flags = c->p.flags;
   ba.stats_on = c->stats_on;
-  int grid = c->p.grid;
-  if (grid == 0) grid = c->cu_count * batch_occupancy(c->p.waves_per_wg);
-  const int sweep_grid = c->cu_count * batch_sweep_occupancy(c->p.sweep_pair_box == 2);
-  const int medium_grid = c->cu_count * batch_medium_occupancy();
+  const BatchGrids grids = batch_grids(c, n_pairs);
+  place_lists(ba, grids);
   if (c->stamps_on) {
     // every wave of the sweeps and of the persistent kernel stamps its start and end
-    const int64_t sweep_waves = (int64_t)sweep_grid * batch_sweep_waves_per_wg();
-    const int64_t medium_waves = (int64_t)medium_grid * batch_medium_waves_per_wg();
-    const int64_t run_waves = (int64_t)grid * c->p.waves_per_wg;
+    const int64_t sweep_waves = (int64_t)grids.sweep * batch_sweep_waves_per_wg();
+    const int64_t medium_waves = (int64_t)grids.medium * batch_medium_waves_per_wg();
+    const int64_t run_waves = (int64_t)grids.run * c->p.waves_per_wg;
     const int64_t want = std::max(std::max(sweep_waves, medium_waves), run_waves);
     if (want > c->wave_cap) {
       (void)hipStreamSynchronize(c->stream);
@@ -607,20 +634,24 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
     c->wave_n[2] = run_waves;
   }
   const bool use_graph = c->stream != nullptr && !(c->p.flags & SCCG_F_NO_GRAPH) && !c->timing_on;
-  if (!use_graph) return launch_batched(c, ba, sweep_grid, medium_grid, grid);
+  if (!use_graph) {
+    r = launch_batched(c, ba, grids);
+    if (r) c->queue_nq = 0;  // part of the sequence ran: ensure_queue clears the state it left
+    return r;
+  }
   // the graph is keyed on every launch argument
   char key[512];
   snprintf(key, sizeof(key), "%lld/%p/%p|%lld/%p/%p|%lld/%p/%p/%p/%p|%d/%d/%d/%d/%d/%d/%u/%d/%d/%d",
            (long long)A->n_polys, (const void*)A->offsets, (const void*)A->xy,
            (long long)B->n_polys, (const void*)B->offsets, (const void*)B->xy, (long long)n_pairs,
            (const void*)pair_a, (const void*)pair_b, (void*)out_inter, (void*)out_union, ba.queue_cap, ba.n_queues,
-           ba.chunk, ba.heavy_verts, ba.min_cells_to_queue, ba.min_classify_cells, ba.flags, ba.stats_on | (c->stamps_on << 1), grid,
+           ba.chunk, ba.heavy_verts, ba.min_cells_to_queue, ba.min_classify_cells, ba.flags, ba.stats_on | (c->stamps_on << 1), grids.run,
            c->p.sweep_pair_box);
   if (!c->gexec || c->gkey != key) {
     drop_graph(c);
     hipGraph_t g = nullptr;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    r = launch_batched(c, ba, sweep_grid, medium_grid, grid);
+    r = launch_batched(c, ba, grids);
     hipError_t e = hipStreamEndCapture(c->stream, &g);
     if (r) {
       if (g) (void)hipGraphDestroy(g);
@@ -663,11 +694,11 @@ int sccg_area_pairs_noalloc(sccg_ctx* c, const sccg_polys* A, const sccg_polys* 
     NoAllocDevice& d = g_noalloc[c->device];
     if (!d.ptr) return fail(c, SCCG_E_HIP, "no-allocation scratch not set up on device %d", c->device);
     base = d.ptr;
-    // the reset kernel clears the slots the previous call used in that
-    // call's layout: a new layout needs every slot cleared first
+    // the sweep clears the slots the previous call used in that call's
+    // layout: a new layout needs every slot, and the state, cleared first
     if (d.nq != 0 && (d.nq != nq || d.cap != cap)) {
       hipLaunchKernelGGL(k_noalloc_clear, dim3(256), dim3(256), 0, c->stream,
-                         reinterpret_cast<unsigned long long*>(base + kNaQueue), (int64_t)kNoAllocQueueSlots);
+                         reinterpret_cast<unsigned long long*>(base), (int64_t)(kNaHbox / sizeof(unsigned long long)));
       HIP_TRY(c, hipGetLastError());
     }
     d.nq = nq;
@@ -684,11 +715,8 @@ int sccg_area_pairs_noalloc(sccg_ctx* c, const sccg_polys* A, const sccg_polys* 
   ba.err = c->err;
   ba.st = reinterpret_cast<BatchState*>(base);
   ba.queue = reinterpret_cast<unsigned long long*>(base + kNaQueue);
-  ba.rec = reinterpret_cast<PairRec*>(base + kNaRec);
   ba.hbox = reinterpret_cast<Meta*>(base + kNaHbox);
   ba.l_list = reinterpret_cast<int32_t*>(base + kNaList);
-  ba.run_list = ba.l_list + (size_t)kLptBuckets * (size_t)n_pairs;
-  ba.m_list = ba.run_list + (size_t)kLptBuckets * (size_t)n_pairs;
   ba.cls = base + kNaCls;
   ba.queue_cap = cap;
   ba.n_queues = nq;
@@ -698,11 +726,15 @@ int sccg_area_pairs_noalloc(sccg_ctx* c, const sccg_polys* A, const sccg_polys* 
   ba.min_classify_cells = c->p.min_classify_cells;
   ba.flags = c->p.flags;
   ba.stats_on = 0;
-  int grid = c->p.grid;
-  if (grid == 0) grid = c->cu_count * batch_occupancy(c->p.waves_per_wg);
-  const int sweep_grid = c->cu_count * batch_sweep_occupancy(c->p.sweep_pair_box == 2);
-  const int medium_grid = c->cu_count * batch_medium_occupancy();
-  return launch_batch_sequence(c, ba, sweep_grid, medium_grid, grid);
+  const BatchGrids grids = batch_grids(c, n_pairs);
+  place_lists(ba, grids);
+  r = launch_batch_sequence(c, ba, grids);
+  if (r) {
+    // part of the sequence ran: the next call clears the state it left
+    std::lock_guard<std::mutex> g(g_noalloc_mu);
+    g_noalloc[c->device].nq = -1;
+  }
+  return r;
 }
 
 int sccg_jaccard_sets(sccg_ctx* c, int64_t n_sets, const int64_t* set_pair_off, const int64_t* inter,

@@ -22,12 +22,8 @@ enum : uint32_t {
   kErrWatchdog = 8u,  // a bounded wait in the persistent kernel ran out
 };
 
-// Pair classes of the batched path: done in a prepass, swept in index order
-// (rings short enough to be held in registers), medium (rings held in
-// registers by the second sweep), or heavy (listed for the persistent
-// kernel); listed pairs are then marked by their box (small: one leaf tile;
-// large: split).
-enum : uint8_t { kClsDone = 0, kClsSweep = 1, kClsHeavy = 2, kClsSmall = 3, kClsLarge = 4, kClsMedium = 5 };
+// Classes of a pair by its box: nothing to count, one leaf tile, or larger.
+enum : uint8_t { kClsDone = 0, kClsSmall = 1, kClsLarge = 2 };
 
 struct Polys {
   int64_t n;
@@ -83,36 +79,47 @@ struct alignas(128) Counter {
 // owns entries s, s + kStreams, s + 2 kStreams, ... of a list.
 constexpr int kStreams = 8;
 
-// Device-side state of the batched path (one block of device memory), reset
-// at the start of every call after the slots the previous call touched
-// (below max(head, tail) of each queue) are cleared.
+// Device-side state of the batched path (one block of device memory), zero
+// before the first call; the kernels of each call leave it ready for the next.
 // Listed pairs are kept in kLptBuckets lists by vertex count (the cost the
-// setup pass can see): at least 4, 2 or 1 times heavy_verts, and the rest;
+// sweep can see): at least 4, 2 or 1 times heavy_verts, and the rest;
 // the persistent kernel claims the largest bucket first.
 constexpr int kLptBuckets = 4;
-// 4-byte list entries per pair: the long pairs' buckets, the persistent
-// kernel's, the medium list
-constexpr int kPairLists = 2 * kLptBuckets + 1;
+// How a kernel shares n items out among its waves: runs of consecutive items
+// (at most `longest`), dealt out in turns.  A wave's whole share is at least
+// 32 runs where there are that many items, so that shares differ by little.
+constexpr int64_t share_run(int64_t n, int64_t waves, int64_t longest) {
+  const int64_t r = n / (waves * 32);
+  return r < 1 ? 1 : (r < longest ? r : longest);
+}
+// the largest share
+constexpr int64_t most_share(int64_t n, int64_t waves, int64_t longest) {
+  const int64_t run = share_run(n, waves, longest), full = n / (waves * run), rest = n - full * waves * run;
+  return full * run + (rest < run ? rest : run);
+}
+
+// The most pairs that the workgroups of one stream of the union sweep take
+// (`grid` workgroups of `per_wg` waves, shares of at most `most` pairs), and
+// room for it whatever the grid: shares differ by at most a 32nd and one pair.
+constexpr int64_t stream_cap_of(int64_t grid, int64_t per_wg, int64_t most) {
+  return (grid + kStreams - 1) / kStreams * per_wg * most;
+}
+constexpr int64_t stream_cap_room(int64_t n_pairs) { return (n_pairs + n_pairs / 16) / kStreams + 8192; }
+// 4-byte list entries for n pairs: the sweep's lists (long buckets, medium),
+// the persistent kernel's buckets
+constexpr int64_t pair_list_room(int64_t n) {
+  return (kLptBuckets + 1) * kStreams * stream_cap_room(n) + kLptBuckets * n;
+}
 
 struct BatchState {
   Counter l_count[kLptBuckets];            // pairs listed for the persistent kernel per bucket
   Counter l_next[kLptBuckets][kStreams];   // per-stream claim counters over each bucket
-  Counter s_next[kStreams];   // per-stream claim counters over pair chunks (the sweep)
-  Counter m_count;            // medium pairs listed (by the setup pass and the sweep)
-  Counter p_count[kLptBuckets];  // long pairs listed by the setup pass per bucket
+  Counter m_count[kStreams];  // medium pairs listed by the sweep per stream
+  Counter p_count[kLptBuckets][kStreams];  // long pairs listed by the sweep per bucket and stream
   Counter p_next[kStreams];      // per-stream claim counters over the long pairs
   Counter q_head[kMaxGrid];   // per-queue ticket counters
   Counter q_tail[kMaxGrid];   // per-queue reservation counters
   unsigned long long stats[kNumStats];
-};
-
-// Per-pair record written by the batched setup pass: ring offsets and
-// vertex counts of both polygons and the pair's class, so that the sweep
-// reads one 32-byte record per pair (through the scalar cache).
-struct PairRec {
-  int64_t op, oq;
-  int32_t np, nq;
-  int32_t cls, pad;
 };
 
 struct BatchArgs {
@@ -123,11 +130,13 @@ struct BatchArgs {
   int64_t* inter;
   int64_t* uni;
   uint32_t* err;
-  uint8_t* cls;                  // [n_pairs]
-  PairRec* rec;                  // [n_pairs]
-  int32_t* l_list;               // [kLptBuckets][n_pairs] long pairs, bucket b from b * n_pairs
+  uint8_t* cls;                  // [n_pairs] class of a pair listed for the persistent kernel
+  // The sweep's lists: every stream has a part of its own, stream_cap entries
+  // long, which the workgroups blockIdx % kStreams append to
+  int32_t* l_list;               // [kLptBuckets][kStreams][stream_cap] long pairs
+  int32_t* m_list;               // [kStreams][stream_cap] medium pairs
+  int64_t stream_cap;            // see sweep_stream_cap
   int32_t* run_list;             // [kLptBuckets][n_pairs] pairs listed for the persistent kernel
-  int32_t* m_list;               // [n_pairs] medium pairs, in the order they were listed
   Meta* hbox;                    // [n_pairs] pair box of a listed pair (by pair index)
   BatchState* st;
   unsigned long long* queue;     // [n_queues * queue_cap] task words, 0 = empty
@@ -147,11 +156,8 @@ struct BatchArgs {
 };
 // kernels whose waves are stamped (see BatchArgs::wave_t)
 constexpr int kStampedKernels = 3;
-hipError_t launch_batch_reset(const BatchArgs& a, hipStream_t s);
-hipError_t launch_batch_setup(const BatchArgs& a, hipStream_t s);
-// The union sweep (sweep_grid workgroups) then the medium sweep with the
-// prepass of the pairs the setup pass listed (medium_grid);
-// pair_box: the union sweep also counts the pairs whose pair box fits a leaf
+// The union sweep (sweep_grid workgroups) then the medium sweep with the long
+// pairs (medium_grid); pair_box: the union sweep also counts the pairs whose pair box fits a leaf
 // tile (else the medium sweep does).
 hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_grid, bool pair_box, hipStream_t s);
 // The persistent kernel (grid workgroups).

@@ -80,3 +80,34 @@ def test_a_ring_wider_than_an_area_of_32_bits_holds():
         finally:
             c.close()
         assert_exact(I, U, np.array([i, i]), np.array([u, u]), f"wide ring of {pad} vertices")
+
+
+@pytest.mark.parametrize("params", [{}, {"sweep_pair_box": 2}, {"sweep_pair_box": 2, "flags": sccg.SCCG_F_NO_UNION_TILE},
+                                    {"queue_chunk": 1}, {"queue_chunk": 64}])
+def test_rings_and_boxes_of_the_union_sweep(params):
+    """Rings around each 64-vertex chunk of the union sweep against each other,
+    on union boxes (and, with the rings shifted apart, pair boxes) around 32
+    and 64 columns and rows."""
+    ra, rb, expect = [], [], []
+    sizes = (8, 63, 64, 65, 127, 128, 129, 191, 192, 193)
+    dims = (5, 31, 32, 33, 62, 63, 64, 65)
+    for n, (np_, nq) in enumerate((p, q) for p in sizes for q in sizes):
+        for m in range(4):
+            w, h = dims[(n + m) % len(dims)], dims[(n // 3 + 3 * m) % len(dims)]
+            far = 0 if m < 2 else 40  # p reaches out of the box on its left and bottom, q on its right and top
+            pa = _band_polygon(w + far, h + far, np_, 1, 100 * n - far, -50 * m - far)
+            pb = _band_polygon(w + far, h + far, nq, -1, 100 * n, -50 * m)
+            ra.append(_padded(band_ring(*pa), np_))
+            rb.append(_padded(band_ring(*pb), nq))
+            qa, qb = band_rects(*pa), band_rects(*pb)
+            i = rects_inter(qa, qb)
+            expect.append((i, rects_area(qa) + rects_area(qb) - i))
+    A, B = concat(ra), concat(rb)
+    assert set(np.diff(A.off).tolist()) == set(sizes)
+    idx = np.arange(len(ra), dtype=np.int32)
+    c = sccg.Context(0, **params)
+    try:
+        I, U = run(c, device_workload(A, B, idx, idx), sccg.SCCG_BATCHED)
+    finally:
+        c.close()
+    assert_exact(I, U, np.array([e[0] for e in expect]), np.array([e[1] for e in expect]), f"sweep {params}")
