@@ -230,6 +230,7 @@ class Context:
         if stream is None:
             stream = torch.cuda.current_stream(device)
         self.stream = stream
+        self._raw_stream = stream.cuda_stream
         p = sccg_params(**params) if params else None
         h = ctypes.c_void_p()
         rc = self.lib.sccg_create(ctypes.byref(h), device, ctypes.c_void_p(stream.cuda_stream),
@@ -312,6 +313,17 @@ class Context:
         self._rc(self.lib.sccg_get_timing(self.h, ctypes.byref(ms), ctypes.byref(n)))
         return float(ms.value), int(n.value)
 
+    def _empty(self, sizes, dtypes, device):
+        """Output tensors in the memory of the context's stream: a block that
+        the allocator holds for another stream may be handed out again while
+        this one still writes to it."""
+        import torch
+        if (self._raw_stream == torch._C._cuda_getCurrentRawStream(self.device)
+                or not isinstance(self.stream, torch.cuda.Stream)):
+            return [torch.empty(n, dtype=t, device=device) for n, t in zip(sizes, dtypes)]
+        with torch.cuda.stream(self.stream):
+            return [torch.empty(n, dtype=t, device=device) for n, t in zip(sizes, dtypes)]
+
     # ---------------------------------------------------------- compute
     def area_pairs(self, A: DevicePolys, B: DevicePolys, pair_a, pair_b, out_inter=None, out_union=None,
                    mode: int = SCCG_BATCHED):
@@ -322,10 +334,10 @@ class Context:
         n = int(pair_a.shape[0])
         if int(pair_b.shape[0]) != n:
             raise ValueError("pair_a and pair_b differ in length")
-        if out_inter is None:
-            out_inter = torch.empty(n, dtype=torch.int64, device=pair_a.device)
-        if out_union is None:
-            out_union = torch.empty(n, dtype=torch.int64, device=pair_a.device)
+        if out_inter is None or out_union is None:
+            new = self._empty((n, n), (torch.int64, torch.int64), pair_a.device)
+            out_inter = new[0] if out_inter is None else out_inter
+            out_union = new[1] if out_union is None else out_union
         _check_dev(out_inter, torch.int64, "out_inter")
         _check_dev(out_union, torch.int64, "out_union")
         ca, cb = A.c(), B.c()
@@ -357,11 +369,9 @@ class Context:
         _check_dev(uni, torch.int64, "uni")
         ns = int(set_pair_off.shape[0]) - 1
         dev = inter.device
-        si = torch.empty(ns, dtype=torch.int64, device=dev)
-        su = torch.empty(ns, dtype=torch.int64, device=dev)
-        nn = torch.empty(ns, dtype=torch.int64, device=dev)
-        j = torch.empty(ns, dtype=torch.float64, device=dev)
-        jp = torch.empty(ns, dtype=torch.float64, device=dev) if jprime else None
+        i64, f64 = torch.int64, torch.float64
+        si, su, nn, j, *rest = self._empty((ns,) * (5 if jprime else 4), (i64, i64, i64, f64, f64), dev)
+        jp = rest[0] if jprime else None
         self._rc(self.lib.sccg_jaccard_sets(self.h, ns, _ptr(set_pair_off), _ptr(inter), _ptr(uni), flags, _ptr(si),
                                             _ptr(su), _ptr(nn), _ptr(j), _ptr(jp)))
         return si, su, nn, j, jp
@@ -378,11 +388,10 @@ class Context:
             raise ValueError("a_set_off and b_set_off differ in length")
         dev = a_set_off.device
         cap = 4 * max(B.n, 1) if cap is None else cap
-        so = torch.empty(ns + 1, dtype=torch.int64, device=dev)
+        so, = self._empty((ns + 1,), (torch.int64,), dev)
         cA, cB = A.c(), B.c()
         for _ in range(2):
-            pa = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
-            pb = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
+            pa, pb = self._empty((max(cap, 1),) * 2, (torch.int32,) * 2, dev)
             total = ctypes.c_int64(0)
             self._rc(self.lib.sccg_join_sets(self.h, ctypes.byref(cA), ctypes.byref(cB), ns, _ptr(a_set_off),
                                              _ptr(b_set_off), cell, cap, _ptr(pa), _ptr(pb), _ptr(so),
@@ -400,7 +409,7 @@ class Context:
         _check_dev(pair_b, torch.int32, "pair_b")
         _check_dev(inter, torch.int64, "inter")
         n = int(pair_a.shape[0])
-        out = torch.empty(n, dtype=torch.int32, device=pair_a.device)
+        out, = self._empty((n,), (torch.int32,), pair_a.device)
         cA, cB = A.c(), B.c()
         self._rc(self.lib.sccg_relate_pairs(self.h, ctypes.byref(cA), ctypes.byref(cB), n, _ptr(pair_a), _ptr(pair_b),
                                             _ptr(inter), _ptr(out)))
@@ -408,7 +417,7 @@ class Context:
 
     def validate_polys(self, P: DevicePolys):
         import torch
-        out = torch.empty(1, dtype=torch.int64, device="cuda")
+        out, = self._empty((1,), (torch.int64,), "cuda")
         cp = P.c()
         self._rc(self.lib.sccg_validate_polys(self.h, ctypes.byref(cp), _ptr(out)))
         return out
