@@ -6,55 +6,60 @@
 
 namespace sccg {
 
-// One polygon's extent and doubled signed area, accumulated over one lane's
-// share of a ring.  The shoelace sum (Section 3.2) is taken
-// in wrapping 64-bit arithmetic: partial sums may overflow, the final value
-// (twice the area, at most 2^63 in size) is exact modulo 2^64.
-struct MetaAcc {
-  int32_t x0 = INT_MAX, y0 = INT_MAX, x1 = INT_MIN, y1 = INT_MIN;
-  uint64_t twice = 0;
-  __device__ void add(int2 v, int2 w) {
-    x0 = min(x0, v.x);
-    y0 = min(y0, v.y);
-    x1 = max(x1, v.x);
-    y1 = max(y1, v.y);
-    twice += (uint64_t)((int64_t)v.x * w.y) - (uint64_t)((int64_t)w.x * v.y);
-  }
+// A row of 16 lanes per ring, four rings per wave: lane j of the row takes
+// vertices j, 16 + j, 32 + j and 48 + j of each 64, four loads in flight of
+// 128 neighbouring bytes each; past the ring's end it takes the first vertex
+// again, which leaves extents alone and is the last vertex's successor.  A
+// vertex's successor comes from the next lane, lane 15's from lane 0 of the
+// next 16.  Bound by the rings' bytes (one lane per ring read 8 bytes of 64
+// lines at a time: 600,000 rings of 90 vertices validated in 850 us; eight
+// lanes with the successors loaded again 147 us for extents and areas).
+constexpr int kRow = 16;        // lanes per ring (a DPP row)
+constexpr int kRowChunks = 4;   // loads of a lane in flight
+constexpr int kRowStep = kRow * kRowChunks;
+
+struct RowChunk {
+  int2 v[kRowChunks], s[kRowChunks];  // vertices and, where asked for, their successors
 };
-
-__device__ void write_meta(const MetaAcc& a, int64_t nv, int64_t k, Meta* meta, int64_t* area, uint32_t* err) {
-  bool empty = nv <= 0;
-  bool bad = !empty && (a.x0 < -kMaxCoord || a.y0 < -kMaxCoord || a.x1 > kMaxCoord || a.y1 > kMaxCoord);
-  if (bad) latch_error(err, kErrCoord);
-  if (empty || bad) {
-    *reinterpret_cast<int4*>(meta + k) = make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN);
-    area[k] = 0;
-    return;
+template <bool kSucc>
+__device__ __forceinline__ RowChunk row_load(const int2* R, int64_t nv, int64_t base, int j) {
+  RowChunk r;
+#pragma unroll
+  for (int c = 0; c < kRowChunks; ++c) {
+    const int64_t k = base + c * kRow + j;
+    r.v[c] = R[k < nv ? k : 0];
   }
-  *reinterpret_cast<int4*>(meta + k) = make_int4(a.x0, a.y0, a.x1, a.y1);
-  // twice the area is at most 2^63 in size: its magnitude is exact unsigned
-  const uint64_t t = (uint64_t)a.twice;
-  area[k] = (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
+  if (kSucc) {
+    const int2 nxt = R[base + kRowStep < nv ? base + kRowStep : 0];
+#pragma unroll
+    for (int c = 0; c < kRowChunks; ++c) {
+      int2 t = nxt;  // lane 15's successor
+      if (c + 1 < kRowChunks) {
+        t.x = __builtin_amdgcn_update_dpp(0, r.v[c + 1 < kRowChunks ? c + 1 : c].x, 0x12f, 0xf, 0xf, false);  // row_ror:15
+        t.y = __builtin_amdgcn_update_dpp(0, r.v[c + 1 < kRowChunks ? c + 1 : c].y, 0x12f, 0xf, 0xf, false);
+      }
+      r.s[c].x = __builtin_amdgcn_update_dpp(t.x, r.v[c].x, 0x101, 0xf, 0xf, false);  // row_shl:1
+      r.s[c].y = __builtin_amdgcn_update_dpp(t.y, r.v[c].y, 0x101, 0xf, 0xf, false);
+    }
+  }
+  return r;
 }
 
-
-// Eight lanes per polygon: lane j of a group walks vertices j, j + 8, ...
-// (eight consecutive vertices, 64 bytes, per step of the group), then the
-// group combines its partial extents and shoelace sums in three exchanges.
-constexpr int kGroup = 8;
-
-__device__ __forceinline__ int32_t group_min(int32_t v) {
-  v = min(v, __shfl_xor(v, 1, kWave));
-  v = min(v, __shfl_xor(v, 2, kWave));
-  return min(v, __shfl_xor(v, 4, kWave));
+__device__ __forceinline__ int32_t row_min(int32_t x) {
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0xb1, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x4e, 0xf, 0xf, false));
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0x141, 0xf, 0xf, false));
+  return min(x, __builtin_amdgcn_update_dpp(x, x, 0x140, 0xf, 0xf, false));
 }
-__device__ __forceinline__ int32_t group_max(int32_t v) {
-  v = max(v, __shfl_xor(v, 1, kWave));
-  v = max(v, __shfl_xor(v, 2, kWave));
-  return max(v, __shfl_xor(v, 4, kWave));
+__device__ __forceinline__ uint32_t row_sum(uint32_t u) {
+  int x = (int)u;
+  x += __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
+  return (uint32_t)(x + __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false));
 }
-__device__ __forceinline__ uint64_t group_sum64(uint64_t v) {
-  for (int d = 1; d < kGroup; d <<= 1) {
+__device__ __forceinline__ uint64_t row_sum64(uint64_t v) {
+  for (int d = 1; d < kRow; d <<= 1) {
     const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, d, kWave);
     const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), d, kWave);
     v += ((uint64_t)hi << 32) | lo;
@@ -62,67 +67,107 @@ __device__ __forceinline__ uint64_t group_sum64(uint64_t v) {
   return v;
 }
 
-__global__ void __launch_bounds__(256) k_meta_group(Polys P, Meta* meta, int64_t* area, uint32_t* err) {
-  const int64_t gid = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kGroup;
-  const int j = (int)(threadIdx.x % kGroup);
-  const bool live = gid < P.n;
-  int64_t o0 = 0, nv = 0;
-  if (live) {
-    o0 = P.off[gid];
-    nv = P.off[gid + 1] - o0;
+// Extents, and kArea |shoelace|/2 (Section 3.2's area formula), of the rings
+// of one or two sets.  Twice the signed area is summed as (x + x') (y' - y)
+// over the edges, x relative to the first vertex, modulo 2^32: exact for a
+// ring at most kMaxSide wide and tall; a larger one has it summed again
+// modulo 2^64, in which twice the area (at most 2^63 in size) is exact.
+template <bool kArea>
+__global__ void __launch_bounds__(256) k_meta_rows(Polys A, Meta* metaA, int64_t* areaA, Polys B, Meta* metaB,
+                                                   int64_t* areaB, uint32_t* err) {
+  int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRow;
+  const int j = (int)(threadIdx.x % kRow);
+  const bool second = k >= A.n;
+  if (second) k -= A.n;
+  if (second && k >= B.n) return;
+  const int64_t* off = second ? B.off : A.off;
+  const int64_t o = off[k], nv = off[k + 1] - o;
+  const int2* R = (second ? B.xy : A.xy) + o;
+  int32_t x0 = INT_MAX, y0 = INT_MAX, nx1 = INT_MAX, ny1 = INT_MAX;
+  uint32_t tn = 0;
+  int2 f = make_int2(0, 0);
+  if (kArea && nv > 0) f = R[0];
+  for (int64_t base = 0; base < nv; base += kRowStep) {
+    const RowChunk r = row_load<kArea>(R, nv, base, j);
+#pragma unroll
+    for (int c = 0; c < kRowChunks; ++c) {
+      x0 = min(x0, r.v[c].x);
+      y0 = min(y0, r.v[c].y);
+      nx1 = min(nx1, ~r.v[c].x);
+      ny1 = min(ny1, ~r.v[c].y);
+      if (kArea)
+        tn += (uint32_t)__mul24((int)((uint32_t)r.v[c].x + (uint32_t)r.s[c].x - 2u * (uint32_t)f.x),
+                                (int)((uint32_t)r.s[c].y - (uint32_t)r.v[c].y));
+    }
   }
-  MetaAcc a;
-  for (int64_t i = j; i < nv; i += kGroup) {
-    const int2 v = P.xy[o0 + i];
-    const int2 w = P.xy[o0 + (i + 1 == nv ? 0 : i + 1)];
-    a.add(v, w);
+  const Meta m{row_min(x0), row_min(y0), ~row_min(nx1), ~row_min(ny1)};
+  const bool empty = nv <= 0;
+  const bool bad = !empty && (m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord);
+  int64_t area = 0;
+  if (kArea && !empty && !bad) {
+    if (side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide) {
+      const int32_t t = (int32_t)row_sum(tn);
+      area = (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
+    } else {
+      uint64_t tw = 0;
+      for (int64_t base = 0; base < nv; base += kRowStep) {
+        const RowChunk r = row_load<true>(R, nv, base, j);
+        for (int c = 0; c < kRowChunks; ++c)
+          tw += (uint64_t)((int64_t)r.v[c].x * r.s[c].y) - (uint64_t)((int64_t)r.s[c].x * r.v[c].y);
+      }
+      const uint64_t t = row_sum64(tw);
+      area = (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
+    }
   }
-  MetaAcc r;
-  r.x0 = group_min(a.x0);
-  r.y0 = group_min(a.y0);
-  r.x1 = group_max(a.x1);
-  r.y1 = group_max(a.y1);
-  r.twice = group_sum64(a.twice);
-  if (live && j == 0) write_meta(r, nv, gid, meta, area, err);
+  if (j != 0) return;
+  if (bad) latch_error(err, kErrCoord);
+  const bool none = empty || bad;
+  *reinterpret_cast<int4*>((second ? metaB : metaA) + k) =
+      none ? make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN) : make_int4(m.x0, m.y0, m.x1, m.y1);
+  if (kArea) (second ? areaB : areaA)[k] = area;
 }
 
-hipError_t launch_poly_meta(const Polys& P, Meta* meta, int64_t* area, int32_t* big_list, int32_t* big_count,
+hipError_t launch_poly_meta(const Polys& A, Meta* metaA, int64_t* areaA, const Polys& B, Meta* metaB, int64_t* areaB,
                             uint32_t* err, hipStream_t s) {
-  (void)big_list;
-  (void)big_count;
-  if (P.n <= 0) return hipSuccess;
-  const int64_t blocks = (P.n * kGroup + 255) / 256;
-  hipLaunchKernelGGL(k_meta_group, dim3((unsigned)blocks), dim3(256), 0, s, P, meta, area, err);
+  if (A.n + B.n <= 0) return hipSuccess;
+  const unsigned blocks = (unsigned)(((A.n + B.n) * kRow + 255) / 256);
+  if (areaA)
+    hipLaunchKernelGGL(k_meta_rows<true>, dim3(blocks), dim3(256), 0, s, A, metaA, areaA, B, metaB, areaB, err);
+  else
+    hipLaunchKernelGGL(k_meta_rows<false>, dim3(blocks), dim3(256), 0, s, A, metaA, areaA, B, metaB, areaB, err);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- validation
+// -1 as the largest unsigned value: what the smallest bad index is taken from,
+// and what is left when there is none
 __global__ void k_validate_init(unsigned long long* first_bad) { *first_bad = ~0ull; }
 
 __global__ void __launch_bounds__(256) k_validate(Polys P, unsigned long long* first_bad) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= P.n) return;
-  const int64_t o0 = P.off[k];
-  const int64_t nv = P.off[k + 1] - o0;
-  bool bad = nv < 4;
-  for (int64_t i = 0; i < nv && !bad; ++i) {
-    const int2 v = P.xy[o0 + i];
-    const int2 w = P.xy[o0 + (i + 1 == nv ? 0 : i + 1)];
-    if (v.x != w.x && v.y != w.y) bad = true;
+  const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRow;
+  const int j = (int)(threadIdx.x % kRow);
+  bool bad = false;
+  if (k < P.n) {
+    const int64_t o = P.off[k], nv = P.off[k + 1] - o;
+    bad = nv < 4;
+    for (int64_t base = 0; base < nv; base += kRowStep) {
+      const RowChunk r = row_load<true>(P.xy + o, nv, base, j);
+#pragma unroll
+      for (int c = 0; c < kRowChunks; ++c) bad |= (r.v[c].x != r.s[c].x) & (r.v[c].y != r.s[c].y);
+    }
   }
-  if (bad) atomicMin(first_bad, (unsigned long long)k);
-}
-
-__global__ void k_validate_fin(unsigned long long* first_bad) {
-  if (*first_bad == ~0ull) *reinterpret_cast<int64_t*>(first_bad) = -1;
+  // the wave's rings stand in order: its first bad lane has its smallest index
+  const uint64_t m = ballot(bad);
+  if (m && lane_id() == __ffsll((long long)m) - 1 &&
+      (unsigned long long)k < __hip_atomic_load(first_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMin(first_bad, (unsigned long long)k);
 }
 
 hipError_t launch_validate(const Polys& P, int64_t* first_bad, hipStream_t s) {
   auto* fb = reinterpret_cast<unsigned long long*>(first_bad);
   hipLaunchKernelGGL(k_validate_init, dim3(1), dim3(1), 0, s, fb);
   if (P.n > 0)
-    hipLaunchKernelGGL(k_validate, dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, s, P, fb);
-  hipLaunchKernelGGL(k_validate_fin, dim3(1), dim3(1), 0, s, fb);
+    hipLaunchKernelGGL(k_validate, dim3((unsigned)((P.n * kRow + 255) / 256)), dim3(256), 0, s, P, fb);
   return hipGetLastError();
 }
 

@@ -28,13 +28,10 @@ struct sccg_ctx {
   // per-polygon scratch
   Meta* metaA = nullptr;
   int64_t* areaA = nullptr;
-  int32_t* bigA = nullptr;
   int64_t capA = 0;
   Meta* metaB = nullptr;
   int64_t* areaB = nullptr;
-  int32_t* bigB = nullptr;
   int64_t capB = 0;
-  int32_t* big_count = nullptr;  // [2]
   uint32_t* err = nullptr;
   // per-pair scratch
   uint8_t* cls = nullptr;
@@ -175,9 +172,8 @@ int ensure_polys(sccg_ctx* c, int which, int64_t n) {
   int64_t want = n + n / 4 + 1024;
   Meta** m = which ? &c->metaB : &c->metaA;
   int64_t** ar = which ? &c->areaB : &c->areaA;
-  int32_t** bg = which ? &c->bigB : &c->bigA;
   int r;
-  if ((r = grow(c, m, want, "metadata")) || (r = grow(c, ar, want, "areas")) || (r = grow(c, bg, want, "big list"))) {
+  if ((r = grow(c, m, want, "metadata")) || (r = grow(c, ar, want, "areas"))) {
     cap = 0;
     return r;
   }
@@ -383,7 +379,6 @@ int sccg_create(sccg_ctx** out, int hip_device, void* hip_stream, const sccg_par
   (void)hipDeviceGetAttribute(&c->cu_count, hipDeviceAttributeMultiprocessorCount, hip_device);
   if (c->cu_count < 1) c->cu_count = 1;
   if (hipMalloc((void**)&c->err, sizeof(uint32_t)) != hipSuccess ||
-      hipMalloc((void**)&c->big_count, 2 * sizeof(int32_t)) != hipSuccess ||
       hipMalloc((void**)&c->st, sizeof(BatchState)) != hipSuccess ||
       hipMalloc((void**)&c->plain_stats, kNumStats * sizeof(unsigned long long)) != hipSuccess) {
     sccg_destroy(c);
@@ -408,7 +403,7 @@ int sccg_destroy(sccg_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   drop_graph(c);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
-  void* ptrs[] = {c->metaA,  c->areaA,  c->bigA,        c->metaB,  c->areaB,   c->bigB,    c->big_count,
+  void* ptrs[] = {c->metaA,  c->areaA,  c->metaB,  c->areaB,
                   c->err,    c->cls,    c->l_list, c->hbox,    c->st,      c->queue,
                   c->plain_stats, c->wave_t,
                   c->j_bbox, c->j_grid, c->j_cells,     c->j_cell_base, c->j_sums, c->j_count, c->j_start,
@@ -549,12 +544,9 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   if (mode == SCCG_PLAIN) {
     if ((r = ensure_polys(c, 0, A->n_polys)) || (r = ensure_polys(c, 1, B->n_polys))) return r;
     hipError_t e;
-    if ((e = launch_poly_meta(to_polys(A), c->metaA, c->areaA, c->bigA, c->big_count, c->err, c->stream)) !=
+    if ((e = launch_poly_meta(to_polys(A), c->metaA, c->areaA, to_polys(B), c->metaB, c->areaB, c->err, c->stream)) !=
         hipSuccess)
-      return hip_fail(c, e, "poly meta A");
-    if ((e = launch_poly_meta(to_polys(B), c->metaB, c->areaB, c->bigB, c->big_count + 1, c->err, c->stream)) !=
-        hipSuccess)
-      return hip_fail(c, e, "poly meta B");
+      return hip_fail(c, e, "poly meta");
     PlainArgs a{};
     a.A = to_polys(A);
     a.B = to_polys(B);
@@ -779,10 +771,9 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
   hipError_t e;
   const Polys pA = to_polys(A), pB = to_polys(B);
   if ((r = ensure_polys(c, 0, A->n_polys)) || (r = ensure_polys(c, 1, B->n_polys))) return r;
-  if ((e = launch_poly_meta(pA, c->metaA, c->areaA, c->bigA, c->big_count, c->err, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "poly meta A");
-  if ((e = launch_poly_meta(pB, c->metaB, c->areaB, c->bigB, c->big_count + 1, c->err, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "poly meta B");
+  // extents only
+  if ((e = launch_poly_meta(pA, c->metaA, nullptr, pB, c->metaB, nullptr, c->err, c->stream)) != hipSuccess)
+    return hip_fail(c, e, "poly meta");
   // grids: per-set extents of A, cells per set, their offsets
   if ((r = need(c, &c->j_bbox, c->j_cap[0], n_sets, "join boxes")) ||
       (r = need(c, &c->j_grid, c->j_cap[1], n_sets, "join grids")) ||
@@ -849,8 +840,7 @@ int sccg_relate_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int
   if ((r = ensure_polys(c, 0, A->n_polys)) || (r = ensure_polys(c, 1, B->n_polys))) return r;
   hipError_t e;
   const Polys pA = to_polys(A), pB = to_polys(B);
-  if ((e = launch_poly_meta(pA, c->metaA, c->areaA, c->bigA, c->big_count, c->err, c->stream)) != hipSuccess ||
-      (e = launch_poly_meta(pB, c->metaB, c->areaB, c->bigB, c->big_count + 1, c->err, c->stream)) != hipSuccess)
+  if ((e = launch_poly_meta(pA, c->metaA, c->areaA, pB, c->metaB, c->areaB, c->err, c->stream)) != hipSuccess)
     return hip_fail(c, e, "poly meta");
   if ((e = launch_relate(pA, pB, c->metaA, c->metaB, c->areaA, c->areaB, n_pairs, pair_a, pair_b, inter, out_rel,
                          c->err, c->stream)) != hipSuccess)

@@ -43,8 +43,9 @@ constexpr int kNumStats = 16;
 // ------------------------------------------------------------------ launches
 // Each returns a hipError_t from the launch.
 
-// Per polygon: vertex extent, |shoelace|/2, coordinate range check.
-hipError_t launch_poly_meta(const Polys& P, Meta* meta, int64_t* area, int32_t* big_list, int32_t* big_count,
+// Per polygon of A and B: vertex extent, coordinate range check, and, unless
+// the area arrays are NULL, |shoelace|/2.
+hipError_t launch_poly_meta(const Polys& A, Meta* metaA, int64_t* areaA, const Polys& B, Meta* metaB, int64_t* areaB,
                             uint32_t* err, hipStream_t s);
 
 struct PlainArgs {
