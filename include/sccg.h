@@ -198,8 +198,8 @@ int sccg_jaccard_sets(sccg_ctx* ctx, int64_t n_sets, const int64_t* set_pair_off
  *     (always written, counting every pair).
  *   *out_total (host): the number of pairs; if it exceeds cap, no pair is
  *     written: call again with cap >= *out_total.
- * The call waits for the context's stream three times (to size its scratch
- * and to read the total), so it cannot be captured in a HIP graph. */
+ * The call waits for the context's stream (to read the total, and again when
+ * its scratch had to grow), so it cannot be captured in a HIP graph. */
 int sccg_join_sets(sccg_ctx* ctx, const sccg_polys* A, const sccg_polys* B, int64_t n_sets,
                    const int64_t* a_set_off, const int64_t* b_set_off, int32_t cell, int64_t cap,
                    int32_t* out_pa, int32_t* out_pb, int64_t* out_set_off, int64_t* out_total);

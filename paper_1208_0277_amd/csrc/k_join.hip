@@ -5,9 +5,15 @@
 // and keeps the A polygons whose MBR shares a pixel with its own, reporting
 // a pair only from the cell that holds the lower-left pixel of the two MBRs'
 // intersection, so that every pair is found once.  Each B polygon's pairs are
-// written to a segment of their own (offsets from a scan of the counts) and
-// sorted there by A index: the output is ordered by set, then B, then A.
+// written to a segment of their own (offsets from a scan of the counts) in
+// the order of A: the output is ordered by set, then B, then A.
+//
+// All of it is queued without a look at the sizes it finds on the way (cells,
+// entries, pairs): the kernels take them from device memory and stop where
+// one exceeds the room for it, and the host reads them once, at the end.
 #include <limits.h>
+
+#include <algorithm>
 
 #include "sccg_device.h"
 
@@ -30,11 +36,30 @@ __device__ __forceinline__ int64_t set_of(const int64_t* off, int64_t n, int64_t
   return lo;
 }
 
+// The same for every lane's k, ascending over the wave (a lane without one
+// passes -1): the set of the first is searched by the wave, 64 offsets per
+// step, the others walk on from it.  Every lane takes part.
+__device__ __forceinline__ int64_t set_of_lane(const int64_t* off, int64_t n, int64_t k) {
+  const int lane = lane_id();
+  const uint64_t some = ballot(n > 0 && k >= off[0] && k < off[n]);
+  if (!some) return -1;
+  const int64_t k0 = uniform64(__shfl((long long)k, __ffsll((long long)some) - 1, kWave));
+  int64_t lo = 0, hi = n;  // off[lo] <= k0 < off[hi]
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave;
+    const uint64_t m = ballot(lo + lane * step < hi && off[min(lo + lane * step, hi - 1)] <= k0);
+    lo = uniform64(lo + (__popcll(m) - 1) * step);
+    hi = uniform64(min(hi, lo + step));
+  }
+  if (!((some >> lane) & 1ull)) return -1;
+  while (k >= off[lo + 1]) ++lo;
+  return lo;
+}
+
 __device__ __forceinline__ bool meta_empty(const Meta& m) { return m.x0 >= m.x1 || m.y0 >= m.y1; }
 
 // cell index of pixel coordinate v in a grid starting at o (floor division,
-// v >= o)
-// cell index of v >= o; v - o can reach 2^31 with coordinates up to 2^30 in size
+// v >= o); v - o can reach 2^31 with coordinates up to 2^30 in size
 __device__ __forceinline__ int cell_of(int v, int o, int cell) {
   return (int)(((uint32_t)v - (uint32_t)o) / (uint32_t)cell);
 }
@@ -46,59 +71,166 @@ __global__ void k_join_init_sets(int64_t n_sets, int4* bbox) {
   if (s < n_sets) bbox[s] = make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN);
 }
 
-// Extent of each set's A polygons.  Sets are contiguous ranges, so the
-// lanes of a wave usually share one set: then the wave reduces first and one
-// lane updates the set (a set holds many thousand polygons; per-polygon
-// atomics on its four words would serialize).
-__global__ void k_join_bbox(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets, int4* bbox) {
-  const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t s = -1;
-  Meta m{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
-  if (a < A.n) {
-    s = set_of(a_off, n_sets, a);
-    const Meta t = load_meta(metaA, a);
-    if (s >= 0 && !meta_empty(t)) m = t;
-  }
-  const int64_t s0 = uniform64(s);
-  if (ballot(s != s0) == 0ull) {
-    if (s0 < 0) return;
-    const int x0 = wave_min_i32(m.x0), y0 = wave_min_i32(m.y0);
-    const int x1 = wave_max_i32(m.x1), y1 = wave_max_i32(m.y1);
-    if (lane_id() == 0 && x0 < x1 && y0 < y1) {
-      atomicMin(&bbox[s0].x, x0);
-      atomicMin(&bbox[s0].y, y0);
-      atomicMax(&bbox[s0].z, x1);
-      atomicMax(&bbox[s0].w, y1);
+// Extent of each set's A polygons.  Sets are contiguous ranges: a workgroup
+// takes kBoxRun consecutive polygons and updates a set once per run of them
+// (the atomics on one set's extent take turns: 600,000 polygons of 16 sets took
+// 250 us with four for every 64 polygons, 55 for every 256, 23 for every 1024).
+constexpr int kBoxRun = 4096;
+__global__ void __launch_bounds__(256) k_join_bbox(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
+                                                   int4* bbox) {
+  __shared__ int4 sh[4];
+  const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
+  const int64_t a0 = (int64_t)blockIdx.x * kBoxRun, a1 = min(a0 + kBoxRun, A.n);
+  int64_t a = a0;
+  while (a < a1) {
+    // the polygons of one set from a on (all threads at the same a)
+    const int64_t s = uniform64(set_of(a_off, n_sets, a));
+    if (s < 0) {
+      // outside every set: skip to the first set, or to the end
+      const int64_t first = uniform64(n_sets > 0 ? a_off[0] : A.n);
+      if (a >= first) break;
+      a = min(first, a1);
+      continue;
     }
-    return;
+    const int64_t end = min(uniform64(a_off[s + 1]), a1);
+    int x0 = INT_MAX, y0 = INT_MAX, x1 = INT_MIN, y1 = INT_MIN;
+#pragma unroll 4
+    for (int64_t k = a + threadIdx.x; k < end; k += 256) {
+      const Meta t = load_meta(metaA, k);
+      const bool some = !meta_empty(t);
+      x0 = min(x0, some ? t.x0 : x0);
+      y0 = min(y0, some ? t.y0 : y0);
+      x1 = max(x1, some ? t.x1 : x1);
+      y1 = max(y1, some ? t.y1 : y1);
+    }
+    const int4 mine = make_int4(wave_min_i32(x0), wave_min_i32(y0), wave_max_i32(x1), wave_max_i32(y1));
+    if (lane == 0) sh[w] = mine;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int4 m = sh[0];
+      for (int k = 1; k < 4; ++k)
+        m = make_int4(min(m.x, sh[k].x), min(m.y, sh[k].y), max(m.z, sh[k].z), max(m.w, sh[k].w));
+      if (m.x < m.z) {
+        atomicMin(&bbox[s].x, m.x);
+        atomicMin(&bbox[s].y, m.y);
+        atomicMax(&bbox[s].z, m.z);
+        atomicMax(&bbox[s].w, m.w);
+      }
+    }
+    __syncthreads();
+    a = end;
   }
-  if (s < 0 || meta_empty(m)) return;
-  atomicMin(&bbox[s].x, m.x0);
-  atomicMin(&bbox[s].y, m.y0);
-  atomicMax(&bbox[s].z, m.x1);
-  atomicMax(&bbox[s].w, m.y1);
 }
 
-// Grid of each set: origin, columns, rows; cells[s] = columns x rows.
-__global__ void k_join_grid(int64_t n_sets, const int4* bbox, int cell, int4* grid, int64_t* cells,
-                            uint32_t* err) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= n_sets) return;
-  const int4 b = bbox[s];
-  int gw = 0, gh = 0;
-  if (b.x < b.z && b.y < b.w) {
-    const int64_t w = ((int64_t)b.z - b.x + cell - 1) / cell, h = ((int64_t)b.w - b.y + cell - 1) / cell;
-    if (w * h > (1 << 24)) {
-      latch_error(err, kErrSide);  // the set's grid is too large for the cell size
-    } else {
-      gw = (int)w;
-      gh = (int)h;
-    }
+// ------------------------------------------------------- exclusive scans
+// exclusive prefix of v over the threads of a block (kScanThreads of them)
+constexpr int kScanThreads = 256;
+constexpr int kScanPer = 8;
+constexpr int kScanBlock = kScanThreads * kScanPer;
+__device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh, int64_t* total) {
+  const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
+  int64_t x = v;
+#pragma unroll
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int64_t u = __shfl_up((long long)x, d, kWave);
+    if (lane >= d) x += u;
   }
-  grid[s] = make_int4(b.x, b.y, gw, gh);
-  cells[s] = (int64_t)gw * gh;
+  if (lane == kWave - 1) sh[w] = x;
+  __syncthreads();
+  int64_t before = 0, all = 0;
+  for (int k = 0; k < kScanThreads / kWave; ++k) {
+    before += k < w ? sh[k] : 0;
+    all += sh[k];
+  }
+  __syncthreads();
+  *total = all;
+  return before + x - v;
 }
 
+// Grid of each set: origin, columns, rows; base[s] = cells of the sets before
+// s, base[n_sets] = all of them.  One block.
+__global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, const int4* bbox, int cell, int4* grid,
+                                                            int64_t* base, uint32_t* err) {
+  __shared__ int64_t sh[kScanThreads / kWave];
+  int64_t run = 0;
+  for (int64_t s0 = 0; s0 < n_sets; s0 += kScanThreads) {
+    const int64_t s = s0 + threadIdx.x;
+    int64_t cells = 0;
+    if (s < n_sets) {
+      const int4 b = bbox[s];
+      int gw = 0, gh = 0;
+      if (b.x < b.z && b.y < b.w) {
+        const int64_t w = ((int64_t)b.z - b.x + cell - 1) / cell, h = ((int64_t)b.w - b.y + cell - 1) / cell;
+        if (w * h > (1 << 24)) {
+          latch_error(err, kErrSide);  // the set's grid is too large for the cell size
+        } else {
+          gw = (int)w;
+          gh = (int)h;
+        }
+      }
+      grid[s] = make_int4(b.x, b.y, gw, gh);
+      cells = (int64_t)gw * gh;
+    }
+    int64_t total;
+    const int64_t before = block_exclusive(cells, sh, &total);
+    if (s < n_sets) base[s] = run + before;
+    run += total;
+  }
+  if (threadIdx.x == 0) base[n_sets] = run;
+}
+
+// out[i] = sum of in[0 .. i) for i <= n, n read from device memory when n_ptr
+// is given (nothing is done when it exceeds `room`): block totals, then every
+// block adds the totals before its own.
+__device__ __forceinline__ int64_t scan_size(int64_t n, const int64_t* n_ptr, int64_t room) {
+  if (n_ptr) n = *n_ptr;
+  return n > room ? -1 : n;
+}
+__global__ void __launch_bounds__(kScanThreads) k_scan_totals(const int32_t* in, int64_t n, const int64_t* n_ptr,
+                                                              int64_t room, int64_t* sums) {
+  __shared__ int64_t sh[kScanThreads / kWave];
+  n = scan_size(n, n_ptr, room);
+  const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
+  if (b0 > n) return;
+  int64_t tot = 0;
+  for (int k = 0; k < kScanPer; ++k) {
+    const int64_t i = b0 + k * kScanThreads + threadIdx.x;
+    tot += i < n ? in[i] : 0;
+  }
+  int64_t total;
+  block_exclusive(tot, sh, &total);
+  if (threadIdx.x == 0) sums[blockIdx.x] = total;
+}
+// kClear: `in` is zeroed behind the scan.
+template <bool kClear>
+__global__ void __launch_bounds__(kScanThreads) k_scan_write(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room,
+                                                             const int64_t* sums, int64_t* out) {
+  __shared__ int64_t sh[kScanThreads / kWave];
+  n = scan_size(n, n_ptr, room);
+  const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
+  if (b0 > n) return;  // the block that holds entry n writes the total
+  int64_t mine = 0, before;
+  for (int64_t k = threadIdx.x; k < (int64_t)blockIdx.x; k += kScanThreads) mine += sums[k];
+  block_exclusive(mine, sh, &before);
+  const int64_t i0 = b0 + (int64_t)threadIdx.x * kScanPer;
+  int32_t v[kScanPer];
+  int64_t tot = 0, total;
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    v[k] = i0 + k < n ? in[i0 + k] : 0;
+    tot += v[k];
+  }
+  int64_t run = before + block_exclusive(tot, sh, &total);
+#pragma unroll
+  for (int k = 0; k < kScanPer; ++k) {
+    if (i0 + k <= n) out[i0 + k] = run;
+    if (kClear && i0 + k < n) in[i0 + k] = 0;
+    run += v[k];
+  }
+}
+int64_t scan_scratch(int64_t n) { return n / kScanBlock + 1; }
+
+// ------------------------------------------------------------------- entries
 // Cells of an MBR clamped to a grid: [cx0, cx1] x [cy0, cy1] (empty if cx0 > cx1).
 __device__ __forceinline__ void cell_range(const Meta& m, const int4& g, int cell, int& cx0, int& cy0, int& cx1,
                                            int& cy1) {
@@ -109,13 +241,17 @@ __device__ __forceinline__ void cell_range(const Meta& m, const int4& g, int cel
   if (m.x1 <= g.x || m.y1 <= g.y) cx1 = -1;  // wholly left of or below the grid
 }
 
-// mode 0: count the A polygons of each cell; mode 1: fill the cell lists.
+// kFill false: count the A polygons of each cell; true: fill the cell lists
+// (the counts start at zero again).  Nothing when the cells (or the entries)
+// exceed the room for them.
+template <bool kFill>
 __global__ void k_join_cells(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets, const int4* grid,
-                             const int64_t* cell_base, int cell, int mode, int32_t* count, const int64_t* start,
-                             int32_t* list) {
+                             const int64_t* cell_base, int cell, int64_t cell_room, int32_t* count, const int64_t* start,
+                             int64_t list_room, int32_t* list) {
   const int64_t a = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= A.n) return;
-  const int64_t s = set_of(a_off, n_sets, a);
+  const int64_t n_cells = cell_base[n_sets];
+  if (n_cells > cell_room || (kFill && start[n_cells] > list_room)) return;
+  const int64_t s = set_of_lane(a_off, n_sets, a < A.n ? a : -1);
   if (s < 0) return;
   const Meta m = load_meta(metaA, a);
   const int4 g = grid[s];
@@ -126,186 +262,174 @@ __global__ void k_join_cells(Polys A, const Meta* metaA, const int64_t* a_off, i
     for (int cx = cx0; cx <= cx1; ++cx) {
       const int64_t c = cell_base[s] + (int64_t)cy * g.z + cx;
       const int32_t k = atomicAdd(count + c, 1);
-      if (mode == 1) list[start[c] + k] = (int32_t)a;
+      if (kFill) list[start[c] + k] = (int32_t)a;
     }
 }
 
-// Per B polygon: the A polygons of its set whose MBR shares a pixel with its
-// own, each found in the cell of the intersection's lower-left pixel.  mode
-// 0 counts them; mode 1 writes them (up to cap) and sorts the segment by A.
-__global__ void k_join_pairs(Polys B, const Meta* metaA, const Meta* metaB, const int64_t* b_off, int64_t n_sets,
-                             const int4* grid, const int64_t* cell_base, const int64_t* start, const int32_t* list,
-                             int cell, int mode, int32_t* b_count, const int64_t* b_start, int64_t cap,
-                             int32_t* out_pa, int32_t* out_pb) {
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B.n) return;
-  const int64_t s = set_of(b_off, n_sets, b);
-  int32_t n = 0;
-  const int64_t base = mode == 1 ? b_start[b] : 0;
-  if (s >= 0) {
-    const Meta mb = load_meta(metaB, b);
-    const int4 g = grid[s];
-    if (!meta_empty(mb) && g.z > 0) {
-      int cx0, cy0, cx1, cy1;
-      cell_range(mb, g, cell, cx0, cy0, cx1, cy1);
-      for (int cy = cy0; cy <= cy1; ++cy)
-        for (int cx = cx0; cx <= cx1; ++cx) {
-          const int64_t c = cell_base[s] + (int64_t)cy * g.z + cx;
-          for (int64_t e = start[c]; e < start[c + 1]; ++e) {
-            const int32_t a = list[e];
-            const Meta ma = load_meta(metaA, a);
-            const int ix0 = max(ma.x0, mb.x0), iy0 = max(ma.y0, mb.y0);
-            const int ix1 = min(ma.x1, mb.x1), iy1 = min(ma.y1, mb.y1);
-            if (ix0 >= ix1 || iy0 >= iy1) continue;
-            if (cell_of(ix0, g.x, cell) != cx || cell_of(iy0, g.y, cell) != cy) continue;
-            if (mode == 1 && base + n < cap) {
-              out_pa[base + n] = a;
-              out_pb[base + n] = (int32_t)b;
-            }
-            ++n;
-          }
+// --------------------------------------------------------------------- pairs
+struct JoinArgs {
+  Polys B;
+  const Meta* metaA;
+  const Meta* metaB;
+  const int64_t* b_off;
+  int64_t n_sets;
+  const int4* grid;
+  const int64_t* cell_base;
+  const int64_t* start;
+  const int32_t* list;
+  int cell;
+  int64_t cell_room, list_room;
+};
+__device__ __forceinline__ bool join_fits(const JoinArgs& a) {
+  const int64_t n_cells = a.cell_base[a.n_sets];
+  return n_cells <= a.cell_room && a.start[n_cells] <= a.list_room;
+}
+
+// The A polygons of B polygon b of set s, found by a group of L lanes (lane j of it;
+// every lane of the group calls with the same b): emit(k, a, keep) is called
+// by all of them for every L entries, k being the place of the lane's polygon
+// among those kept.  The cells of one grid row that an MBR covers stand side
+// by side in the lists, so that a row of them is one run of entries.  Returns
+// the polygons found.
+template <int L, typename F>
+__device__ __forceinline__ int join_entries(const JoinArgs& a, int64_t b, int64_t s, int j, F emit) {
+  if (s < 0) return 0;
+  const Meta mb = load_meta(a.metaB, b);
+  const int4 g = a.grid[s];
+  if (meta_empty(mb) || g.z <= 0) return 0;
+  int cx0, cy0, cx1, cy1, n = 0;
+  cell_range(mb, g, a.cell, cx0, cy0, cx1, cy1);
+  if (cx0 > cx1) return 0;
+  const int shift = lane_id() / L * L;
+  for (int cy = cy0; cy <= cy1; ++cy) {
+    const int64_t row = a.cell_base[s] + (int64_t)cy * g.z;
+    const int64_t e1 = a.start[row + cx1 + 1];
+    for (int64_t e0 = a.start[row + cx0]; e0 < e1; e0 += L) {
+      const int64_t e = e0 + j;
+      bool keep = false;
+      int32_t p = 0;
+      if (e < e1) {
+        p = a.list[e];
+        const Meta ma = load_meta(a.metaA, p);
+        const int ix0 = max(ma.x0, mb.x0), iy0 = max(ma.y0, mb.y0);
+        if (ix0 < min(ma.x1, mb.x1) && iy0 < min(ma.y1, mb.y1) && cell_of(iy0, g.y, a.cell) == cy) {
+          const int64_t c = row + cell_of(ix0, g.x, a.cell);
+          keep = a.start[c] <= e && e < a.start[c + 1];
         }
+      }
+      const uint32_t m = (uint32_t)(ballot(keep) >> shift) & ((1u << L) - 1u);
+      emit(n + __popc(m & ((1u << j) - 1u)), p, keep);
+      n += __popc(m);
     }
   }
-  if (mode == 0) {
-    b_count[b] = n;
+  return n;
+}
+
+// Pairs of each B polygon, eight lanes per polygon: counted, and the first
+// kFound of them kept for the second pass (a thread per polygon that searched
+// again for it took 88 + 157 us for 600,000 of 4.5 pairs each).
+constexpr int kFound = 16;
+constexpr int kCountLanes = 8;
+__global__ void __launch_bounds__(256) k_join_count(JoinArgs a, int32_t* b_count, int32_t* found, int32_t* cell_count) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (!join_fits(a)) return;
+  // the cells' counts are left at zero for the next call
+  const int64_t n_cells = a.cell_base[a.n_sets];
+  for (int64_t c = t; c < n_cells; c += (int64_t)gridDim.x * blockDim.x) cell_count[c] = 0;
+  const int64_t b = t / kCountLanes;
+  const int j = (int)(t % kCountLanes);
+  const int64_t s = set_of_lane(a.b_off, a.n_sets, b < a.B.n ? b : -1);
+  if (b >= a.B.n) return;
+  const int n = join_entries<kCountLanes>(a, b, s, j, [&](int k, int32_t p, bool keep) {
+    if (keep && k < kFound) found[b * kFound + k] = p;
+  });
+  if (j == 0) b_count[b] = n;
+}
+
+// Each B polygon's pairs in the order of A, 16 lanes per polygon: the place of
+// a pair is the number of smaller indices.  The last thread also leaves the
+// sizes for the host, and the first ones the sets' offsets.
+__global__ void __launch_bounds__(256) k_join_write(JoinArgs a, const int32_t* b_count, const int64_t* b_start,
+                                                    const int32_t* found, int64_t cap, int32_t* out_pa, int32_t* out_pb,
+                                                    int64_t* out_set_off, int64_t* sizes) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t n_cells = a.cell_base[a.n_sets];
+  const bool fits = join_fits(a);
+  if (t == 0) {
+    sizes[0] = n_cells;
+    sizes[1] = n_cells <= a.cell_room ? a.start[n_cells] : 0;
+    sizes[2] = fits ? b_start[a.B.n] : 0;
+  }
+  if (!fits) return;
+  if (t <= a.n_sets) out_set_off[t] = b_start[min(max(a.b_off[t], (int64_t)0), a.B.n)];
+  if (b_start[a.B.n] > cap) return;
+  const int64_t b = t / kFound;
+  const int j = (int)(t % kFound);
+  if (b >= a.B.n) return;
+  const int n = b_count[b];
+  const int64_t base = b_start[b];
+  if (n <= kFound) {
+    const int v = j < n ? found[b * kFound + j] : INT_MAX;
+    int rank = 0;
+#define SCCG_RANK(R) rank += __builtin_amdgcn_update_dpp(0, v, 0x120 + R, 0xf, 0xf, false) < v ? 1 : 0;  // row_ror:R
+    SCCG_RANK(1) SCCG_RANK(2) SCCG_RANK(3) SCCG_RANK(4) SCCG_RANK(5) SCCG_RANK(6) SCCG_RANK(7) SCCG_RANK(8)
+    SCCG_RANK(9) SCCG_RANK(10) SCCG_RANK(11) SCCG_RANK(12) SCCG_RANK(13) SCCG_RANK(14) SCCG_RANK(15)
+#undef SCCG_RANK
+    if (j < n) {
+      out_pa[base + rank] = v;
+      out_pb[base + rank] = (int32_t)b;
+    }
     return;
   }
-  // insertion sort of this B polygon's segment by A index
-  const int64_t end = min(base + (int64_t)n, cap);
-  for (int64_t i = base + 1; i < end; ++i) {
-    const int32_t v = out_pa[i];
-    int64_t j = i - 1;
-    while (j >= base && out_pa[j] > v) {
-      out_pa[j + 1] = out_pa[j];
-      --j;
-    }
-    out_pa[j + 1] = v;
+  // more than were kept: searched again, unordered into out_pa, ordered into
+  // out_pb, and back
+  join_entries<kFound>(a, b, set_of(a.b_off, a.n_sets, b), j, [&](int k, int32_t p, bool keep) {
+    if (keep) out_pa[base + k] = p;
+  });
+  __threadfence_block();
+  for (int i = j; i < n; i += kFound) {
+    const int32_t v = out_pa[base + i];
+    int rank = 0;
+    for (int k = 0; k < n; ++k) rank += out_pa[base + k] < v ? 1 : 0;
+    out_pb[base + rank] = v;
   }
-}
-
-__global__ void k_join_set_off(int64_t n_sets, int64_t n_b, const int64_t* b_off, const int64_t* b_start,
-                               int64_t* out_set_off) {
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s <= n_sets) out_set_off[s] = b_start[min(max(b_off[s], (int64_t)0), n_b)];
-}
-
-// ------------------------------------------------------- exclusive scan
-// out[i] = sum of in[0 .. i) for i <= n (out has n + 1 entries).  Blocks of
-// 256 threads scan 1024 entries each; the block totals are scanned by one
-// block; then each block adds its offset.
-constexpr int kScanThreads = 256;
-constexpr int kScanPer = 4;
-constexpr int kScanBlock = kScanThreads * kScanPer;
-
-template <typename T>
-__device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh) {
-  // Hillis-Steele over the threads of the block; returns the exclusive prefix
-  const int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-  for (int d = 1; d < (int)blockDim.x; d <<= 1) {
-    const int64_t add = t >= d ? sh[t - d] : 0;
-    __syncthreads();
-    sh[t] += add;
-    __syncthreads();
-  }
-  const int64_t incl = sh[t];
-  __syncthreads();
-  return incl - v;
-}
-
-template <typename T>
-__global__ void __launch_bounds__(kScanThreads) k_scan_blocks(const T* in, int64_t n, int64_t* out, int64_t* sums) {
-  __shared__ int64_t sh[kScanThreads];
-  const int64_t i0 = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanPer;
-  int64_t v[kScanPer];
-  int64_t tot = 0;
-  for (int k = 0; k < kScanPer; ++k) {
-    v[k] = (i0 + k < n) ? (int64_t)in[i0 + k] : 0;
-    tot += v[k];
-  }
-  int64_t run = block_exclusive<T>(tot, sh);
-  for (int k = 0; k < kScanPer; ++k) {
-    if (i0 + k < n) out[i0 + k] = run;
-    run += v[k];
-  }
-  if (threadIdx.x == blockDim.x - 1) sums[blockIdx.x] = run;
-}
-
-// One block: exclusive scan of the nb block totals in place; sums[nb] = total.
-__global__ void __launch_bounds__(1024) k_scan_sums(int64_t* sums, int64_t nb) {
-  __shared__ int64_t sh[1024];
-  const int64_t per = (nb + blockDim.x - 1) / blockDim.x;
-  const int64_t i0 = (int64_t)threadIdx.x * per;
-  int64_t tot = 0;
-  for (int64_t k = i0; k < min(i0 + per, nb); ++k) tot += sums[k];
-  int64_t run = block_exclusive<int64_t>(tot, sh);
-  for (int64_t k = i0; k < min(i0 + per, nb); ++k) {
-    const int64_t x = sums[k];
-    sums[k] = run;
-    run += x;
-  }
-  if (threadIdx.x == blockDim.x - 1) sums[nb] = run;
-}
-
-__global__ void k_scan_add(int64_t* out, int64_t n, const int64_t* sums) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += sums[i / kScanBlock];
-  if (i == n) out[n] = sums[(n + kScanBlock - 1) / kScanBlock];
-}
-
-int64_t scan_scratch(int64_t n) { return (n + kScanBlock - 1) / kScanBlock + 1; }
-
-template <typename T>
-hipError_t scan_exclusive(const T* in, int64_t n, int64_t* out, int64_t* sums, hipStream_t s) {
-  const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
-  if (nb > 0) hipLaunchKernelGGL(k_scan_blocks<T>, dim3((unsigned)nb), dim3(kScanThreads), 0, s, in, n, out, sums);
-  hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, s, sums, nb);
-  hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((n + 1 + 255) / 256)), dim3(256), 0, s, out, n, sums);
-  return hipGetLastError();
+  __threadfence_block();
+  for (int i = j; i < n; i += kFound) out_pa[base + i] = out_pb[base + i];
+  __threadfence_block();
+  for (int i = j; i < n; i += kFound) out_pb[base + i] = (int32_t)b;
 }
 
 static unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
-hipError_t launch_join_grid(const Polys& A, const Meta* metaA, const int64_t* a_off, int64_t n_sets, int cell,
-                            int4* bbox, int4* grid, int64_t* cells, int64_t* cell_base, int64_t* sums,
-                            uint32_t* err, hipStream_t s) {
-  hipLaunchKernelGGL(k_join_init_sets, dim3(blocks_for(n_sets)), dim3(256), 0, s, n_sets, bbox);
+hipError_t launch_join(const JoinLaunch& l, hipStream_t s) {
+  const Polys &A = l.A, &B = l.B;
+  hipLaunchKernelGGL(k_join_init_sets, dim3(blocks_for(l.n_sets)), dim3(256), 0, s, l.n_sets, l.bbox);
   if (A.n > 0)
-    hipLaunchKernelGGL(k_join_bbox, dim3(blocks_for(A.n)), dim3(256), 0, s, A, metaA, a_off, n_sets, bbox);
-  hipLaunchKernelGGL(k_join_grid, dim3(blocks_for(n_sets)), dim3(256), 0, s, n_sets, bbox, cell, grid, cells, err);
-  return scan_exclusive<int64_t>(cells, n_sets, cell_base, sums, s);
-}
-
-hipError_t launch_join_cells(const Polys& A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
-                             const int4* grid, const int64_t* cell_base, int cell, int mode, int32_t* count,
-                             const int64_t* start, int32_t* list, hipStream_t s) {
+    hipLaunchKernelGGL(k_join_bbox, dim3((unsigned)((A.n + kBoxRun - 1) / kBoxRun)), dim3(256), 0, s, A,
+                       l.metaA, l.a_off, l.n_sets, l.bbox);
+  hipLaunchKernelGGL(k_join_grid, dim3(1), dim3(kScanThreads), 0, s, l.n_sets, l.bbox, l.cell, l.grid, l.cell_base,
+                     l.err);
   if (A.n > 0)
-    hipLaunchKernelGGL(k_join_cells, dim3(blocks_for(A.n)), dim3(256), 0, s, A, metaA, a_off, n_sets, grid,
-                       cell_base, cell, mode, count, start, list);
+    hipLaunchKernelGGL(k_join_cells<false>, dim3(blocks_for(A.n)), dim3(256), 0, s, A, l.metaA, l.a_off, l.n_sets,
+                       l.grid, l.cell_base, l.cell, l.cell_room, l.count, nullptr, 0, nullptr);
+  const int64_t* n_cells = l.cell_base + l.n_sets;
+  const dim3 cb((unsigned)scan_scratch(l.cell_room)), bb((unsigned)scan_scratch(B.n)), st(kScanThreads);
+  hipLaunchKernelGGL(k_scan_totals, cb, st, 0, s, l.count, 0, n_cells, l.cell_room, l.sums);
+  hipLaunchKernelGGL(k_scan_write<true>, cb, st, 0, s, l.count, 0, n_cells, l.cell_room, l.sums, l.start);
+  if (A.n > 0)
+    hipLaunchKernelGGL(k_join_cells<true>, dim3(blocks_for(A.n)), dim3(256), 0, s, A, l.metaA, l.a_off, l.n_sets, l.grid,
+                       l.cell_base, l.cell, l.cell_room, l.count, l.start, l.list_room, l.list);
+  const JoinArgs j{B, l.metaA, l.metaB, l.b_off, l.n_sets, l.grid, l.cell_base, l.start, l.list, l.cell, l.cell_room,
+                   l.list_room};
+  hipLaunchKernelGGL(k_join_count, dim3(std::max(1u, blocks_for(B.n * kCountLanes))), dim3(256), 0, s, j, l.b_count,
+                     l.found, l.count);
+  hipLaunchKernelGGL(k_scan_totals, bb, st, 0, s, l.b_count, B.n, (const int64_t*)nullptr, B.n, l.sums);
+  hipLaunchKernelGGL(k_scan_write<false>, bb, st, 0, s, l.b_count, B.n, (const int64_t*)nullptr, B.n, l.sums, l.b_start);
+  const int64_t threads = std::max(B.n * kFound, l.n_sets + 1);
+  hipLaunchKernelGGL(k_join_write, dim3(blocks_for(threads)), dim3(256), 0, s, j, l.b_count, l.b_start, l.found, l.cap,
+                     l.out_pa, l.out_pb, l.out_set_off, l.sizes);
   return hipGetLastError();
 }
-
-hipError_t launch_join_scan_counts(const int32_t* count, int64_t n, int64_t* start, int64_t* sums, hipStream_t s) {
-  return scan_exclusive<int32_t>(count, n, start, sums, s);
-}
-
-hipError_t launch_join_pairs(const Polys& B, const Meta* metaA, const Meta* metaB, const int64_t* b_off,
-                             int64_t n_sets, const int4* grid, const int64_t* cell_base, const int64_t* start,
-                             const int32_t* list, int cell, int mode, int32_t* b_count, const int64_t* b_start,
-                             int64_t cap, int32_t* out_pa, int32_t* out_pb, hipStream_t s) {
-  if (B.n > 0)
-    hipLaunchKernelGGL(k_join_pairs, dim3(blocks_for(B.n)), dim3(256), 0, s, B, metaA, metaB, b_off, n_sets, grid,
-                       cell_base, start, list, cell, mode, b_count, b_start, cap, out_pa, out_pb);
-  return hipGetLastError();
-}
-
-hipError_t launch_join_set_off(int64_t n_sets, int64_t n_b, const int64_t* b_off, const int64_t* b_start,
-                               int64_t* out_set_off, hipStream_t s) {
-  hipLaunchKernelGGL(k_join_set_off, dim3(blocks_for(n_sets + 1)), dim3(256), 0, s, n_sets, n_b, b_off, b_start,
-                     out_set_off);
-  return hipGetLastError();
-}
+int64_t join_found_room(int64_t n_b) { return n_b * kFound; }
 
 }  // namespace sccg

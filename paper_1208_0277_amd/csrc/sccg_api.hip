@@ -58,7 +58,6 @@ struct sccg_ctx {
   // filter-stage scratch
   int4* j_bbox = nullptr;
   int4* j_grid = nullptr;
-  int64_t* j_cells = nullptr;
   int64_t* j_cell_base = nullptr;
   int64_t* j_sums = nullptr;
   int32_t* j_count = nullptr;
@@ -66,8 +65,13 @@ struct sccg_ctx {
   int32_t* j_list = nullptr;
   int32_t* j_bcount = nullptr;
   int64_t* j_bstart = nullptr;
+  int32_t* j_found = nullptr;
+  int64_t* j_sizes = nullptr;
+  int64_t* j_host = nullptr;                     // the sizes, in pinned host memory
+  int64_t j_cells_seen = 0, j_entries_seen = 0;  // the most that a call had
+  bool j_dirty = true;                           // j_count may hold counts of a call that did not end
   JacAcc* j_acc = nullptr;  // per-set accumulators of sccg_jaccard_sets
-  int64_t j_cap[10] = {};
+  int64_t j_cap[12] = {};
   // kernel timing
   int timing_on = 0;
   std::vector<hipEvent_t> ev;  // start/stop pairs
@@ -406,10 +410,11 @@ int sccg_destroy(sccg_ctx* c) {
   void* ptrs[] = {c->metaA,  c->areaA,  c->metaB,  c->areaB,
                   c->err,    c->cls,    c->l_list, c->hbox,    c->st,      c->queue,
                   c->plain_stats, c->wave_t,
-                  c->j_bbox, c->j_grid, c->j_cells,     c->j_cell_base, c->j_sums, c->j_count, c->j_start,
-                  c->j_list, c->j_bcount, c->j_bstart, c->j_acc};
+                  c->j_bbox, c->j_grid, c->j_cell_base, c->j_sums, c->j_count, c->j_start,
+                  c->j_list, c->j_bcount, c->j_bstart, c->j_found, c->j_sizes, c->j_acc};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
+  if (c->j_host) (void)hipHostFree(c->j_host);
   delete c;
   return SCCG_OK;
 }
@@ -741,7 +746,7 @@ int sccg_jaccard_sets(sccg_ctx* c, int64_t n_sets, const int64_t* set_pair_off, 
   HIP_TRY(c, hipSetDevice(c->device));
   int r;
   // one accumulator per set, and past them the chunk counter
-  if ((r = need(c, &c->j_acc, c->j_cap[8], n_sets + 1, "set accumulators"))) return r;
+  if ((r = need(c, &c->j_acc, c->j_cap[11], n_sets + 1, "set accumulators"))) return r;
   const int grid = c->cu_count * 4;
   hipError_t e = launch_jaccard(n_sets, set_pair_off, inter, uni, flags, out_sum_i, out_sum_u, out_n_contrib, out_j,
                                 out_jprime, c->j_acc, &c->j_acc[n_sets].si, grid, c->stream);
@@ -774,58 +779,75 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
   // extents only
   if ((e = launch_poly_meta(pA, c->metaA, nullptr, pB, c->metaB, nullptr, c->err, c->stream)) != hipSuccess)
     return hip_fail(c, e, "poly meta");
-  // grids: per-set extents of A, cells per set, their offsets
   if ((r = need(c, &c->j_bbox, c->j_cap[0], n_sets, "join boxes")) ||
       (r = need(c, &c->j_grid, c->j_cap[1], n_sets, "join grids")) ||
-      (r = need(c, &c->j_cells, c->j_cap[2], n_sets, "join cells")) ||
-      (r = need(c, &c->j_cell_base, c->j_cap[3], n_sets + 1, "join cell offsets")) ||
-      (r = need(c, &c->j_sums, c->j_cap[4], scan_scratch(n_sets), "scan sums")))
+      (r = need(c, &c->j_cell_base, c->j_cap[2], n_sets + 1, "join cell offsets")) ||
+      (r = need(c, &c->j_bcount, c->j_cap[3], B->n_polys, "pair counts")) ||
+      (r = need(c, &c->j_bstart, c->j_cap[4], B->n_polys + 1, "pair starts")) ||
+      (r = need(c, &c->j_found, c->j_cap[5], join_found_room(B->n_polys), "pairs found")) ||
+      (r = need(c, &c->j_sizes, c->j_cap[6], 3, "join sizes")))
     return r;
-  if ((e = launch_join_grid(pA, c->metaA, a_set_off, n_sets, cell, c->j_bbox, c->j_grid, c->j_cells, c->j_cell_base,
-                            c->j_sums, c->err, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "join grid");
-  int64_t n_cells = 0;
-  HIP_TRY(c, hipMemcpyAsync(&n_cells, c->j_cell_base + n_sets, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  // counting sort of (cell, A polygon) entries
-  if ((r = need(c, &c->j_count, c->j_cap[5], n_cells + 1, "cell counts")) ||
-      (r = need(c, &c->j_start, c->j_cap[6], n_cells + 1, "cell starts")) ||
-      (r = need(c, &c->j_sums, c->j_cap[4], scan_scratch(n_cells), "scan sums")))
-    return r;
-  HIP_TRY(c, hipMemsetAsync(c->j_count, 0, sizeof(int32_t) * (size_t)(n_cells + 1), c->stream));
-  if ((e = launch_join_cells(pA, c->metaA, a_set_off, n_sets, c->j_grid, c->j_cell_base, cell, 0, c->j_count,
-                             nullptr, nullptr, c->stream)) != hipSuccess ||
-      (e = launch_join_scan_counts(c->j_count, n_cells, c->j_start, c->j_sums, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "join cell counts");
-  int64_t n_entries = 0;
-  HIP_TRY(c, hipMemcpyAsync(&n_entries, c->j_start + n_cells, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  if ((r = need(c, &c->j_list, c->j_cap[7], n_entries + 1, "cell lists"))) return r;
-  HIP_TRY(c, hipMemsetAsync(c->j_count, 0, sizeof(int32_t) * (size_t)(n_cells + 1), c->stream));
-  if ((e = launch_join_cells(pA, c->metaA, a_set_off, n_sets, c->j_grid, c->j_cell_base, cell, 1, c->j_count,
-                             c->j_start, c->j_list, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "join cell lists");
-  // pairs: count per B polygon, offsets, then (if they fit) write and sort
-  if ((r = need(c, &c->j_bcount, c->j_cap[8], B->n_polys + 1, "pair counts")) ||
-      (r = need(c, &c->j_bstart, c->j_cap[9], B->n_polys + 1, "pair starts")) ||
-      (r = need(c, &c->j_sums, c->j_cap[4], scan_scratch(B->n_polys), "scan sums")))
-    return r;
-  if ((e = launch_join_pairs(pB, c->metaA, c->metaB, b_set_off, n_sets, c->j_grid, c->j_cell_base, c->j_start,
-                             c->j_list, cell, 0, c->j_bcount, nullptr, 0, nullptr, nullptr, c->stream)) != hipSuccess ||
-      (e = launch_join_scan_counts(c->j_bcount, B->n_polys, c->j_bstart, c->j_sums, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "join pair counts");
-  int64_t total = 0;
-  HIP_TRY(c, hipMemcpyAsync(&total, c->j_bstart + B->n_polys, sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  *out_total = total;
-  if (total <= cap && total > 0) {
-    if ((e = launch_join_pairs(pB, c->metaA, c->metaB, b_set_off, n_sets, c->j_grid, c->j_cell_base, c->j_start,
-                               c->j_list, cell, 1, nullptr, c->j_bstart, cap, out_pa, out_pb, c->stream)) != hipSuccess)
-      return hip_fail(c, e, "join pairs");
+  if (!c->j_host && hipHostMalloc((void**)&c->j_host, 3 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+    c->j_host = nullptr;
+    return fail(c, SCCG_E_NOMEM, "hipHostMalloc(join sizes)");
   }
-  if ((e = launch_join_set_off(n_sets, B->n_polys, b_set_off, c->j_bstart, out_set_off, c->stream)) != hipSuccess)
-    return hip_fail(c, e, "join set offsets");
-  return SCCG_OK;
+  // Room for the cells and for the entries in them, which are only known when
+  // the kernels have run: what earlier calls took, or a first guess (objects
+  // a cell apart, each in four of them); what turns out too small grows, and
+  // the kernels run again.
+  int64_t cells = std::max(c->j_cells_seen, A->n_polys + n_sets + 1024);
+  int64_t entries = std::max(c->j_entries_seen, 4 * A->n_polys + 1024);
+  for (;;) {
+    const int64_t had = c->j_cap[7];
+    if ((r = need(c, &c->j_count, c->j_cap[7], cells, "cell counts")) ||
+        (r = need(c, &c->j_start, c->j_cap[8], c->j_cap[7] + 1, "cell starts")) ||
+        (r = need(c, &c->j_list, c->j_cap[9], entries, "cell lists")) ||
+        (r = need(c, &c->j_sums, c->j_cap[10], std::max(scan_scratch(c->j_cap[7]), scan_scratch(B->n_polys)), "scan sums")))
+      return r;
+    if (c->j_cap[7] != had || c->j_dirty)
+      HIP_TRY(c, hipMemsetAsync(c->j_count, 0, sizeof(int32_t) * (size_t)c->j_cap[7], c->stream));
+    JoinLaunch l{};
+    l.A = pA;
+    l.B = pB;
+    l.metaA = c->metaA;
+    l.metaB = c->metaB;
+    l.n_sets = n_sets;
+    l.a_off = a_set_off;
+    l.b_off = b_set_off;
+    l.cell = cell;
+    l.bbox = c->j_bbox;
+    l.grid = c->j_grid;
+    l.cell_base = c->j_cell_base;
+    l.cell_room = cells;
+    l.count = c->j_count;
+    l.start = c->j_start;
+    l.list_room = c->j_cap[9];
+    l.list = c->j_list;
+    l.sums = c->j_sums;
+    l.b_count = c->j_bcount;
+    l.b_start = c->j_bstart;
+    l.found = c->j_found;
+    l.cap = cap;
+    l.out_pa = out_pa;
+    l.out_pb = out_pb;
+    l.out_set_off = out_set_off;
+    l.sizes = c->j_sizes;
+    l.err = c->err;
+    c->j_dirty = true;
+    if ((e = launch_join(l, c->stream)) != hipSuccess) return hip_fail(c, e, "join");
+    HIP_TRY(c, hipMemcpyAsync(c->j_host, c->j_sizes, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const int64_t n_cells = c->j_host[0], n_entries = c->j_host[1];
+    if (n_cells <= cells && n_entries <= c->j_cap[9]) {
+      c->j_dirty = false;
+      c->j_cells_seen = std::max(c->j_cells_seen, n_cells);
+      c->j_entries_seen = std::max(c->j_entries_seen, n_entries);
+      *out_total = c->j_host[2];
+      return SCCG_OK;
+    }
+    cells = std::max(cells, n_cells);
+    entries = std::max(entries, n_entries);
+  }
 }
 
 int sccg_relate_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_t n_pairs, const int32_t* pair_a,

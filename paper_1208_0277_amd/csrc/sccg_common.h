@@ -185,21 +185,39 @@ hipError_t launch_jaccard(int64_t n_sets, const int64_t* set_off, const int64_t*
 // Ring validation.
 hipError_t launch_validate(const Polys& P, int64_t* first_bad, hipStream_t s);
 
-// Filter stage (candidate pairs by MBR intersection).
+// Filter stage (candidate pairs by MBR intersection): one call's arrays and
+// the room in them.  `count` is all zero before and, when everything fitted,
+// after.
 int64_t scan_scratch(int64_t n);
-hipError_t launch_join_grid(const Polys& A, const Meta* metaA, const int64_t* a_off, int64_t n_sets, int cell,
-                            int4* bbox, int4* grid, int64_t* cells, int64_t* cell_base, int64_t* sums,
-                            uint32_t* err, hipStream_t s);
-hipError_t launch_join_cells(const Polys& A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
-                             const int4* grid, const int64_t* cell_base, int cell, int mode, int32_t* count,
-                             const int64_t* start, int32_t* list, hipStream_t s);
-hipError_t launch_join_scan_counts(const int32_t* count, int64_t n, int64_t* start, int64_t* sums, hipStream_t s);
-hipError_t launch_join_pairs(const Polys& B, const Meta* metaA, const Meta* metaB, const int64_t* b_off,
-                             int64_t n_sets, const int4* grid, const int64_t* cell_base, const int64_t* start,
-                             const int32_t* list, int cell, int mode, int32_t* b_count, const int64_t* b_start,
-                             int64_t cap, int32_t* out_pa, int32_t* out_pb, hipStream_t s);
-hipError_t launch_join_set_off(int64_t n_sets, int64_t n_b, const int64_t* b_off, const int64_t* b_start,
-                               int64_t* out_set_off, hipStream_t s);
+int64_t join_found_room(int64_t n_b);
+struct JoinLaunch {
+  Polys A, B;
+  const Meta* metaA;
+  const Meta* metaB;
+  int64_t n_sets;
+  const int64_t* a_off;
+  const int64_t* b_off;
+  int cell;
+  int4* bbox;            // [n_sets]
+  int4* grid;            // [n_sets]
+  int64_t* cell_base;    // [n_sets + 1]
+  int64_t cell_room;     // cells that count and start hold
+  int32_t* count;        // [cell_room]
+  int64_t* start;        // [cell_room + 1]
+  int64_t list_room;
+  int32_t* list;         // [list_room]
+  int64_t* sums;         // [max of scan_scratch(cell_room), scan_scratch(B.n)]
+  int32_t* b_count;      // [B.n]
+  int64_t* b_start;      // [B.n + 1]
+  int32_t* found;        // [join_found_room(B.n)]
+  int64_t cap;
+  int32_t* out_pa;
+  int32_t* out_pb;
+  int64_t* out_set_off;
+  int64_t* sizes;        // [3]: cells, entries (0 when the cells did not fit), pairs (0 when either did not)
+  uint32_t* err;
+};
+hipError_t launch_join(const JoinLaunch& l, hipStream_t s);
 
 // Section 3.4's operators from counts and edges.
 hipError_t launch_relate(const Polys& A, const Polys& B, const Meta* metaA, const Meta* metaB, const int64_t* areaA,

@@ -1,0 +1,62 @@
+"""The filter stage's kept pairs (16 per polygon), its grown scratch and its
+offsets, against the oracle."""
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1208_0277_amd as sccg
+from sccg_gen import concat
+from tests.shapes import rect_ring
+
+pytestmark = pytest.mark.gpu
+
+
+def _sets(seed):
+    """Sets of small A squares and B rectangles that cover 0, 1, 15, 16, 17 and
+    hundreds of them, empty sets, and polygons before the first and after the
+    last set."""
+    rng = np.random.default_rng(seed)
+    ra, rb, ao, bo = [rect_ring((0, 0, 9, 9))], [rect_ring((1, 1, 5, 5))], [], []
+    for s in range(12):
+        ao.append(len(ra))
+        bo.append(len(rb))
+        if s % 5 == 3:
+            continue
+        ox, oy = int(rng.integers(-5000, 5000)), int(rng.integers(-5000, 5000))
+        side = int(rng.integers(1, 30))
+        for k in rng.permutation(side * side):
+            x, y = ox + 20 * (int(k) % side), oy + 20 * (int(k) // side)
+            ra.append(rect_ring((x, y, x + 12, y + 12)))
+        for n in (0, 1, 5, 15, 16, 17, 18, 31, 33, 900):
+            w, h = (n, 1) if n < 20 else (min(n, 30), (n + 29) // 30)
+            x, y = ox + 20 * int(rng.integers(0, 3)), oy + 20 * int(rng.integers(0, 3))
+            rb.append(rect_ring((x, y, x + max(1, 20 * w - 8), y + max(1, 20 * h - 8))) if n else rect_ring((x + 12, y, x + 20, y + 20)))
+    ao.append(len(ra))
+    bo.append(len(rb))
+    ra += [rect_ring((0, 0, 40, 40))] * 3
+    rb += [rect_ring((0, 0, 40, 40))] * 2
+    return concat(ra), concat(rb), np.array(ao, np.int64), np.array(bo, np.int64)
+
+
+@pytest.mark.parametrize("cells", [(64,), (2, 64, 500), (500, 3, 1)])
+def test_pairs_kept_and_scratch_grown(cells):
+    """Calls in a row on one context, cell sizes whose cells and entries exceed
+    the first guess among them; each equals the oracle's join."""
+    import torch
+    c = sccg.Context(0)
+    try:
+        for seed, cell in enumerate(cells):
+            A, B, ao, bo = _sets(seed)
+            dA, dB = sccg.DevicePolys.from_host(A.off, A.xy), sccg.DevicePolys.from_host(B.off, B.xy)
+            ta, tb = torch.from_numpy(ao).cuda(), torch.from_numpy(bo).cuda()
+            want = oracle.join_sets(A, B, ao, bo)
+            assert np.bincount(want[1]).max() > 100 and {15, 16, 17} & set(np.bincount(want[1]).tolist())
+            for cap in (4, None, len(want[0])):  # too small at first; the default; exact
+                got = c.join_sets(dA, dB, ta, tb, cell=cell, cap=cap)
+                c.sync()
+                for g, w in zip(got, want):
+                    assert np.array_equal(g.cpu().numpy(), w)
+    finally:
+        c.close()
+
