@@ -17,16 +17,9 @@ struct Fix192 {
   uint64_t w[3] = {0, 0, 0};  // little-endian limbs
 
   __host__ __device__ void add(const Fix192& o) {
-    uint64_t c = 0;
+    unsigned long long c = 0;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const uint64_t s = w[i] + o.w[i];
-      const uint64_t c1 = s < w[i];
-      const uint64_t s2 = s + c;
-      const uint64_t c2 = s2 < s;
-      w[i] = s2;
-      c = c1 | c2;
-    }
+    for (int i = 0; i < 3; ++i) w[i] = __builtin_addcll(w[i], o.w[i], c, &c);
   }
 
   __host__ __device__ void add_ratio(double r) {
@@ -39,10 +32,12 @@ struct Fix192 {
     // r = m * 2^(e - 1075); in 2^-128 units: m << (e - 1075 + 128)
     const int sh = e - 947;
     if (sh < 0) return;
-    Fix192 t;
+    Fix192 t;  // limbs chosen by selection: an index would put them in memory
     const int limb = sh >> 6, off = sh & 63;
-    if (limb < 3) t.w[limb] = m << off;
-    if (off && limb + 1 < 3) t.w[limb + 1] = m >> (64 - off);
+    const uint64_t lo = m << off, hi = off ? m >> (64 - off) : 0;
+    t.w[0] = limb == 0 ? lo : 0;
+    t.w[1] = limb == 0 ? hi : limb == 1 ? lo : 0;
+    t.w[2] = limb == 1 ? hi : limb == 2 ? lo : 0;
     add(t);
   }
 

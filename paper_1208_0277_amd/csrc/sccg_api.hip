@@ -70,7 +70,7 @@ struct sccg_ctx {
   int64_t* j_host = nullptr;                     // the sizes, in pinned host memory
   int64_t j_cells_seen = 0, j_entries_seen = 0;  // the most that a call had
   bool j_dirty = true;                           // j_count may hold counts of a call that did not end
-  JacAcc* j_acc = nullptr;  // per-set accumulators of sccg_jaccard_sets
+  unsigned char* j_acc = nullptr;  // the waves' sums of sccg_jaccard_sets
   int64_t j_cap[12] = {};
   // kernel timing
   int timing_on = 0;
@@ -745,11 +745,11 @@ int sccg_jaccard_sets(sccg_ctx* c, int64_t n_sets, const int64_t* set_pair_off, 
     return fail(c, SCCG_E_ARG, "NULL array");
   HIP_TRY(c, hipSetDevice(c->device));
   int r;
-  // one accumulator per set, and past them the chunk counter
-  if ((r = need(c, &c->j_acc, c->j_cap[11], n_sets + 1, "set accumulators"))) return r;
-  const int grid = c->cu_count * 4;
+  // as many waves as the device holds eight per SIMD
+  const int waves = c->cu_count * 32;
+  if ((r = need(c, &c->j_acc, c->j_cap[11], jaccard_scratch(waves), "set sums"))) return r;
   hipError_t e = launch_jaccard(n_sets, set_pair_off, inter, uni, flags, out_sum_i, out_sum_u, out_n_contrib, out_j,
-                                out_jprime, c->j_acc, &c->j_acc[n_sets].si, grid, c->stream);
+                                out_jprime, c->j_acc, waves, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "jaccard");
   return SCCG_OK;
 }

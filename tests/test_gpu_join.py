@@ -60,3 +60,32 @@ def test_pairs_kept_and_scratch_grown(cells):
     finally:
         c.close()
 
+
+@pytest.mark.parametrize("n_pairs", [1, 255, 256, 257, 70_001, 3_000_000])
+@pytest.mark.parametrize("include_zero", [False, True])
+def test_jaccard_over_wave_ranges(n_pairs, include_zero):
+    """Set sums when sets begin, end and lie within, on and across the waves'
+    ranges of 256 or more pairs: one set, sets of 256, tiny, empty and very
+    uneven ones, the first starting past pair 0."""
+    import torch
+    rng = np.random.default_rng(n_pairs)
+    U = rng.integers(1, 5000, n_pairs).astype(np.int64)
+    I = np.where(rng.random(n_pairs) < 0.4, 0, (U * rng.random(n_pairs)).astype(np.int64))
+    U[rng.integers(0, n_pairs, n_pairs // 50)] = 2 ** 40
+    start = min(3, n_pairs - 1)
+    cuts = np.sort(rng.integers(start, n_pairs + 1, 40))
+    layouts = [np.array([0, n_pairs]), np.arange(0, n_pairs + 1, 256), np.concatenate([[start], cuts, cuts[-1:], [n_pairs]]),
+               np.concatenate([[0, 0], np.arange(0, min(n_pairs, 60_000) + 1, 3), [n_pairs, n_pairs]]),
+               np.array([n_pairs, n_pairs])]
+    tI, tU = torch.from_numpy(I).cuda(), torch.from_numpy(U).cuda()
+    flags = sccg.SCCG_J_INCLUDE_ZERO if include_zero else sccg.SCCG_J_NONZERO_ONLY
+    c = sccg.Context(0)
+    try:
+        for so in layouts:
+            so = np.ascontiguousarray(so, np.int64)
+            got = c.jaccard_sets(torch.from_numpy(so).cuda(), tI, tU, flags=flags)
+            c.sync()
+            for g, w in zip(got, oracle.jaccard_sets(so, I, U, include_zero=include_zero)):
+                assert np.array_equal(g.cpu().numpy(), w)
+    finally:
+        c.close()
