@@ -892,22 +892,21 @@ __device__ __forceinline__ bool out_of_range(const Meta& m) {
 // in an order that puts neighbouring runs on one XCD (rings that neighbouring
 // pairs share stay in its L2).
 struct WaveShare {
-  int64_t count;  // items of this wave
-  int64_t me, n_waves;
-  int run;
-  __device__ __forceinline__ WaveShare(int64_t n, int per_wg, int w, int longest) {
+  uint32_t count;  // items of this wave
+  uint32_t me, n_waves, run;
+  __device__ __forceinline__ WaveShare(uint32_t n, int per_wg, int w, int longest) {
     const unsigned g = gridDim.x, b = blockIdx.x;
     const unsigned at = g % kStreams == 0 ? (b % kStreams) * (g / kStreams) + b / kStreams : b;
-    n_waves = uniform64((int64_t)g * per_wg);
-    me = uniform64((int64_t)at * per_wg + w);
-    run = uniform((int)share_run(n, n_waves, longest));
-    const int64_t round = n_waves * run, full = n / round;
-    count = uniform64(full * run + max((int64_t)0, min((int64_t)run, n - full * round - me * run)));
+    n_waves = uniform_u(g * (unsigned)per_wg);
+    me = uniform_u(at * (unsigned)per_wg + (unsigned)w);
+    run = uniform_u(max(1u, min((uint32_t)longest, n / (n_waves * 32u))));  // as share_run
+    const uint32_t round = n_waves * run, full = n / round, rest = n - full * round, before = me * run;
+    count = uniform_u(full * run + (rest > before ? min(run, rest - before) : 0u));
   }
   // the list index of the wave's item k
-  __device__ __forceinline__ int64_t entry(int64_t k) const {
-    const int64_t turn = (int64_t)((uint32_t)k / (uint32_t)run);
-    return (turn * n_waves + me) * run + ((uint32_t)k - (uint32_t)turn * (uint32_t)run);
+  __device__ __forceinline__ uint32_t entry(uint32_t k) const {
+    const uint32_t turn = run == 1u ? k : k / run;
+    return (turn * n_waves + me) * run + (k - turn * run);
   }
 };
 
@@ -979,8 +978,14 @@ __device__ __forceinline__ void next_call_state(const BatchArgs& a) {
     if (t < (unsigned)kStreams) st.p_next[t].v = 0;
     if (t < (unsigned)(kLptBuckets * kStreams)) st.l_next[t / kStreams][t % kStreams].v = 0;
   }
-  for (int q = 0; q < a.n_queues; ++q) {
-    unsigned long long used = max(st.q_tail[q].v, st.q_head[q].v);
+  // most calls used none: every counter in one load (one after the other, eight
+  // latencies were half of a small call's sweep)
+  const int lane = lane_id();
+  unsigned long long mine = 0;
+  if (lane < a.n_queues) mine = max(st.q_tail[lane].v, st.q_head[lane].v);
+  for (uint64_t some = ballot(mine != 0); some; some &= some - 1) {
+    const int q = __ffsll((long long)some) - 1;
+    unsigned long long used = (unsigned long long)readlane64((int64_t)mine, q);
     if (used > (unsigned long long)a.queue_cap) used = (unsigned long long)a.queue_cap;
     unsigned long long* base = a.queue + (size_t)q * a.queue_cap;
     for (unsigned long long k = (unsigned long long)blockIdx.x * blockDim.x + t; k < used;
@@ -1212,11 +1217,11 @@ k_batch_sweep(BatchArgs args) {
   const bool union_ok = direct || !(a.flags & SCCG_F_NO_UNION_TILE);
   const unsigned long long t_start = wave_stamp(a);
   next_call_state(a);
-  const WaveShare share(a.n_pairs, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
+  const WaveShare share((uint32_t)a.n_pairs, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
 #pragma unroll 1
-  for (int64_t k0 = 0; k0 < share.count; k0 += kWave) {
-    const int cnt = uniform((int)min((int64_t)kWave, share.count - k0));
-    const int64_t i = share.entry(k0 + lane);  // the lane's pair
+  for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
+    const int cnt = uniform((int)min((uint32_t)kWave, share.count - k0));
+    const int64_t i = share.entry(k0 + (uint32_t)lane);  // the lane's pair
     SweepRecs rec{0, 0, 0};
     int64_t verts = 0;
     int bucket = -1;  // of a long pair
@@ -1965,15 +1970,15 @@ k_batch_medium(BatchArgs args) {
   // claim per few entries left each wave waiting on a counter, the list, the
   // records and the rings in turn (200,000 uniform pairs, 26,000 of them here:
   // 74 us with claims)
-  const WaveShare share((int64_t)n_med, kTeamWaves, w, 1);
+  const WaveShare share(n_med, kTeamWaves, w, 1);
 #pragma unroll 1
-  for (int64_t k0 = 0; k0 < share.count; k0 += kWave) {
-    const int cnt = uniform((int)min((int64_t)kWave, share.count - k0));
+  for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
+    const int cnt = uniform((int)min((uint32_t)kWave, share.count - k0));
     // lane j: pair index and record of the wave's entry k0 + j
     int idx = 0;
     PairRec recs{0, 0, 0, 0};
     if (lane < cnt) {
-      uint32_t e = (uint32_t)share.entry(k0 + lane);
+      uint32_t e = share.entry(k0 + (uint32_t)lane);
       int64_t part = 0;
       bool found = false;
 #pragma unroll
