@@ -1015,6 +1015,9 @@ __device__ __forceinline__ void next_call_state(const BatchArgs& a) {
 //   else (W = 64): p's are 0-64, q's from 66.
 constexpr int kHalfQ = 34, kFullQ = 66;
 constexpr int kSweepSlots = 132;
+// kPairBox: after them q's tile, with a tile of nothing on both sides of it
+constexpr int kTileQ = kSweepSlots + kWave;
+constexpr int kPairBoxSlots = kSweepSlots + 3 * kWave;
 
 // The lanes whose vertex has a vertical edge to its successor, in a chunk
 // whose lanes past the ring's end hold the first vertex again: the next lane,
@@ -1121,6 +1124,31 @@ __device__ __forceinline__ uint32_t box_count(uint64_t* words, int lane, const P
              : box_count<kClip, false>(words, lane, r, np, nq, x0, y0, w, h);
 }
 
+// The parities of a ring on its own tile at (x0, y0), 64 x 64, which it does
+// not fill to the top row: lane L has column x0 + 63 - L.
+template <bool kOne>
+__device__ __forceinline__ uint64_t ring_tile(uint64_t* slots, int lane, int2 d0, int2 d1, int2 d2, int nr, int x0,
+                                              int y0) {
+  slots[lane] = 0;
+  wave_sync_lds();
+  ring_xor<kWave, uint64_t, false, kOne>(slots, d0, d1, d2, nr, x0 + kWave, y0);
+  wave_sync_lds();
+  const uint64_t m = wave_prefix_xor<false>(slots[lane]);
+  wave_sync_lds();
+  return m;
+}
+__device__ __forceinline__ uint64_t ring_tile(uint64_t* slots, int lane, const int2 (&d)[kUnionChunks], int nr, int x0,
+                                              int y0) {
+  return nr <= kWave ? ring_tile<true>(slots, lane, d[0], d[1], d[2], nr, x0, y0)
+                     : ring_tile<false>(slots, lane, d[0], d[1], d[2], nr, x0, y0);
+}
+// whether a ring's tile holds it (see ring_tile)
+__device__ __forceinline__ bool on_one_tile(const Meta& m) {
+  return !out_of_range(m) && max(side_u(m.x0, m.x1), side_u(m.y0, m.y1) + 1u) <= (uint32_t)kTile;
+}
+// pixels of a mask over the wave
+__device__ __forceinline__ uint32_t wave_pixels(uint64_t m) { return wave_sum_u32((uint32_t)__popcll(m)); }
+
 // Twice the signed area of a ring at most kMaxSide wide and tall, summed as
 // (x + x') (y' - y) over its edges with x relative to its first vertex,
 // modulo 2^32, in which it is exact.
@@ -1189,11 +1217,15 @@ __device__ __forceinline__ SweepPair sweep_pair(const SweepRecs& r, int j) {
                    (int)(n >> 16)};
 }
 
-// kPairBox: pairs whose union box exceeds a leaf tile are counted on their
-// pair box when it fits one (the same counts as the medium sweep's, without
-// loading the rings again), U from the areas; both rings' extents come
-// first, q's kept while consecutive pairs of the wave share it (a join's
-// output grouped by one side repeats it).  A separate instance keeps the
+// kPairBox: pairs whose union box exceeds a leaf tile are counted here as well
+// (the same counts as the medium sweep's, without loading the rings again), U
+// from the areas.  Each ring is pixelized on a tile of its own, and I counts
+// the AND of p's tile and q's, shifted by the distance of their corners; q's
+// ring, tile and area are kept while consecutive pairs of the wave share it (a
+// join's output grouped by one side repeats it).  A ring that no tile holds
+// takes the pair to the pair box, if that fits a tile (both rings scattered,
+// the corners right of the box all into one slot: 2.6M candidate pairs of
+// dense tiles that were all counted so took 1150 us).  A separate instance keeps the
 // extra registers off the plain sweep, which most mixes run.  kStats: the
 // work counters are kept (an instance of its own, so that the others carry no
 // test for them).
@@ -1201,12 +1233,13 @@ template <bool kPairBox, bool kStats>
 __global__ void __launch_bounds__(kSweepWaves* kWave)
     __attribute__((amdgpu_waves_per_eu(SCCG_SWEEP_WAVES_PER_EU)))
 k_batch_sweep(BatchArgs args) {
-  __shared__ __align__(16) uint64_t sweep_slots[kSweepWaves * kSweepSlots];
+  constexpr int kSlots = kPairBox ? kPairBoxSlots : kSweepSlots;
+  __shared__ __align__(16) uint64_t sweep_slots[kSweepWaves * kSlots];
   Ctx c;
   c.a = &args;
   c.stats = kStats;
   c.lane = lane_id();
-  c.slots = sweep_slots + (threadIdx.x / kWave) * kSweepSlots;
+  c.slots = sweep_slots + (threadIdx.x / kWave) * kSlots;
   c.local = nullptr;
   c.lsp = 0;
   c.home = 0;
@@ -1217,6 +1250,10 @@ k_batch_sweep(BatchArgs args) {
   const bool union_ok = direct || !(a.flags & SCCG_F_NO_UNION_TILE);
   const unsigned long long t_start = wave_stamp(a);
   next_call_state(a);
+  if (kPairBox) {
+    c.slots[kTileQ - kWave + lane] = 0;
+    c.slots[kTileQ + kWave + lane] = 0;
+  }
   const WaveShare share((uint32_t)a.n_pairs, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
 #pragma unroll 1
   for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
@@ -1262,6 +1299,8 @@ k_batch_sweep(BatchArgs args) {
     int q_n = 0;
     Meta mq{0, 0, 0, 0};
     int64_t area_q = -1;
+    bool tile_q = false;    // q's tile is in LDS
+    uint32_t pixels_q = 0;  // and holds this many
 #pragma unroll 1
     while (todo) {
       todo &= todo - 1;
@@ -1275,6 +1314,13 @@ k_batch_sweep(BatchArgs args) {
           area_q = -1;
           q_held = s.q;
           q_n = s.nq;
+          tile_q = on_one_tile(mq);
+          if (tile_q) {
+            const uint64_t m = ring_tile(c.slots, lane, cur.q, s.nq, mq.x0, mq.y0);
+            c.slots[kTileQ + lane] = m;
+            wave_sync_lds();
+            pixels_q = wave_pixels(m);
+          }
         }
         u = union_box(mp, mq);
       } else {
@@ -1297,14 +1343,54 @@ k_batch_sweep(BatchArgs args) {
         jn = __ffsll((long long)todo) - 1;
         sn = sweep_pair(rec, jn);
         ring_load(sn.p, sn.np, lane, nxt.p);
-        ring_load(sn.q, sn.nq, lane, nxt.q);
+        if (!kPairBox || sn.q != s.q || sn.nq != s.nq) ring_load(sn.q, sn.nq, lane, nxt.q);
       }
+      const bool same_q = kPairBox && sn.q == s.q && sn.nq == s.nq;
       const uint32_t uw = side_u(u.x0, u.x1), uh = side_u(u.y0, u.y1);
       // every coordinate within 2^30: none plus 2^30 above 2^31
       const uint32_t far = max(max((uint32_t)u.x0 + kMaxCoord, (uint32_t)u.x1 + kMaxCoord),
                                max((uint32_t)u.y0 + kMaxCoord, (uint32_t)u.y1 + kMaxCoord));
       const bool ok = far <= 2u * kMaxCoord;
-      if (ok && (!kPairBox || union_ok) && max(uw, uh + 1u) <= (uint32_t)kTile) {
+      if (kPairBox && tile_q && on_one_tile(mp)) {
+        const bool on_union = union_ok && max(uw, uh) <= (uint32_t)kTile;
+        if (on_union || !direct) {
+          const uint64_t m = ring_tile(c.slots, lane, cur.p, s.np, mp.x0, mp.y0);
+          // column x0 + 63 - L of p is q's lane L + dx, its row r q's row r + dy
+          // (tiles that far apart that the difference wraps have none in common)
+          const int dx = (int)((uint32_t)mq.x0 - (uint32_t)mp.x0), dy = (int)((uint32_t)mp.y0 - (uint32_t)mq.y0);
+          uint64_t t = 0;
+          if (max((uint32_t)dx + (kTile - 1), (uint32_t)dy + (kTile - 1)) <= 2u * (kTile - 1)) {
+            t = c.slots[kTileQ + dx + lane];
+            t = m & (dy >= 0 ? t >> dy : t << -dy);
+          }
+          uint32_t n, areas;
+          if (on_union) {
+            const uint32_t both = wave_sum_u32((uint32_t)__popcll(m) | (uint32_t)__popcll(t) << 16);
+            n = both >> 16;
+            areas = (both & 0xffffu) + pixels_q;
+          } else {
+            n = wave_pixels(t);
+            if (area_q < 0) area_q = ring_area(cur.q, s.nq);
+            areas = (uint32_t)(ring_area(cur.p, s.np) + area_q);
+          }
+          out_i = lane == j ? n : out_i;
+          out_u = lane == j ? areas - n : out_u;
+          finished |= 1ull << j;
+          if (kStats) {
+            const unsigned long long nv = (unsigned long long)(s.np + s.nq);
+            const Meta box = on_union ? u : pair_box(mp, mq);
+            const bool empty = box.x0 >= box.x1 || box.y0 >= box.y1;
+            const unsigned long long px = empty ? 0ull : (unsigned long long)side_u(box.x0, box.x1) * side_u(box.y0, box.y1);
+            stat_add(c, on_union ? 13 : 12, nv);
+            stat_add(c, empty ? 7 : 5, 1ull);
+            stat_add(c, 11, px);
+            stat_add(c, 1, 1ull);
+            stat_add(c, 0, 2ull * px);
+            stat_add(c, 10, nv);
+            stat_add(c, 14, (unsigned long long)s.np);
+          }
+        }
+      } else if (ok && (!kPairBox || union_ok) && max(uw, uh + 1u) <= (uint32_t)kTile) {
         const uint32_t t = box_count<false>(c.slots, lane, cur, s.np, s.nq, one, u.x0, u.y0, uw, uh);
         if (kPairBox) {
           out_i = lane == j ? t >> 17 : out_i;
@@ -1357,7 +1443,7 @@ k_batch_sweep(BatchArgs args) {
       s = sn;
       j = jn;
       ring_move(cur.p, nxt.p, s.np);
-      ring_move(cur.q, nxt.q, s.nq);
+      if (!same_q) ring_move(cur.q, nxt.q, s.nq);
     }
     if (lane_in(finished)) {
       const uint32_t n = kPairBox ? out_i : out_i >> 17;

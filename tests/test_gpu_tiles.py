@@ -111,3 +111,47 @@ def test_rings_and_boxes_of_the_union_sweep(params):
     finally:
         c.close()
     assert_exact(I, U, np.array([e[0] for e in expect]), np.array([e[1] for e in expect]), f"sweep {params}")
+
+
+@pytest.mark.parametrize("base", [(0, 0), (-(1 << 30), (1 << 30) - 70), ((1 << 30) - 64, -(1 << 30))])
+def test_rings_on_tiles_of_their_own(base):
+    """Pairs counted from one tile per ring, with sweep_pair_box = 2: tiles that
+    many columns and rows apart, rings that just fit a tile and that do not, q
+    repeated along a wave's pairs, and coordinates at the ends of their range
+    (there the far rings are held back so that they stay within it)."""
+    lo, hi = -(1 << 30), 1 << 30
+    x0, y0 = base
+    moves = (-5000, -64, -63, -62, -33, -1, 0, 1, 32, 62, 63, 64, 5000)
+
+    def placed(w, h, dx, dy):
+        return min(max(x0 + dx, lo), hi - w), min(max(y0 + dy, lo), hi - h)
+
+    ps, qs = [], []
+    for n, dx in enumerate(moves):
+        for m, dy in enumerate(moves):
+            w, h = ((64, 63), (33, 31), (64, 64), (65, 20), (63, 63))[(n + m) % 5]
+            ps.append(((w, h) + placed(w, h, dx, dy), (8, 64, 65, 129, 192)[(2 * n + m) % 5]))
+    for k, (w, h) in enumerate(((64, 63), (20, 63), (64, 64), (9, 5), (65, 63))):
+        qs.append(((w, h) + placed(w, h, 0, 0), (8, 64, 65, 129, 192)[k]))
+
+    def polygon(item, slope):
+        (w, h, x, y), verts = item
+        return _band_polygon(w, h, verts, slope, x, y)
+
+    pp, qq = [polygon(t, 1) for t in ps], [polygon(t, -1) for t in qs]
+    A = concat([_padded(band_ring(*g), t[1]) for g, t in zip(pp, ps)])
+    B = concat([_padded(band_ring(*g), t[1]) for g, t in zip(qq, qs)])
+    rp, rq = [band_rects(*g) for g in pp], [band_rects(*g) for g in qq]
+    inter = np.array([[rects_inter(a, b) for b in rq] for a in rp])
+    area_p, area_q = np.array([rects_area(r) for r in rp]), np.array([rects_area(r) for r in rq])
+    n = 60000
+    pi = (np.arange(n) * 7 % len(ps)).astype(np.int32)
+    qi = np.minimum(np.arange(n) // 11000, len(qs) - 1).astype(np.int32)
+    qi[::5] = pi[::5] % len(qs)
+    expect = inter[pi, qi]
+    c = sccg.Context(0, sweep_pair_box=2)
+    try:
+        I, U = run(c, device_workload(A, B, pi, qi), sccg.SCCG_BATCHED)
+    finally:
+        c.close()
+    assert_exact(I, U, expect, area_p[pi] + area_q[qi] - expect, f"own tiles at {base}")
