@@ -131,11 +131,14 @@ typedef struct {
                              every tile of a polygon not known to contain it (default 26).  A pair box
                              of at most 64 tiles is pixelized whole, in few passes over the rings,
                              when it has fewer tiles than this or this is at least the default      */
-  int32_t sweep_pair_box; /* BATCHED: 2 = the union sweep also counts, on its pair box MBR(p) ∩ MBR(q)
-                             (Section 3.2), a pair whose union box exceeds a 64 x 64 leaf tile but
-                             whose pair box fits one, from the rings it already holds; pays on mixes
-                             with many such pairs (densely packed sets).  1 = it leaves them to the
-                             medium sweep, which loads the rings again (default 1)                  */
+  int32_t sweep_pair_box; /* BATCHED: 2 = the union sweep also counts a pair whose union box exceeds a
+                             64 x 64 leaf tile, each ring on a tile of its own or both on their pair
+                             box MBR(p) ∩ MBR(q) (Section 3.2), from the rings it already holds; pays
+                             on mixes with many such pairs (densely packed sets).  A call with some
+                             50,000 pairs more than rings pixelizes every ring once beforehand, with
+                             536 bytes of scratch per ring (at most 2^22 rings; without that scratch
+                             it does as with fewer pairs).  1 = such pairs are left to the medium
+                             sweep, which loads the rings again (default 1)                         */
 } sccg_params;
 
 /* Create a context on HIP device `hip_device` using stream `hip_stream`

@@ -910,6 +910,33 @@ struct WaveShare {
   }
 };
 
+// A list that the workgroups of every stream appended a part of their own to,
+// taken as one: the parts' lengths, and where its entry e stands.
+struct ListParts {
+  uint32_t n[kStreams], total;
+  __device__ __forceinline__ void read(const Counter* count) {
+    total = 0;
+#pragma unroll
+    for (int st = 0; st < kStreams; ++st) {
+      n[st] = uniform_u((uint32_t)count[st].v);
+      total += n[st];
+    }
+  }
+  __device__ __forceinline__ int64_t at(uint32_t e, int64_t stream_cap) const {
+    int64_t part = 0;
+    bool found = false;
+#pragma unroll
+    for (int st = 0; st < kStreams; ++st) {
+      found = found || e < n[st];
+      if (!found) {
+        e -= n[st];
+        part += stream_cap;
+      }
+    }
+    return part + e;
+  }
+};
+
 // Both rings of a pair, as the pair arrays and the offsets give them.
 struct PairRec {
   int64_t op, oq;
@@ -1217,6 +1244,219 @@ __device__ __forceinline__ SweepPair sweep_pair(const SweepRecs& r, int j) {
                    (int)(n >> 16)};
 }
 
+// ------------------------------------------------------------- rings' tiles
+// The tiles of all rings of both sets, for a call with more pairs than rings
+// (use_ring_tiles): a ring per wave, the next one's loads in flight.  1.22M
+// rings of 96 vertices: 337 us, 930 MB of rings read and some 350 MB of tiles
+// written (3.8 TB/s).
+template <bool kStats>
+__global__ void __launch_bounds__(kSweepWaves* kWave)
+    __attribute__((amdgpu_waves_per_eu(SCCG_SWEEP_WAVES_PER_EU)))
+k_ring_tiles(BatchArgs args) {
+  constexpr int kSlots = kWave + 2;
+  __shared__ __align__(16) uint64_t tile_slots[kSweepWaves * kSlots];
+  Ctx c;
+  c.a = &args;
+  c.stats = kStats;
+  c.lane = lane_id();
+  c.slots = tile_slots + (threadIdx.x / kWave) * kSlots;
+  const BatchArgs& a = args;
+  const int lane = c.lane;
+  if (blockIdx.x == 0 && threadIdx.x < (unsigned)kStreams) a.st->t_count[threadIdx.x].v = 0;
+  const uint32_t n_a = (uint32_t)a.A.n;
+  const WaveShare share(n_a + (uint32_t)a.B.n, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
+#pragma unroll 1
+  for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
+    const int cnt = uniform((int)min((uint32_t)kWave, share.count - k0));
+    const uint32_t r = share.entry(k0 + (uint32_t)lane);  // the lane's ring
+    uint64_t at = 0;
+    uint32_t nv = 0;
+    if (lane < cnt) {
+      const bool of_b = r >= n_a;
+      const int64_t* off = of_b ? a.B.off + (r - n_a) : a.A.off + r;
+      const int64_t o = off[0], n = off[1] - o;
+      at = (uint64_t)((of_b ? a.B.xy : a.A.xy) + o);
+      nv = n >= 1 && n <= kSweepRing ? (uint32_t)n : 0u;
+    }
+    Meta box{0, 0, 0, 0};  // the lane's ring's
+    uint2 sums = make_uint2(0, 0);
+    uint64_t todo = ballot(nv > 0);
+    int2 cur[kUnionChunks], nxt[kUnionChunks];
+    int j = 0, n = 0;
+    if (todo) {
+      j = __ffsll((long long)todo) - 1;
+      n = __builtin_amdgcn_readlane((int)nv, j);
+      ring_load((ring_ptr)readlane64((int64_t)at, j), n, lane, cur);
+    }
+#pragma unroll 1
+    while (todo) {
+      todo &= todo - 1;
+      const Meta m = meta_of(wave_min4(ring_ext(cur[0], cur[1], cur[2], n)));
+      int jn = j, nn = n;
+      if (todo) {
+        jn = __ffsll((long long)todo) - 1;
+        nn = __builtin_amdgcn_readlane((int)nv, jn);
+        ring_load((ring_ptr)readlane64((int64_t)at, jn), nn, lane, nxt);
+      }
+      if (on_one_tile(m)) {
+        const uint64_t t = ring_tile(c.slots, lane, cur, n, m.x0, m.y0);
+        const uint32_t ring = (uint32_t)__builtin_amdgcn_readlane((int)r, j);
+        const int col = kWave - 1 - lane;
+        if (col < m.x1 - m.x0) a.ring_tiles[(uint64_t)ring * kTile + col] = t;
+        const uint32_t held = wave_pixels(t) | (uint32_t)n << 16, area = (uint32_t)ring_area(cur, n);
+        const bool me = lane == j;
+        box = Meta{me ? m.x0 : box.x0, me ? m.y0 : box.y0, me ? m.x1 : box.x1, me ? m.y1 : box.y1};
+        sums = make_uint2(me ? held : sums.x, me ? area : sums.y);
+        if (kStats) stat_add(c, 14, (unsigned long long)n);
+      }
+      j = jn;
+      n = nn;
+      ring_move(cur, nxt, n);
+    }
+    if (lane < cnt) {
+      *reinterpret_cast<int4*>(a.ring_box + r) = make_int4(box.x0, box.y0, box.x1, box.y1);
+      a.ring_sums[r] = sums;
+    }
+  }
+}
+
+// A pair of rings with tiles: their pair box in both tiles.
+struct TilePair {
+  uint32_t at_p, at_q;  // bytes from ring_tiles to the box's first column
+  uint32_t how;         // columns, then the shifts that bring p's and q's rows together (8 bits each)
+  uint32_t n;           // pixels in common
+};
+
+// The pixels in common of 64 pairs (of no columns: none), into their entries:
+// 16 lanes per pair, two columns per lane and step, eight pairs' columns in
+// flight while the eight before are counted.  Lanes past the box read its
+// first columns.
+__device__ __forceinline__ void count_tile_pairs(const BatchArgs& a, TilePair* pairs, int lane) {
+  typedef uint64_t cols2 __attribute__((ext_vector_type(2), aligned(8)));
+  typedef const char __attribute__((address_space(1))) * tile_ptr;
+  typedef const cols2 __attribute__((address_space(1))) * cols_ptr;
+  const tile_ptr tiles = (tile_ptr)(uint64_t)a.ring_tiles;
+  const uint32_t first = 2u * ((uint32_t)lane & 15u);
+  struct Step {
+    uint32_t how[2];
+    cols2 p[2], q[2];
+  };
+  auto load = [&](Step& d, int t, uint32_t col) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const TilePair x = pairs[4 * (t + u) + (lane >> 4)];
+      const uint32_t o = col < (x.how & 0xffu) ? col * 8u : 0u;
+      d.how[u] = x.how;
+      d.p[u] = *(cols_ptr)(tiles + (x.at_p + o));
+      d.q[u] = *(cols_ptr)(tiles + (x.at_q + o));
+    }
+  };
+  auto count = [&](const Step& d, uint32_t col, uint32_t (&n)[2]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const uint32_t w = d.how[u] & 0xffu, sp = (d.how[u] >> 8) & 0xffu, sq = d.how[u] >> 16;
+      const uint64_t m0 = (d.p[u].x << sp) & (d.q[u].x << sq), m1 = (d.p[u].y << sp) & (d.q[u].y << sq);
+      n[u] += (col < w ? (uint32_t)__popcll(m0) : 0u) + (col + 1u < w ? (uint32_t)__popcll(m1) : 0u);
+    }
+  };
+  Step cur, nxt;
+  load(cur, 0, first);
+#pragma unroll 1
+  for (int t = 0; t < kWave / 4; t += 2) {
+    load(nxt, min(t + 2, kWave / 4 - 2), first);
+    uint32_t n[2] = {0, 0};
+    count(cur, first, n);
+    if (ballot(max(cur.how[0] & 0xffu, cur.how[1] & 0xffu) > 32u)) {
+      load(cur, t, first + 32u);
+      count(cur, first + 32u, n);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t v = n[u];
+      v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, false);
+      v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, false);
+      v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, false);
+      v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, false);
+      if (first == 0) pairs[4 * (t + u) + (lane >> 4)].n = v;
+    }
+    cur = nxt;
+  }
+}
+
+// The pairs whose rings both have a tile and that are no long pairs: their
+// counts, a pair per lane up to its box, then count_tile_pairs.  2.69M pairs:
+// 210 us, waiting on the tiles (0.7 GB from HBM, 2 GB through the L2s); with
+// the loads of a step waited for at once it was 337.  The others are listed for the union sweep (where the persistent kernel's lists will be,
+// which is not written before it).  One register less than eight waves leave:
+// 64-bit shifts by a count in the last register of the allocation came out
+// with another count in some lanes.
+template <bool kStats>
+__global__ void __launch_bounds__(kSweepWaves* kWave)
+    __attribute__((amdgpu_waves_per_eu(SCCG_SWEEP_WAVES_PER_EU), amdgpu_num_vgpr(31)))
+k_tile_pairs(BatchArgs args) {
+  __shared__ TilePair pair_slots[kSweepWaves * kWave];
+  const BatchArgs& a = args;
+  const int lane = lane_id(), w = uniform((int)(threadIdx.x / kWave));
+  TilePair* pairs = pair_slots + w * kWave;
+  const bool direct = direct_union(a), union_ok = direct || !(a.flags & SCCG_F_NO_UNION_TILE);
+  const WaveShare share((uint32_t)a.n_pairs, kSweepWaves, w, a.chunk);
+#pragma unroll 1
+  for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
+    const uint32_t i = share.entry(k0 + (uint32_t)lane);
+    const bool some = lane < (int)min((uint32_t)kWave, share.count - k0);
+    bool quick = false;
+    uint32_t areas = 0;
+    TilePair mine{0, 0, 0, 0};
+    int32_t ia = -1, ib = -1;
+    if (some) {
+      ia = a.pa[i];
+      ib = a.pb[i];
+    }
+    if (ia >= 0 && ia < a.A.n && ib >= 0 && ib < a.B.n) {
+      const uint32_t rq = (uint32_t)a.A.n + (uint32_t)ib;
+      const Meta bp = load_meta(a.ring_box, ia), bq = load_meta(a.ring_box, rq);
+      const uint2 sp = a.ring_sums[ia], sq = a.ring_sums[rq];
+      const uint32_t np = sp.x >> 16, nq = sq.x >> 16;
+      const Meta un = union_box(bp, bq), box = pair_box(bp, bq);
+      const bool on_union = union_ok && max(side_u(un.x0, un.x1), side_u(un.y0, un.y1)) <= (uint32_t)kTile;
+      quick = np && nq && (int)(np + nq) < a.heavy_verts && (on_union || !direct);
+      areas = on_union ? (sp.x & 0xffffu) + (sq.x & 0xffffu) : sp.y + sq.y;
+      if (quick && box.x0 < box.x1 && box.y0 < box.y1) {
+        const int dy = bp.y0 - bq.y0;  // less than a tile's side, as the boxes meet
+        mine.at_p = ((uint32_t)ia * kTile + (uint32_t)(box.x0 - bp.x0)) * 8u;
+        mine.at_q = (rq * kTile + (uint32_t)(box.x0 - bq.x0)) * 8u;
+        mine.how = (uint32_t)(box.x1 - box.x0) | (uint32_t)max(dy, 0) << 8 | (uint32_t)max(-dy, 0) << 16;
+      }
+      if (kStats && quick) {
+        const Meta over = on_union ? un : box;
+        const bool none = over.x0 >= over.x1 || over.y0 >= over.y1;
+        const unsigned long long nv = np + nq,
+                                 px = none ? 0ull : (unsigned long long)side_u(over.x0, over.x1) * side_u(over.y0, over.y1);
+        unsigned long long* st = a.st->stats;
+        atomicAdd(st + (on_union ? 13 : 12), nv);
+        atomicAdd(st + (none ? 7 : 5), 1ull);
+        atomicAdd(st + 11, px);
+        atomicAdd(st + 1, 1ull);
+        atomicAdd(st + 0, 2ull * px);
+        atomicAdd(st + 10, nv);
+      }
+    }
+    const uint64_t left = ballot(some && !quick);
+    const int st = (int)(blockIdx.x % (unsigned)kStreams);
+    if (left) list_append(a.st->t_count[st], a.run_list + st * a.stream_cap, left, (int32_t)i, lane);
+    pairs[lane] = mine;
+    wave_sync_lds();
+    if (ballot(mine.how != 0)) count_tile_pairs(a, pairs, lane);
+    wave_sync_lds();
+    if (quick) {
+      const uint32_t n = pairs[lane].n;
+      a.inter[i] = (int64_t)n;
+      a.uni[i] = (int64_t)(areas - n);
+    }
+    wave_sync_lds();
+  }
+}
+
 // kPairBox: pairs whose union box exceeds a leaf tile are counted here as well
 // (the same counts as the medium sweep's, without loading the rings again), U
 // from the areas.  Each ring is pixelized on a tile of its own, and I counts
@@ -1224,8 +1464,10 @@ __device__ __forceinline__ SweepPair sweep_pair(const SweepRecs& r, int j) {
 // ring, tile and area are kept while consecutive pairs of the wave share it (a
 // join's output grouped by one side repeats it).  A ring that no tile holds
 // takes the pair to the pair box, if that fits a tile (both rings scattered,
-// the corners right of the box all into one slot: 2.6M candidate pairs of
-// dense tiles that were all counted so took 1150 us).  A separate instance keeps the
+// the corners right of the box all into one slot: 2.69M candidate pairs of
+// dense tiles that were all counted so took 1150 us, from own tiles 1015).
+// With ring_tiles this is left with the pairs that they do not hold (100,000 of
+// those, 50 us).  A separate instance keeps the
 // extra registers off the plain sweep, which most mixes run.  kStats: the
 // work counters are kept (an instance of its own, so that the others carry no
 // test for them).
@@ -1254,11 +1496,18 @@ k_batch_sweep(BatchArgs args) {
     c.slots[kTileQ - kWave + lane] = 0;
     c.slots[kTileQ + kWave + lane] = 0;
   }
-  const WaveShare share((uint32_t)a.n_pairs, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
+  // the pairs: all, or those that the rings' tiles left (single ones: they come
+  // in runs, and a share of several runs would take far longer than the others)
+  const bool tiled = kPairBox && a.ring_tiles != nullptr;
+  ListParts parts;
+  if (tiled) parts.read(a.st->t_count);
+  const WaveShare share(tiled ? parts.total : (uint32_t)a.n_pairs, kSweepWaves, uniform((int)(threadIdx.x / kWave)),
+                        tiled ? 1 : a.chunk);
 #pragma unroll 1
   for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
     const int cnt = uniform((int)min((uint32_t)kWave, share.count - k0));
-    const int64_t i = share.entry(k0 + (uint32_t)lane);  // the lane's pair
+    int64_t i = share.entry(k0 + (uint32_t)lane);  // the lane's pair
+    if (tiled && lane < cnt) i = a.run_list[parts.at((uint32_t)i, a.stream_cap)];
     SweepRecs rec{0, 0, 0};
     int64_t verts = 0;
     int bucket = -1;  // of a long pair
@@ -1320,6 +1569,7 @@ k_batch_sweep(BatchArgs args) {
             c.slots[kTileQ + lane] = m;
             wave_sync_lds();
             pixels_q = wave_pixels(m);
+            if (kStats) stat_add(c, 14, (unsigned long long)s.nq);
           }
         }
         u = union_box(mp, mq);
@@ -1450,9 +1700,9 @@ k_batch_sweep(BatchArgs args) {
       a.inter[i] = (int64_t)n;
       a.uni[i] = (int64_t)(kPairBox ? out_u : (out_i & 0xffffu) - n);
     }
-    const uint64_t left = ballot(medium || (sweep && !lane_in(finished)));
+    const uint64_t listed = ballot(medium || (sweep && !lane_in(finished)));
     const int st = (int)(blockIdx.x % (unsigned)kStreams);
-    if (left) list_append(a.st->m_count[st], a.m_list + st * a.stream_cap, left, (int32_t)i, lane);
+    if (listed) list_append(a.st->m_count[st], a.m_list + st * a.stream_cap, listed, (int32_t)i, lane);
     if (ballot(bucket >= 0)) {
 #pragma unroll 1
       for (int b = 0; b < kLptBuckets; ++b) {
@@ -2045,18 +2295,14 @@ k_batch_medium(BatchArgs args) {
     __syncthreads();
   }
   // the medium list, its streams' parts end to end
-  uint32_t n_part[kStreams], n_med = 0;
-#pragma unroll
-  for (int st = 0; st < kStreams; ++st) {
-    n_part[st] = uniform_u((uint32_t)a.st->m_count[st].v);
-    n_med += n_part[st];
-  }
+  ListParts parts;
+  parts.read(a.st->m_count);
   // every wave takes an equal share of the list, in runs of `run` consecutive
   // entries that interleave over the waves: the pairs are alike enough, and a
   // claim per few entries left each wave waiting on a counter, the list, the
   // records and the rings in turn (200,000 uniform pairs, 26,000 of them here:
   // 74 us with claims)
-  const WaveShare share(n_med, kTeamWaves, w, 1);
+  const WaveShare share(parts.total, kTeamWaves, w, 1);
 #pragma unroll 1
   for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
     const int cnt = uniform((int)min((uint32_t)kWave, share.count - k0));
@@ -2064,18 +2310,7 @@ k_batch_medium(BatchArgs args) {
     int idx = 0;
     PairRec recs{0, 0, 0, 0};
     if (lane < cnt) {
-      uint32_t e = share.entry(k0 + (uint32_t)lane);
-      int64_t part = 0;
-      bool found = false;
-#pragma unroll
-      for (int st = 0; st < kStreams; ++st) {
-        found = found || e < n_part[st];
-        if (!found) {
-          e -= n_part[st];
-          part += a.stream_cap;
-        }
-      }
-      idx = a.m_list[part + e];
+      idx = a.m_list[parts.at(share.entry(k0 + (uint32_t)lane), a.stream_cap)];
       recs = pair_rec(a, a.pa[idx], a.pb[idx]);
     }
     // the pair in hand (sc, rc) and the next one (sn, rn), whose loads are in
@@ -2219,6 +2454,16 @@ hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_gr
   // workgroup the device cannot hold yet waits its turn; no wave waits on
   // another)
   const dim3 b(kSweepWaves * kWave);
+  if (pair_box && a.ring_tiles) {
+    // few registers: as many workgroups as of the sweep are resident
+    if (a.stats_on) {
+      hipLaunchKernelGGL(k_ring_tiles<true>, dim3(sweep_grid), b, 0, s, a);
+      hipLaunchKernelGGL(k_tile_pairs<true>, dim3(sweep_grid), b, 0, s, a);
+    } else {
+      hipLaunchKernelGGL(k_ring_tiles<false>, dim3(sweep_grid), b, 0, s, a);
+      hipLaunchKernelGGL(k_tile_pairs<false>, dim3(sweep_grid), b, 0, s, a);
+    }
+  }
   if (pair_box && a.stats_on)
     hipLaunchKernelGGL((k_batch_sweep<true, true>), dim3(sweep_grid), b, 0, s, a);
   else if (pair_box)

@@ -38,6 +38,9 @@ struct sccg_ctx {
   int32_t* l_list = nullptr;
   Meta* hbox = nullptr;
   int64_t cap_pairs = 0;
+  // the rings' tiles, their boxes and sums (see BatchArgs)
+  unsigned char* tiles = nullptr;
+  int64_t cap_tiles = 0;  // rings
   // batched state and queues
   BatchState* st = nullptr;
   unsigned long long* queue = nullptr;
@@ -198,6 +201,31 @@ int ensure_pairs(sccg_ctx* c, int64_t n) {
   }
   c->cap_pairs = want;
   return SCCG_OK;
+}
+
+// Room for the tiles of n rings (at most kRingTilesMost), if there is any: a
+// call without does without tiles.  Nothing is allocated while the stream is
+// captured.
+bool ensure_tiles(sccg_ctx* c, int64_t n) {
+  if (n <= c->cap_tiles) return true;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return false;
+  }
+  (void)hipStreamSynchronize(c->stream);
+  drop_graph(c);
+  if (c->tiles) (void)hipFree(c->tiles);
+  c->tiles = nullptr;
+  c->cap_tiles = 0;
+  const int64_t want = std::min(n + n / 4 + 1024, kRingTilesMost);
+  if (hipMalloc((void**)&c->tiles, (size_t)ring_tiles_bytes(want)) != hipSuccess) {
+    (void)hipGetLastError();
+    c->tiles = nullptr;
+    return false;
+  }
+  c->cap_tiles = want;
+  return true;
 }
 
 // Grow a filter-stage buffer to at least n elements (waits for the stream
@@ -407,7 +435,7 @@ int sccg_destroy(sccg_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   drop_graph(c);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
-  void* ptrs[] = {c->metaA,  c->areaA,  c->metaB,  c->areaB,
+  void* ptrs[] = {c->metaA,  c->areaA,  c->metaB,  c->areaB,  c->tiles,
                   c->err,    c->cls,    c->l_list, c->hbox,    c->st,      c->queue,
                   c->plain_stats, c->wave_t,
                   c->j_bbox, c->j_grid, c->j_cell_base, c->j_sums, c->j_count, c->j_start,
@@ -442,6 +470,9 @@ int sccg_reserve(sccg_ctx* c, int64_t na, int64_t nb, int64_t np) {
   if ((r = ensure_polys(c, 0, na)) || (r = ensure_polys(c, 1, nb)) || (r = ensure_pairs(c, np)) ||
       (r = ensure_queue(c)))
     return r;
+  // tiles are only made of fewer rings than pairs
+  if (c->p.sweep_pair_box == 2 && np >= kRingTilePairs)
+    (void)ensure_tiles(c, std::min(std::min(na + nb, np), kRingTilesMost));
   return SCCG_OK;
 }
 
@@ -607,6 +638,12 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   ba.min_classify_cells = c->p.min_classify_cells;
   ba.flags = c->p.flags;
   ba.stats_on = c->stats_on;
+  const int64_t rings = A->n_polys + B->n_polys;
+  if (c->p.sweep_pair_box == 2 && use_ring_tiles(rings, n_pairs) && ensure_tiles(c, rings)) {
+    ba.ring_tiles = reinterpret_cast<uint64_t*>(c->tiles);
+    ba.ring_box = reinterpret_cast<Meta*>(c->tiles + c->cap_tiles * kTile * (int64_t)sizeof(uint64_t) + 16);
+    ba.ring_sums = reinterpret_cast<uint2*>(ba.ring_box + c->cap_tiles);
+  }
   const BatchGrids grids = batch_grids(c, n_pairs);
   place_lists(ba, grids);
   if (c->stamps_on) {
@@ -638,12 +675,12 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   }
   // the graph is keyed on every launch argument
   char key[512];
-  snprintf(key, sizeof(key), "%lld/%p/%p|%lld/%p/%p|%lld/%p/%p/%p/%p|%d/%d/%d/%d/%d/%d/%u/%d/%d/%d",
+  snprintf(key, sizeof(key), "%lld/%p/%p|%lld/%p/%p|%lld/%p/%p/%p/%p|%d/%d/%d/%d/%d/%d/%u/%d/%d/%d/%p",
            (long long)A->n_polys, (const void*)A->offsets, (const void*)A->xy,
            (long long)B->n_polys, (const void*)B->offsets, (const void*)B->xy, (long long)n_pairs,
            (const void*)pair_a, (const void*)pair_b, (void*)out_inter, (void*)out_union, ba.queue_cap, ba.n_queues,
            ba.chunk, ba.heavy_verts, ba.min_cells_to_queue, ba.min_classify_cells, ba.flags, ba.stats_on | (c->stamps_on << 1), grids.run,
-           c->p.sweep_pair_box);
+           c->p.sweep_pair_box, (void*)ba.ring_tiles);
   if (!c->gexec || c->gkey != key) {
     drop_graph(c);
     hipGraph_t g = nullptr;

@@ -118,6 +118,7 @@ struct BatchState {
   Counter m_count[kStreams];  // medium pairs listed by the sweep per stream
   Counter p_count[kLptBuckets][kStreams];  // long pairs listed by the sweep per bucket and stream
   Counter p_next[kStreams];      // per-stream claim counters over the long pairs
+  Counter t_count[kStreams];  // pairs that the rings' tiles left per stream (cleared by the call that uses it)
   Counter q_head[kMaxGrid];   // per-queue ticket counters
   Counter q_tail[kMaxGrid];   // per-queue reservation counters
   unsigned long long stats[kNumStats];
@@ -149,6 +150,13 @@ struct BatchArgs {
   int32_t min_classify_cells;    // a leaf-level split classifies its tiles only from this many cells
   uint32_t flags;                // SCCG_F_*
   int32_t stats_on;
+  // The rings' tiles (null: the call has none), A's rings, then B's: a ring's
+  // columns from its leftmost on, one 64-bit mask of rows each, the lowest row
+  // first; its box; and its pixels (with the vertices above bit 16; 0 of a
+  // ring that no tile holds) and its area.
+  uint64_t* ring_tiles;          // [rings][kTile], and one column
+  Meta* ring_box;
+  uint2* ring_sums;
   // nullable: per wave, (start, end) stamps of the device's constant-rate
   // counter, wave_cap waves per kernel: the sweep, the medium sweep, then
   // the persistent kernel
@@ -157,10 +165,25 @@ struct BatchArgs {
 };
 // kernels whose waves are stamped (see BatchArgs::wave_t)
 constexpr int kStampedKernels = 3;
-// The union sweep (sweep_grid workgroups) then the medium sweep with the long
+// The union sweep (sweep_grid workgroups; with ring_tiles, after the kernels
+// that make and use them) then the medium sweep with the long
 // pairs (medium_grid); pair_box: the union sweep also counts the pairs whose pair box fits a leaf
 // tile (else the medium sweep does).
 hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_grid, bool pair_box, hipStream_t s);
+// Whether a call of the union sweep with pair boxes pixelizes every ring once
+// beforehand.  Making a ring's tile takes what using it for a pair saves, and
+// the two launches what they save for some 50,000 (dense tiles, pairs that the
+// sweep counts against this: 2.69M pairs of 1.22M rings 1025 -> 640 us, 1.34M
+// 579 -> 537, 896,000 424 -> 502; 168,000 of 76,000 108 -> 73, 84,000 64 -> 68;
+// 41,000 of 19,000 41 -> 51).  Offsets of tiles are 32 bits.
+constexpr int64_t kRingTilesMost = int64_t(1) << 22;  // 2.2 GB of scratch
+constexpr int64_t kRingTilePairs = 49152;
+constexpr bool use_ring_tiles(int64_t rings, int64_t n_pairs) {
+  return rings <= kRingTilesMost && n_pairs >= rings + kRingTilePairs;
+}
+constexpr int64_t ring_tiles_bytes(int64_t rings) {
+  return rings * (int64_t)(kTile * sizeof(uint64_t) + sizeof(Meta) + sizeof(uint2)) + 64;
+}
 // The persistent kernel (grid workgroups).
 hipError_t launch_batch_persistent(const BatchArgs& a, int grid, int waves_per_wg, hipStream_t s);
 int batch_lds_bytes_per_wave();

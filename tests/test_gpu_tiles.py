@@ -113,9 +113,12 @@ def test_rings_and_boxes_of_the_union_sweep(params):
     assert_exact(I, U, np.array([e[0] for e in expect]), np.array([e[1] for e in expect]), f"sweep {params}")
 
 
+@pytest.mark.parametrize("n,params", [(60000, {}), (20000, {}), (60000, {"flags": sccg.SCCG_F_NO_UNION_TILE}),
+                                      (60000, {"flags": sccg.SCCG_F_NO_SEP}), (60000, {"heavy_verts": 130})])
 @pytest.mark.parametrize("base", [(0, 0), (-(1 << 30), (1 << 30) - 70), ((1 << 30) - 64, -(1 << 30))])
-def test_rings_on_tiles_of_their_own(base):
-    """Pairs counted from one tile per ring, with sweep_pair_box = 2: tiles that
+def test_rings_on_tiles_of_their_own(base, n, params):
+    """Pairs counted from one tile per ring, with sweep_pair_box = 2, the tiles
+    made pair by pair or, for many more pairs than rings, beforehand: tiles that
     many columns and rows apart, rings that just fit a tile and that do not, q
     repeated along a wave's pairs, and coordinates at the ends of their range
     (there the far rings are held back so that they stay within it)."""
@@ -144,14 +147,13 @@ def test_rings_on_tiles_of_their_own(base):
     rp, rq = [band_rects(*g) for g in pp], [band_rects(*g) for g in qq]
     inter = np.array([[rects_inter(a, b) for b in rq] for a in rp])
     area_p, area_q = np.array([rects_area(r) for r in rp]), np.array([rects_area(r) for r in rq])
-    n = 60000
     pi = (np.arange(n) * 7 % len(ps)).astype(np.int32)
-    qi = np.minimum(np.arange(n) // 11000, len(qs) - 1).astype(np.int32)
+    qi = np.minimum(np.arange(n) // (n * 11 // 60), len(qs) - 1).astype(np.int32)
     qi[::5] = pi[::5] % len(qs)
     expect = inter[pi, qi]
-    c = sccg.Context(0, sweep_pair_box=2)
+    c = sccg.Context(0, sweep_pair_box=2, **params)
     try:
         I, U = run(c, device_workload(A, B, pi, qi), sccg.SCCG_BATCHED)
     finally:
         c.close()
-    assert_exact(I, U, expect, area_p[pi] + area_q[qi] - expect, f"own tiles at {base}")
+    assert_exact(I, U, expect, area_p[pi] + area_q[qi] - expect, f"own tiles at {base}, {n} pairs, {params}")
