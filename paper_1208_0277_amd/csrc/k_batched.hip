@@ -922,6 +922,15 @@ struct ListParts {
       total += n[st];
     }
   }
+  // the lengths in the lanes from `lane` on
+  __device__ __forceinline__ void of_lanes(int length, int lane) {
+    total = 0;
+#pragma unroll
+    for (int st = 0; st < kStreams; ++st) {
+      n[st] = (uint32_t)__builtin_amdgcn_readlane(length, lane + st);
+      total += n[st];
+    }
+  }
   __device__ __forceinline__ int64_t at(uint32_t e, int64_t stream_cap) const {
     int64_t part = 0;
     bool found = false;
@@ -2266,7 +2275,17 @@ k_batch_medium(BatchArgs args) {
   // kStreams of bucket kLptBuckets - 1 - L / kStreams, from `first` on.
   constexpr int kParts = kLptBuckets * kStreams;
   const int part_b = kLptBuckets - 1 - lane / kStreams, part_s = lane % kStreams;
-  const int n_here = lane < kParts ? (int)a.st->p_count[part_b][part_s].v : 0;
+  // the lengths of these lists and, in the lanes after them, of the medium
+  // list's parts, in one load
+  static_assert(kParts + kStreams <= kWave, "a list per lane");
+  const int length = lane < kParts              ? (int)a.st->p_count[part_b][part_s].v
+                     : lane < kParts + kStreams ? (int)a.st->m_count[lane - kParts].v
+                                                : 0;
+  if (!ballot(length != 0)) {
+    wave_stamps(a, 1, t_start, lane);
+    return;  // both waves of the team
+  }
+  const int n_here = lane < kParts ? length : 0;
   int first = n_here;
 #pragma unroll
   for (int d = 1; d < kParts; d <<= 1) {
@@ -2296,7 +2315,7 @@ k_batch_medium(BatchArgs args) {
   }
   // the medium list, its streams' parts end to end
   ListParts parts;
-  parts.read(a.st->m_count);
+  parts.of_lanes(length, kParts);
   // every wave takes an equal share of the list, in runs of `run` consecutive
   // entries that interleave over the waves: the pairs are alike enough, and a
   // claim per few entries left each wave waiting on a counter, the list, the
@@ -2368,10 +2387,14 @@ __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args)
     n_list[b] = a.st->l_count[b].v;
     n_all += n_list[b];
   }
+  if (n_all == 0) {
+    wave_stamps(a, 2, t_start, c.lane);
+    return;
+  }
   // Boxes reach a queue only from splits with at least min_cells_to_queue
   // continuing cells (at most 64): otherwise no wave ever needs to look at
   // the queues.
-  const bool queues_used = n_all > 0 && !(a.flags & SCCG_F_NO_SPLIT_QUEUE) && a.min_cells_to_queue <= kWave;
+  const bool queues_used = !(a.flags & SCCG_F_NO_SPLIT_QUEUE) && a.min_cells_to_queue <= kWave;
   int bucket = kLptBuckets - 1;  // the bucket being claimed, largest first (wave-uniform)
   // streams of that bucket found exhausted (wave-uniform); as in the sweeps,
   // a wave claims only from its XCD's stream unless kRunSteal
