@@ -66,9 +66,10 @@ __device__ __forceinline__ int cell_of(int v, int o, int cell) {
 
 }  // namespace
 
+__device__ __forceinline__ int4 no_extent() { return make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN); }
 __global__ void k_join_init_sets(int64_t n_sets, int4* bbox) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < n_sets) bbox[s] = make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN);
+  if (s < n_sets) bbox[s] = no_extent();
 }
 
 // Extent of each set's A polygons.  Sets are contiguous ranges: a workgroup
@@ -76,18 +77,19 @@ __global__ void k_join_init_sets(int64_t n_sets, int4* bbox) {
 // (the atomics on one set's extent take turns: 600,000 polygons of 16 sets took
 // 250 us with four for every 64 polygons, 55 for every 256, 23 for every 1024).
 constexpr int kBoxRun = 4096;
-__global__ void __launch_bounds__(256) k_join_bbox(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
-                                                   int4* bbox) {
-  __shared__ int4 sh[4];
+// add(s, box): by thread 0, for each set that the workgroup's polygons [a0, a1)
+// belong to.
+template <typename F>
+__device__ __forceinline__ void run_extents(int64_t a0, int64_t a1, int64_t n_a, const Meta* metaA, const int64_t* a_off,
+                                            int64_t n_sets, int4* sh, F add) {
   const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
-  const int64_t a0 = (int64_t)blockIdx.x * kBoxRun, a1 = min(a0 + kBoxRun, A.n);
   int64_t a = a0;
   while (a < a1) {
     // the polygons of one set from a on (all threads at the same a)
     const int64_t s = uniform64(set_of(a_off, n_sets, a));
     if (s < 0) {
       // outside every set: skip to the first set, or to the end
-      const int64_t first = uniform64(n_sets > 0 ? a_off[0] : A.n);
+      const int64_t first = uniform64(n_sets > 0 ? a_off[0] : n_a);
       if (a >= first) break;
       a = min(first, a1);
       continue;
@@ -110,23 +112,30 @@ __global__ void __launch_bounds__(256) k_join_bbox(Polys A, const Meta* metaA, c
       int4 m = sh[0];
       for (int k = 1; k < 4; ++k)
         m = make_int4(min(m.x, sh[k].x), min(m.y, sh[k].y), max(m.z, sh[k].z), max(m.w, sh[k].w));
-      if (m.x < m.z) {
-        atomicMin(&bbox[s].x, m.x);
-        atomicMin(&bbox[s].y, m.y);
-        atomicMax(&bbox[s].z, m.z);
-        atomicMax(&bbox[s].w, m.w);
-      }
+      if (m.x < m.z) add(s, m);
     }
     __syncthreads();
     a = end;
   }
 }
+__global__ void __launch_bounds__(256) k_join_bbox(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
+                                                   int4* bbox) {
+  __shared__ int4 sh[4];
+  const int64_t a0 = (int64_t)blockIdx.x * kBoxRun;
+  run_extents(a0, min(a0 + kBoxRun, A.n), A.n, metaA, a_off, n_sets, sh, [&](int64_t s, const int4& m) {
+    atomicMin(&bbox[s].x, m.x);
+    atomicMin(&bbox[s].y, m.y);
+    atomicMax(&bbox[s].z, m.z);
+    atomicMax(&bbox[s].w, m.w);
+  });
+}
 
 // ------------------------------------------------------- exclusive scans
-// exclusive prefix of v over the threads of a block (kScanThreads of them)
+// exclusive prefix of v over the threads of a block (kThreads of them; sh: one per wave)
 constexpr int kScanThreads = 256;
 constexpr int kScanPer = 8;
 constexpr int kScanBlock = kScanThreads * kScanPer;
+template <int kThreads = kScanThreads>
 __device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh, int64_t* total) {
   const int t = threadIdx.x, lane = t % kWave, w = t / kWave;
   int64_t x = v;
@@ -138,7 +147,7 @@ __device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh, int64
   if (lane == kWave - 1) sh[w] = x;
   __syncthreads();
   int64_t before = 0, all = 0;
-  for (int k = 0; k < kScanThreads / kWave; ++k) {
+  for (int k = 0; k < kThreads / kWave; ++k) {
     before += k < w ? sh[k] : 0;
     all += sh[k];
   }
@@ -149,9 +158,8 @@ __device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh, int64
 
 // Grid of each set: origin, columns, rows; base[s] = cells of the sets before
 // s, base[n_sets] = all of them.  One block.
-__global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, const int4* bbox, int cell, int4* grid,
-                                                            int64_t* base, uint32_t* err) {
-  __shared__ int64_t sh[kScanThreads / kWave];
+__device__ __forceinline__ void set_grids(int64_t n_sets, const int4* bbox, int cell, int4* grid, int64_t* base,
+                                          uint32_t* err, int64_t* sh) {
   int64_t run = 0;
   for (int64_t s0 = 0; s0 < n_sets; s0 += kScanThreads) {
     const int64_t s = s0 + threadIdx.x;
@@ -177,6 +185,28 @@ __global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, cons
     run += total;
   }
   if (threadIdx.x == 0) base[n_sets] = run;
+}
+__global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, const int4* bbox, int cell, int4* grid,
+                                                            int64_t* base, uint32_t* err) {
+  __shared__ int64_t sh[kScanThreads / kWave];
+  set_grids(n_sets, bbox, cell, grid, base, err, sh);
+}
+
+// A single tile's comparison is bound by its launches, a dozen of 2 to 5 us
+// each with one or two more between them; what a workgroup does in about the
+// time of a launch is done by one: the extents and grids of up to kFewSets sets
+// of up to kBoxRun polygons in all, and the scans of up to kOneScan counts.
+constexpr int kFewSets = 256;
+__global__ void __launch_bounds__(kScanThreads) k_join_grid_few(Polys A, const Meta* metaA, const int64_t* a_off,
+                                                                int64_t n_sets, int cell, int4* grid, int64_t* base,
+                                                                uint32_t* err) {
+  __shared__ int4 boxes[kFewSets], sh4[4];
+  __shared__ int64_t sh[kScanThreads / kWave];
+  for (int64_t s = threadIdx.x; s < n_sets; s += kScanThreads) boxes[s] = no_extent();
+  __syncthreads();
+  run_extents(0, A.n, A.n, metaA, a_off, n_sets, sh4, [&](int64_t s, const int4& m) { boxes[s] = m; });
+  __syncthreads();
+  set_grids(n_sets, boxes, cell, grid, base, err, sh);
 }
 
 // out[i] = sum of in[0 .. i) for i <= n, n read from device memory when n_ptr
@@ -228,7 +258,45 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_write(int32_t* in, int64_
     run += v[k];
   }
 }
+// The whole scan by one workgroup.
+constexpr int kOneThreads = 1024;
+constexpr int64_t kOneScan = 2 * kOneThreads * kScanPer;
+template <bool kClear>
+__global__ void __launch_bounds__(kOneThreads) k_scan_one(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room,
+                                                          int64_t* out) {
+  __shared__ int64_t sh[kOneThreads / kWave];
+  n = scan_size(n, n_ptr, room);
+  int64_t run = 0;
+  for (int64_t b0 = 0; b0 <= n; b0 += kOneThreads * kScanPer) {
+    const int64_t i0 = b0 + (int64_t)threadIdx.x * kScanPer;
+    int32_t v[kScanPer];
+    int64_t tot = 0, total;
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      v[k] = i0 + k < n ? in[i0 + k] : 0;
+      tot += v[k];
+    }
+    int64_t at = run + block_exclusive<kOneThreads>(tot, sh, &total);
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      if (i0 + k <= n) out[i0 + k] = at;
+      if (kClear && i0 + k < n) in[i0 + k] = 0;
+      at += v[k];
+    }
+    run += total;
+  }
+}
 int64_t scan_scratch(int64_t n) { return n / kScanBlock + 1; }
+template <bool kClear>
+void launch_scan(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room, int64_t* sums, int64_t* out, hipStream_t s) {
+  if (room <= kOneScan) {
+    hipLaunchKernelGGL(k_scan_one<kClear>, dim3(1), dim3(kOneThreads), 0, s, in, n, n_ptr, room, out);
+    return;
+  }
+  const dim3 g((unsigned)scan_scratch(room)), b(kScanThreads);
+  hipLaunchKernelGGL(k_scan_totals, g, b, 0, s, in, n, n_ptr, room, sums);
+  hipLaunchKernelGGL(k_scan_write<kClear>, g, b, 0, s, in, n, n_ptr, room, sums, out);
+}
 
 // ------------------------------------------------------------------- entries
 // Cells of an MBR clamped to a grid: [cx0, cx1] x [cy0, cy1] (empty if cx0 > cx1).
@@ -355,10 +423,11 @@ __global__ void __launch_bounds__(256) k_join_write(JoinArgs a, const int32_t* b
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n_cells = a.cell_base[a.n_sets];
   const bool fits = join_fits(a);
-  if (t == 0) {
+  if (t == 0) {  // in host memory
     sizes[0] = n_cells;
     sizes[1] = n_cells <= a.cell_room ? a.start[n_cells] : 0;
     sizes[2] = fits ? b_start[a.B.n] : 0;
+    __threadfence_system();
   }
   if (!fits) return;
   if (t <= a.n_sets) out_set_off[t] = b_start[min(max(a.b_off[t], (int64_t)0), a.B.n)];
@@ -403,19 +472,21 @@ static unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 hipError_t launch_join(const JoinLaunch& l, hipStream_t s) {
   const Polys &A = l.A, &B = l.B;
-  hipLaunchKernelGGL(k_join_init_sets, dim3(blocks_for(l.n_sets)), dim3(256), 0, s, l.n_sets, l.bbox);
-  if (A.n > 0)
-    hipLaunchKernelGGL(k_join_bbox, dim3((unsigned)((A.n + kBoxRun - 1) / kBoxRun)), dim3(256), 0, s, A,
-                       l.metaA, l.a_off, l.n_sets, l.bbox);
-  hipLaunchKernelGGL(k_join_grid, dim3(1), dim3(kScanThreads), 0, s, l.n_sets, l.bbox, l.cell, l.grid, l.cell_base,
-                     l.err);
+  if (A.n <= kBoxRun && l.n_sets <= kFewSets) {
+    hipLaunchKernelGGL(k_join_grid_few, dim3(1), dim3(kScanThreads), 0, s, A, l.metaA, l.a_off, l.n_sets, l.cell, l.grid,
+                       l.cell_base, l.err);
+  } else {
+    hipLaunchKernelGGL(k_join_init_sets, dim3(blocks_for(l.n_sets)), dim3(256), 0, s, l.n_sets, l.bbox);
+    if (A.n > 0)
+      hipLaunchKernelGGL(k_join_bbox, dim3((unsigned)((A.n + kBoxRun - 1) / kBoxRun)), dim3(256), 0, s, A, l.metaA,
+                         l.a_off, l.n_sets, l.bbox);
+    hipLaunchKernelGGL(k_join_grid, dim3(1), dim3(kScanThreads), 0, s, l.n_sets, l.bbox, l.cell, l.grid, l.cell_base,
+                       l.err);
+  }
   if (A.n > 0)
     hipLaunchKernelGGL(k_join_cells<false>, dim3(blocks_for(A.n)), dim3(256), 0, s, A, l.metaA, l.a_off, l.n_sets,
                        l.grid, l.cell_base, l.cell, l.cell_room, l.count, nullptr, 0, nullptr);
-  const int64_t* n_cells = l.cell_base + l.n_sets;
-  const dim3 cb((unsigned)scan_scratch(l.cell_room)), bb((unsigned)scan_scratch(B.n)), st(kScanThreads);
-  hipLaunchKernelGGL(k_scan_totals, cb, st, 0, s, l.count, 0, n_cells, l.cell_room, l.sums);
-  hipLaunchKernelGGL(k_scan_write<true>, cb, st, 0, s, l.count, 0, n_cells, l.cell_room, l.sums, l.start);
+  launch_scan<true>(l.count, 0, l.cell_base + l.n_sets, l.cell_room, l.sums, l.start, s);
   if (A.n > 0)
     hipLaunchKernelGGL(k_join_cells<true>, dim3(blocks_for(A.n)), dim3(256), 0, s, A, l.metaA, l.a_off, l.n_sets, l.grid,
                        l.cell_base, l.cell, l.cell_room, l.count, l.start, l.list_room, l.list);
@@ -423,8 +494,7 @@ hipError_t launch_join(const JoinLaunch& l, hipStream_t s) {
                    l.list_room};
   hipLaunchKernelGGL(k_join_count, dim3(std::max(1u, blocks_for(B.n * kCountLanes))), dim3(256), 0, s, j, l.b_count,
                      l.found, l.count);
-  hipLaunchKernelGGL(k_scan_totals, bb, st, 0, s, l.b_count, B.n, (const int64_t*)nullptr, B.n, l.sums);
-  hipLaunchKernelGGL(k_scan_write<false>, bb, st, 0, s, l.b_count, B.n, (const int64_t*)nullptr, B.n, l.sums, l.b_start);
+  launch_scan<false>(l.b_count, B.n, nullptr, B.n, l.sums, l.b_start, s);
   const int64_t threads = std::max(B.n * kFound, l.n_sets + 1);
   hipLaunchKernelGGL(k_join_write, dim3(blocks_for(threads)), dim3(256), 0, s, j, l.b_count, l.b_start, l.found, l.cap,
                      l.out_pa, l.out_pb, l.out_set_off, l.sizes);

@@ -69,8 +69,8 @@ struct sccg_ctx {
   int32_t* j_bcount = nullptr;
   int64_t* j_bstart = nullptr;
   int32_t* j_found = nullptr;
-  int64_t* j_sizes = nullptr;
-  int64_t* j_host = nullptr;                     // the sizes, in pinned host memory
+  int64_t* j_host = nullptr;                     // the sizes a join found, in pinned host memory
+  int64_t* j_sizes = nullptr;                    // its device address
   int64_t j_cells_seen = 0, j_entries_seen = 0;  // the most that a call had
   bool j_dirty = true;                           // j_count may hold counts of a call that did not end
   unsigned char* j_acc = nullptr;  // the waves' sums of sccg_jaccard_sets
@@ -439,7 +439,7 @@ int sccg_destroy(sccg_ctx* c) {
                   c->err,    c->cls,    c->l_list, c->hbox,    c->st,      c->queue,
                   c->plain_stats, c->wave_t,
                   c->j_bbox, c->j_grid, c->j_cell_base, c->j_sums, c->j_count, c->j_start,
-                  c->j_list, c->j_bcount, c->j_bstart, c->j_found, c->j_sizes, c->j_acc};
+                  c->j_list, c->j_bcount, c->j_bstart, c->j_found, c->j_acc};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   if (c->j_host) (void)hipHostFree(c->j_host);
@@ -821,12 +821,14 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
       (r = need(c, &c->j_cell_base, c->j_cap[2], n_sets + 1, "join cell offsets")) ||
       (r = need(c, &c->j_bcount, c->j_cap[3], B->n_polys, "pair counts")) ||
       (r = need(c, &c->j_bstart, c->j_cap[4], B->n_polys + 1, "pair starts")) ||
-      (r = need(c, &c->j_found, c->j_cap[5], join_found_room(B->n_polys), "pairs found")) ||
-      (r = need(c, &c->j_sizes, c->j_cap[6], 3, "join sizes")))
+      (r = need(c, &c->j_found, c->j_cap[5], join_found_room(B->n_polys), "pairs found")))
     return r;
-  if (!c->j_host && hipHostMalloc((void**)&c->j_host, 3 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
-    c->j_host = nullptr;
-    return fail(c, SCCG_E_NOMEM, "hipHostMalloc(join sizes)");
+  if (!c->j_sizes) {
+    if (!c->j_host && hipHostMalloc((void**)&c->j_host, 3 * sizeof(int64_t), hipHostMallocMapped) != hipSuccess) {
+      c->j_host = nullptr;
+      return fail(c, SCCG_E_NOMEM, "hipHostMalloc(join sizes)");
+    }
+    HIP_TRY(c, hipHostGetDevicePointer((void**)&c->j_sizes, c->j_host, 0));
   }
   // Room for the cells and for the entries in them, which are only known when
   // the kernels have run: what earlier calls took, or a first guess (objects
@@ -872,7 +874,6 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
     l.err = c->err;
     c->j_dirty = true;
     if ((e = launch_join(l, c->stream)) != hipSuccess) return hip_fail(c, e, "join");
-    HIP_TRY(c, hipMemcpyAsync(c->j_host, c->j_sizes, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     const int64_t n_cells = c->j_host[0], n_entries = c->j_host[1];
     if (n_cells <= cells && n_entries <= c->j_cap[9]) {

@@ -89,3 +89,38 @@ def test_jaccard_over_wave_ranges(n_pairs, include_zero):
                 assert np.array_equal(g.cpu().numpy(), w)
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("n_a,n_b,sets", [(1, 1, 1), (4095, 300, 256), (4096, 16383, 3), (4097, 16384, 256), (4096, 16385, 257),
+                                          (300, 8192, 2), (9000, 40000, 1)])
+def test_small_joins(n_a, n_b, sets):
+    """Around the sizes that one workgroup does by itself: the A polygons and
+    sets of the grids, the counts of the scans.  B polygons are small and meet
+    one or two squares of a row of A's, none, or, in empty sets, have none."""
+    import torch
+    rng = np.random.default_rng(n_a + n_b)
+    ao = np.sort(rng.integers(0, n_a + 1, sets + 1)).astype(np.int64)
+    bo = np.sort(rng.integers(0, n_b + 1, sets + 1)).astype(np.int64)
+    ao[0], ao[-1], bo[0], bo[-1] = 0, n_a, 0, n_b
+    row = int(np.ceil(np.sqrt(n_a / sets)))
+    ra, rb = [], []
+    for s in range(sets):
+        for k in range(int(ao[s + 1] - ao[s])):
+            x, y = 20 * (k % row) - 300, 20 * (k // row) - 77 * s
+            ra.append(rect_ring((x, y, x + 12, y + 12)))
+        m = max(1, int(ao[s + 1] - ao[s]))
+        for k in rng.integers(0, m, int(bo[s + 1] - bo[s])):
+            x, y = 20 * (int(k) % row) - 300 + int(rng.integers(-3, 18)), 20 * (int(k) // row) - 77 * s + int(rng.integers(0, 12))
+            rb.append(rect_ring((x, y, x + 9, y + 7)))
+    A, B = concat(ra), concat(rb)
+    c = sccg.Context(0)
+    try:
+        dA, dB = sccg.DevicePolys.from_host(A.off, A.xy), sccg.DevicePolys.from_host(B.off, B.xy)
+        want = oracle.join_sets(A, B, ao, bo)
+        for _ in range(2):
+            got = c.join_sets(dA, dB, torch.from_numpy(ao).cuda(), torch.from_numpy(bo).cuda())
+            c.sync()
+            for g, w in zip(got, want):
+                assert np.array_equal(g.cpu().numpy(), w)
+    finally:
+        c.close()
