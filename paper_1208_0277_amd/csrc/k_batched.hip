@@ -2017,12 +2017,21 @@ struct TeamRing {
   int32_t nv, bad;
 };
 
-// A pair left to the persistent kernel (one lane).
-__device__ __forceinline__ void list_run(const BatchArgs& a, int64_t i, int64_t verts, const Meta& box) {
-  const int bk = lpt_bucket(a, verts);
-  const unsigned long long k = atomicAdd(&a.st->l_count[bk].v, 1ull);
-  a.run_list[(int64_t)bk * a.n_pairs + (int64_t)k] = (int32_t)i;
+// List the pairs i of the lanes `m`, of `verts` vertices each, for the
+// persistent kernel: one append per bucket (one per pair, on one counter, took
+// 25 ns each: 400 us for 16,000 pairs that were all listed).
+__device__ __forceinline__ void list_run(const BatchArgs& a, uint64_t m, int32_t i, int64_t verts, int lane) {
+  const int bucket = lpt_bucket(a, verts);
+#pragma unroll 1
+  for (int b = 0; b < kLptBuckets; ++b) {
+    const uint64_t mb = m & ballot(bucket == b);
+    if (mb) list_append(a.st->l_count[b], a.run_list + (int64_t)b * a.n_pairs, mb, i, lane);
+  }
+}
+// A listed pair's box and class (by one lane).
+__device__ __forceinline__ void listed_pair(const BatchArgs& a, int64_t i, const Meta& box, uint8_t cls) {
   *reinterpret_cast<int4*>(a.hbox + i) = make_int4(box.x0, box.y0, box.x1, box.y1);
+  a.cls[i] = cls;
 }
 
 // Every chunk of both rings of a medium pair (clamped to each ring's last
@@ -2065,7 +2074,8 @@ __device__ __forceinline__ uint8_t pair_class(Ctx& c, const Meta& mp, const Meta
   return small ? kClsSmall : kClsLarge;
 }
 
-__device__ __forceinline__ void medium_one(Ctx& c, const PairRec& s, const PairRegs<kMediumChunks>& r, int64_t i) {
+// Returns whether the pair is to be listed for the persistent kernel.
+__device__ __forceinline__ bool medium_one(Ctx& c, const PairRec& s, const PairRegs<kMediumChunks>& r, int64_t i) {
   const BatchArgs& a = *c.a;
   const int lane = c.lane;
   Meta mp{INT_MAX, INT_MAX, INT_MIN, INT_MIN}, mq = mp, box;
@@ -2133,16 +2143,15 @@ __device__ __forceinline__ void medium_one(Ctx& c, const PairRec& s, const PairR
   if (lane == 0) {
     a.inter[i] = I;
     a.uni[i] = U - I;
-    if (listed) {
-      list_run(a, i, (int64_t)s.np + s.nq, box);
-      a.cls[i] = cls;
-    }
+    if (listed) listed_pair(a, i, box, cls);
   }
+  return listed;
 }
 
-// One long pair, both waves of the team (wave w has ring w).
+// One long pair, both waves of the team (wave w has ring w).  Returns as
+// medium_one does.
 template <bool kStats>
-__device__ __forceinline__ void long_one(Ctx& c, int64_t i, int w, uint64_t* team_slots, TeamRing* ex) {
+__device__ __forceinline__ bool long_one(Ctx& c, int64_t i, int w, uint64_t* team_slots, TeamRing* ex) {
   const BatchArgs& a = *c.a;
   const int lane = c.lane;
   const int2* xy = w ? a.B.xy : a.A.xy;
@@ -2236,11 +2245,9 @@ __device__ __forceinline__ void long_one(Ctx& c, int64_t i, int w, uint64_t* tea
   if (w == 0 && lane == 0) {
     a.inter[i] = (int64_t)n;
     a.uni[i] = U - (int64_t)n;
-    if (listed) {
-      list_run(a, i, verts, box);
-      a.cls[i] = cls;
-    }
+    if (listed) listed_pair(a, i, box, cls);
   }
+  return listed;
 }
 
 template <bool kStats>
@@ -2295,6 +2302,19 @@ k_batch_medium(BatchArgs args) {
   const int64_t n_long = __builtin_amdgcn_readlane(first, kParts - 1);
   first -= n_here;
   if (n_long > 0) {
+    // wave 0's lanes keep the pairs to be listed
+    int32_t listed = 0;
+    int n_listed = 0;
+    auto list_long = [&]() {
+      const bool mine = lane < n_listed;
+      int64_t verts = 0;
+      if (mine) {
+        const PairRec r = pair_rec(a, a.pa[listed], a.pb[listed]);
+        verts = (int64_t)r.np + r.nq;
+      }
+      list_run(a, ballot(mine), listed, verts, lane);
+      n_listed = 0;
+    };
     int64_t next = -1;
     if (w == 0) next = claim_chunk(a.st->p_next, n_long, 1, c.xcd, lane, p_empty);
 #pragma unroll 1
@@ -2309,8 +2329,12 @@ k_batch_medium(BatchArgs args) {
       const int part = kWave - 1 - __clzll((long long)ballot(lane < kParts && first <= (int)k));
       const int64_t at = (int64_t)((kLptBuckets - 1 - part / kStreams) * kStreams + part % kStreams) * a.stream_cap;
       const int64_t i = a.l_list[at + (k - __builtin_amdgcn_readlane(first, part))];
-      long_one<kStats>(c, uniform64(i), w, team_slots, ex[it]);
+      if (long_one<kStats>(c, uniform64(i), w, team_slots, ex[it]) && w == 0) {
+        listed = lane == n_listed ? (int32_t)i : listed;
+        if (++n_listed == kWave) list_long();
+      }
     }
+    if (n_listed > 0) list_long();
     __syncthreads();
   }
   // the medium list, its streams' parts end to end
@@ -2338,15 +2362,17 @@ k_batch_medium(BatchArgs args) {
     // for the pair in hand's loads
     PairRegs<kMediumChunks> rc, rn;
     PairRec sc = rec_of_lane(recs, 0);
+    uint64_t listed = 0;
     medium_load(a, sc, lane, rc);
 #pragma unroll 1
     for (int j = 0; j < cnt; ++j) {
       const PairRec sn = j + 1 < cnt ? rec_of_lane(recs, j + 1) : PairRec{0, 0, 0, 0};
       medium_load(a, sn, lane, rn);
-      medium_one(c, sc, rc, (int64_t)__builtin_amdgcn_readlane(idx, j));
+      if (medium_one(c, sc, rc, (int64_t)__builtin_amdgcn_readlane(idx, j))) listed |= 1ull << j;
       sc = sn;
       rc = rn;
     }
+    if (listed) list_run(a, listed, idx, (int64_t)recs.np + recs.nq, lane);
   }
   wave_stamps(a, 1, t_start, lane);
 }
