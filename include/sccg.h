@@ -136,7 +136,7 @@ typedef struct {
                              box MBR(p) ∩ MBR(q) (Section 3.2), from the rings it already holds; pays
                              on mixes with many such pairs (densely packed sets).  A call with some
                              50,000 pairs more than rings pixelizes every ring once beforehand, with
-                             536 bytes of scratch per ring (at most 2^22 rings; without that scratch
+                             536 bytes of scratch per ring (fewer than 2^23 rings; without that scratch
                              it does as with fewer pairs).  1 = such pairs are left to the medium
                              sweep, which loads the rings again (default 1)                         */
 } sccg_params;

@@ -176,7 +176,7 @@ hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_gr
 // sweep counts against this: 2.69M pairs of 1.22M rings 1025 -> 640 us, 1.34M
 // 579 -> 537, 896,000 424 -> 502; 168,000 of 76,000 108 -> 73, 84,000 64 -> 68;
 // 41,000 of 19,000 41 -> 51).  Offsets of tiles are 32 bits.
-constexpr int64_t kRingTilesMost = int64_t(1) << 22;  // 2.2 GB of scratch
+constexpr int64_t kRingTilesMost = (int64_t(1) << 23) - 1;  // 4.5 GB of scratch
 constexpr int64_t kRingTilePairs = 49152;
 constexpr bool use_ring_tiles(int64_t rings, int64_t n_pairs) {
   return rings <= kRingTilesMost && n_pairs >= rings + kRingTilePairs;
