@@ -61,15 +61,15 @@ extern "C" {
  * sub-box per thread placed by Lemma 1 against every edge, one pixel per
  * thread at the leaves tested against every edge. */
 #define SCCG_PLAIN 0u
-/* BATCHED: a sweep over all pairs, then one persistent launch over the
- * pairs whose box is larger than a leaf tile, with a device task queue that
- * spreads the hovering sampling boxes of large pairs over workgroups.
- * Leaves are bit-sliced 64x64-pixel tiles: a prefix XOR over the columns of
- * per-column row masks gives the crossing parities.  The sweep counts a
- * pair whose MBR union fits one tile directly there (every ring vertex with
- * one vertical edge XORs the rows at or above it into the column left of
- * it); the persistent kernel classifies boxes edge-parallel and XORs each
- * band edge's row mask into one column slot. */
+/* BATCHED: three launches.  A sweep over all pairs counts those of rings of at
+ * most 192 vertices whose MBR union fits one leaf tile directly there; a second
+ * kernel takes the longer rings and the larger boxes, pixelizing pair boxes of
+ * up to 64 leaf tiles whole; a persistent kernel takes what is left, with a
+ * device task queue that spreads the hovering sampling boxes of large pairs
+ * over workgroups.  Leaves are bit-sliced 64x64-pixel tiles: a prefix XOR over
+ * the columns of per-column row masks gives the crossing parities (every ring
+ * vertex with one vertical edge XORs the rows at or above it into the column
+ * left of it); the persistent kernel classifies boxes edge-parallel. */
 #define SCCG_BATCHED 1u
 
 /* sccg_params.flags (ablation switches; none changes any count) */
@@ -87,7 +87,7 @@ extern "C" {
 #define SCCG_F_PIXEL_ONLY 0x10u
 #define SCCG_F_NO_SEP 0x20u
 /* batched: by default a pair (not shared through the queue, rings of at most
- * 128 vertices) whose MBR(p) ∪ MBR(q) fits one 64 x 64 leaf tile is counted
+ * 192 vertices) whose MBR(p) ∪ MBR(q) fits one 64 x 64 leaf tile is counted
  * directly on that tile: the intersection and the union are popcounts of the
  * AND and the OR of the two row masks, so the ring areas are not needed.
  * This flag turns that off (every pair derives U from the areas). */

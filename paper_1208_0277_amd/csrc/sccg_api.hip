@@ -242,8 +242,9 @@ int need(sccg_ctx* c, T** ptr, int64_t& cap, int64_t n, const char* what) {
 
 int ensure_queue(sccg_ctx* c) {
   const int64_t want = (int64_t)c->p.n_queues * c->p.queue_cap;
-  // The sweep of a call clears the slots the previous call used, found from that call's head and tail counters in that call's layout, so
-  // the slots are cleared here whenever the layout changes.
+  // The sweep of a call clears the slots the previous call used, found from
+  // that call's head and tail counters in that call's layout, so the slots are
+  // cleared here whenever the layout changes.
   if (c->queue && c->queue_slots == want && c->queue_nq == c->p.n_queues && c->queue_per == c->p.queue_cap)
     return SCCG_OK;
   (void)hipStreamSynchronize(c->stream);

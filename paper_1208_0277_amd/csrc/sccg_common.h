@@ -137,7 +137,7 @@ struct BatchArgs {
   // long, which the workgroups blockIdx % kStreams append to
   int32_t* l_list;               // [kLptBuckets][kStreams][stream_cap] long pairs
   int32_t* m_list;               // [kStreams][stream_cap] medium pairs
-  int64_t stream_cap;            // see sweep_stream_cap
+  int64_t stream_cap;            // see stream_cap_of
   int32_t* run_list;             // [kLptBuckets][n_pairs] pairs listed for the persistent kernel
   Meta* hbox;                    // [n_pairs] pair box of a listed pair (by pair index)
   BatchState* st;
@@ -166,16 +166,17 @@ struct BatchArgs {
 // kernels whose waves are stamped (see BatchArgs::wave_t)
 constexpr int kStampedKernels = 3;
 // The union sweep (sweep_grid workgroups; with ring_tiles, after the kernels
-// that make and use them) then the medium sweep with the long
-// pairs (medium_grid); pair_box: the union sweep also counts the pairs whose pair box fits a leaf
-// tile (else the medium sweep does).
+// that make and use them), then the medium sweep with the long pairs
+// (medium_grid); pair_box: the union sweep also counts the pairs whose pair box
+// fits a leaf tile (else the medium sweep does).
 hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_grid, bool pair_box, hipStream_t s);
 // Whether a call of the union sweep with pair boxes pixelizes every ring once
-// beforehand.  Making a ring's tile takes what using it for a pair saves, and
-// the two launches what they save for some 50,000 (dense tiles, pairs that the
-// sweep counts against this: 2.69M pairs of 1.22M rings 1025 -> 640 us, 1.34M
+// beforehand.  Making a ring's tile takes about what using it for a pair saves,
+// and the two launches what they save for some 50,000 (dense tiles, the sweep
+// alone against this: 2.69M pairs of 1.22M rings 1025 -> 640 us, 1.34M
 // 579 -> 537, 896,000 424 -> 502; 168,000 of 76,000 108 -> 73, 84,000 64 -> 68;
-// 41,000 of 19,000 41 -> 51).  Offsets of tiles are 32 bits.
+// 41,000 of 19,000 41 -> 51; 9.5M of 4.8M with their set sums 3.50 -> 2.21 ms).
+// Offsets of tiles are 32 bits.
 constexpr int64_t kRingTilesMost = (int64_t(1) << 23) - 1;  // 4.5 GB of scratch
 constexpr int64_t kRingTilePairs = 49152;
 constexpr bool use_ring_tiles(int64_t rings, int64_t n_pairs) {
