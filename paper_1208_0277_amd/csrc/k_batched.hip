@@ -1273,6 +1273,7 @@ k_ring_tiles(BatchArgs args) {
   const int lane = c.lane;
   if (blockIdx.x == 0 && threadIdx.x < (unsigned)kStreams) a.st->t_count[threadIdx.x].v = 0;
   const uint32_t n_a = (uint32_t)a.A.n;
+  const int64_t end_a = a.A.off[a.A.n], end_b = a.B.off[a.B.n];
   const WaveShare share(n_a + (uint32_t)a.B.n, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
 #pragma unroll 1
   for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {
@@ -1285,7 +1286,9 @@ k_ring_tiles(BatchArgs args) {
       const int64_t* off = of_b ? a.B.off + (r - n_a) : a.A.off + r;
       const int64_t o = off[0], n = off[1] - o;
       at = (uint64_t)((of_b ? a.B.xy : a.A.xy) + o);
-      nv = n >= 1 && n <= kSweepRing ? (uint32_t)n : 0u;
+      // a ring that no pair names may have any offsets: read within the vertices only
+      const bool within = o >= 0 && off[1] <= (of_b ? end_b : end_a);
+      nv = within && n >= 1 && n <= kSweepRing ? (uint32_t)n : 0u;
     }
     Meta box{0, 0, 0, 0};  // the lane's ring's
     uint2 sums = make_uint2(0, 0);

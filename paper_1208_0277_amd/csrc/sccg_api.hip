@@ -41,6 +41,7 @@ struct sccg_ctx {
   // the rings' tiles, their boxes and sums (see BatchArgs)
   unsigned char* tiles = nullptr;
   int64_t cap_tiles = 0;  // rings
+  bool ring_tiles_off = false;
   // batched state and queues
   BatchState* st = nullptr;
   unsigned long long* queue = nullptr;
@@ -382,6 +383,7 @@ int noalloc_setup(sccg_ctx* c) {
 }  // namespace
 
 uint32_t* sccg::ctx_error_word(sccg_ctx* c) { return c->err; }
+void sccg::ctx_without_ring_tiles(sccg_ctx* c) { c->ring_tiles_off = true; }
 
 extern "C" {
 
@@ -472,7 +474,7 @@ int sccg_reserve(sccg_ctx* c, int64_t na, int64_t nb, int64_t np) {
       (r = ensure_queue(c)))
     return r;
   // tiles are only made of fewer rings than pairs
-  if (c->p.sweep_pair_box == 2 && np >= kRingTilePairs)
+  if (c->p.sweep_pair_box == 2 && np >= kRingTilePairs && !c->ring_tiles_off)
     (void)ensure_tiles(c, std::min(std::min(na + nb, np), kRingTilesMost));
   return SCCG_OK;
 }
@@ -640,7 +642,7 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
   ba.flags = c->p.flags;
   ba.stats_on = c->stats_on;
   const int64_t rings = A->n_polys + B->n_polys;
-  if (c->p.sweep_pair_box == 2 && use_ring_tiles(rings, n_pairs) && ensure_tiles(c, rings)) {
+  if (c->p.sweep_pair_box == 2 && !c->ring_tiles_off && use_ring_tiles(rings, n_pairs) && ensure_tiles(c, rings)) {
     ba.ring_tiles = reinterpret_cast<uint64_t*>(c->tiles);
     ba.ring_box = reinterpret_cast<Meta*>(c->tiles + c->cap_tiles * kTile * (int64_t)sizeof(uint64_t) + 16);
     ba.ring_sums = reinterpret_cast<uint2*>(ba.ring_box + c->cap_tiles);

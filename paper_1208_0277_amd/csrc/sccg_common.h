@@ -252,5 +252,9 @@ hipError_t launch_valu_peak(int grid, int iters, unsigned long long* sink, hipSt
 // The device error word of a context (read and cleared by the server, which
 // owns its context and runs on the context's stream).
 uint32_t* ctx_error_word(sccg_ctx* c);
+// The context's calls make no ring tiles: of the server's arena only the rings
+// that the pairs name are there, the other slots hold anything and are written
+// while a call runs.
+void ctx_without_ring_tiles(sccg_ctx* c);
 
 }  // namespace sccg

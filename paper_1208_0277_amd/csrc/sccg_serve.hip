@@ -606,6 +606,7 @@ int sccg_server_create(sccg_server** out, int hip_device, const sccg_server_conf
     free_server(s);
     return r;
   }
+  ctx_without_ring_tiles(s->ctx);
   if ((r = sccg_reserve(s->ctx, 0, 0, c.pair_cap)) != SCCG_OK) {
     free_server(s);
     return r;

@@ -5,10 +5,11 @@ register chunks, against closed forms."""
 import numpy as np
 import pytest
 
+import oracle
 import paper_1208_0277_amd as sccg
 from sccg_gen import concat
 from tests.gpu_util import assert_exact, device_workload, run
-from tests.shapes import band_rects, band_ring, rects_area, rects_inter
+from tests.shapes import band_rects, band_ring, rect_ring, rects_area, rects_inter
 
 pytestmark = pytest.mark.gpu
 
@@ -157,3 +158,28 @@ def test_rings_on_tiles_of_their_own(base, n, params):
     finally:
         c.close()
     assert_exact(I, U, expect, area_p[pi] + area_q[qi] - expect, f"own tiles at {base}, {n} pairs, {params}")
+
+
+def test_server_with_more_pairs_than_rings():
+    """With sweep_pair_box = 2 a context pixelizes all rings of its sets first
+    when pairs outnumber them; a server's set is its arena, of whose slots
+    only the jobs' are valid: its calls count pair by pair."""
+    rng = np.random.default_rng(5)
+    rings = [rect_ring((int(x), int(y), int(x) + int(w), int(y) + int(h)))
+             for x, y, w, h in zip(rng.integers(0, 60, 64), rng.integers(0, 60, 64), rng.integers(3, 50, 64), rng.integers(3, 50, 64))]
+    P = concat(rings)
+    pa, pb = (rng.integers(0, 64, 60000).astype(np.int32) for _ in range(2))
+    wI, wU = oracle.area_pairs(P, P, np.repeat(np.arange(64, dtype=np.int32), 64), np.tile(np.arange(64, dtype=np.int32), 64))
+    srv = sccg.Server(0, params={"sweep_pair_box": 2}, vertex_cap=4096, slot_cap=1024, pair_cap=1 << 17)
+    try:
+        for _ in range(2):
+            I, U = np.zeros(60000, np.int64), np.zeros(60000, np.int64)
+            srv.submit(P.off, P.xy, P.off, P.xy, pa, pb, I, U)
+            done = []
+            while not done:
+                done = srv.poll(timeout=None)
+            assert done[0]["status"] == sccg.SCCG_OK
+            k = pa.astype(np.int64) * 64 + pb
+            assert np.array_equal(I, wI[k]) and np.array_equal(U, wU[k])
+    finally:
+        srv.close()
