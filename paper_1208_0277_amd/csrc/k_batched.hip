@@ -1273,7 +1273,7 @@ k_ring_tiles(BatchArgs args) {
   const int lane = c.lane;
   if (blockIdx.x == 0 && threadIdx.x < (unsigned)kStreams) a.st->t_count[threadIdx.x].v = 0;
   const uint32_t n_a = (uint32_t)a.A.n;
-  const int64_t end_a = a.A.off[a.A.n], end_b = a.B.off[a.B.n];
+  const int64_t end_a = a.A.n > 0 ? a.A.off[a.A.n] : 0, end_b = a.B.n > 0 ? a.B.off[a.B.n] : 0;
   const WaveShare share(n_a + (uint32_t)a.B.n, kSweepWaves, uniform((int)(threadIdx.x / kWave)), a.chunk);
 #pragma unroll 1
   for (uint32_t k0 = 0; k0 < share.count; k0 += kWave) {

@@ -176,7 +176,10 @@ hipError_t launch_batch_sweeps(const BatchArgs& a, int sweep_grid, int medium_gr
 // alone against this: 2.69M pairs of 1.22M rings 1025 -> 640 us, 1.34M
 // 579 -> 537, 896,000 424 -> 502; 168,000 of 76,000 108 -> 73, 84,000 64 -> 68;
 // 41,000 of 19,000 41 -> 51; 9.5M of 4.8M with their set sums 3.50 -> 2.21 ms).
-// Offsets of tiles are 32 bits.
+// Where hardly a ring fits a tile the two passes are lost: the 331,000 pairs of
+// 151,000 rings of dense tiles scaled by 1 188 -> 100 us, by 2 366 -> 417, by 4
+// 513 -> 560 (the rings' sizes are not known before they are read).  Offsets of
+// tiles are 32 bits.
 constexpr int64_t kRingTilesMost = (int64_t(1) << 23) - 1;  // 4.5 GB of scratch
 constexpr int64_t kRingTilePairs = 49152;
 constexpr bool use_ring_tiles(int64_t rings, int64_t n_pairs) {
