@@ -840,13 +840,13 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
   int64_t cells = std::max(c->j_cells_seen, A->n_polys + n_sets + 1024);
   int64_t entries = std::max(c->j_entries_seen, 4 * A->n_polys + 1024);
   for (;;) {
-    const int64_t had = c->j_cap[7];
+    if (cells > c->j_cap[7]) c->j_dirty = true;  // to be new memory, whichever allocation fails from here on
     if ((r = need(c, &c->j_count, c->j_cap[7], cells, "cell counts")) ||
         (r = need(c, &c->j_start, c->j_cap[8], c->j_cap[7] + 1, "cell starts")) ||
         (r = need(c, &c->j_list, c->j_cap[9], entries, "cell lists")) ||
         (r = need(c, &c->j_sums, c->j_cap[10], std::max(scan_scratch(c->j_cap[7]), scan_scratch(B->n_polys)), "scan sums")))
       return r;
-    if (c->j_cap[7] != had || c->j_dirty)
+    if (c->j_dirty)
       HIP_TRY(c, hipMemsetAsync(c->j_count, 0, sizeof(int32_t) * (size_t)c->j_cap[7], c->stream));
     JoinLaunch l{};
     l.A = pA;

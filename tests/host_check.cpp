@@ -1,0 +1,87 @@
+// Checks of the library's host side on the stand-in runtime (host_hip.h): what
+// a call leaves behind when memory runs out.  One check per name; exits with
+// the number of expectations that failed.
+#include <stdio.h>
+#include <string.h>
+
+#include "host_hip.h"
+#include "sccg.h"
+
+static int failed = 0;
+#define EXPECT(cond, ...)                              \
+  do {                                                 \
+    if (!(cond)) {                                     \
+      ++failed;                                        \
+      printf("%s:%d: %s: ", __FILE__, __LINE__, #cond); \
+      printf(__VA_ARGS__);                             \
+      printf("\n");                                    \
+    }                                                  \
+  } while (0)
+
+static int64_t* const off = (int64_t*)((uintptr_t)1 << 45);  // device arrays that no allocation of the library holds
+static int32_t* const arr = (int32_t*)((uintptr_t)1 << 46);
+static sccg_polys polys(int64_t n) { return sccg_polys{n, off, arr}; }
+
+// ---------------------------------------------------------------- the join
+static int64_t join_cells, join_entries, join_pairs;  // what the kernels would find
+static int join(sccg_ctx* c, int64_t n, int64_t cells, int64_t entries, int64_t sets = 1) {
+  join_cells = cells;
+  join_entries = entries;
+  join_pairs = 5;
+  const sccg_polys A = polys(n), B = polys(n);
+  int64_t total = -1;
+  const int r = sccg_join_sets(c, &A, &B, sets, off, off, 0, 100, arr, arr, off, &total);
+  if (r == SCCG_OK) EXPECT(total == join_pairs, "%lld pairs", (long long)total);
+  return r;
+}
+static void watch_join(const Launch& l) {
+  if (l.is("k_join_cellsILb0")) {  // counts are added to what is there
+    const int64_t room = l.arg<int64_t>(7);
+    EXPECT(fake.cleared(l.arg<void*>(8), (size_t)room * 4), "counts of %lld cells", (long long)room);
+  }
+  if (l.is("k_join_write")) {
+    int64_t* sizes = l.arg<int64_t*>(8);
+    sizes[0] = join_cells;
+    sizes[1] = join_entries;
+    sizes[2] = join_pairs;
+  }
+}
+
+// Whichever allocation of a larger call is refused, the next call finds its
+// counts cleared.
+static void join_out_of_memory() {
+  fake.on_launch = watch_join;
+  for (int k = 0;; ++k) {
+    sccg_ctx* c = nullptr;
+    EXPECT(sccg_create(&c, 0, nullptr, nullptr) == SCCG_OK, "create");
+    EXPECT(join(c, 1000, 500, 900) == SCCG_OK, "small join");
+    fake.fail_at = fake.allocations + k;
+    const int r = join(c, 100000, 50000, 90000);
+    const bool refused = fake.allocations > fake.fail_at;
+    fake.fail_at = -1;
+    EXPECT(r == (refused ? SCCG_E_NOMEM : SCCG_OK), "allocation %d refused: %d", k, r);
+    (void)hipGetLastError();
+    EXPECT(join(c, 100000, 50000, 90000) == SCCG_OK, "after allocation %d was refused: %s", k, sccg_last_error(c));
+    sccg_destroy(c);
+    if (!refused) {
+      EXPECT(k >= 9, "only %d allocations", k);
+      return;
+    }
+  }
+}
+
+int main(int argc, char** argv) {
+  static const struct {
+    const char* name;
+    void (*run)();
+  } checks[] = {
+      {"join_out_of_memory", join_out_of_memory},
+  };
+  for (const auto& k : checks)
+    if (argc > 1 && !strcmp(argv[1], k.name)) {
+      k.run();
+      return failed > 100 ? 100 : failed;
+    }
+  printf("no such check\n");
+  return 101;
+}
