@@ -98,7 +98,10 @@ int fail(sccg_ctx* c, int code, const char* fmt, ...) {
   return code;
 }
 
+// The runtime keeps an error until it is asked for: left there, the check of
+// the next call's launches would find it.
 int hip_fail(sccg_ctx* c, hipError_t e, const char* what) {
+  (void)hipGetLastError();
   return fail(c, SCCG_E_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
@@ -167,6 +170,7 @@ int grow(sccg_ctx* c, T** ptr, int64_t n, const char* what) {
   if (n <= 0) return SCCG_OK;
   hipError_t e = hipMalloc((void**)ptr, sizeof(T) * (size_t)n);
   if (e != hipSuccess) {
+    (void)hipGetLastError();  // as in hip_fail
     *ptr = nullptr;
     return fail(c, SCCG_E_NOMEM, "hipMalloc(%s, %lld elements): %s", what, (long long)n, hipGetErrorString(e));
   }
@@ -416,6 +420,7 @@ int sccg_create(sccg_ctx** out, int hip_device, void* hip_stream, const sccg_par
   if (hipMalloc((void**)&c->err, sizeof(uint32_t)) != hipSuccess ||
       hipMalloc((void**)&c->st, sizeof(BatchState)) != hipSuccess ||
       hipMalloc((void**)&c->plain_stats, kNumStats * sizeof(unsigned long long)) != hipSuccess) {
+    (void)hipGetLastError();
     sccg_destroy(c);
     return SCCG_E_NOMEM;
   }
@@ -828,6 +833,7 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
     return r;
   if (!c->j_sizes) {
     if (!c->j_host && hipHostMalloc((void**)&c->j_host, 3 * sizeof(int64_t), hipHostMallocMapped) != hipSuccess) {
+      (void)hipGetLastError();
       c->j_host = nullptr;
       return fail(c, SCCG_E_NOMEM, "hipHostMalloc(join sizes)");
     }

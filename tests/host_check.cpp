@@ -60,7 +60,6 @@ static void join_out_of_memory() {
     const bool refused = fake.allocations > fake.fail_at;
     fake.fail_at = -1;
     EXPECT(r == (refused ? SCCG_E_NOMEM : SCCG_OK), "allocation %d refused: %d", k, r);
-    (void)hipGetLastError();
     EXPECT(join(c, 100000, 50000, 90000) == SCCG_OK, "after allocation %d was refused: %s", k, sccg_last_error(c));
     sccg_destroy(c);
     if (!refused) {
@@ -70,12 +69,46 @@ static void join_out_of_memory() {
   }
 }
 
+// A refused allocation is reported once: the next call of any kind works.
+static void errors_are_reported_once() {
+  fake.on_launch = watch_join;
+  const sccg_polys P = polys(100000);
+  for (int k = 0; k < 3; ++k) {
+    sccg_ctx* c = nullptr;
+    fake.fail_at = fake.allocations + k;
+    EXPECT(sccg_create(&c, 0, nullptr, nullptr) == SCCG_E_NOMEM, "allocation %d of a context", k);
+    fake.fail_at = -1;
+    EXPECT(sccg_create(&c, 0, nullptr, nullptr) == SCCG_OK, "create");
+    EXPECT(join(c, 1000, 500, 900) == SCCG_OK, "after allocation %d of a context was refused: %s", k, sccg_last_error(c));
+    sccg_destroy(c);
+  }
+  for (int first = 0; first < 5; ++first)
+    for (int second = 0; second < 5; ++second) {
+      sccg_ctx* c = nullptr;
+      EXPECT(sccg_create(&c, 0, nullptr, nullptr) == SCCG_OK, "create");
+      auto call = [&](int k) {
+        int64_t* o = off;
+        if (k == 0) return sccg_area_pairs(c, &P, &P, 1000, arr, arr, o, o, SCCG_BATCHED);
+        if (k == 1) return sccg_area_pairs(c, &P, &P, 1000, arr, arr, o, o, SCCG_PLAIN);
+        if (k == 2) return join(c, 1000, 500, 900);
+        if (k == 3) return sccg_relate_pairs(c, &P, &P, 1000, arr, arr, o, (uint32_t*)arr);
+        return sccg_jaccard_sets(c, 10, o, o, o, 0, o, o, o, (double*)o, nullptr);
+      };
+      fake.fail_at = fake.allocations;
+      EXPECT(call(first) == SCCG_E_NOMEM, "call %d", first);
+      fake.fail_at = -1;
+      EXPECT(call(second) == SCCG_OK, "call %d after call %d had no memory: %s", second, first, sccg_last_error(c));
+      sccg_destroy(c);
+    }
+}
+
 int main(int argc, char** argv) {
   static const struct {
     const char* name;
     void (*run)();
   } checks[] = {
       {"join_out_of_memory", join_out_of_memory},
+      {"errors_are_reported_once", errors_are_reported_once},
   };
   for (const auto& k : checks)
     if (argc > 1 && !strcmp(argv[1], k.name)) {
