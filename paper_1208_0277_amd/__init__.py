@@ -219,7 +219,12 @@ def _check_dev(t, dtype, name):
 
 
 class Context:
-    """One sccg context on a device and stream (the current torch stream by default)."""
+    """One sccg context on a device and stream (the current torch stream by default).
+
+    Tensors that its calls allocate and return are written on that stream.  They
+    may be read, after sync() or an event, on it and on the stream that was
+    current at the call, and dropped there at once; a reader on a third stream
+    calls `record_stream` on them first, as for any torch tensor."""
 
     def __init__(self, device: int = 0, stream=None, **params):
         import torch
@@ -316,13 +321,19 @@ class Context:
     def _empty(self, sizes, dtypes, device):
         """Output tensors in the memory of the context's stream: a block that
         the allocator holds for another stream may be handed out again while
-        this one still writes to it."""
+        this one still writes to it.  The caller's current stream is recorded
+        as a user of them, so that dropping one whose reader is still queued
+        there does not hand it to this stream's next call."""
         import torch
         if (self._raw_stream == torch._C._cuda_getCurrentRawStream(self.device)
                 or not isinstance(self.stream, torch.cuda.Stream)):
             return [torch.empty(n, dtype=t, device=device) for n, t in zip(sizes, dtypes)]
+        reader = torch.cuda.current_stream(self.device)
         with torch.cuda.stream(self.stream):
-            return [torch.empty(n, dtype=t, device=device) for n, t in zip(sizes, dtypes)]
+            out = [torch.empty(n, dtype=t, device=device) for n, t in zip(sizes, dtypes)]
+        for t in out:
+            t.record_stream(reader)
+        return out
 
     # ---------------------------------------------------------- compute
     def area_pairs(self, A: DevicePolys, B: DevicePolys, pair_a, pair_b, out_inter=None, out_union=None,

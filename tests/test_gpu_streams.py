@@ -34,3 +34,45 @@ def test_outputs_belong_to_the_contexts_stream():
     finally:
         c.close()
     assert np.diff(wl.A.off).min() > 0
+
+
+def test_outputs_read_on_the_current_stream_and_dropped():
+    """Dropped outputs that work queued on the caller's stream still reads are
+    not handed to the context's next call."""
+    import torch
+    wl = sccg_gen.pairs(1)
+    work = device_workload(wl.A, wl.B, wl.pa, wl.pb)
+    other = device_workload(wl.A, wl.B, wl.pa, np.roll(wl.pb, 1))
+    so = torch.tensor([0, wl.n_pairs], dtype=torch.int64, device="cuda")
+    off = torch.tensor([0, wl.A.n], dtype=torch.int64, device="cuda")
+    x = torch.rand(8192, 8192, device="cuda")
+    y = torch.empty_like(x)
+    c = sccg.Context(0, stream=torch.cuda.Stream())
+
+    def calls(w):
+        I, U = c.area_pairs(*w)
+        return [I, U, *c.jaccard_sets(so, I, U), *c.join_sets(w[0], w[1], off, off, cap=4 * wl.n_pairs),
+                c.relate_pairs(*w, I), c.validate_polys(w[0])]
+
+    try:
+        calls(other)
+        torch.cuda.synchronize()
+        outs = calls(work)
+        c.sync()
+        want = [t.cpu() for t in outs]
+        reader = torch.cuda.Event()
+        torch.cuda.synchronize()
+        for _ in range(20):  # some hundred milliseconds that the readers wait behind
+            torch.mm(x, x, out=y)
+        got = [t.clone() for t in outs]
+        reader.record()
+        held = {t.untyped_storage().data_ptr() for t in outs}
+        del outs
+        again = calls(other)
+        assert not reader.query(), "the readers had run before the calls: nothing was tested"
+        assert not held & {t.untyped_storage().data_ptr() for t in again}
+        torch.cuda.synchronize()
+        for g, w in zip(got, want):
+            assert torch.equal(g.cpu(), w)
+    finally:
+        c.close()
