@@ -137,7 +137,8 @@ typedef struct {
                              on mixes with many such pairs (densely packed sets).  A call with some
                              50,000 pairs more than rings pixelizes every ring once beforehand, with
                              536 bytes of scratch per ring (fewer than 2^23 rings; without that scratch
-                             it does as with fewer pairs).  1 = such pairs are left to the medium
+                             it does as with fewer pairs, and so do calls of as many rings until
+                             sccg_set_params or sccg_reserve).  1 = such pairs are left to the medium
                              sweep, which loads the rings again (default 1)                         */
 } sccg_params;
 

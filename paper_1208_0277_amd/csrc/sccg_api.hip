@@ -41,6 +41,7 @@ struct sccg_ctx {
   // the rings' tiles, their boxes and sums (see BatchArgs)
   unsigned char* tiles = nullptr;
   int64_t cap_tiles = 0;  // rings
+  int64_t tiles_refused = kRingTilesMost + 1;  // the fewest rings whose tiles could not be allocated
   bool ring_tiles_off = false;
   // batched state and queues
   BatchState* st = nullptr;
@@ -209,26 +210,31 @@ int ensure_pairs(sccg_ctx* c, int64_t n) {
 }
 
 // Room for the tiles of n rings (at most kRingTilesMost), if there is any: a
-// call without does without tiles.  Nothing is allocated while the stream is
-// captured.
+// call without does without tiles.  What could not be had is not asked for
+// again by every call (each would wait for an allocation of up to 4.5 GB to
+// fail), only once the parameters are set or scratch is reserved.  Nothing is
+// allocated while the stream is captured.
 bool ensure_tiles(sccg_ctx* c, int64_t n) {
   if (n <= c->cap_tiles) return true;
+  if (n >= c->tiles_refused) return false;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
     (void)hipGetLastError();
     return false;
   }
-  (void)hipStreamSynchronize(c->stream);
-  drop_graph(c);
-  if (c->tiles) (void)hipFree(c->tiles);
-  c->tiles = nullptr;
-  c->cap_tiles = 0;
   const int64_t want = std::min(n + n / 4 + 1024, kRingTilesMost);
-  if (hipMalloc((void**)&c->tiles, (size_t)ring_tiles_bytes(want)) != hipSuccess) {
+  unsigned char* more = nullptr;
+  if (hipMalloc((void**)&more, (size_t)ring_tiles_bytes(want)) != hipSuccess) {
     (void)hipGetLastError();
-    c->tiles = nullptr;
+    c->tiles_refused = n;
     return false;
   }
+  if (c->tiles) {
+    (void)hipStreamSynchronize(c->stream);
+    drop_graph(c);
+    (void)hipFree(c->tiles);
+  }
+  c->tiles = more;
   c->cap_tiles = want;
   return true;
 }
@@ -461,6 +467,7 @@ int sccg_set_params(sccg_ctx* c, const sccg_params* params) {
   int r = resolve_params(c, params, &p);
   if (r) return r;
   c->p = p;
+  c->tiles_refused = kRingTilesMost + 1;
   drop_graph(c);
   return SCCG_OK;
 }
@@ -478,6 +485,7 @@ int sccg_reserve(sccg_ctx* c, int64_t na, int64_t nb, int64_t np) {
   if ((r = ensure_polys(c, 0, na)) || (r = ensure_polys(c, 1, nb)) || (r = ensure_pairs(c, np)) ||
       (r = ensure_queue(c)))
     return r;
+  c->tiles_refused = kRingTilesMost + 1;
   // tiles are only made of fewer rings than pairs
   if (c->p.sweep_pair_box == 2 && np >= kRingTilePairs && !c->ring_tiles_off)
     (void)ensure_tiles(c, std::min(std::min(na + nb, np), kRingTilesMost));

@@ -102,6 +102,69 @@ static void errors_are_reported_once() {
     }
 }
 
+// ------------------------------------------------------------- rings' tiles
+// A call whose tiles cannot be allocated does without, and later ones too: no
+// waits, no dropped graph, no further attempts, until the scratch is asked for
+// again; smaller tiles that are there stay.
+static void tiles_out_of_memory() {
+  sccg_params p;
+  memset(&p, 0, sizeof(p));
+  p.sweep_pair_box = 2;
+  sccg_ctx* c = nullptr;
+  EXPECT(sccg_create(&c, 0, (void*)1, &p) == SCCG_OK, "create");
+  const int64_t pairs = 1000000, few = 10000, many = 400000;  // rings of a set
+  auto call = [&](int64_t n) {
+    const sccg_polys P = polys(n);
+    const int r = sccg_area_pairs(c, &P, &P, pairs, arr, arr, off, off, SCCG_BATCHED);
+    EXPECT(r == SCCG_OK, "%lld rings: %s", (long long)n, sccg_last_error(c));
+  };
+  call(few);
+  EXPECT(fake.launched("k_ring_tiles") == 1, "no tiles of few rings");
+  fake.most = (size_t)64 << 20;
+  call(many);
+  EXPECT(fake.refused == 1, "%ld refused", fake.refused);
+  EXPECT(fake.launched("k_ring_tiles") == 1, "tiles without memory");
+  const FakeHip before = fake;
+  for (int k = 0; k < 5; ++k) call(many);
+  call(many - 1);  // of what was asked for there was too little
+  EXPECT(fake.captures == before.captures + 1, "%ld captures", fake.captures - before.captures);
+  EXPECT(fake.replays == before.replays + 6, "%ld replays", fake.replays - before.replays);
+  EXPECT(fake.waits == before.waits, "%ld waits", fake.waits - before.waits);
+  EXPECT(fake.refused <= before.refused + 1, "%ld attempts", fake.refused - before.refused);
+  call(few);
+  EXPECT(fake.allocations == before.allocations + (fake.refused - before.refused), "the tiles of few rings were given up");
+  EXPECT(fake.launched("k_ring_tiles") == 2, "no tiles of few rings");
+  // asked for again: refused, then, with memory, there
+  long refused = fake.refused;
+  EXPECT(sccg_reserve(c, many, many, pairs) == SCCG_OK, "reserve");
+  EXPECT(fake.refused == refused + 1, "%ld attempts", fake.refused - refused);
+  fake.most = ~(size_t)0;
+  call(many);
+  EXPECT(fake.launched("k_ring_tiles") == 2, "memory looked for by a call");
+  EXPECT(sccg_reserve(c, many, many, pairs) == SCCG_OK, "reserve");
+  call(many);
+  EXPECT(fake.launched("k_ring_tiles") == 3, "no tiles after reserve");
+  sccg_destroy(c);
+}
+// So do calls after set_params.
+static void tiles_tried_again_with_new_parameters() {
+  sccg_params p;
+  memset(&p, 0, sizeof(p));
+  p.sweep_pair_box = 2;
+  sccg_ctx* c = nullptr;
+  EXPECT(sccg_create(&c, 0, (void*)1, &p) == SCCG_OK, "create");
+  const sccg_polys P = polys(400000);
+  auto call = [&]() { EXPECT(sccg_area_pairs(c, &P, &P, 1000000, arr, arr, off, off, SCCG_BATCHED) == SCCG_OK, "%s", sccg_last_error(c)); };
+  fake.most = (size_t)64 << 20;
+  call();
+  EXPECT(fake.launched("k_ring_tiles") == 0, "tiles without memory");
+  fake.most = ~(size_t)0;
+  EXPECT(sccg_set_params(c, &p) == SCCG_OK, "set_params");
+  call();
+  EXPECT(fake.launched("k_ring_tiles") == 1, "no tiles");
+  sccg_destroy(c);
+}
+
 int main(int argc, char** argv) {
   static const struct {
     const char* name;
@@ -109,6 +172,8 @@ int main(int argc, char** argv) {
   } checks[] = {
       {"join_out_of_memory", join_out_of_memory},
       {"errors_are_reported_once", errors_are_reported_once},
+      {"tiles_out_of_memory", tiles_out_of_memory},
+      {"tiles_tried_again_with_new_parameters", tiles_tried_again_with_new_parameters},
   };
   for (const auto& k : checks)
     if (argc > 1 && !strcmp(argv[1], k.name)) {

@@ -30,7 +30,8 @@ def check(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("name", ["join_out_of_memory", "errors_are_reported_once"])
+@pytest.mark.parametrize("name", ["join_out_of_memory", "errors_are_reported_once", "tiles_out_of_memory",
+                                  "tiles_tried_again_with_new_parameters"])
 def test_host_side(check, name):
     r = subprocess.run([check, name], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout + r.stderr
