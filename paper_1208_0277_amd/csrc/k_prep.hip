@@ -17,6 +17,7 @@ namespace sccg {
 constexpr int kRow = 16;        // lanes per ring (a DPP row)
 constexpr int kRowChunks = 4;   // loads of a lane in flight
 constexpr int kRowStep = kRow * kRowChunks;
+constexpr int kRowRings = 256 / kRow;  // rings of a workgroup at a time
 
 struct RowChunk {
   int2 v[kRowChunks], s[kRowChunks];  // vertices and, where asked for, their successors
@@ -75,62 +76,64 @@ __device__ __forceinline__ uint64_t row_sum64(uint64_t v) {
 template <bool kArea>
 __global__ void __launch_bounds__(256) k_meta_rows(Polys A, Meta* metaA, int64_t* areaA, Polys B, Meta* metaB,
                                                    int64_t* areaB, uint32_t* err) {
-  int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRow;
   const int j = (int)(threadIdx.x % kRow);
-  const bool second = k >= A.n;
-  if (second) k -= A.n;
-  if (second && k >= B.n) return;
-  const int64_t* off = second ? B.off : A.off;
-  const int64_t o = off[k], nv = off[k + 1] - o;
-  const int2* R = (second ? B.xy : A.xy) + o;
-  int32_t x0 = INT_MAX, y0 = INT_MAX, nx1 = INT_MAX, ny1 = INT_MAX;
-  uint32_t tn = 0;
-  int2 f = make_int2(0, 0);
-  if (kArea && nv > 0) f = R[0];
-  for (int64_t base = 0; base < nv; base += kRowStep) {
-    const RowChunk r = row_load<kArea>(R, nv, base, j);
-#pragma unroll
-    for (int c = 0; c < kRowChunks; ++c) {
-      x0 = min(x0, r.v[c].x);
-      y0 = min(y0, r.v[c].y);
-      nx1 = min(nx1, ~r.v[c].x);
-      ny1 = min(ny1, ~r.v[c].y);
-      if (kArea)
-        tn += (uint32_t)__mul24((int)((uint32_t)r.v[c].x + (uint32_t)r.s[c].x - 2u * (uint32_t)f.x),
-                                (int)((uint32_t)r.s[c].y - (uint32_t)r.v[c].y));
-    }
-  }
-  const Meta m{row_min(x0), row_min(y0), ~row_min(nx1), ~row_min(ny1)};
-  const bool empty = nv <= 0;
-  const bool bad = !empty && (m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord);
-  int64_t area = 0;
-  if (kArea && !empty && !bad) {
-    if (side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide) {
-      const int32_t t = (int32_t)row_sum(tn);
-      area = (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
-    } else {
-      uint64_t tw = 0;
-      for (int64_t base = 0; base < nv; base += kRowStep) {
-        const RowChunk r = row_load<true>(R, nv, base, j);
-        for (int c = 0; c < kRowChunks; ++c)
-          tw += (uint64_t)((int64_t)r.v[c].x * r.s[c].y) - (uint64_t)((int64_t)r.s[c].x * r.v[c].y);
+  for (int64_t k0 = (int64_t)blockIdx.x * kRowRings; k0 < A.n + B.n; k0 += (int64_t)gridDim.x * kRowRings) {
+    int64_t k = k0 + threadIdx.x / kRow;
+    const bool second = k >= A.n;
+    if (second) k -= A.n;
+    if (second && k >= B.n) continue;
+    const int64_t* off = second ? B.off : A.off;
+    const int64_t o = off[k], nv = off[k + 1] - o;
+    const int2* R = (second ? B.xy : A.xy) + o;
+    int32_t x0 = INT_MAX, y0 = INT_MAX, nx1 = INT_MAX, ny1 = INT_MAX;
+    uint32_t tn = 0;
+    int2 f = make_int2(0, 0);
+    if (kArea && nv > 0) f = R[0];
+    for (int64_t base = 0; base < nv; base += kRowStep) {
+      const RowChunk r = row_load<kArea>(R, nv, base, j);
+  #pragma unroll
+      for (int c = 0; c < kRowChunks; ++c) {
+        x0 = min(x0, r.v[c].x);
+        y0 = min(y0, r.v[c].y);
+        nx1 = min(nx1, ~r.v[c].x);
+        ny1 = min(ny1, ~r.v[c].y);
+        if (kArea)
+          tn += (uint32_t)__mul24((int)((uint32_t)r.v[c].x + (uint32_t)r.s[c].x - 2u * (uint32_t)f.x),
+                                  (int)((uint32_t)r.s[c].y - (uint32_t)r.v[c].y));
       }
-      const uint64_t t = row_sum64(tw);
-      area = (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
     }
+    const Meta m{row_min(x0), row_min(y0), ~row_min(nx1), ~row_min(ny1)};
+    const bool empty = nv <= 0;
+    const bool bad = !empty && (m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord);
+    int64_t area = 0;
+    if (kArea && !empty && !bad) {
+      if (side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide) {
+        const int32_t t = (int32_t)row_sum(tn);
+        area = (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
+      } else {
+        uint64_t tw = 0;
+        for (int64_t base = 0; base < nv; base += kRowStep) {
+          const RowChunk r = row_load<true>(R, nv, base, j);
+          for (int c = 0; c < kRowChunks; ++c)
+            tw += (uint64_t)((int64_t)r.v[c].x * r.s[c].y) - (uint64_t)((int64_t)r.s[c].x * r.v[c].y);
+        }
+        const uint64_t t = row_sum64(tw);
+        area = (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
+      }
+    }
+    if (j != 0) continue;
+    if (bad) latch_error(err, kErrCoord);
+    const bool none = empty || bad;
+    *reinterpret_cast<int4*>((second ? metaB : metaA) + k) =
+        none ? make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN) : make_int4(m.x0, m.y0, m.x1, m.y1);
+    if (kArea) (second ? areaB : areaA)[k] = area;
   }
-  if (j != 0) return;
-  if (bad) latch_error(err, kErrCoord);
-  const bool none = empty || bad;
-  *reinterpret_cast<int4*>((second ? metaB : metaA) + k) =
-      none ? make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN) : make_int4(m.x0, m.y0, m.x1, m.y1);
-  if (kArea) (second ? areaB : areaA)[k] = area;
 }
 
 hipError_t launch_poly_meta(const Polys& A, Meta* metaA, int64_t* areaA, const Polys& B, Meta* metaB, int64_t* areaB,
                             uint32_t* err, hipStream_t s) {
   if (A.n + B.n <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)(((A.n + B.n) * kRow + 255) / 256);
+  const unsigned blocks = blocks_of(A.n + B.n, kRowRings);
   if (areaA)
     hipLaunchKernelGGL(k_meta_rows<true>, dim3(blocks), dim3(256), 0, s, A, metaA, areaA, B, metaB, areaB, err);
   else
@@ -144,30 +147,32 @@ hipError_t launch_poly_meta(const Polys& A, Meta* metaA, int64_t* areaA, const P
 __global__ void k_validate_init(unsigned long long* first_bad) { *first_bad = ~0ull; }
 
 __global__ void __launch_bounds__(256) k_validate(Polys P, unsigned long long* first_bad) {
-  const int64_t k = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kRow;
   const int j = (int)(threadIdx.x % kRow);
-  bool bad = false;
-  if (k < P.n) {
-    const int64_t o = P.off[k], nv = P.off[k + 1] - o;
-    bad = nv < 4;
-    for (int64_t base = 0; base < nv; base += kRowStep) {
-      const RowChunk r = row_load<true>(P.xy + o, nv, base, j);
+  for (int64_t k0 = (int64_t)blockIdx.x * kRowRings; k0 < P.n; k0 += (int64_t)gridDim.x * kRowRings) {
+    const int64_t k = k0 + threadIdx.x / kRow;
+    bool bad = false;
+    if (k < P.n) {
+      const int64_t o = P.off[k], nv = P.off[k + 1] - o;
+      bad = nv < 4;
+      for (int64_t base = 0; base < nv; base += kRowStep) {
+        const RowChunk r = row_load<true>(P.xy + o, nv, base, j);
 #pragma unroll
-      for (int c = 0; c < kRowChunks; ++c) bad |= (r.v[c].x != r.s[c].x) & (r.v[c].y != r.s[c].y);
+        for (int c = 0; c < kRowChunks; ++c) bad |= (r.v[c].x != r.s[c].x) & (r.v[c].y != r.s[c].y);
+      }
     }
+    // the wave's rings stand in order: its first bad lane has its smallest index
+    const uint64_t m = ballot(bad);
+    if (m && lane_id() == __ffsll((long long)m) - 1 &&
+        (unsigned long long)k < __hip_atomic_load(first_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMin(first_bad, (unsigned long long)k);
   }
-  // the wave's rings stand in order: its first bad lane has its smallest index
-  const uint64_t m = ballot(bad);
-  if (m && lane_id() == __ffsll((long long)m) - 1 &&
-      (unsigned long long)k < __hip_atomic_load(first_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomicMin(first_bad, (unsigned long long)k);
 }
 
 hipError_t launch_validate(const Polys& P, int64_t* first_bad, hipStream_t s) {
   auto* fb = reinterpret_cast<unsigned long long*>(first_bad);
   hipLaunchKernelGGL(k_validate_init, dim3(1), dim3(1), 0, s, fb);
   if (P.n > 0)
-    hipLaunchKernelGGL(k_validate, dim3((unsigned)((P.n * kRow + 255) / 256)), dim3(256), 0, s, P, fb);
+    hipLaunchKernelGGL(k_validate, dim3(blocks_of(P.n, kRowRings)), dim3(256), 0, s, P, fb);
   return hipGetLastError();
 }
 
@@ -297,32 +302,36 @@ __global__ void __launch_bounds__(256) k_jaccard_sets(int64_t n_sets, const int6
                                                       int64_t* n_contrib, double* jout, double* jprime) {
   __shared__ JacSums sh[4];
   const int lane = lane_id(), me = (int)(threadIdx.x / kWave) % kWaves;
-  const int64_t s = ((int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) / kWaves;
-  if (s >= n_sets) return;
   const JacRange range(n_sets, set_off, waves);
-  const int64_t o0 = set_off[s], o1 = set_off[s + 1];
-  JacSums t{};
-  if (o0 < o1) {
-    const int64_t w0 = range.wave_of(o0), w1 = range.wave_of(o1 - 1);
-    if (w0 == w1) return;
-    uint64_t x[kJacWords] = {};
-    for (int64_t w = w0 + me * kWave + lane; w <= w1; w += kWaves * kWave) {
-      const JacSums& p = part[2 * w + (w == w0 ? 1 : 0)];
+  constexpr int kSets = 256 / kWave / kWaves;  // sets of a workgroup at a time
+  for (int64_t s0 = (int64_t)blockIdx.x * kSets; s0 < n_sets; s0 += (int64_t)gridDim.x * kSets) {
+    const int64_t s = s0 + threadIdx.x / (kWaves * kWave);
+    if (s >= n_sets) continue;
+    const int64_t o0 = set_off[s], o1 = set_off[s + 1];
+    JacSums t{};
+    if (o0 < o1) {
+      const int64_t w0 = range.wave_of(o0), w1 = range.wave_of(o1 - 1);
+      if (w0 == w1) continue;
+      uint64_t x[kJacWords] = {};
+      for (int64_t w = w0 + me * kWave + lane; w <= w1; w += kWaves * kWave) {
+        const JacSums& p = part[2 * w + (w == w0 ? 1 : 0)];
 #pragma unroll
-      for (int k = 0; k < kJacWords; ++k) x[k] += p.w[k];
+        for (int k = 0; k < kJacWords; ++k) x[k] += p.w[k];
+      }
+#pragma unroll
+      for (int k = 0; k < kJacWords; ++k) t.w[k] = wave_sum_u64(x[k]);
     }
+    if (kWaves > 1) {  // one set for the whole workgroup
+      if (lane == 0) sh[me] = t;
+      __syncthreads();
+      if (me == 0)
+        for (int u = 1; u < kWaves; ++u)
 #pragma unroll
-    for (int k = 0; k < kJacWords; ++k) t.w[k] = wave_sum_u64(x[k]);
+          for (int k = 0; k < kJacWords; ++k) t.w[k] += sh[u].w[k];
+      __syncthreads();
+    }
+    if (lane == 0 && me == 0) jac_store(s, t, jprime != nullptr, sum_i, sum_u, n_contrib, jout, jprime);
   }
-  if (kWaves > 1) {
-    if (lane == 0) sh[me] = t;
-    __syncthreads();
-    if (me == 0)
-      for (int u = 1; u < kWaves; ++u)
-#pragma unroll
-        for (int k = 0; k < kJacWords; ++k) t.w[k] += sh[u].w[k];
-  }
-  if (lane == 0 && me == 0) jac_store(s, t, jprime != nullptr, sum_i, sum_u, n_contrib, jout, jprime);
 }
 
 int64_t jaccard_scratch(int waves) { return 2 * (int64_t)waves * (int64_t)sizeof(JacSums); }
@@ -338,7 +347,7 @@ hipError_t launch_jaccard(int64_t n_sets, const int64_t* set_off, const int64_t*
     hipLaunchKernelGGL(k_jaccard_sets<4>, dim3((unsigned)n_sets), dim3(256), 0, s, n_sets, set_off, (int64_t)waves, part,
                        sum_i, sum_u, n_contrib, j, jprime);
   else
-    hipLaunchKernelGGL(k_jaccard_sets<1>, dim3((unsigned)((n_sets + 3) / 4)), dim3(256), 0, s, n_sets, set_off,
+    hipLaunchKernelGGL(k_jaccard_sets<1>, dim3(blocks_of(n_sets, 256 / kWave)), dim3(256), 0, s, n_sets, set_off,
                        (int64_t)waves, part, sum_i, sum_u, n_contrib, j, jprime);
   return hipGetLastError();
 }

@@ -40,6 +40,15 @@ struct Meta {
 // Number of statistics counters (see sccg_get_stats).
 constexpr int kNumStats = 16;
 
+// Workgroups of a kernel that takes `n` items, `per` each: a dispatch has fewer
+// than 2^32 threads, so the kernels with several lanes per item go over their
+// grid again from 2^20 workgroups on.
+constexpr int64_t kMostBlocks = int64_t(1) << 20;
+constexpr unsigned blocks_of(int64_t n, int64_t per) {
+  const int64_t b = (n + per - 1) / per;
+  return (unsigned)(b < 1 ? 1 : b < kMostBlocks ? b : kMostBlocks);
+}
+
 // ------------------------------------------------------------------ launches
 // Each returns a hipError_t from the launch.
 

@@ -165,6 +165,32 @@ static void tiles_tried_again_with_new_parameters() {
   sccg_destroy(c);
 }
 
+// ---------------------------------------------------------------- launches
+// A dispatch has fewer than 2^32 threads: whatever sizes the entry points
+// take, their launches do.
+static void launches_within_a_dispatch() {
+  fake.on_launch = watch_join;
+  const int64_t most = ((int64_t)1 << 31) - 1;
+  for (const int64_t n : {((int64_t)1 << 24) + 1, (int64_t)1 << 27, (int64_t)1 << 28, (int64_t)1 << 29, most}) {
+    sccg_ctx* c = nullptr;
+    EXPECT(sccg_create(&c, 0, nullptr, nullptr) == SCCG_OK, "create");
+    const sccg_polys P = polys(n);
+    const int64_t pairs = n == most ? (int64_t)1 << 34 : n;
+    EXPECT(sccg_validate_polys(c, &P, off) == SCCG_OK, "validate %lld: %s", (long long)n, sccg_last_error(c));
+    EXPECT(sccg_area_pairs(c, &P, &P, n, arr, arr, off, off, SCCG_PLAIN) == SCCG_OK, "plain %lld: %s", (long long)n, sccg_last_error(c));
+    EXPECT(sccg_area_pairs(c, &P, &P, n, arr, arr, off, off, SCCG_BATCHED) == SCCG_OK, "batched %lld: %s", (long long)n, sccg_last_error(c));
+    EXPECT(join(c, n, n, n) == SCCG_OK, "join %lld: %s", (long long)n, sccg_last_error(c));
+    EXPECT(join(c, 1000, n, n, n) == SCCG_OK, "join of %lld sets: %s", (long long)n, sccg_last_error(c));
+    EXPECT(sccg_relate_pairs(c, &P, &P, pairs, arr, arr, off, (uint32_t*)arr) == SCCG_OK, "relate %lld: %s", (long long)pairs,
+           sccg_last_error(c));
+    EXPECT(sccg_jaccard_sets(c, n, off, off, off, 0, off, off, off, (double*)off, nullptr) == SCCG_OK, "jaccard of %lld sets: %s",
+           (long long)n, sccg_last_error(c));
+    for (const auto& k : fake.too_large) EXPECT(false, "%lld: %s", (long long)n, k.c_str());
+    fake.too_large.clear();
+    sccg_destroy(c);
+  }
+}
+
 int main(int argc, char** argv) {
   static const struct {
     const char* name;
@@ -173,6 +199,7 @@ int main(int argc, char** argv) {
       {"join_out_of_memory", join_out_of_memory},
       {"errors_are_reported_once", errors_are_reported_once},
       {"tiles_out_of_memory", tiles_out_of_memory},
+      {"launches_within_a_dispatch", launches_within_a_dispatch},
       {"tiles_tried_again_with_new_parameters", tiles_tried_again_with_new_parameters},
   };
   for (const auto& k : checks)
