@@ -38,7 +38,9 @@ __device__ __forceinline__ int64_t set_of(const int64_t* off, int64_t n, int64_t
 
 // The same for every lane's k, ascending over the wave (a lane without one
 // passes -1): the set of the first is searched by the wave, 64 offsets per
-// step, the others walk on from it.  Every lane takes part.
+// step, the others from it in steps that double (most are in the same set or
+// the next; a walk over the sets between took 89 ms for 100 polygons in a
+// million sets).  Every lane takes part.
 __device__ __forceinline__ int64_t set_of_lane(const int64_t* off, int64_t n, int64_t k) {
   const int lane = lane_id();
   const uint64_t some = ballot(n > 0 && k >= off[0] && k < off[n]);
@@ -52,7 +54,19 @@ __device__ __forceinline__ int64_t set_of_lane(const int64_t* off, int64_t n, in
     hi = uniform64(min(hi, lo + step));
   }
   if (!((some >> lane) & 1ull)) return -1;
-  while (k >= off[lo + 1]) ++lo;
+  int64_t step = 1;  // off[lo] <= k < off[n]
+  while (lo + step < n && off[lo + step] <= k) {
+    lo += step;
+    step *= 2;
+  }
+  hi = min(lo + step, n);
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (off[mid] <= k)
+      lo = mid;
+    else
+      hi = mid;
+  }
   return lo;
 }
 
