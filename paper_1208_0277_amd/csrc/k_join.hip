@@ -36,6 +36,24 @@ __device__ __forceinline__ int64_t set_of(const int64_t* off, int64_t n, int64_t
   return lo;
 }
 
+// The same from set lo on: off[lo] <= k < off[n].
+__device__ __forceinline__ int64_t set_from(const int64_t* off, int64_t n, int64_t lo, int64_t k) {
+  int64_t step = 1;
+  while (lo + step < n && off[lo + step] <= k) {
+    lo += step;
+    step *= 2;
+  }
+  int64_t hi = min(lo + step, n);
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (off[mid] <= k)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  return lo;
+}
+
 // The same for every lane's k, ascending over the wave (a lane without one
 // passes -1): the set of the first is searched by the wave, 64 offsets per
 // step, the others from it in steps that double (most are in the same set or
@@ -54,20 +72,7 @@ __device__ __forceinline__ int64_t set_of_lane(const int64_t* off, int64_t n, in
     hi = uniform64(min(hi, lo + step));
   }
   if (!((some >> lane) & 1ull)) return -1;
-  int64_t step = 1;  // off[lo] <= k < off[n]
-  while (lo + step < n && off[lo + step] <= k) {
-    lo += step;
-    step *= 2;
-  }
-  hi = min(lo + step, n);
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (off[mid] <= k)
-      lo = mid;
-    else
-      hi = mid;
-  }
-  return lo;
+  return set_from(off, n, lo, k);
 }
 
 __device__ __forceinline__ bool meta_empty(const Meta& m) { return m.x0 >= m.x1 || m.y0 >= m.y1; }
@@ -87,61 +92,110 @@ __global__ void k_join_init_sets(int64_t n_sets, int4* bbox) {
 }
 
 // Extent of each set's A polygons.  Sets are contiguous ranges: a workgroup
-// takes kBoxRun consecutive polygons and updates a set once per run of them
-// (the atomics on one set's extent take turns: 600,000 polygons of 16 sets took
-// 250 us with four for every 64 polygons, 55 for every 256, 23 for every 1024).
+// takes kBoxRun consecutive polygons, a thread up to 16 neighbouring ones
+// of them (through LDS), and a set is updated by a thread when it leaves it and by the
+// workgroup for the threads that end in the same one.  (The atomics on one
+// set's extent take turns: 600,000 polygons of 16 sets took 250 us with four
+// for every 64 polygons, 55 for every 256, 23 for every 1024.  A workgroup that
+// took one set after the other needed 1.4 us for each: 370 us, now 9, for 4096
+// polygons of 256 sets.)
 constexpr int kBoxRun = 4096;
-// add(s, box): by thread 0, for each set that the workgroup's polygons [a0, a1)
-// belong to.
-template <typename F>
-__device__ __forceinline__ void run_extents(int64_t a0, int64_t a1, int64_t n_a, const Meta* metaA, const int64_t* a_off,
-                                            int64_t n_sets, int4* sh, F add) {
-  const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
-  int64_t a = a0;
-  while (a < a1) {
-    // the polygons of one set from a on (all threads at the same a)
-    const int64_t s = uniform64(set_of(a_off, n_sets, a));
-    if (s < 0) {
-      // outside every set: skip to the first set, or to the end
-      const int64_t first = uniform64(n_sets > 0 ? a_off[0] : n_a);
-      if (a >= first) break;
-      a = min(first, a1);
-      continue;
-    }
-    const int64_t end = min(uniform64(a_off[s + 1]), a1);
-    int x0 = INT_MAX, y0 = INT_MAX, x1 = INT_MIN, y1 = INT_MIN;
-#pragma unroll 4
-    for (int64_t k = a + threadIdx.x; k < end; k += 256) {
-      const Meta t = load_meta(metaA, k);
-      const bool some = !meta_empty(t);
-      x0 = min(x0, some ? t.x0 : x0);
-      y0 = min(y0, some ? t.y0 : y0);
-      x1 = max(x1, some ? t.x1 : x1);
-      y1 = max(y1, some ? t.y1 : y1);
-    }
-    const int4 mine = make_int4(wave_min_i32(x0), wave_min_i32(y0), wave_max_i32(x1), wave_max_i32(y1));
-    if (lane == 0) sh[w] = mine;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int4 m = sh[0];
-      for (int k = 1; k < 4; ++k)
-        m = make_int4(min(m.x, sh[k].x), min(m.y, sh[k].y), max(m.z, sh[k].z), max(m.w, sh[k].w));
-      if (m.x < m.z) add(s, m);
-    }
-    __syncthreads();
-    a = end;
+// What the waves' last sets come to: one per wave, -1 where its threads differ.
+struct WaveBox {
+  int64_t set;
+  int4 box;
+};
+__device__ __forceinline__ int4 box_or(const int4& a, const int4& b) {
+  return make_int4(min(a.x, b.x), min(a.y, b.y), max(a.z, b.z), max(a.w, b.w));
+}
+// add(s, box): the polygons [a0, a1), a1 - a0 <= kBoxRun, of set s (by any
+// thread, several times a set).
+// Whether the lanes' sets (ascending, -1 for none) are one; then every lane has
+// it and the extent of all.  Else the first lane of each set has its lanes', the
+// others nothing (one by one the atomics of 16 such waves took 18 us).
+__device__ __forceinline__ bool one_set(int64_t& s, int4& box) {
+  const uint64_t some = ballot(s >= 0);
+  if (s < 0) box = no_extent();
+  const int64_t s0 = some ? uniform64(__shfl((long long)s, __ffsll((long long)some) - 1, kWave)) : -1;
+  if (ballot(s >= 0 && s != s0) == 0) {
+    s = s0;
+    box = make_int4(wave_min_i32(box.x), wave_min_i32(box.y), wave_max_i32(box.z), wave_max_i32(box.w));
+    return true;
   }
+  const int lane = lane_id(), mine = (int)s;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int4 o = make_int4(__shfl_down(box.x, d, kWave), __shfl_down(box.y, d, kWave), __shfl_down(box.z, d, kWave),
+                             __shfl_down(box.w, d, kWave));
+    const bool same = __shfl_down(mine, d, kWave) == mine;
+    if (same && lane + d < kWave) box = box_or(box, o);
+  }
+  const int before = __shfl_up(mine, 1, kWave);
+  if (lane > 0 && before == mine) s = -1;
+  return false;
+}
+template <int kThreads>
+struct RunLds {
+  int4 meta[kBoxRun + kThreads];  // an entry between two threads' polygons: their banks differ
+  WaveBox wave[kThreads / kWave];
+};
+template <int kThreads, typename F>
+__device__ __forceinline__ void run_extents(int64_t a0, int64_t a1, const Meta* metaA, const int64_t* a_off,
+                                            int64_t n_sets, RunLds<kThreads>& lds, F add) {
+  const int t = (int)threadIdx.x, w = t / kWave;
+  const int cnt = (int)(a1 - a0);
+  int sh = 0;  // 2^sh polygons a thread
+  while ((kThreads << sh) < cnt) ++sh;
+#pragma unroll 4
+  for (int i = t; i < cnt; i += kThreads) {
+    const Meta m = load_meta(metaA, a0 + i);
+    lds.meta[i + (i >> sh)] = make_int4(m.x0, m.y0, m.x1, m.y1);
+  }
+  // the thread's polygons [a, end) that are in a set
+  const int64_t first = n_sets > 0 ? a_off[0] : a1, last = n_sets > 0 ? a_off[n_sets] : a0;
+  const int64_t b = a0 + (t << sh), a = max(b, first), end = min(min(b + (1 << sh), a1), last);
+  int64_t s = set_of_lane(a_off, n_sets, a < end ? a : -1), s_end = s >= 0 ? a_off[s + 1] : 0;
+  int4 box = no_extent();
+  __syncthreads();
+#pragma unroll 1
+  for (int64_t k = a; k < end; ++k) {
+    if (k >= s_end) {
+      if (box.x < box.z) add(s, box);
+      box = no_extent();
+      s = set_from(a_off, n_sets, s, k);
+      s_end = a_off[s + 1];
+    }
+    const int4 m = lds.meta[(t << sh) + t + (int)(k - b)];
+    if (m.x < m.z && m.y < m.w) box = box_or(box, m);
+  }
+  // the threads' last sets: a wave that has one only leaves it to the workgroup
+  if (one_set(s, box)) {
+    if (lane_id() == 0) lds.wave[w] = WaveBox{s, box};
+  } else {
+    if (s >= 0 && box.x < box.z) add(s, box);
+    if (lane_id() == 0) lds.wave[w] = WaveBox{-1, box};
+  }
+  __syncthreads();
+  if (w == 0) {
+    const int l = min(lane_id(), kThreads / kWave - 1);
+    s = lds.wave[l].set;
+    box = lds.wave[l].box;
+    if (lane_id() != l) s = -1;
+    if (one_set(s, box)) s = lane_id() == 0 ? s : -1;
+    if (s >= 0 && box.x < box.z) add(s, box);
+  }
+}
+__device__ __forceinline__ void add_extent(int4* to, const int4& m) {
+  atomicMin(&to->x, m.x);
+  atomicMin(&to->y, m.y);
+  atomicMax(&to->z, m.z);
+  atomicMax(&to->w, m.w);
 }
 __global__ void __launch_bounds__(256) k_join_bbox(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
                                                    int4* bbox) {
-  __shared__ int4 sh[4];
+  __shared__ RunLds<256> lds;
   const int64_t a0 = (int64_t)blockIdx.x * kBoxRun;
-  run_extents(a0, min(a0 + kBoxRun, A.n), A.n, metaA, a_off, n_sets, sh, [&](int64_t s, const int4& m) {
-    atomicMin(&bbox[s].x, m.x);
-    atomicMin(&bbox[s].y, m.y);
-    atomicMax(&bbox[s].z, m.z);
-    atomicMax(&bbox[s].w, m.w);
-  });
+  run_extents<256>(a0, min(a0 + kBoxRun, A.n), metaA, a_off, n_sets, lds,
+              [&](int64_t s, const int4& m) { add_extent(bbox + s, m); });
 }
 
 // ------------------------------------------------------- exclusive scans
@@ -172,10 +226,11 @@ __device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh, int64
 
 // Grid of each set: origin, columns, rows; base[s] = cells of the sets before
 // s, base[n_sets] = all of them.  One block.
+template <int kThreads>
 __device__ __forceinline__ void set_grids(int64_t n_sets, const int4* bbox, int cell, int4* grid, int64_t* base,
                                           uint32_t* err, int64_t* sh) {
   int64_t run = 0;
-  for (int64_t s0 = 0; s0 < n_sets; s0 += kScanThreads) {
+  for (int64_t s0 = 0; s0 < n_sets; s0 += kThreads) {
     const int64_t s = s0 + threadIdx.x;
     int64_t cells = 0;
     if (s < n_sets) {
@@ -194,7 +249,7 @@ __device__ __forceinline__ void set_grids(int64_t n_sets, const int4* bbox, int 
       cells = (int64_t)gw * gh;
     }
     int64_t total;
-    const int64_t before = block_exclusive(cells, sh, &total);
+    const int64_t before = block_exclusive<kThreads>(cells, sh, &total);
     if (s < n_sets) base[s] = run + before;
     run += total;
   }
@@ -203,7 +258,7 @@ __device__ __forceinline__ void set_grids(int64_t n_sets, const int4* bbox, int 
 __global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, const int4* bbox, int cell, int4* grid,
                                                             int64_t* base, uint32_t* err) {
   __shared__ int64_t sh[kScanThreads / kWave];
-  set_grids(n_sets, bbox, cell, grid, base, err, sh);
+  set_grids<kScanThreads>(n_sets, bbox, cell, grid, base, err, sh);
 }
 
 // A single tile's comparison is bound by its launches, a dozen of 2 to 5 us
@@ -211,16 +266,18 @@ __global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, cons
 // time of a launch is done by one: the extents and grids of up to kFewSets sets
 // of up to kBoxRun polygons in all, and the scans of up to kOneScan counts.
 constexpr int kFewSets = 256;
-__global__ void __launch_bounds__(kScanThreads) k_join_grid_few(Polys A, const Meta* metaA, const int64_t* a_off,
+constexpr int kFewThreads = 1024;
+__global__ void __launch_bounds__(kFewThreads) k_join_grid_few(Polys A, const Meta* metaA, const int64_t* a_off,
                                                                 int64_t n_sets, int cell, int4* grid, int64_t* base,
                                                                 uint32_t* err) {
-  __shared__ int4 boxes[kFewSets], sh4[4];
-  __shared__ int64_t sh[kScanThreads / kWave];
-  for (int64_t s = threadIdx.x; s < n_sets; s += kScanThreads) boxes[s] = no_extent();
+  __shared__ int4 boxes[kFewSets];
+  __shared__ RunLds<kFewThreads> lds;
+  __shared__ int64_t sh[kFewThreads / kWave];
+  for (int64_t s = threadIdx.x; s < n_sets; s += kFewThreads) boxes[s] = no_extent();
   __syncthreads();
-  run_extents(0, A.n, A.n, metaA, a_off, n_sets, sh4, [&](int64_t s, const int4& m) { boxes[s] = m; });
+  run_extents<kFewThreads>(0, A.n, metaA, a_off, n_sets, lds, [&](int64_t s, const int4& m) { add_extent(boxes + s, m); });
   __syncthreads();
-  set_grids(n_sets, boxes, cell, grid, base, err, sh);
+  set_grids<kFewThreads>(n_sets, boxes, cell, grid, base, err, sh);
 }
 
 // out[i] = sum of in[0 .. i) for i <= n, n read from device memory when n_ptr
@@ -494,7 +551,7 @@ static unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 hipError_t launch_join(const JoinLaunch& l, hipStream_t s) {
   const Polys &A = l.A, &B = l.B;
   if (A.n <= kBoxRun && l.n_sets <= kFewSets) {
-    hipLaunchKernelGGL(k_join_grid_few, dim3(1), dim3(kScanThreads), 0, s, A, l.metaA, l.a_off, l.n_sets, l.cell, l.grid,
+    hipLaunchKernelGGL(k_join_grid_few, dim3(1), dim3(kFewThreads), 0, s, A, l.metaA, l.a_off, l.n_sets, l.cell, l.grid,
                        l.cell_base, l.err);
   } else {
     hipLaunchKernelGGL(k_join_init_sets, dim3(blocks_for(l.n_sets)), dim3(256), 0, s, l.n_sets, l.bbox);

@@ -37,10 +37,19 @@ def _layout(name):
         b[:] = a
         a[0], b[0], b[-1] = 64, 3, 2
         return a, b, 20_000
+    if name == "256 sets of 16":
+        return np.full(256, 16), np.full(256, 16), 250
+    if name == "60,000 sets of 10 and two large ones":
+        a = np.full(60_000, 10)
+        a[[17, 40_000]] = 3000, 5000
+        a[100:120] = 0
+        b = np.full(60_000, 9)
+        b[[17, 40_000]] = 500, 10
+        return a, b, 1100
     raise ValueError(name)
 
 
-@pytest.mark.parametrize("name", ["polygons many sets apart"])
+@pytest.mark.parametrize("name", ["polygons many sets apart", "256 sets of 16", "60,000 sets of 10 and two large ones"])
 def test_many_sets(name):
     import torch
     sa, sb, most_us = _layout(name)
