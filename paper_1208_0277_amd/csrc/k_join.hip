@@ -469,23 +469,21 @@ __device__ __forceinline__ int join_entries(const JoinArgs& a, int64_t b, int64_
 // again for it took 88 + 157 us for 600,000 of 4.5 pairs each).
 constexpr int kFound = 16;
 constexpr int kCountLanes = 8;
-__global__ void __launch_bounds__(256) k_join_count(JoinArgs a, int32_t* b_count, int32_t* found, int32_t* cell_count) {
+__global__ void __launch_bounds__(256) k_join_count(JoinArgs a, int32_t* b_count, int32_t* found, int32_t* cell_count,
+                                                    int64_t first) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (!join_fits(a)) return;
   // the cells' counts are left at zero for the next call
   const int64_t n_cells = a.cell_base[a.n_sets];
-  for (int64_t c = t; c < n_cells; c += (int64_t)gridDim.x * blockDim.x) cell_count[c] = 0;
-  const int j = (int)(threadIdx.x % kCountLanes);
-  constexpr int kPolys = 256 / kCountLanes;  // of a workgroup at a time
-  for (int64_t b0 = (int64_t)blockIdx.x * kPolys; b0 < a.B.n; b0 += (int64_t)gridDim.x * kPolys) {
-    const int64_t b = b0 + threadIdx.x / kCountLanes;
-    const int64_t s = set_of_lane(a.b_off, a.n_sets, b < a.B.n ? b : -1);
-    if (b >= a.B.n) continue;
-    const int n = join_entries<kCountLanes>(a, b, s, j, [&](int k, int32_t p, bool keep) {
-      if (keep && k < kFound) found[b * kFound + k] = p;
-    });
-    if (j == 0) b_count[b] = n;
-  }
+  for (int64_t c = t; first == 0 && c < n_cells; c += (int64_t)gridDim.x * blockDim.x) cell_count[c] = 0;
+  const int64_t b = first + t / kCountLanes;
+  const int j = (int)(t % kCountLanes);
+  const int64_t s = set_of_lane(a.b_off, a.n_sets, b < a.B.n ? b : -1);
+  if (b >= a.B.n) return;
+  const int n = join_entries<kCountLanes>(a, b, s, j, [&](int k, int32_t p, bool keep) {
+    if (keep && k < kFound) found[b * kFound + k] = p;
+  });
+  if (j == 0) b_count[b] = n;
 }
 
 // Each B polygon's pairs in the order of A, 16 lanes per polygon: the place of
@@ -493,57 +491,53 @@ __global__ void __launch_bounds__(256) k_join_count(JoinArgs a, int32_t* b_count
 // sizes for the host, and the first ones the sets' offsets.
 __global__ void __launch_bounds__(256) k_join_write(JoinArgs a, const int32_t* b_count, const int64_t* b_start,
                                                     const int32_t* found, int64_t cap, int32_t* out_pa, int32_t* out_pb,
-                                                    int64_t* out_set_off, int64_t* sizes) {
+                                                    int64_t* out_set_off, int64_t* sizes, int64_t first) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t n_cells = a.cell_base[a.n_sets];
   const bool fits = join_fits(a);
-  if (t == 0) {  // in host memory
+  if (t == 0 && first == 0) {  // in host memory
     sizes[0] = n_cells;
     sizes[1] = n_cells <= a.cell_room ? a.start[n_cells] : 0;
     sizes[2] = fits ? b_start[a.B.n] : 0;
     __threadfence_system();
   }
   if (!fits) return;
-  for (int64_t k = t; k <= a.n_sets; k += (int64_t)gridDim.x * blockDim.x)
-    out_set_off[k] = b_start[min(max(a.b_off[k], (int64_t)0), a.B.n)];
+  if (first == 0 && t <= a.n_sets) out_set_off[t] = b_start[min(max(a.b_off[t], (int64_t)0), a.B.n)];
   if (b_start[a.B.n] > cap) return;
-  const int j = (int)(threadIdx.x % kFound);
-  constexpr int kPolys = 256 / kFound;  // of a workgroup at a time
-  for (int64_t b0 = (int64_t)blockIdx.x * kPolys; b0 < a.B.n; b0 += (int64_t)gridDim.x * kPolys) {
-    const int64_t b = b0 + threadIdx.x / kFound;
-    if (b >= a.B.n) continue;
-    const int n = b_count[b];
-    const int64_t base = b_start[b];
-    if (n <= kFound) {
-      const int v = j < n ? found[b * kFound + j] : INT_MAX;
-      int rank = 0;
+  const int64_t b = first + t / kFound;
+  const int j = (int)(t % kFound);
+  if (b >= a.B.n) return;
+  const int n = b_count[b];
+  const int64_t base = b_start[b];
+  if (n <= kFound) {
+    const int v = j < n ? found[b * kFound + j] : INT_MAX;
+    int rank = 0;
 #define SCCG_RANK(R) rank += __builtin_amdgcn_update_dpp(0, v, 0x120 + R, 0xf, 0xf, false) < v ? 1 : 0;  // row_ror:R
-      SCCG_RANK(1) SCCG_RANK(2) SCCG_RANK(3) SCCG_RANK(4) SCCG_RANK(5) SCCG_RANK(6) SCCG_RANK(7) SCCG_RANK(8)
-      SCCG_RANK(9) SCCG_RANK(10) SCCG_RANK(11) SCCG_RANK(12) SCCG_RANK(13) SCCG_RANK(14) SCCG_RANK(15)
+    SCCG_RANK(1) SCCG_RANK(2) SCCG_RANK(3) SCCG_RANK(4) SCCG_RANK(5) SCCG_RANK(6) SCCG_RANK(7) SCCG_RANK(8)
+    SCCG_RANK(9) SCCG_RANK(10) SCCG_RANK(11) SCCG_RANK(12) SCCG_RANK(13) SCCG_RANK(14) SCCG_RANK(15)
 #undef SCCG_RANK
-      if (j < n) {
-        out_pa[base + rank] = v;
-        out_pb[base + rank] = (int32_t)b;
-      }
-      continue;
+    if (j < n) {
+      out_pa[base + rank] = v;
+      out_pb[base + rank] = (int32_t)b;
     }
-    // more than were kept: searched again, unordered into out_pa, ordered into
-    // out_pb, and back
-    join_entries<kFound>(a, b, set_of(a.b_off, a.n_sets, b), j, [&](int k, int32_t p, bool keep) {
-      if (keep) out_pa[base + k] = p;
-    });
-    __threadfence_block();
-    for (int i = j; i < n; i += kFound) {
-      const int32_t v = out_pa[base + i];
-      int rank = 0;
-      for (int k = 0; k < n; ++k) rank += out_pa[base + k] < v ? 1 : 0;
-      out_pb[base + rank] = v;
-    }
-    __threadfence_block();
-    for (int i = j; i < n; i += kFound) out_pa[base + i] = out_pb[base + i];
-    __threadfence_block();
-    for (int i = j; i < n; i += kFound) out_pb[base + i] = (int32_t)b;
+    return;
   }
+  // more than were kept: searched again, unordered into out_pa, ordered into
+  // out_pb, and back
+  join_entries<kFound>(a, b, set_of(a.b_off, a.n_sets, b), j, [&](int k, int32_t p, bool keep) {
+    if (keep) out_pa[base + k] = p;
+  });
+  __threadfence_block();
+  for (int i = j; i < n; i += kFound) {
+    const int32_t v = out_pa[base + i];
+    int rank = 0;
+    for (int k = 0; k < n; ++k) rank += out_pa[base + k] < v ? 1 : 0;
+    out_pb[base + rank] = v;
+  }
+  __threadfence_block();
+  for (int i = j; i < n; i += kFound) out_pa[base + i] = out_pb[base + i];
+  __threadfence_block();
+  for (int i = j; i < n; i += kFound) out_pb[base + i] = (int32_t)b;
 }
 
 static unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -570,11 +564,15 @@ hipError_t launch_join(const JoinLaunch& l, hipStream_t s) {
                        l.cell_base, l.cell, l.cell_room, l.count, l.start, l.list_room, l.list);
   const JoinArgs j{B, l.metaA, l.metaB, l.b_off, l.n_sets, l.grid, l.cell_base, l.start, l.list, l.cell, l.cell_room,
                    l.list_room};
-  hipLaunchKernelGGL(k_join_count, dim3(blocks_of(B.n, 256 / kCountLanes)), dim3(256), 0, s, j, l.b_count,
-                     l.found, l.count);
+  for_slices(B.n, 256 / kCountLanes, [&](int64_t first, unsigned blocks) {
+    hipLaunchKernelGGL(k_join_count, dim3(blocks), dim3(256), 0, s, j, l.b_count, l.found, l.count, first);
+  });
   launch_scan<false>(l.b_count, B.n, nullptr, B.n, l.sums, l.b_start, s);
-  hipLaunchKernelGGL(k_join_write, dim3(std::max(blocks_of(B.n, 256 / kFound), blocks_of(l.n_sets + 1, 256))), dim3(256), 0, s, j, l.b_count, l.b_start, l.found, l.cap,
-                     l.out_pa, l.out_pb, l.out_set_off, l.sizes);
+  for_slices(B.n, 256 / kFound, [&](int64_t first, unsigned blocks) {
+    if (first == 0) blocks = std::max(blocks, blocks_for(l.n_sets + 1));
+    hipLaunchKernelGGL(k_join_write, dim3(blocks), dim3(256), 0, s, j, l.b_count, l.b_start, l.found, l.cap, l.out_pa,
+                       l.out_pb, l.out_set_off, l.sizes, first);
+  });
   return hipGetLastError();
 }
 int64_t join_found_room(int64_t n_b) { return n_b * kFound; }

@@ -299,39 +299,35 @@ __global__ void __launch_bounds__(256) k_jaccard_waves(int64_t n_sets, const int
 template <int kWaves>
 __global__ void __launch_bounds__(256) k_jaccard_sets(int64_t n_sets, const int64_t* set_off, int64_t waves,
                                                       const JacSums* part, int64_t* sum_i, int64_t* sum_u,
-                                                      int64_t* n_contrib, double* jout, double* jprime) {
+                                                      int64_t* n_contrib, double* jout, double* jprime, int64_t first) {
   __shared__ JacSums sh[4];
   const int lane = lane_id(), me = (int)(threadIdx.x / kWave) % kWaves;
+  const int64_t s = first + ((int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) / kWaves;
+  if (s >= n_sets) return;
   const JacRange range(n_sets, set_off, waves);
-  constexpr int kSets = 256 / kWave / kWaves;  // sets of a workgroup at a time
-  for (int64_t s0 = (int64_t)blockIdx.x * kSets; s0 < n_sets; s0 += (int64_t)gridDim.x * kSets) {
-    const int64_t s = s0 + threadIdx.x / (kWaves * kWave);
-    if (s >= n_sets) continue;
-    const int64_t o0 = set_off[s], o1 = set_off[s + 1];
-    JacSums t{};
-    if (o0 < o1) {
-      const int64_t w0 = range.wave_of(o0), w1 = range.wave_of(o1 - 1);
-      if (w0 == w1) continue;
-      uint64_t x[kJacWords] = {};
-      for (int64_t w = w0 + me * kWave + lane; w <= w1; w += kWaves * kWave) {
-        const JacSums& p = part[2 * w + (w == w0 ? 1 : 0)];
+  const int64_t o0 = set_off[s], o1 = set_off[s + 1];
+  JacSums t{};
+  if (o0 < o1) {
+    const int64_t w0 = range.wave_of(o0), w1 = range.wave_of(o1 - 1);
+    if (w0 == w1) return;
+    uint64_t x[kJacWords] = {};
+    for (int64_t w = w0 + me * kWave + lane; w <= w1; w += kWaves * kWave) {
+      const JacSums& p = part[2 * w + (w == w0 ? 1 : 0)];
 #pragma unroll
-        for (int k = 0; k < kJacWords; ++k) x[k] += p.w[k];
-      }
-#pragma unroll
-      for (int k = 0; k < kJacWords; ++k) t.w[k] = wave_sum_u64(x[k]);
+      for (int k = 0; k < kJacWords; ++k) x[k] += p.w[k];
     }
-    if (kWaves > 1) {  // one set for the whole workgroup
-      if (lane == 0) sh[me] = t;
-      __syncthreads();
-      if (me == 0)
-        for (int u = 1; u < kWaves; ++u)
 #pragma unroll
-          for (int k = 0; k < kJacWords; ++k) t.w[k] += sh[u].w[k];
-      __syncthreads();
-    }
-    if (lane == 0 && me == 0) jac_store(s, t, jprime != nullptr, sum_i, sum_u, n_contrib, jout, jprime);
+    for (int k = 0; k < kJacWords; ++k) t.w[k] = wave_sum_u64(x[k]);
   }
+  if (kWaves > 1) {
+    if (lane == 0) sh[me] = t;
+    __syncthreads();
+    if (me == 0)
+      for (int u = 1; u < kWaves; ++u)
+#pragma unroll
+        for (int k = 0; k < kJacWords; ++k) t.w[k] += sh[u].w[k];
+  }
+  if (lane == 0 && me == 0) jac_store(s, t, jprime != nullptr, sum_i, sum_u, n_contrib, jout, jprime);
 }
 
 int64_t jaccard_scratch(int waves) { return 2 * (int64_t)waves * (int64_t)sizeof(JacSums); }
@@ -345,10 +341,12 @@ hipError_t launch_jaccard(int64_t n_sets, const int64_t* set_off, const int64_t*
                      sum_i, sum_u, n_contrib, j, jprime, part);
   if (n_sets <= 2048)
     hipLaunchKernelGGL(k_jaccard_sets<4>, dim3((unsigned)n_sets), dim3(256), 0, s, n_sets, set_off, (int64_t)waves, part,
-                       sum_i, sum_u, n_contrib, j, jprime);
+                       sum_i, sum_u, n_contrib, j, jprime, 0);
   else
-    hipLaunchKernelGGL(k_jaccard_sets<1>, dim3(blocks_of(n_sets, 256 / kWave)), dim3(256), 0, s, n_sets, set_off,
-                       (int64_t)waves, part, sum_i, sum_u, n_contrib, j, jprime);
+    for_slices(n_sets, 256 / kWave, [&](int64_t first, unsigned blocks) {
+      hipLaunchKernelGGL(k_jaccard_sets<1>, dim3(blocks), dim3(256), 0, s, n_sets, set_off, (int64_t)waves, part, sum_i,
+                         sum_u, n_contrib, j, jprime, first);
+    });
   return hipGetLastError();
 }
 

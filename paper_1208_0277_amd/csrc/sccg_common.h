@@ -40,13 +40,24 @@ struct Meta {
 // Number of statistics counters (see sccg_get_stats).
 constexpr int kNumStats = 16;
 
-// Workgroups of a kernel that takes `n` items, `per` each: a dispatch has fewer
-// than 2^32 threads, so the kernels with several lanes per item go over their
-// grid again from 2^20 workgroups on.
+// Workgroups of a kernel that takes `n` items, `per` each.  A dispatch has fewer
+// than 2^32 threads: of a kernel with several lanes per item a grid stops at
+// 2^20 workgroups, and the kernel goes over it again, or is launched again from
+// the item it got to (the loop cost the join's writing pass 33.9 -> 38.6 us, a first item 35.1; the
+// per-ring passes were no slower with it).
 constexpr int64_t kMostBlocks = int64_t(1) << 20;
 constexpr unsigned blocks_of(int64_t n, int64_t per) {
   const int64_t b = (n + per - 1) / per;
   return (unsigned)(b < 1 ? 1 : b < kMostBlocks ? b : kMostBlocks);
+}
+// launch(first item, workgroups), at least once
+template <typename F>
+void for_slices(int64_t n, int64_t per, F launch) {
+  int64_t first = 0;
+  do {
+    launch(first, blocks_of(n - first, per));
+    first += kMostBlocks * per;
+  } while (first < n);
 }
 
 // ------------------------------------------------------------------ launches
