@@ -133,14 +133,14 @@ __device__ __forceinline__ bool one_set(int64_t& s, int4& box) {
   if (lane > 0 && before == mine) s = -1;
   return false;
 }
-template <int kThreads>
+template <int kThreads, int kRun>
 struct RunLds {
-  int4 meta[kBoxRun + kThreads];  // an entry between two threads' polygons: their banks differ
+  int4 meta[kRun + kThreads];  // an entry between two threads' polygons: their banks differ
   WaveBox wave[kThreads / kWave];
 };
-template <int kThreads, typename F>
+template <int kThreads, int kRun, typename F>
 __device__ __forceinline__ void run_extents(int64_t a0, int64_t a1, const Meta* metaA, const int64_t* a_off,
-                                            int64_t n_sets, RunLds<kThreads>& lds, F add) {
+                                            int64_t n_sets, RunLds<kThreads, kRun>& lds, F add) {
   const int t = (int)threadIdx.x, w = t / kWave;
   const int cnt = (int)(a1 - a0);
   int sh = 0;  // 2^sh polygons a thread
@@ -190,13 +190,19 @@ __device__ __forceinline__ void add_extent(int4* to, const int4& m) {
   atomicMax(&to->z, m.z);
   atomicMax(&to->w, m.w);
 }
+template <int kRun>
 __global__ void __launch_bounds__(256) k_join_bbox(Polys A, const Meta* metaA, const int64_t* a_off, int64_t n_sets,
                                                    int4* bbox) {
-  __shared__ RunLds<256> lds;
-  const int64_t a0 = (int64_t)blockIdx.x * kBoxRun;
-  run_extents<256>(a0, min(a0 + kBoxRun, A.n), metaA, a_off, n_sets, lds,
-              [&](int64_t s, const int4& m) { add_extent(bbox + s, m); });
+  __shared__ RunLds<256, kRun> lds;
+  const int64_t a0 = (int64_t)blockIdx.x * kRun;
+  run_extents<256, kRun>(a0, min(a0 + kRun, A.n), metaA, a_off, n_sets, lds,
+                         [&](int64_t s, const int4& m) { add_extent(bbox + s, m); });
 }
+// Of sets of fewer polygons on average a thread takes one polygon, not several
+// sets (runs of 4096 / 256 polygons, 600,000 of them in sets of 600: 8.0 / 9.4 us;
+// of 100: 14 / 11; of 10: 17.5 / 12; a million in sets of one: 157 / 49).
+constexpr int64_t kSmallSets = 128;
+constexpr int kSmallRun = 256;
 
 // ------------------------------------------------------- exclusive scans
 // exclusive prefix of v over the threads of a block (kThreads of them; sh: one per wave)
@@ -224,30 +230,31 @@ __device__ __forceinline__ int64_t block_exclusive(int64_t v, int64_t* sh, int64
   return before + x - v;
 }
 
-// Grid of each set: origin, columns, rows; base[s] = cells of the sets before
-// s, base[n_sets] = all of them.  One block.
+// Grid of set s: origin, columns, rows.  Returns its cells.
+__device__ __forceinline__ int64_t set_grid(int64_t s, const int4* bbox, int cell, int4* grid, uint32_t* err) {
+  const int4 b = bbox[s];
+  int gw = 0, gh = 0;
+  if (b.x < b.z && b.y < b.w) {
+    const int64_t w = ((int64_t)b.z - b.x + cell - 1) / cell, h = ((int64_t)b.w - b.y + cell - 1) / cell;
+    if (w * h > (1 << 24)) {
+      latch_error(err, kErrSide);  // the set's grid is too large for the cell size
+    } else {
+      gw = (int)w;
+      gh = (int)h;
+    }
+  }
+  grid[s] = make_int4(b.x, b.y, gw, gh);
+  return (int64_t)gw * gh;
+}
+// The grids of all sets by one block; base[s] = cells of the sets before s,
+// base[n_sets] = all of them.
 template <int kThreads>
 __device__ __forceinline__ void set_grids(int64_t n_sets, const int4* bbox, int cell, int4* grid, int64_t* base,
                                           uint32_t* err, int64_t* sh) {
   int64_t run = 0;
   for (int64_t s0 = 0; s0 < n_sets; s0 += kThreads) {
     const int64_t s = s0 + threadIdx.x;
-    int64_t cells = 0;
-    if (s < n_sets) {
-      const int4 b = bbox[s];
-      int gw = 0, gh = 0;
-      if (b.x < b.z && b.y < b.w) {
-        const int64_t w = ((int64_t)b.z - b.x + cell - 1) / cell, h = ((int64_t)b.w - b.y + cell - 1) / cell;
-        if (w * h > (1 << 24)) {
-          latch_error(err, kErrSide);  // the set's grid is too large for the cell size
-        } else {
-          gw = (int)w;
-          gh = (int)h;
-        }
-      }
-      grid[s] = make_int4(b.x, b.y, gw, gh);
-      cells = (int64_t)gw * gh;
-    }
+    const int64_t cells = s < n_sets ? set_grid(s, bbox, cell, grid, err) : 0;
     int64_t total;
     const int64_t before = block_exclusive<kThreads>(cells, sh, &total);
     if (s < n_sets) base[s] = run + before;
@@ -260,6 +267,15 @@ __global__ void __launch_bounds__(kScanThreads) k_join_grid(int64_t n_sets, cons
   __shared__ int64_t sh[kScanThreads / kWave];
   set_grids<kScanThreads>(n_sets, bbox, cell, grid, base, err, sh);
 }
+// More than kOneGrids sets: a thread each, the cells left in place of the
+// extents' first words for a scan.  (The whole join of 40,000 polygons, one
+// block / this: 600 sets 98 / 101 us, 1024 108 / 108, 2048 111 / 109, 8192
+// 132 / 116, 32768 241 / 134; a million sets 17 ms / 0.6.)
+__global__ void __launch_bounds__(256) k_join_grids(int64_t n_sets, int4* bbox, int cell, int4* grid, uint32_t* err) {
+  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (s < n_sets) bbox[s].x = (int)set_grid(s, bbox, cell, grid, err);
+}
+constexpr int64_t kOneGrids = 1024;
 
 // A single tile's comparison is bound by its launches, a dozen of 2 to 5 us
 // each with one or two more between them; what a workgroup does in about the
@@ -271,22 +287,23 @@ __global__ void __launch_bounds__(kFewThreads) k_join_grid_few(Polys A, const Me
                                                                 int64_t n_sets, int cell, int4* grid, int64_t* base,
                                                                 uint32_t* err) {
   __shared__ int4 boxes[kFewSets];
-  __shared__ RunLds<kFewThreads> lds;
+  __shared__ RunLds<kFewThreads, kBoxRun> lds;
   __shared__ int64_t sh[kFewThreads / kWave];
   for (int64_t s = threadIdx.x; s < n_sets; s += kFewThreads) boxes[s] = no_extent();
   __syncthreads();
-  run_extents<kFewThreads>(0, A.n, metaA, a_off, n_sets, lds, [&](int64_t s, const int4& m) { add_extent(boxes + s, m); });
+  run_extents<kFewThreads, kBoxRun>(0, A.n, metaA, a_off, n_sets, lds, [&](int64_t s, const int4& m) { add_extent(boxes + s, m); });
   __syncthreads();
   set_grids<kFewThreads>(n_sets, boxes, cell, grid, base, err, sh);
 }
 
-// out[i] = sum of in[0 .. i) for i <= n, n read from device memory when n_ptr
+// out[i] = sum of the first i of in[0], in[kStride], ... for i <= n, n read from device memory when n_ptr
 // is given (nothing is done when it exceeds `room`): block totals, then every
 // block adds the totals before its own.
 __device__ __forceinline__ int64_t scan_size(int64_t n, const int64_t* n_ptr, int64_t room) {
   if (n_ptr) n = *n_ptr;
   return n > room ? -1 : n;
 }
+template <int kStride>
 __global__ void __launch_bounds__(kScanThreads) k_scan_totals(const int32_t* in, int64_t n, const int64_t* n_ptr,
                                                               int64_t room, int64_t* sums) {
   __shared__ int64_t sh[kScanThreads / kWave];
@@ -296,14 +313,14 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_totals(const int32_t* in,
   int64_t tot = 0;
   for (int k = 0; k < kScanPer; ++k) {
     const int64_t i = b0 + k * kScanThreads + threadIdx.x;
-    tot += i < n ? in[i] : 0;
+    tot += i < n ? in[i * kStride] : 0;
   }
   int64_t total;
   block_exclusive(tot, sh, &total);
   if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 // kClear: `in` is zeroed behind the scan.
-template <bool kClear>
+template <bool kClear, int kStride>
 __global__ void __launch_bounds__(kScanThreads) k_scan_write(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room,
                                                              const int64_t* sums, int64_t* out) {
   __shared__ int64_t sh[kScanThreads / kWave];
@@ -318,21 +335,21 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_write(int32_t* in, int64_
   int64_t tot = 0, total;
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
-    v[k] = i0 + k < n ? in[i0 + k] : 0;
+    v[k] = i0 + k < n ? in[(i0 + k) * kStride] : 0;
     tot += v[k];
   }
   int64_t run = before + block_exclusive(tot, sh, &total);
 #pragma unroll
   for (int k = 0; k < kScanPer; ++k) {
     if (i0 + k <= n) out[i0 + k] = run;
-    if (kClear && i0 + k < n) in[i0 + k] = 0;
+    if (kClear && i0 + k < n) in[(i0 + k) * kStride] = 0;
     run += v[k];
   }
 }
 // The whole scan by one workgroup.
 constexpr int kOneThreads = 1024;
 constexpr int64_t kOneScan = 2 * kOneThreads * kScanPer;
-template <bool kClear>
+template <bool kClear, int kStride>
 __global__ void __launch_bounds__(kOneThreads) k_scan_one(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room,
                                                           int64_t* out) {
   __shared__ int64_t sh[kOneThreads / kWave];
@@ -344,29 +361,29 @@ __global__ void __launch_bounds__(kOneThreads) k_scan_one(int32_t* in, int64_t n
     int64_t tot = 0, total;
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
-      v[k] = i0 + k < n ? in[i0 + k] : 0;
+      v[k] = i0 + k < n ? in[(i0 + k) * kStride] : 0;
       tot += v[k];
     }
     int64_t at = run + block_exclusive<kOneThreads>(tot, sh, &total);
 #pragma unroll
     for (int k = 0; k < kScanPer; ++k) {
       if (i0 + k <= n) out[i0 + k] = at;
-      if (kClear && i0 + k < n) in[i0 + k] = 0;
+      if (kClear && i0 + k < n) in[(i0 + k) * kStride] = 0;
       at += v[k];
     }
     run += total;
   }
 }
 int64_t scan_scratch(int64_t n) { return n / kScanBlock + 1; }
-template <bool kClear>
+template <bool kClear, int kStride = 1>
 void launch_scan(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room, int64_t* sums, int64_t* out, hipStream_t s) {
   if (room <= kOneScan) {
-    hipLaunchKernelGGL(k_scan_one<kClear>, dim3(1), dim3(kOneThreads), 0, s, in, n, n_ptr, room, out);
+    hipLaunchKernelGGL((k_scan_one<kClear, kStride>), dim3(1), dim3(kOneThreads), 0, s, in, n, n_ptr, room, out);
     return;
   }
   const dim3 g((unsigned)scan_scratch(room)), b(kScanThreads);
-  hipLaunchKernelGGL(k_scan_totals, g, b, 0, s, in, n, n_ptr, room, sums);
-  hipLaunchKernelGGL(k_scan_write<kClear>, g, b, 0, s, in, n, n_ptr, room, sums, out);
+  hipLaunchKernelGGL(k_scan_totals<kStride>, g, b, 0, s, in, n, n_ptr, room, sums);
+  hipLaunchKernelGGL((k_scan_write<kClear, kStride>), g, b, 0, s, in, n, n_ptr, room, sums, out);
 }
 
 // ------------------------------------------------------------------- entries
@@ -549,11 +566,19 @@ hipError_t launch_join(const JoinLaunch& l, hipStream_t s) {
                        l.cell_base, l.err);
   } else {
     hipLaunchKernelGGL(k_join_init_sets, dim3(blocks_for(l.n_sets)), dim3(256), 0, s, l.n_sets, l.bbox);
-    if (A.n > 0)
-      hipLaunchKernelGGL(k_join_bbox, dim3((unsigned)((A.n + kBoxRun - 1) / kBoxRun)), dim3(256), 0, s, A, l.metaA,
-                         l.a_off, l.n_sets, l.bbox);
-    hipLaunchKernelGGL(k_join_grid, dim3(1), dim3(kScanThreads), 0, s, l.n_sets, l.bbox, l.cell, l.grid, l.cell_base,
-                       l.err);
+    if (A.n > 0 && A.n < kSmallSets * l.n_sets)
+      hipLaunchKernelGGL(k_join_bbox<kSmallRun>, dim3((unsigned)((A.n + kSmallRun - 1) / kSmallRun)), dim3(256), 0, s, A,
+                         l.metaA, l.a_off, l.n_sets, l.bbox);
+    else if (A.n > 0)
+      hipLaunchKernelGGL(k_join_bbox<kBoxRun>, dim3((unsigned)((A.n + kBoxRun - 1) / kBoxRun)), dim3(256), 0, s, A,
+                         l.metaA, l.a_off, l.n_sets, l.bbox);
+    if (l.n_sets <= kOneGrids) {
+      hipLaunchKernelGGL(k_join_grid, dim3(1), dim3(kScanThreads), 0, s, l.n_sets, l.bbox, l.cell, l.grid, l.cell_base,
+                         l.err);
+    } else {
+      hipLaunchKernelGGL(k_join_grids, dim3(blocks_for(l.n_sets)), dim3(256), 0, s, l.n_sets, l.bbox, l.cell, l.grid, l.err);
+      launch_scan<false, 4>(reinterpret_cast<int32_t*>(l.bbox), l.n_sets, nullptr, l.n_sets, l.sums, l.cell_base, s);
+    }
   }
   if (A.n > 0)
     hipLaunchKernelGGL(k_join_cells<false>, dim3(blocks_for(A.n)), dim3(256), 0, s, A, l.metaA, l.a_off, l.n_sets,

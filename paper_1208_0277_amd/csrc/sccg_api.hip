@@ -858,7 +858,8 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
     if ((r = need(c, &c->j_count, c->j_cap[7], cells, "cell counts")) ||
         (r = need(c, &c->j_start, c->j_cap[8], c->j_cap[7] + 1, "cell starts")) ||
         (r = need(c, &c->j_list, c->j_cap[9], entries, "cell lists")) ||
-        (r = need(c, &c->j_sums, c->j_cap[10], std::max(scan_scratch(c->j_cap[7]), scan_scratch(B->n_polys)), "scan sums")))
+        (r = need(c, &c->j_sums, c->j_cap[10], 
+                  std::max(scan_scratch(c->j_cap[7]), scan_scratch(std::max(B->n_polys, n_sets))), "scan sums")))
       return r;
     if (c->j_dirty)
       HIP_TRY(c, hipMemsetAsync(c->j_count, 0, sizeof(int32_t) * (size_t)c->j_cap[7], c->stream));

@@ -43,8 +43,8 @@ constexpr int kNumStats = 16;
 // Workgroups of a kernel that takes `n` items, `per` each.  A dispatch has fewer
 // than 2^32 threads: of a kernel with several lanes per item a grid stops at
 // 2^20 workgroups, and the kernel goes over it again, or is launched again from
-// the item it got to (the loop cost the join's writing pass 33.9 -> 38.6 us, a first item 35.1; the
-// per-ring passes were no slower with it).
+// the item it got to (the loop cost the join's writing pass 33.9 -> 38.6 us, a
+// first item 35.1; the per-ring passes were no slower with it).
 constexpr int64_t kMostBlocks = int64_t(1) << 20;
 constexpr unsigned blocks_of(int64_t n, int64_t per) {
   const int64_t b = (n + per - 1) / per;
@@ -250,7 +250,7 @@ struct JoinLaunch {
   int64_t* start;        // [cell_room + 1]
   int64_t list_room;
   int32_t* list;         // [list_room]
-  int64_t* sums;         // [max of scan_scratch(cell_room), scan_scratch(B.n)]
+  int64_t* sums;         // [scan_scratch of the most of cell_room, B.n and n_sets]
   int32_t* b_count;      // [B.n]
   int64_t* b_start;      // [B.n + 1]
   int32_t* found;        // [join_found_room(B.n)]

@@ -46,10 +46,21 @@ def _layout(name):
         b = np.full(60_000, 9)
         b[[17, 40_000]] = 500, 10
         return a, b, 1100
+    if name.startswith("sets around the grids' limits"):
+        n = int(name.split()[-1])
+        a = rng.integers(0, 4, n)
+        a[n // 2] = 5000  # more polygons than one workgroup takes
+        b = rng.integers(0, 4, n)
+        return a, b, 400
+    if name == "a million sets":
+        a = np.zeros(1_000_000, np.int64)
+        a[[0, 5, 999_999]] = 64, 1000, 9
+        return a, a, 2000
     raise ValueError(name)
 
 
-@pytest.mark.parametrize("name", ["polygons many sets apart", "256 sets of 16", "60,000 sets of 10 and two large ones"])
+@pytest.mark.parametrize("name", ["polygons many sets apart", "256 sets of 16", "60,000 sets of 10 and two large ones",
+                                  "a million sets", *(f"sets around the grids' limits {n}" for n in (255, 256, 257, 1024, 1025, 16384, 16385))])
 def test_many_sets(name):
     import torch
     sa, sb, most_us = _layout(name)
