@@ -14,10 +14,21 @@ namespace sccg {
 // next 16.  Bound by the rings' bytes (one lane per ring read 8 bytes of 64
 // lines at a time: 600,000 rings of 90 vertices validated in 850 us; eight
 // lanes with the successors loaded again 147 us for extents and areas).
+//
+// Short rings leave most of a row idle.  Many of few vertices on average are
+// taken 16 of a wave at a time, on the four lanes of a quad each, 16 vertices a
+// step, whatever their own length.  The average is read on the device, and is
+// where the two cross, on rows / on quads: a million rings validated, of 4
+// vertices 55 / 27 us, 20 57 / 38, 32 62 / 48, 40 80 / 77, 48 83 / 85; extents and
+// areas of two million, of 4 157 / 65 us, 20 160 / 87, 32 196 / 120, 48 236 / 199
+// (a thread per ring validated the first in 28 us, eight lanes per ring took 64
+// for the extents and areas of 4 vertices, 178 of 40).
 constexpr int kRow = 16;        // lanes per ring (a DPP row)
 constexpr int kRowChunks = 4;   // loads of a lane in flight
 constexpr int kRowStep = kRow * kRowChunks;
-constexpr int kRowRings = 256 / kRow;  // rings of a workgroup at a time
+constexpr int kRowRings = 256 / kRow;  // rings of a workgroup's rows
+constexpr int kQuadStep = 4 * kRowChunks;
+constexpr int kShortMeta = 48, kShortValidate = 32;  // vertices on average of rings taken on quads
 
 struct RowChunk {
   int2 v[kRowChunks], s[kRowChunks];  // vertices and, where asked for, their successors
@@ -45,6 +56,29 @@ __device__ __forceinline__ RowChunk row_load(const int2* R, int64_t nv, int64_t 
   }
   return r;
 }
+// 16 vertices of a short ring on the four lanes of a quad (lane j of it).
+template <bool kSucc>
+__device__ __forceinline__ RowChunk quad_load(const int2* R, int64_t nv, int64_t base, int j) {
+  RowChunk r;
+#pragma unroll
+  for (int c = 0; c < kRowChunks; ++c) r.v[c] = R[base + c * 4 + j < nv ? base + c * 4 + j : 0];
+  if (kSucc) {
+    int2 next = R[base + kQuadStep < nv ? base + kQuadStep : 0];  // lane 3's successor in the last chunk
+#pragma unroll
+    for (int c = kRowChunks - 1; c >= 0; --c) {
+      // quad_perm 1 2 3 0: the next lane's, and in lane 3 lane 0's
+      const int2 t = make_int2(__builtin_amdgcn_update_dpp(0, r.v[c].x, 0x39, 0xf, 0xf, false),
+                               __builtin_amdgcn_update_dpp(0, r.v[c].y, 0x39, 0xf, 0xf, false));
+      r.s[c] = j == 3 ? next : t;
+      next = t;
+    }
+  }
+  return r;
+}
+__device__ __forceinline__ int32_t quad_min(int32_t x) {
+  x = min(x, __builtin_amdgcn_update_dpp(x, x, 0xb1, 0xf, 0xf, false));
+  return min(x, __builtin_amdgcn_update_dpp(x, x, 0x4e, 0xf, 0xf, false));
+}
 
 __device__ __forceinline__ int32_t row_min(int32_t x) {
   x = min(x, __builtin_amdgcn_update_dpp(x, x, 0xb1, 0xf, 0xf, false));
@@ -59,14 +93,145 @@ __device__ __forceinline__ uint32_t row_sum(uint32_t u) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xf, 0xf, false);
   return (uint32_t)(x + __builtin_amdgcn_update_dpp(0, x, 0x140, 0xf, 0xf, false));
 }
-__device__ __forceinline__ uint64_t row_sum64(uint64_t v) {
-  for (int d = 1; d < kRow; d <<= 1) {
+
+// A ring of one of two sets, by its number over both.
+struct RingOf {
+  bool second;
+  int64_t k, nv;
+  const int2* R;
+  __device__ __forceinline__ RingOf(const Polys& A, const Polys& B, int64_t at) {
+    second = at >= A.n;
+    k = second ? at - A.n : at;
+    const int64_t* off = second ? B.off : A.off;
+    const int64_t o = off[k];
+    nv = off[k + 1] - o;
+    R = (second ? B.xy : A.xy) + o;
+  }
+};
+
+// What a lane's vertices add to its ring's extent (minima, and complemented
+// maxima) and doubled area.
+struct RingAcc {
+  int32_t x0 = INT_MAX, y0 = INT_MAX, nx1 = INT_MAX, ny1 = INT_MAX;
+  uint32_t tn = 0;
+  template <bool kArea>
+  __device__ __forceinline__ void add(const RowChunk& r, int2 f) {
+#pragma unroll
+    for (int c = 0; c < kRowChunks; ++c) {
+      x0 = min(x0, r.v[c].x);
+      y0 = min(y0, r.v[c].y);
+      nx1 = min(nx1, ~r.v[c].x);
+      ny1 = min(ny1, ~r.v[c].y);
+      if (kArea)
+        tn += (uint32_t)__mul24((int)((uint32_t)r.v[c].x + (uint32_t)r.s[c].x - 2u * (uint32_t)f.x),
+                                (int)((uint32_t)r.s[c].y - (uint32_t)r.v[c].y));
+    }
+  }
+};
+// twice the signed area modulo 2^64 of a lane's edges
+__device__ __forceinline__ uint64_t wide_area(const RowChunk& r) {
+  uint64_t t = 0;
+  for (int c = 0; c < kRowChunks; ++c)
+    t += (uint64_t)((int64_t)r.v[c].x * r.s[c].y) - (uint64_t)((int64_t)r.s[c].x * r.v[c].y);
+  return t;
+}
+template <int kLanes>
+__device__ __forceinline__ uint64_t lanes_sum64(uint64_t v) {
+  for (int d = 1; d < kLanes; d <<= 1) {
     const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, d, kWave);
     const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), d, kWave);
     v += ((uint64_t)hi << 32) | lo;
   }
   return v;
 }
+__device__ __forceinline__ int64_t half_size(int64_t t) { return (int64_t)((t < 0 ? 0 - (uint64_t)t : (uint64_t)t) / 2); }
+__device__ __forceinline__ bool narrow(const Meta& m) {
+  return side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide;
+}
+
+__device__ __forceinline__ bool beyond(const Meta& m) {
+  return m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord;
+}
+
+// A ring's results, by its first lane.
+template <bool kArea>
+__device__ __forceinline__ void put_meta(const RingOf& g, const Meta& m, bool bad, int64_t area, Meta* metaA,
+                                         int64_t* areaA, Meta* metaB, int64_t* areaB, uint32_t* err) {
+  if (bad) latch_error(err, kErrCoord);
+  Meta* to = g.second ? metaB : metaA;
+  *reinterpret_cast<int4*>(to + g.k) =
+      bad || g.nv <= 0 ? make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN) : make_int4(m.x0, m.y0, m.x1, m.y1);
+  int64_t* areas = g.second ? areaB : areaA;
+  if (kArea) areas[g.k] = area;
+}
+// A ring on the 16 lanes of a row (lane j of it), `on` or an idle row.
+template <bool kArea>
+__device__ __forceinline__ void row_meta(const RingOf& g, bool on, int j, Meta* metaA, int64_t* areaA, Meta* metaB,
+                                         int64_t* areaB, uint32_t* err) {
+  const int64_t nv = on ? g.nv : 0;
+  RingAcc acc;
+  int2 f = make_int2(0, 0);
+  if (kArea && nv > 0) f = g.R[0];
+  for (int64_t base = 0; base < nv; base += kRowStep) acc.add<kArea>(row_load<kArea>(g.R, nv, base, j), f);
+  const Meta m{row_min(acc.x0), row_min(acc.y0), ~row_min(acc.nx1), ~row_min(acc.ny1)};
+  const bool bad = nv > 0 && beyond(m);
+  int64_t area = 0;
+  if (kArea && nv > 0 && !bad) {
+    if (narrow(m)) {
+      area = half_size((int32_t)row_sum(acc.tn));
+    } else {
+      uint64_t tw = 0;
+      for (int64_t base = 0; base < nv; base += kRowStep) tw += wide_area(row_load<true>(g.R, nv, base, j));
+      area = half_size((int64_t)lanes_sum64<kRow>(tw));
+    }
+  }
+  if (j == 0 && on) put_meta<kArea>(g, m, bad, area, metaA, areaA, metaB, areaB, err);
+}
+// A short ring on the four lanes of a quad.
+template <bool kArea>
+__device__ __forceinline__ void quad_meta(const RingOf& g, bool on, int j, Meta* metaA, int64_t* areaA, Meta* metaB,
+                                          int64_t* areaB, uint32_t* err) {
+  const int64_t nv = on ? g.nv : 0;
+  RingAcc acc;
+  int2 f = make_int2(0, 0);
+  if (kArea && nv > 0) f = g.R[0];
+  for (int64_t base = 0; base < nv; base += kQuadStep) acc.add<kArea>(quad_load<kArea>(g.R, nv, base, j), f);
+  const Meta m{quad_min(acc.x0), quad_min(acc.y0), ~quad_min(acc.nx1), ~quad_min(acc.ny1)};
+  const bool bad = nv > 0 && beyond(m);
+  int64_t area = 0;
+  if (kArea && nv > 0 && !bad) {
+    if (narrow(m)) {
+      int t = (int)acc.tn;
+      t += __builtin_amdgcn_update_dpp(0, t, 0xb1, 0xf, 0xf, false);
+      t += __builtin_amdgcn_update_dpp(0, t, 0x4e, 0xf, 0xf, false);
+      area = half_size(t);
+    } else {
+      uint64_t tw = 0;
+      for (int64_t base = 0; base < nv; base += kQuadStep) tw += wide_area(quad_load<true>(g.R, nv, base, j));
+      area = half_size((int64_t)lanes_sum64<4>(tw));
+    }
+  }
+  if (j == 0 && on) put_meta<kArea>(g, m, bad, area, metaA, areaA, metaB, areaB, err);
+}
+
+// Rings with few vertices on average: the workgroups below `quads` take 64 of a
+// wave at a time, 16 at once on the four lanes of a quad each, and the others
+// none.  f(ring, on) is called by the quads.
+__device__ __forceinline__ bool mostly_short(int64_t verts, int64_t rings, int most) { return verts <= most * rings; }
+template <typename F>
+__device__ __forceinline__ void on_quads(const Polys& A, const Polys& B, unsigned quads, F f) {
+  const int64_t n = A.n + B.n;
+  if (blockIdx.x >= quads) return;
+  for (int64_t k0 = uniform64((int64_t)blockIdx.x * 256 + threadIdx.x / kWave * kWave); k0 < n;
+       k0 = uniform64(k0 + (int64_t)quads * 256))
+#pragma unroll 1
+    for (int i = 0; i < kWave && k0 + i < n; i += kWave / 4) {
+      const int64_t at = k0 + i + lane_id() / 4;
+      f(RingOf(A, B, min(at, n - 1)), at < n);
+    }
+}
+// Where a launch looks at the average at all (fewer rings take as long in rows).
+unsigned quad_blocks(int64_t n) { return n >= int64_t(1) << 17 ? blocks_of(n, 256) : 0u; }
 
 // Extents, and kArea |shoelace|/2 (Section 3.2's area formula), of the rings
 // of one or two sets.  Twice the signed area is summed as (x + x') (y' - y)
@@ -74,70 +239,35 @@ __device__ __forceinline__ uint64_t row_sum64(uint64_t v) {
 // ring at most kMaxSide wide and tall; a larger one has it summed again
 // modulo 2^64, in which twice the area (at most 2^63 in size) is exact.
 template <bool kArea>
-__global__ void __launch_bounds__(256) k_meta_rows(Polys A, Meta* metaA, int64_t* areaA, Polys B, Meta* metaB,
-                                                   int64_t* areaB, uint32_t* err) {
-  const int j = (int)(threadIdx.x % kRow);
-  for (int64_t k0 = (int64_t)blockIdx.x * kRowRings; k0 < A.n + B.n; k0 += (int64_t)gridDim.x * kRowRings) {
-    int64_t k = k0 + threadIdx.x / kRow;
-    const bool second = k >= A.n;
-    if (second) k -= A.n;
-    if (second && k >= B.n) continue;
-    const int64_t* off = second ? B.off : A.off;
-    const int64_t o = off[k], nv = off[k + 1] - o;
-    const int2* R = (second ? B.xy : A.xy) + o;
-    int32_t x0 = INT_MAX, y0 = INT_MAX, nx1 = INT_MAX, ny1 = INT_MAX;
-    uint32_t tn = 0;
-    int2 f = make_int2(0, 0);
-    if (kArea && nv > 0) f = R[0];
-    for (int64_t base = 0; base < nv; base += kRowStep) {
-      const RowChunk r = row_load<kArea>(R, nv, base, j);
-  #pragma unroll
-      for (int c = 0; c < kRowChunks; ++c) {
-        x0 = min(x0, r.v[c].x);
-        y0 = min(y0, r.v[c].y);
-        nx1 = min(nx1, ~r.v[c].x);
-        ny1 = min(ny1, ~r.v[c].y);
-        if (kArea)
-          tn += (uint32_t)__mul24((int)((uint32_t)r.v[c].x + (uint32_t)r.s[c].x - 2u * (uint32_t)f.x),
-                                  (int)((uint32_t)r.s[c].y - (uint32_t)r.v[c].y));
-      }
-    }
-    const Meta m{row_min(x0), row_min(y0), ~row_min(nx1), ~row_min(ny1)};
-    const bool empty = nv <= 0;
-    const bool bad = !empty && (m.x0 < -kMaxCoord || m.y0 < -kMaxCoord || m.x1 > kMaxCoord || m.y1 > kMaxCoord);
-    int64_t area = 0;
-    if (kArea && !empty && !bad) {
-      if (side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide) {
-        const int32_t t = (int32_t)row_sum(tn);
-        area = (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
-      } else {
-        uint64_t tw = 0;
-        for (int64_t base = 0; base < nv; base += kRowStep) {
-          const RowChunk r = row_load<true>(R, nv, base, j);
-          for (int c = 0; c < kRowChunks; ++c)
-            tw += (uint64_t)((int64_t)r.v[c].x * r.s[c].y) - (uint64_t)((int64_t)r.s[c].x * r.v[c].y);
-        }
-        const uint64_t t = row_sum64(tw);
-        area = (int64_t)(((int64_t)t < 0 ? 0 - t : t) / 2);
-      }
-    }
-    if (j != 0) continue;
-    if (bad) latch_error(err, kErrCoord);
-    const bool none = empty || bad;
-    *reinterpret_cast<int4*>((second ? metaB : metaA) + k) =
-        none ? make_int4(INT_MAX, INT_MAX, INT_MIN, INT_MIN) : make_int4(m.x0, m.y0, m.x1, m.y1);
-    if (kArea) (second ? areaB : areaA)[k] = area;
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
+k_meta_rows(Polys A, Meta* metaA, int64_t* areaA, Polys B, Meta* metaB, int64_t* areaB, uint32_t* err, unsigned quads) {
+  const int64_t n = A.n + B.n;
+  if (quads && mostly_short(A.off[A.n] + B.off[B.n], n, kShortMeta)) {
+    on_quads(A, B, quads, [&](const RingOf& g, bool on) {
+      quad_meta<kArea>(g, on, lane_id() & 3, metaA, areaA, metaB, areaB, err);
+    });
+    return;
+  }
+  for (int64_t k0 = (int64_t)blockIdx.x * kRowRings; k0 < n; k0 += (int64_t)gridDim.x * kRowRings) {
+    const int64_t at = k0 + threadIdx.x / kRow;
+    if (at < n) row_meta<kArea>(RingOf(A, B, at), true, threadIdx.x % kRow, metaA, areaA, metaB, areaB, err);
   }
 }
 
+template <bool kArea>
+void launch_meta(const Polys& A, Meta* metaA, int64_t* areaA, const Polys& B, Meta* metaB, int64_t* areaB, uint32_t* err,
+                 hipStream_t s) {
+  const int64_t n = A.n + B.n;
+  hipLaunchKernelGGL(k_meta_rows<kArea>, dim3(blocks_of(n, kRowRings)), dim3(256), 0, s, A, metaA, areaA, B, metaB, areaB,
+                     err, quad_blocks(n));
+}
 hipError_t launch_poly_meta(const Polys& A, Meta* metaA, int64_t* areaA, const Polys& B, Meta* metaB, int64_t* areaB,
                             uint32_t* err, hipStream_t s) {
   if (A.n + B.n <= 0) return hipSuccess;
-  const unsigned blocks = blocks_of(A.n + B.n, kRowRings);
   if (areaA)
-    hipLaunchKernelGGL(k_meta_rows<true>, dim3(blocks), dim3(256), 0, s, A, metaA, areaA, B, metaB, areaB, err);
+    launch_meta<true>(A, metaA, areaA, B, metaB, areaB, err, s);
   else
-    hipLaunchKernelGGL(k_meta_rows<false>, dim3(blocks), dim3(256), 0, s, A, metaA, areaA, B, metaB, areaB, err);
+    launch_meta<false>(A, metaA, areaA, B, metaB, areaB, err, s);
   return hipGetLastError();
 }
 
@@ -146,25 +276,37 @@ hipError_t launch_poly_meta(const Polys& A, Meta* metaA, int64_t* areaA, const P
 // and what is left when there is none
 __global__ void k_validate_init(unsigned long long* first_bad) { *first_bad = ~0ull; }
 
-__global__ void __launch_bounds__(256) k_validate(Polys P, unsigned long long* first_bad) {
-  const int j = (int)(threadIdx.x % kRow);
+// the smallest bad ring of a wave's lanes, whose rings k stand in order
+__device__ __forceinline__ void report_bad(bool bad, int64_t k, unsigned long long* first_bad) {
+  const uint64_t m = ballot(bad);
+  if (m && lane_id() == __ffsll((long long)m) - 1 &&
+      (unsigned long long)k < __hip_atomic_load(first_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMin(first_bad, (unsigned long long)k);
+}
+__device__ __forceinline__ bool slanted(const RowChunk& r) {
+  bool bad = false;
+#pragma unroll
+  for (int c = 0; c < kRowChunks; ++c) bad |= (r.v[c].x != r.s[c].x) & (r.v[c].y != r.s[c].y);
+  return bad;
+}
+__global__ void __launch_bounds__(256) k_validate(Polys P, unsigned long long* first_bad, unsigned quads) {
+  if (quads && mostly_short(P.off[P.n], P.n, kShortValidate)) {
+    on_quads(P, Polys{}, quads, [&](const RingOf& g, bool on) {
+      bool bad = g.nv < 4;
+      for (int64_t base = 0; base < g.nv; base += kQuadStep) bad |= slanted(quad_load<true>(g.R, g.nv, base, lane_id() & 3));
+      report_bad(on && bad, g.k, first_bad);
+    });
+    return;
+  }
   for (int64_t k0 = (int64_t)blockIdx.x * kRowRings; k0 < P.n; k0 += (int64_t)gridDim.x * kRowRings) {
     const int64_t k = k0 + threadIdx.x / kRow;
     bool bad = false;
     if (k < P.n) {
       const int64_t o = P.off[k], nv = P.off[k + 1] - o;
       bad = nv < 4;
-      for (int64_t base = 0; base < nv; base += kRowStep) {
-        const RowChunk r = row_load<true>(P.xy + o, nv, base, j);
-#pragma unroll
-        for (int c = 0; c < kRowChunks; ++c) bad |= (r.v[c].x != r.s[c].x) & (r.v[c].y != r.s[c].y);
-      }
+      for (int64_t base = 0; base < nv; base += kRowStep) bad |= slanted(row_load<true>(P.xy + o, nv, base, threadIdx.x % kRow));
     }
-    // the wave's rings stand in order: its first bad lane has its smallest index
-    const uint64_t m = ballot(bad);
-    if (m && lane_id() == __ffsll((long long)m) - 1 &&
-        (unsigned long long)k < __hip_atomic_load(first_bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMin(first_bad, (unsigned long long)k);
+    report_bad(bad, k, first_bad);
   }
 }
 
@@ -172,7 +314,7 @@ hipError_t launch_validate(const Polys& P, int64_t* first_bad, hipStream_t s) {
   auto* fb = reinterpret_cast<unsigned long long*>(first_bad);
   hipLaunchKernelGGL(k_validate_init, dim3(1), dim3(1), 0, s, fb);
   if (P.n > 0)
-    hipLaunchKernelGGL(k_validate, dim3(blocks_of(P.n, kRowRings)), dim3(256), 0, s, P, fb);
+    hipLaunchKernelGGL(k_validate, dim3(blocks_of(P.n, kRowRings)), dim3(256), 0, s, P, fb, quad_blocks(P.n));
   return hipGetLastError();
 }
 
