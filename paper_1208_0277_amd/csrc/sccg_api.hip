@@ -73,7 +73,8 @@ struct sccg_ctx {
   int32_t* j_found = nullptr;
   int64_t* j_host = nullptr;                     // the sizes a join found, in pinned host memory
   int64_t* j_sizes = nullptr;                    // its device address
-  int64_t j_cells_seen = 0, j_entries_seen = 0;  // the most that a call had
+  int64_t j_cells_seen = 0, j_entries_seen = 0;  // what a call is launched for (see sccg_join_sets)
+  int64_t j_cells_recent = 0, j_calls = 0;
   bool j_dirty = true;                           // j_count may hold counts of a call that did not end
   unsigned char* j_acc = nullptr;  // the waves' sums of sccg_jaccard_sets
   int64_t j_cap[12] = {};
@@ -850,7 +851,8 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
   // Room for the cells and for the entries in them, which are only known when
   // the kernels have run: what earlier calls took, or a first guess (objects
   // a cell apart, each in four of them); what turns out too small grows, and
-  // the kernels run again.
+  // the kernels run again.  The cells also size the launches of their scan, so
+  // they are the most of the last 16 to 32 calls; the entries size memory only.
   int64_t cells = std::max(c->j_cells_seen, A->n_polys + n_sets + 1024);
   int64_t entries = std::max(c->j_entries_seen, 4 * A->n_polys + 1024);
   for (;;) {
@@ -897,6 +899,11 @@ int sccg_join_sets(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64_
     if (n_cells <= cells && n_entries <= c->j_cap[9]) {
       c->j_dirty = false;
       c->j_cells_seen = std::max(c->j_cells_seen, n_cells);
+      c->j_cells_recent = std::max(c->j_cells_recent, n_cells);
+      if (++c->j_calls % 16 == 0) {
+        c->j_cells_seen = c->j_cells_recent;
+        c->j_cells_recent = 0;
+      }
       c->j_entries_seen = std::max(c->j_entries_seen, n_entries);
       *out_total = c->j_host[2];
       return SCCG_OK;

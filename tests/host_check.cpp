@@ -69,6 +69,38 @@ static void join_out_of_memory() {
   }
 }
 
+// A join is launched for the cells that it and the calls shortly before it have:
+// small ones after a large one are soon launched as small again, and a large one
+// every other call is not run twice.
+static void join_launch_sizes() {
+  unsigned scan = 0;  // workgroups of the scan of the cells' counts
+  long runs = 0;
+  fake.on_launch = [&](const Launch& l) {
+    watch_join(l);
+    if (l.is("k_scan_write") || l.is("k_scan_one")) {
+      if (l.is("ILb1E")) scan = l.grid;
+    }
+    if (l.is("k_join_write")) runs += 1;
+  };
+  sccg_ctx* c = nullptr;
+  EXPECT(sccg_create(&c, 0, nullptr, nullptr) == SCCG_OK, "create");
+  EXPECT(join(c, 2000, 900, 4000) == SCCG_OK && scan == 1, "%u workgroups for a small join", scan);
+  EXPECT(join(c, 2000, 10000000, 4000) == SCCG_OK, "large join");
+  EXPECT(scan > 1000, "%u workgroups for a large join", scan);
+  const long before = runs;
+  for (int k = 0; k < 40; ++k) EXPECT(join(c, 2000, 900, 4000) == SCCG_OK, "small join");
+  EXPECT(scan == 1, "%u workgroups for the 40th small join", scan);
+  EXPECT(runs == before + 40, "%ld runs of 40 joins", runs - before);
+  EXPECT(join(c, 2000, 10000000, 4000) == SCCG_OK, "large join");
+  const long pairs = runs;
+  for (int k = 0; k < 50; ++k) {
+    EXPECT(join(c, 2000, 900, 4000) == SCCG_OK, "small join");
+    EXPECT(join(c, 2000, 10000000, 4000) == SCCG_OK, "large join");
+  }
+  EXPECT(runs == pairs + 100, "%ld runs of a hundred joins", runs - pairs);
+  sccg_destroy(c);
+}
+
 // A refused allocation is reported once: the next call of any kind works.
 static void errors_are_reported_once() {
   fake.on_launch = watch_join;
@@ -197,6 +229,7 @@ int main(int argc, char** argv) {
     void (*run)();
   } checks[] = {
       {"join_out_of_memory", join_out_of_memory},
+      {"join_launch_sizes", join_launch_sizes},
       {"errors_are_reported_once", errors_are_reported_once},
       {"tiles_out_of_memory", tiles_out_of_memory},
       {"launches_within_a_dispatch", launches_within_a_dispatch},

@@ -30,7 +30,7 @@ def check(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("name", ["join_out_of_memory", "errors_are_reported_once", "tiles_out_of_memory",
+@pytest.mark.parametrize("name", ["join_out_of_memory", "join_launch_sizes", "errors_are_reported_once", "tiles_out_of_memory",
                                   "tiles_tried_again_with_new_parameters", "launches_within_a_dispatch"])
 def test_host_side(check, name):
     r = subprocess.run([check, name], capture_output=True, text=True, timeout=120)
