@@ -296,9 +296,11 @@ __global__ void __launch_bounds__(kFewThreads) k_join_grid_few(Polys A, const Me
   set_grids<kFewThreads>(n_sets, boxes, cell, grid, base, err, sh);
 }
 
-// out[i] = sum of the first i of in[0], in[kStride], ... for i <= n, n read from device memory when n_ptr
-// is given (nothing is done when it exceeds `room`): block totals, then every
-// block adds the totals before its own.
+// out[i] = sum of the first i of in[0], in[kStride], ... for i <= n, n read
+// from device memory when n_ptr is given (nothing is done when it exceeds
+// `room`): block totals, then every block adds the totals before its own, or,
+// of more than kSumsApart blocks, takes their sum from a scan of the totals in
+// between.
 __device__ __forceinline__ int64_t scan_size(int64_t n, const int64_t* n_ptr, int64_t room) {
   if (n_ptr) n = *n_ptr;
   return n > room ? -1 : n;
@@ -319,17 +321,50 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_totals(const int32_t* in,
   block_exclusive(tot, sh, &total);
   if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
-// kClear: `in` is zeroed behind the scan.
-template <bool kClear, int kStride>
+// Every block reading half the totals is what a scan of them costs at 16,384
+// blocks of 2048 counts (the writing pass alone / with the totals' scan: 8M
+// counts 67 / 73 us, 16M 127 / 137, 32M 260 / 259, 128M 1554 / 1028).
+constexpr int64_t kSumsApart = 16384;
+// The blocks' totals turned into the sums before them, by one workgroup.
+constexpr int kOneThreads = 1024;
+__global__ void __launch_bounds__(kOneThreads) k_scan_sums(int64_t n, const int64_t* n_ptr, int64_t room, int64_t* sums) {
+  __shared__ int64_t sh[kOneThreads / kWave];
+  n = scan_size(n, n_ptr, room);
+  const int64_t blocks = n < 0 ? 0 : n / kScanBlock + 1;
+  int64_t run = 0;
+  for (int64_t b0 = 0; b0 < blocks; b0 += kOneThreads * kScanPer) {
+    const int64_t i0 = b0 + (int64_t)threadIdx.x * kScanPer;
+    int64_t v[kScanPer], tot = 0, total;
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      v[k] = i0 + k < blocks ? sums[i0 + k] : 0;
+      tot += v[k];
+    }
+    int64_t at = run + block_exclusive<kOneThreads>(tot, sh, &total);
+#pragma unroll
+    for (int k = 0; k < kScanPer; ++k) {
+      if (i0 + k < blocks) sums[i0 + k] = at;
+      at += v[k];
+    }
+    run += total;
+  }
+}
+// kClear: `in` is zeroed behind the scan; kSummed: the totals have been scanned.
+template <bool kClear, int kStride, bool kSummed>
 __global__ void __launch_bounds__(kScanThreads) k_scan_write(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room,
                                                              const int64_t* sums, int64_t* out) {
   __shared__ int64_t sh[kScanThreads / kWave];
   n = scan_size(n, n_ptr, room);
   const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
   if (b0 > n) return;  // the block that holds entry n writes the total
-  int64_t mine = 0, before;
-  for (int64_t k = threadIdx.x; k < (int64_t)blockIdx.x; k += kScanThreads) mine += sums[k];
-  block_exclusive(mine, sh, &before);
+  int64_t before;
+  if (kSummed) {
+    before = sums[blockIdx.x];
+  } else {
+    int64_t mine = 0;
+    for (int64_t k = threadIdx.x; k < (int64_t)blockIdx.x; k += kScanThreads) mine += sums[k];
+    block_exclusive(mine, sh, &before);
+  }
   const int64_t i0 = b0 + (int64_t)threadIdx.x * kScanPer;
   int32_t v[kScanPer];
   int64_t tot = 0, total;
@@ -347,7 +382,6 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_write(int32_t* in, int64_
   }
 }
 // The whole scan by one workgroup.
-constexpr int kOneThreads = 1024;
 constexpr int64_t kOneScan = 2 * kOneThreads * kScanPer;
 template <bool kClear, int kStride>
 __global__ void __launch_bounds__(kOneThreads) k_scan_one(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room,
@@ -383,7 +417,12 @@ void launch_scan(int32_t* in, int64_t n, const int64_t* n_ptr, int64_t room, int
   }
   const dim3 g((unsigned)scan_scratch(room)), b(kScanThreads);
   hipLaunchKernelGGL(k_scan_totals<kStride>, g, b, 0, s, in, n, n_ptr, room, sums);
-  hipLaunchKernelGGL((k_scan_write<kClear, kStride>), g, b, 0, s, in, n, n_ptr, room, sums, out);
+  if (scan_scratch(room) > kSumsApart) {
+    hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kOneThreads), 0, s, n, n_ptr, room, sums);
+    hipLaunchKernelGGL((k_scan_write<kClear, kStride, true>), g, b, 0, s, in, n, n_ptr, room, sums, out);
+  } else {
+    hipLaunchKernelGGL((k_scan_write<kClear, kStride, false>), g, b, 0, s, in, n, n_ptr, room, sums, out);
+  }
 }
 
 // ------------------------------------------------------------------- entries
