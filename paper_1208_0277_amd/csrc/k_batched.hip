@@ -1463,7 +1463,7 @@ k_tile_pairs(BatchArgs args) {
     if (quick) {
       const uint32_t n = pairs[lane].n;
       a.inter[i] = (int64_t)n;
-      a.uni[i] = (int64_t)(areas - n);
+      a.uni[i] = (int64_t)(int32_t)(areas - n);  // signed: see k_batch_sweep
     }
     wave_sync_lds();
   }
@@ -1710,7 +1710,9 @@ k_batch_sweep(BatchArgs args) {
     if (lane_in(finished)) {
       const uint32_t n = kPairBox ? out_i : out_i >> 17;
       a.inter[i] = (int64_t)n;
-      a.uni[i] = (int64_t)(kPairBox ? out_u : (out_i & 0xffffu) - n);
+      // |p| + |q| - I below 2^31, and below 0 where a ring's loops cancel in its
+      // area (no simple ring's do)
+      a.uni[i] = kPairBox ? (int64_t)(int32_t)out_u : (int64_t)((out_i & 0xffffu) - n);
     }
     const uint64_t listed = ballot(medium || (sweep && !lane_in(finished)));
     const int st = (int)(blockIdx.x % (unsigned)kStreams);

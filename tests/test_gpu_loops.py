@@ -1,0 +1,45 @@
+"""Rings that are not simple, which validation does not look for: their areas are
+the sums of their loops, the same through every path (loops that cancel leave
+|p| + |q| - I below 0)."""
+
+import numpy as np
+import pytest
+
+import paper_1208_0277_amd as sccg
+from sccg_gen import concat
+from tests.gpu_util import device_workload, run
+
+pytestmark = pytest.mark.gpu
+
+#: an eight of two squares of side 20, one run through clockwise: no area, 800 pixels
+EIGHT = np.array([(0, 0), (20, 0), (20, 40), (40, 40), (40, 20), (0, 20)], np.int32)
+
+
+def _area(ring):
+    x, y = ring[:, 0].astype(object), ring[:, 1].astype(object)
+    return abs(int((x * np.roll(y, -1) - y * np.roll(x, -1)).sum())) // 2
+
+
+@pytest.mark.parametrize("n", [200, 60000])
+def test_loops_that_cancel(n):
+    """Pairs whose union exceeds a tile, so that U comes from the areas: own
+    tiles pair by pair and made beforehand (more pairs than rings), pair boxes
+    of rings that no tile holds, the medium sweep and PLAIN."""
+    wide = EIGHT * (4, 1)  # 160 wide
+    rings = [EIGHT, EIGHT + (35, 25), EIGHT + (30, -30), wide, wide + (20, 10)]
+    P = concat(rings)
+    pa, pb = np.meshgrid(np.arange(5), np.arange(5))
+    pa, pb = (np.resize(v.ravel(), n).astype(np.int32) for v in (pa, pb))
+    assert all(_area(r) == 0 for r in rings)
+    got = {}
+    for name, mode, params in (("plain", sccg.SCCG_PLAIN, {}), ("medium", sccg.SCCG_BATCHED, {"flags": sccg.SCCG_F_NO_UNION_TILE}),
+                               ("pair box", sccg.SCCG_BATCHED, {"flags": sccg.SCCG_F_NO_UNION_TILE, "sweep_pair_box": 2})):
+        c = sccg.Context(0, **params)
+        try:
+            got[name] = run(c, device_workload(P, P, pa, pb), mode)
+        finally:
+            c.close()
+    I, U = got["plain"]
+    assert I.max() > 0 and np.array_equal(U, -I)
+    for name, (i, u) in got.items():
+        assert np.array_equal(i, I) and np.array_equal(u, U), name
