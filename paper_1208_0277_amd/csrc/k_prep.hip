@@ -145,8 +145,11 @@ __device__ __forceinline__ uint64_t lanes_sum64(uint64_t v) {
   return v;
 }
 __device__ __forceinline__ int64_t half_size(int64_t t) { return (int64_t)((t < 0 ? 0 - (uint64_t)t : (uint64_t)t) / 2); }
-__device__ __forceinline__ bool narrow(const Meta& m) {
-  return side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide;
+// Whether twice a ring's signed area fits 32 bits and its terms 24: a ring of nv
+// vertices runs at most nv / 2 times around any pixel of its extent.
+__device__ __forceinline__ bool narrow(const Meta& m, int64_t nv) {
+  const uint32_t w = side_u(m.x0, m.x1), h = side_u(m.y0, m.y1);
+  return max(w, h) <= (uint32_t)kMaxSide && (uint64_t)nv * (w * h) < (uint64_t)1 << 31;
 }
 
 __device__ __forceinline__ bool beyond(const Meta& m) {
@@ -177,7 +180,7 @@ __device__ __forceinline__ void row_meta(const RingOf& g, bool on, int j, Meta* 
   const bool bad = nv > 0 && beyond(m);
   int64_t area = 0;
   if (kArea && nv > 0 && !bad) {
-    if (narrow(m)) {
+    if (narrow(m, nv)) {
       area = half_size((int32_t)row_sum(acc.tn));
     } else {
       uint64_t tw = 0;
@@ -200,7 +203,7 @@ __device__ __forceinline__ void quad_meta(const RingOf& g, bool on, int j, Meta*
   const bool bad = nv > 0 && beyond(m);
   int64_t area = 0;
   if (kArea && nv > 0 && !bad) {
-    if (narrow(m)) {
+    if (narrow(m, nv)) {
       int t = (int)acc.tn;
       t += __builtin_amdgcn_update_dpp(0, t, 0xb1, 0xf, 0xf, false);
       t += __builtin_amdgcn_update_dpp(0, t, 0x4e, 0xf, 0xf, false);
@@ -235,9 +238,9 @@ unsigned quad_blocks(int64_t n) { return n >= int64_t(1) << 17 ? blocks_of(n, 25
 
 // Extents, and kArea |shoelace|/2 (Section 3.2's area formula), of the rings
 // of one or two sets.  Twice the signed area is summed as (x + x') (y' - y)
-// over the edges, x relative to the first vertex, modulo 2^32: exact for a
-// ring at most kMaxSide wide and tall; a larger one has it summed again
-// modulo 2^64, in which twice the area (at most 2^63 in size) is exact.
+// over the edges, x relative to the first vertex, modulo 2^32 where that holds
+// it (see narrow); else again modulo 2^64, in which it (at most 2^63 in size)
+// is exact.
 template <bool kArea>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
 k_meta_rows(Polys A, Meta* metaA, int64_t* areaA, Polys B, Meta* metaB, int64_t* areaB, uint32_t* err, unsigned quads) {

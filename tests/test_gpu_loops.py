@@ -43,3 +43,27 @@ def test_loops_that_cancel(n):
     assert I.max() > 0 and np.array_equal(U, -I)
     for name, (i, u) in got.items():
         assert np.array_equal(i, I) and np.array_equal(u, U), name
+
+
+@pytest.mark.parametrize("turns,side", [(2, 30000), (3, 32767), (40, 9000)])
+def test_loops_that_add_up(turns, side):
+    """A square run through several times: twice its area exceeds 32 bits.  U of
+    PLAIN, and the relations of the square with as many pixels."""
+    import torch
+    square = np.array([(0, 0), (side, 0), (side, side), (0, side)], np.int32) - 11
+    wound = np.tile(square, (turns, 1))
+    small = np.array([(5, 5), (25, 5), (25, 30), (5, 30)], np.int32)
+    P, Q = concat([wound, small]), concat([small, wound])
+    area = _area(wound)
+    assert area == turns * side * side
+    inside = 500 * (turns % 2)
+    work = device_workload(P, Q, np.arange(2, dtype=np.int32), np.arange(2, dtype=np.int32))
+    c = sccg.Context(0)
+    try:
+        I, U = run(c, work, sccg.SCCG_PLAIN)
+        assert I.tolist() == [inside] * 2 and U.tolist() == [area + 500 - inside] * 2
+        got = c.relate_pairs(*work, torch.full((2,), area, dtype=torch.int64, device="cuda"))
+        c.sync()
+        assert got.tolist() == [sccg.SCCG_REL_INTERSECTS | sccg.SCCG_REL_WITHIN, sccg.SCCG_REL_INTERSECTS | sccg.SCCG_REL_CONTAINS]
+    finally:
+        c.close()
