@@ -1817,16 +1817,16 @@ __device__ __forceinline__ int64_t ring_area_wide(const int2* xy, int64_t o, int
 }
 
 // Extent and area of a non-empty ring from its lanes' extents and doubled
-// areas (see ring_pass).  A ring with a coordinate beyond 2^30 sets `bad` and
-// covers nothing.
+// areas (see ring_pass), which are summed again if a side exceeds `narrow`.  A
+// ring with a coordinate beyond 2^30 sets `bad` and covers nothing.
 __device__ __forceinline__ void ring_meta(const int2* xy, int64_t o, int nv, int lane, const Ext& lanes, uint32_t tn,
-                                          Meta& m, int64_t& area, bool& bad) {
+                                          uint32_t narrow, Meta& m, int64_t& area, bool& bad) {
   m = meta_of(wave_min4(lanes));
   bad = out_of_range(m);
   if (bad) {
     m = Meta{INT_MAX, INT_MAX, INT_MIN, INT_MIN};
     area = 0;
-  } else if (side_u(m.x0, m.x1) <= (uint32_t)kMaxSide && side_u(m.y0, m.y1) <= (uint32_t)kMaxSide) {
+  } else if (max(side_u(m.x0, m.x1), side_u(m.y0, m.y1)) <= narrow) {
     const int32_t t = (int32_t)wave_sum_u32(tn);
     area = (t < 0 ? -(int64_t)t : (int64_t)t) / 2;
   } else {
@@ -2095,7 +2095,7 @@ __device__ __forceinline__ bool medium_one(Ctx& c, const PairRec& s, const PairR
     uint32_t tn = 0;
     const uint32_t carry = __builtin_amdgcn_readlane(d[kMediumChunks - 1].x, kWave - 1) == f.x ? 1u : 0u;
     const uint32_t corners = ring_pass<kMediumChunks>(d, nv, lane, f, carry, e, tn);
-    ring_meta(xy, o, nv, lane, e, tn, m, area, bad);
+    ring_meta(xy, o, nv, lane, e, tn, kMaxSide, m, area, bad);
     return corners;
   };
   const uint32_t cp = meta(r.p, a.A.xy, s.op, s.np, mp, ap, bp);
@@ -2194,7 +2194,8 @@ __device__ __forceinline__ bool long_one(Ctx& c, int64_t i, int w, uint64_t* tea
         tn += rs.valid() ? t : 0u;
       } while (rs.next());
     }
-    ring_meta(xy, o, nv, lane, e, tn, m, area, bad);
+    // sides from 2^14 on in 64 bits: a long ring may run around its pixels often
+    ring_meta(xy, o, nv, lane, e, tn, (1u << 14) - 1u, m, area, bad);
   }
   if (lane == 0) ex[w] = TeamRing{m, area, nv, bad ? 1 : 0};
   __syncthreads();

@@ -67,3 +67,20 @@ def test_loops_that_add_up(turns, side):
         assert got.tolist() == [sccg.SCCG_REL_INTERSECTS | sccg.SCCG_REL_WITHIN, sccg.SCCG_REL_INTERSECTS | sccg.SCCG_REL_CONTAINS]
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("side", [16384, 20000, 32767])
+def test_long_rings_that_add_up(side):
+    """The same of 320 and 1200 vertices in BATCHED calls."""
+    square = np.array([(0, 0), (side, 0), (side, side), (0, side)], np.int32) - 11
+    small = np.array([(5, 5), (25, 5), (25, 30), (5, 30)], np.int32)
+    rings = [np.tile(square, (turns, 1)) for turns in (81, 300)]
+    P, Q = concat(rings + [small] * 2), concat([small] * 2 + rings)
+    area = [_area(r) + 500 - 500 * (len(r) // 4 % 2) for r in rings]
+    idx = np.arange(4, dtype=np.int32)
+    c = sccg.Context(0)
+    try:
+        I, U = run(c, device_workload(P, Q, idx, idx), sccg.SCCG_BATCHED)
+    finally:
+        c.close()
+    assert I.tolist() == [500, 0] * 2 and U.tolist() == area * 2
