@@ -183,3 +183,71 @@ def test_server_with_more_pairs_than_rings():
             assert np.array_equal(I, wI[k]) and np.array_equal(U, wU[k])
     finally:
         srv.close()
+
+
+def test_counters_with_tiles_made_beforehand():
+    """The counting instances of the kernels that make and use all rings' tiles:
+    the oracle's counts, and the counters of the same pairs taken in calls too
+    small for that (but for the vertices XORed into slots: each ring once)."""
+    rng = np.random.default_rng(11)
+
+    def rings(n, sizes):
+        out = []
+        for k in range(n):
+            w, h = int(rng.integers(3, 66)), int(rng.integers(3, 66))
+            g = _band_polygon(w, h, sizes[k % len(sizes)], 1 if k % 2 else -1, int(rng.integers(0, 90)), int(rng.integers(0, 90)))
+            out.append(_padded(band_ring(*g), sizes[k % len(sizes)]))
+        return out
+
+    A, B = concat(rings(150, (4, 12, 64, 65, 130, 192, 200))), concat(rings(90, (8, 40, 63, 128, 129, 190)))
+    n = 60000
+    pa, pb = np.meshgrid(np.arange(A.n), np.arange(B.n))
+    every = oracle.area_pairs(A, B, pa.ravel().astype(np.int32), pb.ravel().astype(np.int32), form=oracle.ROWS)
+    pick = rng.integers(0, A.n * B.n, n)
+    pa, pb = pa.ravel()[pick].astype(np.int32), pb.ravel()[pick].astype(np.int32)
+    dA, dB, tpa, tpb = device_workload(A, B, pa, pb)
+    c = sccg.Context(0, sweep_pair_box=2)
+    try:
+        c.set_stats(True)
+        I, U = run(c, (dA, dB, tpa, tpb), sccg.SCCG_BATCHED)
+        whole = c.get_stats()
+        parts = dict.fromkeys(whole, 0)
+        for k in range(0, n, 20000):
+            run(c, (dA, dB, tpa[k:k + 20000].contiguous(), tpb[k:k + 20000].contiguous()), sccg.SCCG_BATCHED)
+            parts = {key: parts[key] + v for key, v in c.get_stats().items()}
+    finally:
+        c.close()
+    assert_exact(I, U, every[0][pick], every[1][pick], "counters on, tiles beforehand")
+    assert whole["small_pairs"] + whole["large_pairs"] + whole["empty_pairs"] == n
+    verts = int((np.diff(A.off)[pa] + np.diff(B.off)[pb]).sum())
+    assert whole["ring_scan_vertices"] + whole["union_tile_vertices"] == verts
+    updates = "leaf_vertex_updates"
+    assert 0 < whole.pop(updates) < parts.pop(updates) and whole == parts
+
+
+def test_server_makes_no_tiles_of_its_arena():
+    """A server's set is its arena, of whose slots only the jobs' are valid.  A
+    job with more pairs than that has slots would have their tiles made: 700 MB
+    of scratch, which is not taken."""
+    import torch
+    rng = np.random.default_rng(6)
+    P = concat([rect_ring((int(x), int(y), int(x) + 20, int(y) + 30)) for x, y in rng.integers(0, 60, (64, 2))])
+    n = 1_200_000
+    pa, pb = (rng.integers(0, 64, n).astype(np.int32) for _ in range(2))
+    both = np.arange(64, dtype=np.int32)
+    wI, wU = oracle.area_pairs(P, P, np.repeat(both, 64), np.tile(both, 64))
+    srv = sccg.Server(0, params={"sweep_pair_box": 2}, vertex_cap=4096, slot_cap=1 << 19, pair_cap=1 << 21)
+    try:
+        I, U = np.zeros(n, np.int64), np.zeros(n, np.int64)
+        free = torch.cuda.mem_get_info()[0]
+        srv.submit(P.off, P.xy, P.off, P.xy, pa, pb, I, U)
+        done = []
+        while not done:
+            done = srv.poll(timeout=None)
+        taken = free - torch.cuda.mem_get_info()[0]
+        assert done[0]["status"] == sccg.SCCG_OK and done[0]["jobs_in_launch"] == 1
+        k = pa.astype(np.int64) * 64 + pb
+        assert np.array_equal(I, wI[k]) and np.array_equal(U, wU[k])
+        assert taken < 200 << 20, f"{taken >> 20} MB taken"
+    finally:
+        srv.close()
