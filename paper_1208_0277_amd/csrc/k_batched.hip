@@ -775,9 +775,8 @@ __device__ __forceinline__ PairInfo heavy_info(const BatchArgs& a, int64_t pair)
 
 // The list bucket of a pair with n vertices (largest first; one bucket when
 // the order is switched off).
-__device__ __forceinline__ int lpt_bucket(const BatchArgs& a, int64_t n) {
-  if (a.flags & SCCG_F_NO_LPT) return 0;
-  const int64_t h = a.heavy_verts;
+__device__ __forceinline__ int lpt_bucket(uint32_t flags, int64_t h, int64_t n) {
+  if (flags & SCCG_F_NO_LPT) return 0;
   return n >= 4 * h ? 3 : n >= 2 * h ? 2 : n >= h ? 1 : 0;
 }
 
@@ -946,6 +945,32 @@ struct ListParts {
   }
 };
 
+// The lists of all buckets and streams, taken as one, the largest bucket first:
+// lane L < kParts has that of stream L % kStreams of bucket kLptBuckets - 1 -
+// L / kStreams.
+constexpr int kParts = kLptBuckets * kStreams;
+struct BucketLists {
+  int first;    // where the lane's list begins in the whole
+  int64_t all;  // entries of all
+  __device__ __forceinline__ static int bucket(int part) { return kLptBuckets - 1 - part / kStreams; }
+  // length: of the lane's list (0 in the lanes from kParts on)
+  __device__ __forceinline__ BucketLists(int length, int lane) {
+    first = length;
+#pragma unroll
+    for (int d = 1; d < kParts; d <<= 1) {
+      const int v = __shfl_up(first, d, kWave);
+      if (lane >= d) first += v;
+    }
+    all = __builtin_amdgcn_readlane(first, kParts - 1);
+    first -= length;
+  }
+  // where entry k stands in lists of `cap` entries each
+  __device__ __forceinline__ int64_t at(int64_t k, int64_t cap, int lane) const {
+    const int part = kWave - 1 - __clzll((long long)ballot(lane < kParts && first <= (int)k));
+    return (int64_t)(bucket(part) * kStreams + part % kStreams) * cap + (k - __builtin_amdgcn_readlane(first, part));
+  }
+};
+
 // Both rings of a pair, as the pair arrays and the offsets give them.
 struct PairRec {
   int64_t op, oq;
@@ -967,9 +992,9 @@ __device__ __forceinline__ PairRec rec_of_lane(const PairRec& r, int j) {
 
 // Append each lane's value to a list, for the lanes in `m`, with one
 // reservation.
-__device__ __forceinline__ void list_append(Counter& count, int32_t* list, uint64_t m, int32_t value, int lane) {
+__device__ __forceinline__ void list_append(unsigned long long& count, int32_t* list, uint64_t m, int32_t value, int lane) {
   unsigned long long base = 0;
-  if (lane == 0) base = atomicAdd(&count.v, (unsigned long long)__popcll(m));
+  if (lane == 0) base = atomicAdd(&count, (unsigned long long)__popcll(m));
   base = (unsigned long long)uniform64((int64_t)__shfl((long long)base, 0, kWave));
   if (lane_in(m)) list[base + (unsigned long long)lanes_below(m)] = value;
 }
@@ -1010,9 +1035,11 @@ __device__ __forceinline__ void next_call_state(const BatchArgs& a) {
   BatchState& st = *a.st;
   const unsigned t = threadIdx.x;
   if (blockIdx.x == 0) {
-    if (t < (unsigned)kLptBuckets) st.l_count[t].v = 0;
-    if (t < (unsigned)kStreams) st.p_next[t].v = 0;
-    if (t < (unsigned)(kLptBuckets * kStreams)) st.l_next[t / kStreams][t % kStreams].v = 0;
+    if (t < (unsigned)kStreams) {
+      st.p_next[t].v = 0;
+      st.l_next[t].v = 0;
+    }
+    if (t < (unsigned)(kLptBuckets * kStreams)) st.l_count[t % kStreams].v[t / kStreams] = 0;
   }
   // most calls used none: every counter in one load (one after the other, eight
   // latencies were half of a small call's sweep)
@@ -1455,7 +1482,7 @@ k_tile_pairs(BatchArgs args) {
     }
     const uint64_t left = ballot(some && !quick);
     const int st = (int)(blockIdx.x % (unsigned)kStreams);
-    if (left) list_append(a.st->t_count[st], a.run_list + st * a.stream_cap, left, (int32_t)i, lane);
+    if (left) list_append(a.st->t_count[st].v, a.run_list + st * a.stream_cap, left, (int32_t)i, lane);
     pairs[lane] = mine;
     wave_sync_lds();
     if (ballot(mine.how != 0)) count_tile_pairs(a, pairs, lane);
@@ -1535,7 +1562,7 @@ k_batch_sweep(BatchArgs args) {
         const PairRec r = pair_rec(a, ia, ib);
         verts = (int64_t)r.np + r.nq;
         if (r.np > kMediumRing || r.nq > kMediumRing || verts >= a.heavy_verts)
-          bucket = lpt_bucket(a, verts);
+          bucket = lpt_bucket(a.flags, a.heavy_verts, verts);
         else if (r.np > kSweepRing || r.nq > kSweepRing || r.np <= 0 || r.nq <= 0 || (!union_ok && !kPairBox))
           medium = true;
         else
@@ -1716,12 +1743,12 @@ k_batch_sweep(BatchArgs args) {
     }
     const uint64_t listed = ballot(medium || (sweep && !lane_in(finished)));
     const int st = (int)(blockIdx.x % (unsigned)kStreams);
-    if (listed) list_append(a.st->m_count[st], a.m_list + st * a.stream_cap, listed, (int32_t)i, lane);
+    if (listed) list_append(a.st->m_count[st].v, a.m_list + st * a.stream_cap, listed, (int32_t)i, lane);
     if (ballot(bucket >= 0)) {
 #pragma unroll 1
       for (int b = 0; b < kLptBuckets; ++b) {
         const uint64_t m = ballot(bucket == b);
-        if (m) list_append(a.st->p_count[b][st], a.l_list + (b * kStreams + st) * a.stream_cap, m, (int32_t)i, lane);
+        if (m) list_append(a.st->p_count[b][st].v, a.l_list + (b * kStreams + st) * a.stream_cap, m, (int32_t)i, lane);
       }
     }
   }
@@ -2023,14 +2050,23 @@ struct TeamRing {
 };
 
 // List the pairs i of the lanes `m`, of `verts` vertices each, for the
-// persistent kernel: one append per bucket (one per pair, on one counter, took
-// 25 ns each: 400 us for 16,000 pairs that were all listed).
-__device__ __forceinline__ void list_run(const BatchArgs& a, uint64_t m, int32_t i, int64_t verts, int lane) {
-  const int bucket = lpt_bucket(a, verts);
+// persistent kernel: one append per bucket, to the workgroup's stream (on one
+// counter an append took 25 ns: 400 us for 16,000 pairs that were all listed one
+// by one; of 3000 pairs a wave each and 10,000 in 5120 waves, appended a wave's
+// at a time, the medium sweep took 96 and 155 us, on a counter per stream 32 and
+// 37, and the persistent kernel, which reads them all, no longer).
+// The arguments are read again where they are needed, from the kernel's own: in
+// registers throughout they were 42 more spilled scalars in the loops around.
+__device__ __forceinline__ void list_run(uint64_t m, int32_t i, int64_t verts, int lane) {
+  typedef const BatchArgs __attribute__((address_space(4))) * args_ptr;
+  args_ptr a = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();  // the kernel's only parameter
+  asm volatile("" : "+s"(a));
+  const int st = (int)(blockIdx.x % (unsigned)kStreams);
+  const int bucket = lpt_bucket(a->flags, a->heavy_verts, verts);
 #pragma unroll 1
   for (int b = 0; b < kLptBuckets; ++b) {
     const uint64_t mb = m & ballot(bucket == b);
-    if (mb) list_append(a.st->l_count[b], a.run_list + (int64_t)b * a.n_pairs, mb, i, lane);
+    if (mb) list_append(a->st->l_count[st].v[b], a->run_list + (int64_t)(b * kStreams + st) * a->run_cap, mb, i, lane);
   }
 }
 // A listed pair's box and class (by one lane).
@@ -2283,30 +2319,19 @@ k_batch_medium(BatchArgs args) {
   const uint32_t own = gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
   uint32_t p_empty = own;
   // the long pairs, bucket after bucket from the largest, one pair per claim;
-  // wave 0 claims the next one while the team works on the one in hand.  The
-  // lists' parts stand end to end, lane L's part being that of stream L %
-  // kStreams of bucket kLptBuckets - 1 - L / kStreams, from `first` on.
-  constexpr int kParts = kLptBuckets * kStreams;
-  const int part_b = kLptBuckets - 1 - lane / kStreams, part_s = lane % kStreams;
+  // wave 0 claims the next one while the team works on the one in hand
   // the lengths of these lists and, in the lanes after them, of the medium
   // list's parts, in one load
   static_assert(kParts + kStreams <= kWave, "a list per lane");
-  const int length = lane < kParts              ? (int)a.st->p_count[part_b][part_s].v
+  const int length = lane < kParts              ? (int)a.st->p_count[BucketLists::bucket(lane)][lane % kStreams].v
                      : lane < kParts + kStreams ? (int)a.st->m_count[lane - kParts].v
                                                 : 0;
   if (!ballot(length != 0)) {
     wave_stamps(a, 1, t_start, lane);
     return;  // both waves of the team
   }
-  const int n_here = lane < kParts ? length : 0;
-  int first = n_here;
-#pragma unroll
-  for (int d = 1; d < kParts; d <<= 1) {
-    const int v = __shfl_up(first, d, kWave);
-    if (lane >= d) first += v;
-  }
-  const int64_t n_long = __builtin_amdgcn_readlane(first, kParts - 1);
-  first -= n_here;
+  const BucketLists longs(lane < kParts ? length : 0, lane);
+  const int64_t n_long = longs.all;
   if (n_long > 0) {
     // wave 0's lanes keep the pairs to be listed
     int32_t listed = 0;
@@ -2318,7 +2343,7 @@ k_batch_medium(BatchArgs args) {
         const PairRec r = pair_rec(a, a.pa[listed], a.pb[listed]);
         verts = (int64_t)r.np + r.nq;
       }
-      list_run(a, ballot(mine), listed, verts, lane);
+      list_run(ballot(mine), listed, verts, lane);
       n_listed = 0;
     };
     int64_t next = -1;
@@ -2332,9 +2357,7 @@ k_batch_medium(BatchArgs args) {
       __syncthreads();
       const int64_t k = uniform64(claimed[it]);
       if (k < 0) break;
-      const int part = kWave - 1 - __clzll((long long)ballot(lane < kParts && first <= (int)k));
-      const int64_t at = (int64_t)((kLptBuckets - 1 - part / kStreams) * kStreams + part % kStreams) * a.stream_cap;
-      const int64_t i = a.l_list[at + (k - __builtin_amdgcn_readlane(first, part))];
+      const int64_t i = a.l_list[longs.at(k, a.stream_cap, lane)];
       if (long_one<kStats>(c, uniform64(i), w, team_slots, ex[it]) && w == 0) {
         listed = lane == n_listed ? (int32_t)i : listed;
         if (++n_listed == kWave) list_long();
@@ -2378,7 +2401,7 @@ k_batch_medium(BatchArgs args) {
       sc = sn;
       rc = rn;
     }
-    if (listed) list_run(a, listed, idx, (int64_t)recs.np + recs.nq, lane);
+    if (listed) list_run(listed, idx, (int64_t)recs.np + recs.nq, lane);
   }
   wave_stamps(a, 1, t_start, lane);
 }
@@ -2413,25 +2436,19 @@ __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args)
         a.st->m_count[t % kStreams].v = 0;
     }
   }
-  unsigned long long n_list[kLptBuckets], n_all = 0;
-#pragma unroll
-  for (int b = 0; b < kLptBuckets; ++b) {
-    n_list[b] = a.st->l_count[b].v;
-    n_all += n_list[b];
-  }
-  if (n_all == 0) {
+  const int length = c.lane < kParts ? (int)a.st->l_count[c.lane % kStreams].v[BucketLists::bucket(c.lane)] : 0;
+  if (!ballot(length != 0)) {
     wave_stamps(a, 2, t_start, c.lane);
     return;
   }
+  const BucketLists lists(length, c.lane);
   // Boxes reach a queue only from splits with at least min_cells_to_queue
   // continuing cells (at most 64): otherwise no wave ever needs to look at
   // the queues.
   const bool queues_used = !(a.flags & SCCG_F_NO_SPLIT_QUEUE) && a.min_cells_to_queue <= kWave;
-  int bucket = kLptBuckets - 1;  // the bucket being claimed, largest first (wave-uniform)
-  // streams of that bucket found exhausted (wave-uniform); as in the sweeps,
-  // a wave claims only from its XCD's stream unless kRunSteal
-  const uint32_t l_start = kRunSteal || gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
-  uint32_t l_empty = l_start;
+  // streams of the lists found exhausted (wave-uniform); as in the sweeps, a
+  // wave claims only from its XCD's stream unless kRunSteal
+  uint32_t l_empty = kRunSteal || gridDim.x < (unsigned)kStreams ? 0u : (0xffu & ~(1u << c.xcd));
   for (;;) {
     PairInfo pi;
     uint64_t task = 0;  // 0: a box that fits one leaf tile
@@ -2442,19 +2459,13 @@ __global__ void __launch_bounds__(512) SCCG_RUN_ATTR k_batch_run(BatchArgs args)
       task = w;
       have = true;
     }
-    while (!have && bucket >= 0) {
-      const unsigned long long nb = bucket == 3 ? n_list[3] : bucket == 2 ? n_list[2] : bucket == 1 ? n_list[1]
-                                                                                                     : n_list[0];
-      const int64_t e = claim_chunk(a.st->l_next[bucket], (int64_t)nb, 1, c.xcd, c.lane, l_empty);
-      if (e < 0) {
-        bucket = uniform(bucket - 1);
-        l_empty = l_start;
-        continue;
+    if (!have) {
+      const int64_t e = claim_chunk(a.st->l_next, lists.all, 1, c.xcd, c.lane, l_empty);
+      if (e >= 0) {
+        pi = heavy_info(a, (int64_t)a.run_list[lists.at(e, a.run_cap, c.lane)]);
+        if (a.cls[pi.pair] == kClsLarge) task = root_task(pi);
+        have = true;
       }
-      pi = heavy_info(a, (int64_t)a.run_list[(int64_t)bucket * a.n_pairs + e]);
-      const uint8_t cls = a.cls[pi.pair];
-      have = true;
-      if (cls == kClsLarge) task = root_task(pi);
     }
     // nothing of its own left: help with every queue, then stop
     if (!have) {

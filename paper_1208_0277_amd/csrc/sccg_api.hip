@@ -309,6 +309,7 @@ void place_lists(BatchArgs& ba, const BatchGrids& g) {
   ba.stream_cap = stream_cap_of(g.sweep, batch_sweep_waves_per_wg(), most_share(ba.n_pairs, waves, ba.chunk));
   ba.m_list = ba.l_list + kLptBuckets * kStreams * ba.stream_cap;
   ba.run_list = ba.m_list + kStreams * ba.stream_cap;
+  ba.run_cap = (int32_t)run_cap_of(ba.n_pairs, g.medium);
 }
 
 // Start/stop events for the next timed launch (created on first use).

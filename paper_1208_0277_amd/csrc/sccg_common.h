@@ -121,20 +121,33 @@ constexpr int64_t most_share(int64_t n, int64_t waves, int64_t longest) {
 
 // The most pairs that the workgroups of one stream of the union sweep take
 // (`grid` workgroups of `per_wg` waves, shares of at most `most` pairs), and
-// room for it whatever the grid: shares differ by at most a 32nd and one pair.
+// room for it whatever the grid, of up to 6000 workgroups: shares differ by at
+// most a 32nd and one pair.
 constexpr int64_t stream_cap_of(int64_t grid, int64_t per_wg, int64_t most) {
   return (grid + kStreams - 1) / kStreams * per_wg * most;
 }
-constexpr int64_t stream_cap_room(int64_t n_pairs) { return (n_pairs + n_pairs / 16) / kStreams + 8192; }
+constexpr int64_t stream_cap_room(int64_t n_pairs) { return (n_pairs + n_pairs / 16) / kStreams + 3072; }
+// The most pairs that the workgroups of one stream of the medium sweep (`grid`
+// of them) list for the persistent kernel: every eighth long pair and their
+// shares of the medium ones; and room for it whatever the grid, of 32 to 6000
+// workgroups.
+constexpr int64_t run_cap_of(int64_t n_pairs, int64_t grid) { return n_pairs / kStreams + grid / 4 + n_pairs / grid + 16; }
+constexpr int64_t run_cap_room(int64_t n_pairs) { return n_pairs / kStreams + n_pairs / 32 + 2048; }
 // 4-byte list entries for n pairs: the sweep's lists (long buckets, medium),
 // the persistent kernel's buckets
 constexpr int64_t pair_list_room(int64_t n) {
-  return (kLptBuckets + 1) * kStreams * stream_cap_room(n) + kLptBuckets * n;
+  return (kLptBuckets + 1) * kStreams * stream_cap_room(n) + kLptBuckets * kStreams * run_cap_room(n);
 }
 
+// Those of all buckets on one line: every wave of the persistent kernel reads
+// them (32 lines each cost a call of 20,000 pairs 0.3 us).
+struct alignas(128) BucketCounters {
+  unsigned long long v[kLptBuckets];
+};
+
 struct BatchState {
-  Counter l_count[kLptBuckets];            // pairs listed for the persistent kernel per bucket
-  Counter l_next[kLptBuckets][kStreams];   // per-stream claim counters over each bucket
+  BucketCounters l_count[kStreams];  // pairs listed for the persistent kernel per stream and bucket
+  Counter l_next[kStreams];      // per-stream claim counters over them, one after the other
   Counter m_count[kStreams];  // medium pairs listed by the sweep per stream
   Counter p_count[kLptBuckets][kStreams];  // long pairs listed by the sweep per bucket and stream
   Counter p_next[kStreams];      // per-stream claim counters over the long pairs
@@ -158,7 +171,8 @@ struct BatchArgs {
   int32_t* l_list;               // [kLptBuckets][kStreams][stream_cap] long pairs
   int32_t* m_list;               // [kStreams][stream_cap] medium pairs
   int64_t stream_cap;            // see stream_cap_of
-  int32_t* run_list;             // [kLptBuckets][n_pairs] pairs listed for the persistent kernel
+  int32_t* run_list;             // [kLptBuckets][kStreams][run_cap] pairs listed for the persistent kernel
+  int32_t run_cap;               // see run_cap_of
   Meta* hbox;                    // [n_pairs] pair box of a listed pair (by pair index)
   BatchState* st;
   unsigned long long* queue;     // [n_queues * queue_cap] task words, 0 = empty

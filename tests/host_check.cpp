@@ -1,11 +1,16 @@
 // Checks of the library's host side on the stand-in runtime (host_hip.h): what
 // a call leaves behind when memory runs out.  One check per name; exits with
 // the number of expectations that failed.
+#include <math.h>
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
+#include <random>
+
 #include "host_hip.h"
 #include "sccg.h"
+#include "sccg_common.h"
 
 static int failed = 0;
 #define EXPECT(cond, ...)                              \
@@ -223,6 +228,32 @@ static void launches_within_a_dispatch() {
   }
 }
 
+// ------------------------------------------------------------------- lists
+// Whatever the pairs, the grids and the shares' runs: a stream's pairs fit its
+// parts of the lists, and the parts the room that is allocated for the pairs.
+static void lists_hold_their_pairs() {
+  using namespace sccg;
+  std::mt19937_64 rng(1);
+  auto below = [&](int64_t n) { return (int64_t)(rng() % (uint64_t)n); };
+  for (int k = 0; k < 3000000 && failed < 10; ++k) {
+    const int64_t n = std::max<int64_t>(1, (int64_t)exp((double)below(1000000) / 1e6 * log(2147483647.0)));
+    const int64_t cus = int64_t(32) << below(4), chunk = 1 + below(64);
+    const int64_t sweep = std::min(cus * (1 + below(8)), (n + 3) / 4), medium = std::min(cus * (1 + below(16)), n);
+    const int64_t cap = stream_cap_of(sweep, 4, most_share(n, sweep * 4, chunk)), run = run_cap_of(n, medium);
+    // every eighth long pair, and shares of the others that differ by one
+    const int64_t longs = below(3) == 0 ? n : below(n + 1), rest = n - longs, waves = 2 * medium;
+    const int64_t share = (medium + kStreams - 1) / kStreams * 2 * ((rest + waves - 1) / waves);
+    const int64_t listed = medium < kStreams ? n : std::min(n, (longs + kStreams - 1) / kStreams + std::min(rest, share));
+    EXPECT(listed <= run, "%lld pairs, %lld long, %lld workgroups: %lld in %lld", (long long)n, (long long)longs, (long long)medium,
+           (long long)listed, (long long)run);
+    const int64_t room = pair_list_room(n + below(n / 4 + 2));
+    EXPECT((kLptBuckets + 1) * kStreams * cap + kLptBuckets * kStreams * run <= room, "%lld pairs, %lld and %lld workgroups", (long long)n,
+           (long long)sweep, (long long)medium);
+    // the pairs that the rings' tiles leave stand where the persistent kernel's will
+    if (n >= kRingTilePairs) EXPECT(cap <= kLptBuckets * run, "%lld pairs", (long long)n);
+  }
+}
+
 int main(int argc, char** argv) {
   static const struct {
     const char* name;
@@ -233,6 +264,7 @@ int main(int argc, char** argv) {
       {"errors_are_reported_once", errors_are_reported_once},
       {"tiles_out_of_memory", tiles_out_of_memory},
       {"launches_within_a_dispatch", launches_within_a_dispatch},
+      {"lists_hold_their_pairs", lists_hold_their_pairs},
       {"tiles_tried_again_with_new_parameters", tiles_tried_again_with_new_parameters},
   };
   for (const auto& k : checks)
