@@ -325,8 +325,10 @@ class Context:
         as a user of them, so that dropping one whose reader is still queued
         there does not hand it to this stream's next call."""
         import torch
-        if (self._raw_stream == torch._C._cuda_getCurrentRawStream(self.device)
-                or not isinstance(self.stream, torch.cuda.Stream)):
+        # the handle alone, without a Stream object made per call, where this torch has the getter
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        current = raw(self.device) if raw else torch.cuda.current_stream(self.device).cuda_stream
+        if self._raw_stream == current or not isinstance(self.stream, torch.cuda.Stream):
             return [torch.empty(n, dtype=t, device=device) for n, t in zip(sizes, dtypes)]
         reader = torch.cuda.current_stream(self.device)
         with torch.cuda.stream(self.stream):

@@ -76,3 +76,23 @@ def test_outputs_read_on_the_current_stream_and_dropped():
             assert torch.equal(g.cpu(), w)
     finally:
         c.close()
+
+
+def test_outputs_without_the_raw_stream_getter(monkeypatch):
+    """A torch without the private getter of the current stream's handle."""
+    import torch
+    wl = sccg_gen.pairs(1)
+    work = device_workload(wl.A, wl.B, wl.pa, wl.pb)
+    torch.cuda.synchronize()
+    for stream in (None, torch.cuda.Stream()):
+        c = sccg.Context(0, stream=stream) if stream else sccg.Context(0)
+        try:
+            want = [t.cpu() for t in c.area_pairs(*work)]
+            with monkeypatch.context() as m:
+                m.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+                got = c.area_pairs(*work)
+            c.sync()
+            for g, w in zip(got, want):
+                assert torch.equal(g.cpu(), w)
+        finally:
+            c.close()
