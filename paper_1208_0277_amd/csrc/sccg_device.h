@@ -51,24 +51,11 @@ __device__ __forceinline__ uint32_t op_add_u32(uint32_t a, uint32_t b) { return 
 __device__ __forceinline__ uint32_t op_or_u32(uint32_t a, uint32_t b) { return a | b; }
 __device__ __forceinline__ uint32_t op_xor_u32(uint32_t a, uint32_t b) { return a ^ b; }
 
-typedef short sccg_short2 __attribute__((ext_vector_type(2)));
-// lane-wise min / max of two packed int16 pairs (v_pk_min_i16 / v_pk_max_i16)
-__device__ __forceinline__ uint32_t op_pkmin_i16(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(sccg_short2, a),
-                                                                 __builtin_bit_cast(sccg_short2, b)));
-}
-__device__ __forceinline__ uint32_t op_pkmax_i16(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(sccg_short2, a),
-                                                                 __builtin_bit_cast(sccg_short2, b)));
-}
-
 SCCG_DPP_REDUCE(wave_min_i32, int32_t, op_min_i32, 0x7fffffff)
 SCCG_DPP_REDUCE(wave_max_i32, int32_t, op_max_i32, 0x80000000u)
 SCCG_DPP_REDUCE(wave_sum_u32, uint32_t, op_add_u32, 0u)
 SCCG_DPP_REDUCE(wave_or_u32, uint32_t, op_or_u32, 0u)
 SCCG_DPP_REDUCE(wave_xor_u32, uint32_t, op_xor_u32, 0u)
-SCCG_DPP_REDUCE(wave_pkmin_i16, uint32_t, op_pkmin_i16, 0x7fff7fffu)
-SCCG_DPP_REDUCE(wave_pkmax_i16, uint32_t, op_pkmax_i16, 0x80008000u)
 
 __device__ __forceinline__ uint64_t wave_or64(uint64_t v) {
   return ((uint64_t)wave_or_u32((uint32_t)(v >> 32)) << 32) | wave_or_u32((uint32_t)v);
