@@ -242,7 +242,7 @@ int sccg_host_area_pairs(const sccg_polys* A, const sccg_polys* B, int64_t n_pai
  * BATCHED mode of sccg_area_pairs, with the same arguments and the same
  * results, that calls no hipMalloc, hipFree or other allocating routine.
  * Its scratch (batched state, task queues, per-pair records and lists) is a
- * static device array of about 17 MiB that every GPU the library runs on
+ * static device array of about 16 MiB that every GPU the library runs on
  * holds until the process ends; its device address is taken once per device
  * by sccg_create.  Limits: at most 2^18 = 262144 pairs per call (more gives
  * SCCG_E_ARG with a message naming the limit), task queues of at most 2^17
@@ -282,11 +282,12 @@ int sccg_sync(sccg_ctx* ctx);
  *   [4] boxes kept by the splitting wave although enough to publish (BATCHED)
  *   [5] small pairs (one leaf tile)   [6] large pairs   [7] pairs with an empty
  *       or rejected pair box (BATCHED)
- *   [8] leaf edge updates: BATCHED, staged band edges x leaf tiles;
+ *   [8] leaf edge updates: BATCHED, edges XORed into a leaf tile's or a band
+ *       row's slots;
  *       PLAIN, leaf pixels x ring edges tested
  *   [9] classification edge visits: BATCHED, ring edges x splits;
  *       PLAIN, sub-boxes x ring edges tested
- *   [10] ring edges read while staging leaf tiles (BATCHED)
+ *   [10] ring edges read for the leaf tiles and band rows (BATCHED)
  *   [11] covered pixels: sum of the non-empty pair-box areas (BATCHED)
  *   [12] vertices reduced for MBRs and areas, of pairs not counted on their
  *        union tile (BATCHED)
@@ -308,8 +309,8 @@ int sccg_get_stats(sccg_ctx* ctx, int64_t* out, int n);
 int64_t sccg_get_wave_times(sccg_ctx* ctx, int kernel, int64_t* out, int64_t max_waves);
 
 /* Time the kernels of every sccg_area_pairs call (the plain kernel, or every
- * launch of BATCHED mode, from the reset of its state to the persistent
- * kernel, back to back) with HIP events recorded on the context's stream
+ * launch of BATCHED mode, from the rings' tiles or the union sweep to the
+ * persistent kernel, back to back) with HIP events recorded on the context's stream
  * around them.  While timing is on, BATCHED mode
  * launches its kernels directly instead of through the HIP graph.
  * sccg_get_timing waits for the stream, returns the summed milliseconds and

@@ -31,8 +31,9 @@
 //     atomic per edge), and a prefix XOR over the lanes turns the slots into
 //     every column's crossing parities.  A polygon known to contain a tile
 //     is not tested again (its mask is all ones).  When a split leaves
-//     several leaf tiles, each ring is read once into per-row lists of its
-//     band edges in LDS, and every tile scatters from its row's list.
+//     several leaf tiles, each ring is streamed once per band row, its edges
+//     scattered into the slots of the row's columns in LDS, and the tiles of
+//     the row are scanned from those, right to left.
 //   - The pair's MBRs and shoelace areas are reduced by the wave that takes
 //     the pair, from the same coalesced ring loads it needs anyway; the
 //     pairs with many vertices ("long", claimed first: a largest-first
@@ -2369,8 +2370,8 @@ k_batch_medium(BatchArgs args) {
   // the medium list, its streams' parts end to end
   ListParts parts;
   parts.of_lanes(length, kParts);
-  // every wave takes an equal share of the list, in runs of `run` consecutive
-  // entries that interleave over the waves: the pairs are alike enough, and a
+  // every wave takes an equal share of the list, single entries dealt out in
+  // turns over the waves: the pairs are alike enough, and a
   // claim per few entries left each wave waiting on a counter, the list, the
   // records and the rings in turn (200,000 uniform pairs, 26,000 of them here:
   // 74 us with claims)
