@@ -373,6 +373,18 @@ def serve_bench(args):
     return 0
 
 
+def free_space(mode, fixed):
+    """The tuner's candidates without the parameters that a variant fixes: what
+    is swept has to be timed with those in place.  (PixelBox, tuned while the
+    classification threshold was swept too, met no box of the persistent
+    kernel, took its queue's threshold by noise and then ran in 1.3 or 0.14 ms
+    at scale 5.)"""
+    import paper_1208_0277_amd as sccg
+    from paper_1208_0277_amd import autotune
+    space = autotune.BATCHED_SPACE if mode == sccg.SCCG_BATCHED else autotune.PLAIN_SPACE
+    return [(name, values) for name, values in space if name not in fixed]
+
+
 def run_fig8(steps, warmup, autotuned=True):
     """Section 5.2's comparison (Figure 8) on a synthetic stand-in for its
     15,724-pair set: the same pairs with every coordinate multiplied by k.
@@ -412,7 +424,8 @@ def run_fig8(steps, warmup, autotuned=True):
                 tuned = {}
                 if autotuned:
                     tuned = autotune.tune(ctx, dA, dB, pa, pb, I, U, mode=mode, workload_key=f"fig8/{name}/{k}",
-                                          steps=2, use_cache=False, log=lambda m: None)
+                                          steps=2, use_cache=False, log=lambda m: None,
+                                          space=free_space(mode, fixed))
                     ctx.set_params(**{**tuned, **fixed})
                 for _ in range(warmup):
                     ctx.area_pairs(dA, dB, pa, pb, out_inter=I, out_union=U, mode=mode)

@@ -49,3 +49,15 @@ def test_more_than_one_gpu_is_refused():
                        text=True, cwd=ROOT, timeout=300)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_variants_are_tuned_with_what_they_fix():
+    """A variant's fixed parameters are not swept: the others would be chosen
+    by calls that the variant never makes."""
+    import paper_1208_0277_amd as sccg
+    from paper_1208_0277_amd import autotune
+    for mode, space in ((sccg.SCCG_BATCHED, autotune.BATCHED_SPACE), (sccg.SCCG_PLAIN, autotune.PLAIN_SPACE)):
+        assert bench.free_space(mode, {"flags": sccg.SCCG_F_NO_SEP}) == space
+        for name, _ in space:
+            left = bench.free_space(mode, {name: 1})
+            assert [s for s in space if s[0] != name] == left
