@@ -520,11 +520,14 @@ __device__ __forceinline__ int join_entries(const JoinArgs& a, int64_t b, int64_
   return n;
 }
 
-// Pairs of each B polygon, eight lanes per polygon: counted, and the first
+// Pairs of each B polygon, four lanes per polygon: counted, and the first
 // kFound of them kept for the second pass (a thread per polygon that searched
-// again for it took 88 + 157 us for 600,000 of 4.5 pairs each).
+// again for it took 88 + 157 us for 600,000 of 4.5 pairs each).  Joins with
+// eight / four / two / one: those 600,000 290 / 268 / 276 / 272 us, a million
+// polygons in as many sets, where a wave's search of its set weighs, 409 / 359 /
+// 343 / 327, 4096 polygons in 64 sets 73 / 72 / 84 / 88.
 constexpr int kFound = 16;
-constexpr int kCountLanes = 8;
+constexpr int kCountLanes = 4;
 __global__ void __launch_bounds__(256) k_join_count(JoinArgs a, int32_t* b_count, int32_t* found, int32_t* cell_count,
                                                     int64_t first) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

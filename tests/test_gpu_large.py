@@ -137,3 +137,20 @@ def test_cells_scanned(ctx, sets, most_ms):
         assert torch.equal(so, off) and torch.equal(pa, k.to(torch.int32)) and torch.equal(pb, k.to(torch.int32))
     print(f"{sets} sets: {best:.1f} ms", flush=True)
     assert best < most_ms
+
+
+def test_polygons_counted(ctx):
+    """The same with B polygons of more than one pass of the count, 64 a
+    workgroup; a few have a pair."""
+    import torch
+    n = (1 << 26) + 77
+    A, B = _squares(2), _squares(n)
+    A.xy[4:] += 100
+    B.xy += 10
+    for k in (3, 1 << 25, (1 << 26) - 1, 1 << 26, (1 << 26) + 63, n - 1):
+        B.xy[4 * k:4 * k + 4] -= 9
+    off = torch.tensor([0, 2], dtype=torch.int64, device="cuda")
+    pa, pb, so = ctx.join_sets(A, B, off, torch.tensor([0, n], dtype=torch.int64, device="cuda"), cap=100)
+    ctx.sync()
+    assert so.tolist() == [0, 6] and not pa.any()
+    assert pb.tolist() == [3, 1 << 25, (1 << 26) - 1, 1 << 26, (1 << 26) + 63, n - 1]
