@@ -51,13 +51,15 @@ def test_outputs_read_on_the_current_stream_and_dropped():
 
     def calls(w):
         I, U = c.area_pairs(*w)
-        return [I, U, *c.jaccard_sets(so, I, U), *c.join_sets(w[0], w[1], off, off, cap=4 * wl.n_pairs),
-                c.relate_pairs(*w, I), c.validate_polys(w[0])]
+        return [I, U, *c.jaccard_sets(so, I, U), c.relate_pairs(*w, I), c.validate_polys(w[0])]
+
+    def join(w):  # waits for its stream, which may share a hardware queue with the readers
+        return [*c.join_sets(w[0], w[1], off, off, cap=4 * wl.n_pairs)]
 
     try:
-        calls(other)
+        calls(other), join(other)
         torch.cuda.synchronize()
-        outs = calls(work)
+        outs = calls(work) + join(work)
         c.sync()
         want = [t.cpu() for t in outs]
         reader = torch.cuda.Event()
@@ -70,6 +72,7 @@ def test_outputs_read_on_the_current_stream_and_dropped():
         del outs
         again = calls(other)
         assert not reader.query(), "the readers had run before the calls: nothing was tested"
+        again += join(other)
         assert not held & {t.untyped_storage().data_ptr() for t in again}
         torch.cuda.synchronize()
         for g, w in zip(got, want):
