@@ -324,7 +324,9 @@ const char* sccg_last_error(const sccg_ctx* ctx);
 
 /* Number of BATCHED sccg_area_pairs calls on this context that ran as a
  * replay of its captured HIP graph (on a non-null stream, without
- * SCCG_F_NO_GRAPH and with timing off); -1 for a NULL context. */
+ * SCCG_F_NO_GRAPH and with timing off); -1 for a NULL context.  A call whose
+ * arguments are not the graph's is launched directly; the eighth of such calls
+ * in a row with the same arguments is captured in its place. */
 int64_t sccg_graph_launches(const sccg_ctx* ctx);
 
 /* ------------------------------------------------------------ serving ---- */

@@ -59,6 +59,8 @@ struct sccg_ctx {
   // graph cache for the batched sequence
   hipGraphExec_t gexec = nullptr;
   std::string gkey;
+  std::string gmissed;         // the last call's arguments, if they were not the graph's, and
+  int gmisses = 0;             // the calls in a row that had them
   int64_t graph_launches = 0;  // batched calls that ran as a replay of the captured graph
   // filter-stage scratch
   int4* j_bbox = nullptr;
@@ -157,12 +159,24 @@ int resolve_params(sccg_ctx* c, const sccg_params* in, sccg_params* out) {
   return SCCG_OK;
 }
 
+// Calls in a row with the same arguments, other than the captured graph's, of
+// which the last is captured in its place.
+constexpr int kGraphAfter = 8;
+
 // The captured graph holds the scratch pointers as kernel arguments: it is
 // dropped whenever scratch it may use is freed or reallocated.
 void drop_graph(sccg_ctx* c) {
   if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
   c->gexec = nullptr;
   c->gkey.clear();
+}
+
+// Whether the caller captures the context's stream.
+bool capturing(sccg_ctx* c) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
 }
 
 template <typename T>
@@ -218,11 +232,7 @@ int ensure_pairs(sccg_ctx* c, int64_t n) {
 bool ensure_tiles(sccg_ctx* c, int64_t n) {
   if (n <= c->cap_tiles) return true;
   if (n >= c->tiles_refused) return false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return false;
-  }
+  if (capturing(c)) return false;
   const int64_t want = std::min(n + n / 4 + 1024, kRingTilesMost);
   unsigned char* more = nullptr;
   if (hipMalloc((void**)&more, (size_t)ring_tiles_bytes(want)) != hipSuccess) {
@@ -685,12 +695,13 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
     c->wave_n[1] = medium_waves;
     c->wave_n[2] = run_waves;
   }
+  const auto launch = [&] {
+    const int rc = launch_batched(c, ba, grids);
+    if (rc) c->queue_nq = 0;  // part of the sequence ran: ensure_queue clears the state it left
+    return rc;
+  };
   const bool use_graph = c->stream != nullptr && !(c->p.flags & SCCG_F_NO_GRAPH) && !c->timing_on;
-  if (!use_graph) {
-    r = launch_batched(c, ba, grids);
-    if (r) c->queue_nq = 0;  // part of the sequence ran: ensure_queue clears the state it left
-    return r;
-  }
+  if (!use_graph) return launch();
   // the graph is keyed on every launch argument
   char key[512];
   snprintf(key, sizeof(key), "%lld/%p/%p|%lld/%p/%p|%lld/%p/%p/%p/%p|%d/%d/%d/%d/%d/%d/%u/%d/%d/%d/%p",
@@ -700,6 +711,14 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
            ba.chunk, ba.heavy_verts, ba.min_cells_to_queue, ba.min_classify_cells, ba.flags, ba.stats_on | (c->stamps_on << 1), grids.run,
            c->p.sweep_pair_box, (void*)ba.ring_tiles);
   if (!c->gexec || c->gkey != key) {
+    if (c->gmissed != key) c->gmisses = 0;
+    c->gmissed = key;
+    // Outputs that the caller allocates for each call come at changing
+    // addresses, a few times at the same ones in between, and a graph captured
+    // for each (1,000 pairs on a stream of its own: 65 us a call) is of no use:
+    // launched, the same calls take 29.  A replay is no faster than launches, so
+    // that a graph that comes some calls later costs nothing.
+    if (c->gexec && ++c->gmisses < kGraphAfter && !capturing(c)) return launch();
     drop_graph(c);
     hipGraph_t g = nullptr;
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
@@ -718,6 +737,7 @@ int sccg_area_pairs(sccg_ctx* c, const sccg_polys* A, const sccg_polys* B, int64
     }
     c->gkey = key;
   }
+  c->gmissed.clear();
   HIP_TRY(c, hipGraphLaunch(c->gexec, c->stream));
   c->graph_launches += 1;
   return SCCG_OK;

@@ -162,7 +162,7 @@ static void tiles_out_of_memory() {
   EXPECT(fake.refused == 1, "%ld refused", fake.refused);
   EXPECT(fake.launched("k_ring_tiles") == 1, "tiles without memory");
   const FakeHip before = fake;
-  for (int k = 0; k < 5; ++k) call(many);
+  for (int k = 0; k < 12; ++k) call(many);
   call(many - 1);  // of what was asked for there was too little
   EXPECT(fake.captures == before.captures + 1, "%ld captures", fake.captures - before.captures);
   EXPECT(fake.replays == before.replays + 6, "%ld replays", fake.replays - before.replays);
@@ -199,6 +199,39 @@ static void tiles_tried_again_with_new_parameters() {
   EXPECT(sccg_set_params(c, &p) == SCCG_OK, "set_params");
   call();
   EXPECT(fake.launched("k_ring_tiles") == 1, "no tiles");
+  sccg_destroy(c);
+}
+
+// ---------------------------------------------------------------- the graph
+// Captured with the first call's arguments, replayed with the same, and given
+// up only for others that come eight times in a row.
+static void graph_of_repeated_arguments() {
+  sccg_ctx* c = nullptr;
+  EXPECT(sccg_create(&c, 0, (void*)1, nullptr) == SCCG_OK, "create");
+  const sccg_polys P = polys(1000);
+  long sweeps = 0;
+  auto call = [&](int out, long captures, long replays, const char* what) {
+    const FakeHip before = fake;
+    EXPECT(sccg_area_pairs(c, &P, &P, 1000, arr, arr, off + out, off, SCCG_BATCHED) == SCCG_OK, "%s", sccg_last_error(c));
+    EXPECT(fake.captures == before.captures + captures, "%s: %ld captures", what, fake.captures - before.captures);
+    EXPECT(fake.replays == before.replays + replays, "%s: %ld replays", what, fake.replays - before.replays);
+    sweeps += captures || !replays;  // kernels launched, into the graph or the stream
+    EXPECT(fake.launched("k_batch_sweep") == sweeps, "%s: %ld sweeps", what, (long)fake.launched("k_batch_sweep"));
+  };
+  call(0, 1, 1, "first call");
+  call(0, 0, 1, "the same");
+  for (int k = 0; k < 3; ++k) {
+    call(1, 0, 0, "others");
+    call(2, 0, 0, "others again");
+  }
+  call(0, 0, 1, "the graph's");
+  for (int k = 0; k < 7; ++k) call(2, 0, 0, "others after it");
+  call(0, 0, 1, "the graph's again");
+  for (int k = 0; k < 7; ++k) call(2, 0, 0, "others, counted anew");
+  call(2, 1, 1, "eight in a row");
+  call(2, 0, 1, "the new graph's");
+  for (int k = 0; k < 7; ++k) call(0, 0, 0, "the old graph's");
+  call(0, 1, 1, "eight of those");
   sccg_destroy(c);
 }
 
@@ -263,6 +296,7 @@ int main(int argc, char** argv) {
       {"join_launch_sizes", join_launch_sizes},
       {"errors_are_reported_once", errors_are_reported_once},
       {"tiles_out_of_memory", tiles_out_of_memory},
+      {"graph_of_repeated_arguments", graph_of_repeated_arguments},
       {"launches_within_a_dispatch", launches_within_a_dispatch},
       {"lists_hold_their_pairs", lists_hold_their_pairs},
       {"tiles_tried_again_with_new_parameters", tiles_tried_again_with_new_parameters},

@@ -31,7 +31,7 @@ def check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name", ["join_out_of_memory", "join_launch_sizes", "errors_are_reported_once", "tiles_out_of_memory",
-                                  "tiles_tried_again_with_new_parameters", "launches_within_a_dispatch",
+                                  "tiles_tried_again_with_new_parameters", "graph_of_repeated_arguments", "launches_within_a_dispatch",
                                   "lists_hold_their_pairs"])
 def test_host_side(check, name):
     r = subprocess.run([check, name], capture_output=True, text=True, timeout=120)
