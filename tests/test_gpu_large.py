@@ -40,8 +40,8 @@ def test_rings_validated(ctx):
 
 
 def test_polygons_joined(ctx):
-    """Two A squares, one of them in every pair (32 B polygons a workgroup of
-    the count, 16 of the writing pass), some B polygons with no pair."""
+    """Two A squares, one of them in every pair (16 B polygons a workgroup of
+    the writing pass), some B polygons with no pair."""
     import torch
     n = (1 << 25) + 45
     A, B = _squares(2), _squares(n)
